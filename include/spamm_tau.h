@@ -60,8 +60,8 @@ spamm_status spamm_mlp_forward(const float* params, const float* x, int32_t batc
 
 /* Mean squared error of the predictions for x against targets t [batch]
  * (log10 tau) into *loss (device float), and its gradient with respect to the
- * parameters into grad (same layout as params).  Sums over the batch run in
- * ascending order (results are reproducible).  acts as above. */
+ * parameters into grad (same layout as params).  Sums run in a fixed order
+ * (results are reproducible).  acts as above. */
 spamm_status spamm_mlp_loss_grad(const float* params, const float* x, const float* t, int32_t batch, float* acts,
                                  float* grad, float* loss, void* stream);
 

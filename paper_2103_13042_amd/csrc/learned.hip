@@ -173,7 +173,16 @@ hipError_t launch_sumsq(const float* x, int64_t count, double* partials, double*
 // The network, FP32.  Parameters flat: W1 [128][129], b1 [128], W2 [128][128],
 // b2 [128], w3 [128], b3 [1].  Layer l maps X [B][I] to Z = X W^T + b and
 // H = gelu(Z) (erf form) for the hidden layers; the output layer has no
-// activation.  Sums run over the input index in ascending order.
+// activation.
+//
+// A minibatch (256 rows) is 0.04 GFLOP, so the step is bound by launches and
+// by the latency inside each of them.  Two launches make the gradient: one
+// runs a row through the whole network and back to dZ1 with both weight
+// matrices in LDS (mlp_rows_kernel), the other forms every parameter gradient
+// as a product over the batch on FP32 MFMA (mlp_weight_grad_kernel).  Batch
+// 256, gradient and Adam step: 260 -> 19 us; with one launch per layer and
+// direction 221 us of it were weight gradients that walked the batch one row
+// at a time.
 
 __device__ __forceinline__ float gelu_f(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
 
@@ -181,70 +190,218 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
     return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
 }
 
-constexpr int kMaxIn = 132;
+constexpr int kRowThreads = 512;
+constexpr int kRowParts = kRowThreads / kMlpHid;          // input ranges summed by different threads
+constexpr int kRowW = kMlpIn;                             // LDS row stride of both matrices (odd: no bank conflicts)
+constexpr int kRowPart1 = (kMlpIn + kRowParts - 1) / kRowParts, kRowPart2 = kMlpHid / kRowParts;
+constexpr int kRowLoads = (kMlpHid * kMlpIn + kRowThreads - 1) / kRowThreads;
+constexpr int kRowBlocks = 256;  // one block per CU: both matrices fill its LDS
 
-// block b = one sample; thread o = one output unit (O <= blockDim.x)
-__global__ __launch_bounds__(128) void dense_fwd_kernel(const float* __restrict__ x, int in, const float* __restrict__ w,
-                                                        const float* __restrict__ bias, int out_units,
-                                                        float* __restrict__ z, float* __restrict__ h) {
-    __shared__ float xs[kMaxIn];
-    const int b = blockIdx.x, o = threadIdx.x;
-    for (int i = threadIdx.x; i < in; i += blockDim.x) xs[i] = x[int64_t(b) * in + i];
-    __syncthreads();
-    if (o >= out_units) return;
-    const float* wr = w + int64_t(o) * in;
-    float acc = bias[o];
-    for (int i = 0; i < in; ++i) acc = fmaf(xs[i], wr[i], acc);
-    z[int64_t(b) * out_units + o] = acc;
-    if (h) h[int64_t(b) * out_units + o] = gelu_f(acc);
+// Block b takes rows b*RB .. of the batch, then every gridDim.x*RB further.
+// Thread (o, part) sums one range of the inputs of unit o for RB rows; the
+// ranges are added in ascending order.  RB rows share each weight read, but
+// the operand broadcasts grow with them, so RB is the smallest of 1, 2 and 4
+// that gives every row a block of its own.  GRAD: also the residual and
+// dZ2, dZ1, and what mlp_weight_grad_kernel reads (h1, h2, d1, d2, y, dy).
+template <int RB, bool GRAD>
+__global__ __launch_bounds__(kRowThreads) void mlp_rows_kernel(const float* __restrict__ params,
+                                                               const float* __restrict__ x,
+                                                               const float* __restrict__ t, int batch, MlpLayout P,
+                                                               MlpLayout A, float* __restrict__ acts,
+                                                               float* __restrict__ y) {
+    typedef float rows_t __attribute__((ext_vector_type(RB)));
+    __shared__ float w1s[kMlpHid * kRowW], w2s[kMlpHid * kRowW];
+    __shared__ __attribute__((aligned(16))) float in[kMlpIn * RB];  // the layer's input, [unit][row]
+    __shared__ __attribute__((aligned(16))) float part[kRowParts * kMlpHid * RB];
+    __shared__ float outp[kMlpHid / 64][RB], dys[RB];
+    const int tid = threadIdx.x, o = tid & (kMlpHid - 1), q = tid / kMlpHid;
+
+    float w2r[kMlpHid * kMlpHid / kRowThreads];
+    {
+        float w1r[kRowLoads];
+#pragma unroll
+        for (int u = 0; u < kRowLoads; ++u) {
+            const int e = tid + u * kRowThreads;
+            w1r[u] = e < kMlpHid * kMlpIn ? params[P.w1 + e] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < kMlpHid * kMlpHid / kRowThreads; ++u) w2r[u] = params[P.w2 + tid + u * kRowThreads];
+#pragma unroll
+        for (int u = 0; u < kRowLoads; ++u) {
+            const int e = tid + u * kRowThreads;
+            if (e < kMlpHid * kMlpIn) w1s[e] = w1r[u];  // rows of kMlpIn = kRowW floats already
+        }
+    }
+    const float bias1 = params[P.b1 + o], bias2 = params[P.b2 + o], w3 = params[P.w3 + o], b3 = params[P.b3];
+    bool w2_staged = false;
+
+    auto zero = [](rows_t& v) {
+#pragma unroll
+        for (int r = 0; r < RB; ++r) reinterpret_cast<float*>(&v)[r] = 0.0f;
+    };
+    for (int64_t r0 = int64_t(blockIdx.x) * RB; r0 < batch; r0 += int64_t(gridDim.x) * RB) {
+        const int rows = batch - r0 < RB ? int(batch - r0) : RB;
+        for (int e = tid; e < kMlpIn * RB; e += kRowThreads) {
+            const int r = e / kMlpIn, i = e - r * kMlpIn;
+            in[i * RB + r] = r < rows ? x[(r0 + r) * kMlpIn + i] : 0.0f;
+        }
+        __syncthreads();
+        rows_t acc;
+        // sum over one range of input units u0 .. u1 of w(u) * in[u]
+        auto run = [&](int u0, int u1, auto weight) {
+            zero(acc);
+#pragma unroll 4
+            for (int u = u0; u < u1; ++u) {
+                const float w = weight(u);
+                const rows_t v = *reinterpret_cast<const rows_t*>(in + u * RB);
+#pragma unroll
+                for (int r = 0; r < RB; ++r)
+                    reinterpret_cast<float*>(&acc)[r] =
+                        fmaf(w, reinterpret_cast<const float*>(&v)[r], reinterpret_cast<float*>(&acc)[r]);
+            }
+            *reinterpret_cast<rows_t*>(part + (q * kMlpHid + o) * RB) = acc;
+            __syncthreads();
+        };
+        // thread (o, q) finishes rows q, q + kRowParts, ... of unit o
+        auto total = [&](int r) {
+            float s = part[o * RB + r];
+#pragma unroll
+            for (int p = 1; p < kRowParts; ++p) s += part[(p * kMlpHid + o) * RB + r];
+            return s;
+        };
+        static_assert(RB <= kRowParts, "one row per thread and unit");
+        const bool mine = q < RB;
+        const bool live = q < rows;
+        const int64_t at = (r0 + q) * kMlpHid + o;
+        float z1 = 0.0f, z2 = 0.0f;
+
+        run(q * kRowPart1, q * kRowPart1 + kRowPart1 < kMlpIn ? q * kRowPart1 + kRowPart1 : kMlpIn,
+            [&](int u) { return w1s[o * kRowW + u]; });
+        if (mine) {
+            z1 = total(q) + bias1;
+            const float h = gelu_f(z1);
+            in[o * RB + q] = h;
+            if (GRAD && live) acts[A.h1 + at] = h;
+        }
+        if (!w2_staged) {
+#pragma unroll
+            for (int u = 0; u < kMlpHid * kMlpHid / kRowThreads; ++u) {
+                const int e = tid + u * kRowThreads;
+                w2s[(e / kMlpHid) * kRowW + e % kMlpHid] = w2r[u];
+            }
+            w2_staged = true;
+        }
+        __syncthreads();
+        run(q * kRowPart2, (q + 1) * kRowPart2, [&](int u) { return w2s[o * kRowW + u]; });
+        if (mine) {
+            z2 = total(q) + bias2;
+            const float h = gelu_f(z2);
+            if (GRAD && live) acts[A.h2 + at] = h;
+            float s = h * w3;
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+            if ((tid & 63) == 0) outp[o >> 6][q] = s;
+        }
+        __syncthreads();
+        if (tid < rows) {
+            float s = outp[0][tid];
+#pragma unroll
+            for (int w = 1; w < kMlpHid / 64; ++w) s += outp[w][tid];
+            s += b3;
+            if (!GRAD) {
+                y[r0 + tid] = s;
+            } else {
+                const float dy = 2.0f * (s - t[r0 + tid]) / float(batch);
+                acts[A.y + r0 + tid] = s;
+                acts[A.dy + r0 + tid] = dy;
+                dys[tid] = dy;
+            }
+        }
+        if (GRAD) {
+            __syncthreads();
+            if (mine) {
+                const float d = live ? dys[q] * w3 * gelu_grad_f(z2) : 0.0f;
+                in[o * RB + q] = d;
+                if (live) acts[A.d2 + at] = d;
+            }
+            __syncthreads();
+            run(q * kRowPart2, (q + 1) * kRowPart2, [&](int u) { return w2s[u * kRowW + o]; });
+            if (mine && live) acts[A.d1 + at] = total(q) * gelu_grad_f(z1);
+        }
+        __syncthreads();  // in, part and outp are reused
+    }
 }
 
-// loss = mean (y - t)^2, dy = 2 (y - t) / B  (one block)
-__global__ __launch_bounds__(256) void mse_kernel(const float* __restrict__ y, const float* __restrict__ t, int batch,
-                                                  float* __restrict__ dy, float* __restrict__ loss) {
+// Parameter gradients from the rows kernel's arrays: per layer
+// dW[o][i] = sum_b dZ[b][o] X[b][i] with X extended by a column of ones whose
+// products are db.  One 16 x 16 tile of dW per block of four waves: wave w
+// takes rows 16 s + 4 w .. + 3 of the batch in step s (v_mfma_f32_16x16x4f32,
+// operands straight from L2, eight steps of loads in flight), and the four
+// partial tiles are added in wave order.  The last block reduces the loss.
+constexpr int kGradTiles = (kMlpIn + 1 + 15) / 16;           // column tiles of a layer with its ones column
+constexpr int kGradRowTiles = kMlpHid / 16;
+constexpr int kGradLayerBlocks = kGradRowTiles * kGradTiles;  // layers 1 and 2
+constexpr int kGradBlocks = 2 * kGradLayerBlocks + kGradTiles + 1;
+
+__global__ __launch_bounds__(256) void mlp_weight_grad_kernel(const float* __restrict__ x, const float* __restrict__ t,
+                                                              int batch, MlpLayout P, MlpLayout A,
+                                                              const float* __restrict__ acts,
+                                                              float* __restrict__ grad, float* __restrict__ loss) {
+    typedef float f4g __attribute__((ext_vector_type(4)));
+    __shared__ float part[3][256];
     __shared__ double red[4];
-    double acc = 0.0;
-    for (int q = threadIdx.x; q < batch; q += 256) {
-        const float r = y[q] - t[q];
-        dy[q] = 2.0f * r / float(batch);
-        acc += double(r) * r;
+    const int blk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (blk == kGradBlocks - 1) {  // loss = mean (y - t)^2
+        double acc = 0.0;
+        for (int b = tid; b < batch; b += 256) {
+            const float r = acts[A.y + b] - t[b];
+            acc += double(r) * r;
+        }
+        const double tot = block_sum<256>(acc, red);
+        if (tid == 0 && loss) *loss = float(tot / batch);
+        return;
     }
-    const double tot = block_sum<256>(acc, red);
-    if (threadIdx.x == 0 && loss) *loss = float(tot / batch);
-}
-
-// dZ = dH * gelu'(Z) elementwise (dh and dz may be the same array)
-__global__ void gelu_bwd_kernel(const float* dh, const float* __restrict__ z, int64_t count, float* dz) {
-    const int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (q < count) dz[q] = dh[q] * gelu_grad_f(z[q]);
-}
-
-// dW[o][i] = sum_b dZ[b][o] X[b][i] (i < I); db[o] = sum_b dZ[b][o] (i == I).
-// Thread per (o, i); b ascending.
-__global__ void dense_bwd_weight_kernel(const float* __restrict__ dz, const float* __restrict__ x, int batch, int in,
-                                        int out_units, float* __restrict__ dw, float* __restrict__ db) {
-    const int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (q >= int64_t(out_units) * (in + 1)) return;
-    const int o = int(q / (in + 1)), i = int(q % (in + 1));
-    float acc = 0.0f;
-    if (i < in) {
-        for (int b = 0; b < batch; ++b) acc = fmaf(dz[int64_t(b) * out_units + o], x[int64_t(b) * in + i], acc);
-        dw[int64_t(o) * in + i] = acc;
-    } else {
-        for (int b = 0; b < batch; ++b) acc += dz[int64_t(b) * out_units + o];
-        db[o] = acc;
+    const int layer = blk < kGradLayerBlocks ? 1 : (blk < 2 * kGradLayerBlocks ? 2 : 3);
+    const int e = layer == 3 ? blk - 2 * kGradLayerBlocks : blk % kGradLayerBlocks;
+    const int o0 = (e / kGradTiles) * 16, i0 = (e % kGradTiles) * 16;
+    const int in = layer == 1 ? kMlpIn : kMlpHid, outs = layer == 3 ? 1 : kMlpHid;
+    const float* dz = acts + (layer == 1 ? A.d1 : layer == 2 ? A.d2 : A.dy);
+    const float* xs = layer == 1 ? x : acts + (layer == 2 ? A.h1 : A.h2);
+    const int c = lane & 15, g = lane >> 4;
+    const int o = o0 + c, i = i0 + c;
+    const bool o_in = o < outs, i_in = i < in, i_one = i == in;
+    f4g acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    constexpr int U = 8;
+    for (int b0 = 4 * wave + g; b0 - g < batch; b0 += 16 * U) {
+        float av[U], bv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int b = b0 + 16 * u;
+            const bool in_b = b < batch;
+            av[u] = (in_b && o_in) ? dz[int64_t(b) * outs + o] : 0.0f;
+            bv[u] = (in_b && i_in) ? xs[int64_t(b) * in + i] : (in_b && i_one ? 1.0f : 0.0f);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], bv[u], acc, 0, 0, 0);
     }
-}
-
-// dX[b][i] = sum_o dZ[b][o] W[o][i]; thread per (b, i); o ascending
-__global__ void dense_bwd_input_kernel(const float* __restrict__ dz, const float* __restrict__ w, int batch, int in,
-                                       int out_units, float* __restrict__ dx) {
-    const int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (q >= int64_t(batch) * in) return;
-    const int b = int(q / in), i = int(q % in);
-    float acc = 0.0f;
-    for (int o = 0; o < out_units; ++o) acc = fmaf(dz[int64_t(b) * out_units + o], w[int64_t(o) * in + i], acc);
-    dx[q] = acc;
+    if (wave > 0) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) part[wave - 1][v * 64 + lane] = acc[v];
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    float* dw = grad + (layer == 1 ? P.w1 : layer == 2 ? P.w2 : P.w3);
+    float* db = grad + (layer == 1 ? P.b1 : layer == 2 ? P.b2 : P.b3);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {  // accumulator v of lane (c, g): row 4 g + v, column c
+        const float s = ((acc[v] + part[0][v * 64 + lane]) + part[1][v * 64 + lane]) + part[2][v * 64 + lane];
+        const int row = o0 + 4 * g + v;
+        if (row >= outs) continue;
+        if (i_in)
+            dw[int64_t(row) * in + i] = s;
+        else if (i_one)
+            db[row] = s;
+    }
 }
 
 // Adam with bias correction: m = b1 m + (1-b1) g; v = b2 v + (1-b2) g^2;
@@ -266,37 +423,31 @@ namespace {
 unsigned blocks_for(int64_t count, int threads) { return unsigned((count + threads - 1) / threads); }
 }  // namespace
 
-hipError_t launch_mlp_forward(const float* params, const float* x, int batch, float* acts, float* y, hipStream_t s) {
+template <bool GRAD>
+static hipError_t launch_mlp_rows(const float* params, const float* x, const float* t, int batch, float* acts,
+                                  float* y, hipStream_t s) {
     const MlpLayout P{}, A = MlpLayout::acts(batch);
-    dense_fwd_kernel<<<batch, 128, 0, s>>>(x, kMlpIn, params + P.w1, params + P.b1, kMlpHid, acts + A.z1, acts + A.h1);
-    dense_fwd_kernel<<<batch, 128, 0, s>>>(acts + A.h1, kMlpHid, params + P.w2, params + P.b2, kMlpHid, acts + A.z2,
-                                            acts + A.h2);
-    dense_fwd_kernel<<<batch, 128, 0, s>>>(acts + A.h2, kMlpHid, params + P.w3, params + P.b3, 1, y, nullptr);
+    const int rb = batch <= kRowBlocks ? 1 : (batch <= 2 * kRowBlocks ? 2 : 4);
+    const unsigned need = blocks_for(batch, rb), blocks = need < unsigned(kRowBlocks) ? need : unsigned(kRowBlocks);
+    if (rb == 1)
+        mlp_rows_kernel<1, GRAD><<<blocks, kRowThreads, 0, s>>>(params, x, t, batch, P, A, acts, y);
+    else if (rb == 2)
+        mlp_rows_kernel<2, GRAD><<<blocks, kRowThreads, 0, s>>>(params, x, t, batch, P, A, acts, y);
+    else
+        mlp_rows_kernel<4, GRAD><<<blocks, kRowThreads, 0, s>>>(params, x, t, batch, P, A, acts, y);
     return hipGetLastError();
+}
+
+hipError_t launch_mlp_forward(const float* params, const float* x, int batch, float* acts, float* y, hipStream_t s) {
+    return launch_mlp_rows<false>(params, x, nullptr, batch, acts, y, s);
 }
 
 hipError_t launch_mlp_loss_grad(const float* params, const float* x, const float* t, int batch, float* acts,
                                 float* grad, float* loss, hipStream_t s) {
-    const MlpLayout P{}, A = MlpLayout::acts(batch);
-    hipError_t e = launch_mlp_forward(params, x, batch, acts, acts + A.y, s);
+    const hipError_t e = launch_mlp_rows<true>(params, x, t, batch, acts, nullptr, s);
     if (e != hipSuccess) return e;
-    float* dy = acts + A.dy;
-    mse_kernel<<<1, 256, 0, s>>>(acts + A.y, t, batch, dy, loss);
-    const int64_t bh = int64_t(batch) * kMlpHid;
-    // output layer: dw3, db3; dH2 = dy w3^T; dZ2 = dH2 gelu'(Z2)
-    dense_bwd_weight_kernel<<<blocks_for(kMlpHid + 1, 256), 256, 0, s>>>(dy, acts + A.h2, batch, kMlpHid, 1,
-                                                                          grad + P.w3, grad + P.b3);
-    dense_bwd_input_kernel<<<blocks_for(bh, 256), 256, 0, s>>>(dy, params + P.w3, batch, kMlpHid, 1, acts + A.d2);
-    gelu_bwd_kernel<<<blocks_for(bh, 256), 256, 0, s>>>(acts + A.d2, acts + A.z2, bh, acts + A.d2);
-    // hidden layer 2: dW2, db2; dH1 = dZ2 W2; dZ1 = dH1 gelu'(Z1)
-    dense_bwd_weight_kernel<<<blocks_for(int64_t(kMlpHid) * (kMlpHid + 1), 256), 256, 0, s>>>(
-        acts + A.d2, acts + A.h1, batch, kMlpHid, kMlpHid, grad + P.w2, grad + P.b2);
-    dense_bwd_input_kernel<<<blocks_for(bh, 256), 256, 0, s>>>(acts + A.d2, params + P.w2, batch, kMlpHid, kMlpHid,
-                                                                 acts + A.d1);
-    gelu_bwd_kernel<<<blocks_for(bh, 256), 256, 0, s>>>(acts + A.d1, acts + A.z1, bh, acts + A.d1);
-    // hidden layer 1: dW1, db1
-    dense_bwd_weight_kernel<<<blocks_for(int64_t(kMlpHid) * (kMlpIn + 1), 256), 256, 0, s>>>(
-        acts + A.d1, x, batch, kMlpIn, kMlpHid, grad + P.w1, grad + P.b1);
+    mlp_weight_grad_kernel<<<kGradBlocks, 256, 0, s>>>(x, t, batch, MlpLayout{}, MlpLayout::acts(batch), acts, grad,
+                                                       loss);
     return hipGetLastError();
 }
 

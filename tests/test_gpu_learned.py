@@ -199,3 +199,22 @@ def test_search_edge_cases():
         sp.search_tau_for_error(ga, gb, leaf, 0.0, pa, pb, ab_sq)
     with pytest.raises(sp.SpammError):
         sp.search_tau_for_error(ga, gb, leaf, 1e-3, pa, pb, 0.0)
+
+
+@pytest.mark.parametrize("batch", [2, 16, 257, 513, 1027])
+def test_forward_and_gradient_at_batch_edges(batch):
+    """One, two and four rows per block of the row kernel with its last block
+    ragged, and batches that end inside a step of the weight gradients.  FP32
+    sums of at most max(batch, 129) + 129 terms: n u relative to the sum of
+    magnitudes, taken at 1e-4 of each tensor's largest gradient as above."""
+    params = inputs.mlp_init(12)
+    x, t = _batch(batch, 13)
+    y_ref, _ = learned.forward(params.astype(np.float64), x.astype(np.float64))
+    y = sp.mlp_forward(gpu(params), gpu(x)).cpu().numpy()
+    assert np.max(np.abs(y - y_ref)) <= 1e-5 * max(1.0, np.max(np.abs(y_ref)))
+    loss_ref, g_ref = learned.loss_and_grad(params.astype(np.float64), x.astype(np.float64), t.astype(np.float64))
+    loss, g = sp.mlp_loss_grad(gpu(params), gpu(x), gpu(t))
+    assert float(loss.item()) == pytest.approx(loss_ref, rel=1e-5)
+    got, ref = learned.unpack(g.cpu().numpy().astype(np.float64)), learned.unpack(g_ref)
+    for name in ref:
+        assert np.max(np.abs(got[name] - ref[name])) <= 1e-4 * max(np.max(np.abs(ref[name])), 1e-30), name
