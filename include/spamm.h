@@ -337,8 +337,8 @@ spamm_status spamm_batch_run(int32_t count, const int64_t* n, const int32_t* lea
  *   tau_out       HOST double: the threshold found (the last one tried).
  *   pairs_out     HOST int64 (may be NULL): kept triples at tau_out.
  *   iters_out     HOST int32 (may be NULL): bisection steps taken.
- * Synchronous: reads each count back to the host (the stream is synchronised
- * once per tried tau).  EINVAL: target outside (0, 1], tol < 0,
+ * Synchronous: the search runs on the device in rounds of several thresholds
+ * and the stream is synchronised once every few rounds.  EINVAL: target outside (0, 1], tol < 0,
  * max_iters < 0, null pointer. */
 spamm_status spamm_search_valid_ratio(const double* pyr_a, const double* pyr_b, int64_t n, int32_t leaf,
                                       double target, double tol, int32_t max_iters, double* tau_out,

@@ -12,6 +12,7 @@
 #include "dma.h"
 #include "host.h"
 #include "internal.h"
+#include "search.h"
 
 namespace spamm_host {
 
@@ -832,59 +833,39 @@ spamm_status spamm_search_valid_ratio(const double* pyr_a, const double* pyr_b, 
     if ((st = check_workspace(g, workspace, workspace_bytes)) != SPAMM_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Layout L = make_layout(g);
-    double* d_ave = at<double>(workspace, L.scalars);
-    int32_t* bsums = at<int32_t>(workspace, L.bsums);
-    int64_t* d_pairs = at<int64_t>(workspace, L.pairs);
-    const int64_t nb = g.bdim * g.nwords;
-    const double triples = double(g.bdim) * double(g.bdim) * double(g.bdim);
-
-    if ((st = hip_check(spamm::launch_mean_norm_product(pyr_a, pyr_b, g.bdim, g.lv, d_ave, s), "mean kernel")) !=
-        SPAMM_OK)
+    // the norms sorted for counting, the counts and the state of the search, in
+    // regions of the workspace that hold no caller-visible pyramid or plan
+    double* rows_b = at<double>(workspace, L.spyr[0]);
+    double* cols_a = at<double>(workspace, L.spyr[1]);
+    double* ksums = at<double>(workspace, L.partials);
+    int32_t* counts[2] = {at<int32_t>(workspace, L.klist), at<int32_t>(workspace, L.pair_scratch)};
+    auto* states = at<spamm::SearchState>(workspace, L.bounds);
+    spamm::SearchState h{};
+    h.target = target;
+    h.tol = tol;
+    h.triples = double(g.bdim) * double(g.bdim) * double(g.bdim);
+    h.max_iters = max_iters;
+    if ((st = hip_check(spamm::launch_norms_sort(pyr_a, pyr_b, g.bdim, g.lv, rows_b, cols_a, ksums, states, h, s),
+                        "norm sort kernel")) != SPAMM_OK)
         return st;
-    double ave = 0.0;
-    if ((st = hip_check(hipMemcpyAsync(&ave, d_ave, sizeof(double), hipMemcpyDeviceToHost, s), "copy")) != SPAMM_OK)
-        return st;
-    if ((st = hip_check(hipStreamSynchronize(s), "synchronize")) != SPAMM_OK) return st;
-
-    int64_t cnt = 0;
-    auto ratio = [&](double t, double* r) -> spamm_status {
-        spamm_status e = hip_check(spamm::launch_plan_count(pyr_a, pyr_b, g.bdim, g.lv, t, bsums, s), "count kernel");
-        if (e != SPAMM_OK) return e;
-        e = hip_check(spamm::launch_plan_scan(bsums, nb, nullptr, nullptr, nb, d_pairs, s), "scan kernel");
-        if (e != SPAMM_OK) return e;
-        e = hip_check(hipMemcpyAsync(&cnt, d_pairs, sizeof(int64_t), hipMemcpyDeviceToHost, s), "copy");
-        if (e != SPAMM_OK) return e;
-        e = hip_check(hipStreamSynchronize(s), "synchronize");
-        *r = double(cnt) / triples;
-        return e;
-    };
-    // section 3.5.2: tau starts at ave; the upper bound k*ave grows by ave
-    // while the ratio there is still above the target; then bisection in
-    // [0, k*ave] until the ratio is within tol or max_iters bisections ran
-    constexpr int kMaxExpand = 1024;
-    int k = 1;
-    double hi = ave, r = 0.0;
-    if ((st = ratio(hi, &r)) != SPAMM_OK) return st;
-    while (r > target + tol && k < kMaxExpand) {
-        ++k;
-        hi = k * ave;
-        if ((st = ratio(hi, &r)) != SPAMM_OK) return st;
+    // kRounds rounds per host read: one round of bounds and up to 4 bisection
+    // steps in each of the others (a search at tol 0.01 takes 5 to 10)
+    constexpr int kRounds = 4;
+    for (int round = 0; !h.done;) {
+        for (int q = 0; q < kRounds; ++q, ++round)
+            if ((st = hip_check(spamm::launch_ratio_probe(rows_b, cols_a, ksums, g.bdim, states, counts, round, s),
+                                "count kernel")) != SPAMM_OK)
+                return st;
+        if ((st = hip_check(spamm::launch_ratio_finish(g.bdim, states, counts, round, s), "count kernel")) != SPAMM_OK)
+            return st;
+        if ((st = hip_check(hipMemcpyAsync(&h, states + (round & 1), sizeof(h), hipMemcpyDeviceToHost, s), "copy")) !=
+            SPAMM_OK)
+            return st;
+        if ((st = hip_check(hipStreamSynchronize(s), "synchronize")) != SPAMM_OK) return st;
     }
-    double tau = hi, lo = 0.0;
-    int it = 0;
-    while (std::fabs(r - target) > tol && it < max_iters) {
-        const double mid = 0.5 * (lo + hi);
-        if ((st = ratio(mid, &r)) != SPAMM_OK) return st;
-        tau = mid;
-        ++it;
-        if (r > target)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    *tau_out = tau;
-    if (pairs_out) *pairs_out = cnt;
-    if (iters_out) *iters_out = it;
+    *tau_out = h.tau;
+    if (pairs_out) *pairs_out = h.kept;
+    if (iters_out) *iters_out = h.iters;
     return SPAMM_OK;
 }
 

@@ -43,9 +43,6 @@ hipError_t launch_plan_mask(const double* pyr_a, const double* pyr_b, int64_t bd
 // Plan counts only (no bitmaps): per block of 64 tiles the number of kept triples.
 hipError_t launch_plan_count(const double* pyr_a, const double* pyr_b, int64_t bdim, int lv, double tau,
                              int32_t* block_sums, hipStream_t s);
-// Mean norm product over the bdim^3 leaf triples, into one device double.
-hipError_t launch_mean_norm_product(const double* pyr_a, const double* pyr_b, int64_t bdim, int lv, double* out,
-                                    hipStream_t s);
 // Plan: exclusive scan of the block sums into block_offsets; the total goes to
 // offsets[T] and *pairs.  Each of the three outputs may be null; block_offsets
 // and offsets may be the same array (they are written at disjoint indices).

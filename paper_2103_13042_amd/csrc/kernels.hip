@@ -501,40 +501,6 @@ hipError_t launch_plan_count(const double* pyr_a, const double* pyr_b, int64_t b
     return hipGetLastError();
 }
 
-// Mean of nA[i,k] * nB[k,j] over all leaf triples of the bdim^3 grid, as
-// sum_k (sum_i nA[i,k]) (sum_j nB[k,j]) / bdim^3 (one block; FP64; fixed order).
-constexpr int kAveThreads = 1024;
-
-__global__ __launch_bounds__(kAveThreads) void mean_norm_product_kernel(const double* __restrict__ pyr_a,
-                                                                        const double* __restrict__ pyr_b,
-                                                                        int64_t bdim, int lv, double* __restrict__ out) {
-    __shared__ double wsum[kAveThreads / 64];
-    const int64_t side = int64_t(1) << lv;
-    const double* la = pyr_a + level_offset(lv);
-    const double* lb = pyr_b + level_offset(lv);
-    double part = 0.0;
-    for (int64_t k = threadIdx.x; k < bdim; k += kAveThreads) {
-        double ca = 0.0, rb = 0.0;
-        for (int64_t i = 0; i < bdim; ++i) ca += la[i * side + k];
-        for (int64_t j = 0; j < bdim; ++j) rb += lb[k * side + j];
-        part += ca * rb;
-    }
-    for (int o = 32; o >= 1; o >>= 1) part += __shfl_xor(part, o);
-    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = part;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double tot = 0.0;
-        for (int w = 0; w < kAveThreads / 64; ++w) tot += wsum[w];
-        *out = tot / (double(bdim) * double(bdim) * double(bdim));
-    }
-}
-
-hipError_t launch_mean_norm_product(const double* pyr_a, const double* pyr_b, int64_t bdim, int lv, double* out,
-                                    hipStream_t s) {
-    mean_norm_product_kernel<<<1, kAveThreads, 0, s>>>(pyr_a, pyr_b, bdim, lv, out);
-    return hipGetLastError();
-}
-
 // Exclusive scan of the block sums (one per 64 output tiles): one block, each
 // thread a contiguous segment, wave scans with shuffles, then across waves.
 constexpr int kScanThreads = 256;

@@ -97,3 +97,49 @@ def test_search_reproduces_table1(golden, n):
         assert abs(tau - tau_paper) <= 1.5e-6, (n, target, tau, tau_paper)
         assert abs(cnt / bd**3 - target / 100.0) <= 0.01
         assert 1 <= it < 20
+
+
+@pytest.mark.parametrize("n,alpha,target", [(20, 0.05, 0.5), (64, 0.2, 0.3), (2080, 0.3, 0.004), (2049, 0.02, 0.1),
+                                            (4200, 0.5, 0.002)])
+def test_search_matches_brute_force_at_grid_edges(n, alpha, target):
+    """1, 2, 65 and 132 tiles per side, and bounds that grow well past the 15
+    multiples of the mean that one round tries: tau, count and bisections of
+    the paper's search written out over the plain list of products."""
+    leaf, tol, max_iters = 32, 0.0005, 20
+    a, b = inputs.exp_decay_torch(n, alpha, 40, DEV), inputs.exp_decay_torch(n, alpha, 41, DEV)
+    pa, pb = sp.pyramid(a, leaf), sp.pyramid(b, leaf)
+    tau, pairs, iters = sp.search_valid_ratio(pa, pb, n, leaf, target, tol, max_iters)
+    bd = sp.bdim(n, leaf)
+    na = sp.pyramid_levels(pa, n, leaf)[-1][:bd, :bd].cpu().numpy()
+    nb = sp.pyramid_levels(pb, n, leaf)[-1][:bd, :bd].cpu().numpy()
+    prods = np.sort((na[:, :, None] * nb[None, :, :]).ravel())
+    count = lambda t: prods.size - int(np.searchsorted(prods, t, side="left"))
+    ave = float(np.sum(na.sum(axis=0) * nb.sum(axis=1))) / bd**3
+    k, hi = 1, ave
+    while count(hi) / bd**3 > target + tol and k < 1024:
+        k += 1
+        hi = k * ave
+    lo, want, steps = 0.0, hi, 0
+    while abs(count(want) / bd**3 - target) > tol and steps < max_iters:
+        want = 0.5 * (lo + hi)
+        steps += 1
+        if count(want) / bd**3 > target:
+            lo = want
+        else:
+            hi = want
+    assert (pairs, iters) == (count(want), steps) and tau == pytest.approx(want, rel=1e-12)
+
+
+def test_search_counts_as_the_plan_with_infinite_and_zero_norms():
+    """A zero norm against an infinite one gives a NaN product, which the plan
+    drops: the search's count is the plan's at the threshold it returns."""
+    n, leaf = 256, 32
+    a, b = torch.zeros(n, n, device=DEV), torch.rand(n, n, device=DEV)
+    a[:64] = 1.0
+    b[32, 200] = float("inf")
+    pa, pb = sp.pyramid(a, leaf), sp.pyramid(b, leaf)
+    tau, pairs, _ = sp.search_valid_ratio(pa, pb, n, leaf, 0.3)
+    if tau == tau:  # the mean of products with an infinity may be NaN: then nothing is kept
+        assert int(sp.plan(pa, pb, n, leaf, tau)[2].item()) == pairs
+    else:
+        assert pairs == 0
