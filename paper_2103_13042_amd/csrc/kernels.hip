@@ -27,22 +27,39 @@ namespace spamm {
 constexpr int kNormThreads = 256;
 constexpr int kNormCols = kNormThreads * 4;
 
-// strip `strip` (tile row) x column chunk `chunk` of x; tile (strip, tj) goes to
-// sumsq / norms[strip * ld + tj] (either may be null)
 // NT: nontemporal loads, for a pass whose input is larger than the
 // infinity cache: A and B are read once here, and keeping them out of the
 // caches leaves room for the multiply's tiles (measured on the N = 8192 step:
 // norm pass 112 -> 90 us, multiply unchanged).  Below that size the multiply
 // profits from what the pass leaves in the cache (batch of small products:
-// 2 % slower with NT).
-template <bool NT, typename T>
-__device__ __forceinline__ T load_nt(const T* p) {
-    if constexpr (NT)
-        return __builtin_nontemporal_load(p);
-    else
-        return *p;
+// 2 % slower with NT).  ALIGNED: the address is a multiple of 16, else of 4.
+template <bool ALIGNED, bool NT>
+__device__ __forceinline__ f4 load_row(const float* p) {
+    if constexpr (ALIGNED) {
+        const f4* q = reinterpret_cast<const f4*>(p);
+        if constexpr (NT)
+            return __builtin_nontemporal_load(q);
+        else
+            return *q;
+    } else {
+        const f4_dw* q = reinterpret_cast<const f4_dw*>(p);
+        if constexpr (NT)
+            return __builtin_nontemporal_load(q);
+        else
+            return *q;
+    }
 }
 
+// strip `strip` (tile row) x column chunk `chunk` of x; tile (strip, tj) goes to
+// sumsq / norms[strip * ld + tj] (either may be null)
+//
+// Rows that are not 16-byte aligned (VEC false: n % 4 != 0, or x itself only
+// 4-byte aligned) are read by the same 16-byte loads at 4-byte alignment,
+// which global loads accept.  The thread whose four columns cross the
+// matrix's edge reads the row's last four instead and drops the ones that its
+// neighbour holds, so no lane runs a loop of its own (one 64-row column of
+// 4-byte loads by that thread took as long as the strip: n = 5003, leaf 64,
+// one matrix 42 -> 20 us, as fast as n = 5000).
 template <int LEAF, bool VEC, bool NT = false>
 __device__ __forceinline__ void leaf_sumsq_strip(const float* __restrict__ x, int64_t n, int64_t bdim, int64_t strip,
                                                  int64_t chunk, double* sumsq, double* norms, int64_t ld) {
@@ -50,133 +67,43 @@ __device__ __forceinline__ void leaf_sumsq_strip(const float* __restrict__ x, in
     const int64_t r0 = strip * LEAF;
     const int64_t r1 = r0 + LEAF < n ? r0 + LEAF : n;
     const int t = threadIdx.x;
-    if (VEC) {  // rows 16-byte aligned (n % 4 == 0): columns 4t .. 4t+3 of the chunk
-        const int64_t col = chunk * kNormCols + 4 * t;
-        double acc0 = 0.0, acc1 = 0.0;
-        if (col < n) {
-            const float* p = x + r0 * n + col;
-            int64_t r = r0;
+    const int64_t col = chunk * kNormCols + 4 * t;  // columns 4t .. 4t+3 of the chunk
+    double acc0 = 0.0, acc1 = 0.0;
+    if (!VEC && n < 4) {  // no four columns to read
+        for (int64_t r = r0; r < r1; ++r)
+            for (int64_t c = col; c < n; ++c) acc0 += double(x[r * n + c]) * double(x[r * n + c]);
+    } else if (col < n) {
+        const int back = VEC || col + 4 <= n ? 0 : int(col + 4 - n);  // columns that the thread before holds
+        const float* p = x + r0 * n + col - back;
+        auto add = [&](f4 v) {
+            if (!VEC) {
+                v.x = back > 0 ? 0.0f : v.x;
+                v.y = back > 1 ? 0.0f : v.y;
+                v.z = back > 2 ? 0.0f : v.z;
+            }
+            acc0 += double(v.x) * double(v.x) + double(v.y) * double(v.y);
+            acc1 += double(v.z) * double(v.z) + double(v.w) * double(v.w);
+        };
+        int64_t r = r0;
 #pragma unroll 4
-            for (; r + 1 < r1; r += 2) {
-                f4 v = load_nt<NT>(reinterpret_cast<const f4*>(p));
-                f4 w = load_nt<NT>(reinterpret_cast<const f4*>(p + n));
-                p += 2 * n;
-                acc0 += double(v.x) * double(v.x) + double(v.y) * double(v.y);
-                acc1 += double(v.z) * double(v.z) + double(v.w) * double(v.w);
-                acc0 += double(w.x) * double(w.x) + double(w.y) * double(w.y);
-                acc1 += double(w.z) * double(w.z) + double(w.w) * double(w.w);
-            }
-            if (r < r1) {
-                f4 v = load_nt<NT>(reinterpret_cast<const f4*>(p));
-                acc0 += double(v.x) * double(v.x) + double(v.y) * double(v.y);
-                acc1 += double(v.z) * double(v.z) + double(v.w) * double(v.w);
-            }
+        for (; r + 1 < r1; r += 2) {
+            const f4 v = load_row<VEC, NT>(p);
+            const f4 w = load_row<VEC, NT>(p + n);
+            p += 2 * n;
+            add(v);
+            add(w);
         }
-        double s = acc0 + acc1;
-#pragma unroll
-        for (int off = 1; off < G; off <<= 1) s += __shfl_xor(s, off);
-        const int64_t tj = col / LEAF;
-        if ((t % G) == 0 && tj < bdim) {
-            const int64_t i = strip * ld + tj;
-            if (sumsq) sumsq[i] = s;
-            if (norms) norms[i] = sqrt(s);
-        }
-        return;
+        if (r < r1) add(load_row<VEC, NT>(p));
     }
-    // Rows not 16-byte aligned (n % 4 != 0, or x itself only 4-byte aligned):
-    // 16-byte loads at aligned positions, counted from xa, the 16-byte
-    // boundary at or below x (xoff floats before it, inside the same
-    // allocation since allocations are at least 16-byte aligned).  In row r
-    // the chunk starts s = (xoff + r n + cb) mod 4 elements past such a
-    // position, so thread t's load holds columns 4t - s .. 4t - s + 3 of the
-    // chunk: those below the thread's own tile (first thread of a tile, s > 0)
-    // belong to the tile before it, those below 0 to the previous chunk (which
-    // loads them with its last thread's second load, below).  A load that
-    // would reach past the end of the matrix is done element-wise.
-    const int xoff = int((reinterpret_cast<uintptr_t>(x) >> 2) & 3);
-    const float* xa = x - xoff;
-    const int64_t cb = chunk * kNormCols, nn = n * n, end = nn + xoff;  // end: counted from xa
-    const int lim = int(n - cb < kNormCols ? n - cb : kNormCols);  // columns of this chunk
-    const int home = (4 * t) / LEAF * LEAF;  // first column of the thread's tile
-    double acc_home = 0.0, acc_prev = 0.0;
-    auto add = [&](int64_t q, int c0) {  // the 4 elements at xa[q ..] = columns c0 .. c0+3
-        if (c0 + 3 < 0 || c0 >= lim) return;
-        float v[4];
-        if (q + 4 <= end) {
-            const f4 w = *reinterpret_cast<const f4*>(xa + q);
-            v[0] = w.x;
-            v[1] = w.y;
-            v[2] = w.z;
-            v[3] = w.w;
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = (q + e < end) ? xa[q + e] : 0.0f;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int c = c0 + e;
-            if (c >= 0 && c < lim) {
-                const double d = double(v[e]);
-                if (c < home)
-                    acc_prev += d * d;
-                else
-                    acc_home += d * d;
-            }
-        }
-    };
-    // rows whose loads all end inside the matrix (r n + cb + kNormCols + 4 <=
-    // n^2): unconditional loads, the chunk's columns picked by a select
-    const int64_t room = nn - cb - kNormCols - 4;
-    int64_t r_fast = room < 0 ? r0 : room / n + 1;
-    r_fast = r_fast < r0 ? r0 : (r_fast > r1 ? r1 : r_fast);
-    auto take = [&](const f4& w, int c0) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int c = c0 + e;
-            const double d = (c >= 0 && c < lim) ? double(w[e]) : 0.0;
-            if (c < home)
-                acc_prev += d * d;
-            else
-                acc_home += d * d;
-        }
-    };
-#pragma unroll 4
-    for (int64_t r = r0; r < r_fast; ++r) {
-        const int64_t base = xoff + r * n + cb;
-        const int s = int(base & 3);
-        take(load_nt<NT>(reinterpret_cast<const f4*>(xa + base - s + 4 * t)), 4 * t - s);
-    }
-    if (t == kNormThreads - 1) {  // the chunk's last s columns of those rows
-        for (int64_t r = r0; r < r_fast; ++r) {
-            const int64_t base = xoff + r * n + cb;
-            const int s = int(base & 3);
-            if (s > 0) take(*reinterpret_cast<const f4*>(xa + base - s + kNormCols), kNormCols - s);
-        }
-    }
-    for (int64_t r = r_fast; r < r1; ++r) {  // the matrix's last rows: guarded loads
-        const int64_t base = xoff + r * n + cb;
-        const int s = int(base & 3);
-        const int64_t a0 = base - s;
-        add(a0 + 4 * t, 4 * t - s);
-        if (t == kNormThreads - 1 && s > 0) add(a0 + kNormCols, kNormCols - s);
-    }
-    double s = acc_home;
+    double s = acc0 + acc1;
 #pragma unroll
     for (int off = 1; off < G; off <<= 1) s += __shfl_xor(s, off);
-    __shared__ double prev[kNormThreads];  // per tile of the chunk: its part held by the next tile's first thread
-    if ((t % G) == 0) prev[t / G] = acc_prev;
-    __syncthreads();
-    if ((t % G) == 0) {
-        const int g = t / G;
-        if (g + 1 < kNormThreads / G) s += prev[g + 1];
-        const int64_t tj = cb / LEAF + g;
-        if (tj < bdim) {
-            const int64_t i = strip * ld + tj;
-            if (sumsq) sumsq[i] = s;
-            if (norms) norms[i] = sqrt(s);
-        }
+    const int64_t tj = col / LEAF;
+    if ((t % G) == 0 && tj < bdim) {
+        const int64_t i = strip * ld + tj;
+        if (sumsq) sumsq[i] = s;
+        if (norms) norms[i] = sqrt(s);
     }
-    __syncthreads();  // prev is reused by the block's next strip
 }
 
 // words the first block of a norm pass sets to zero (a pair counter, the

@@ -639,3 +639,21 @@ def test_fused_plan_equals_staged_plan(n, leaf, tau, kind):
         assert torch.equal(c1, c2), rep
     if n == 8192:
         assert total == closed_form_pair_count(n, leaf, tau)[0]
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 6, 63, 129, 1021, 1022, 1023, 1025, 1027])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_norms_of_unaligned_rows(n, offset):
+    """Rows at 4-byte alignment (n odd, or the matrix itself one float past a
+    16-byte boundary), the matrix's edge in each of a thread's four columns and
+    past a 1024-column chunk, fewer than four columns.  FP64 sums of at most
+    2^16 exact squares: 2^16 u = 7e-12 relative at the worst order."""
+    flat = torch.rand(n * n + 4, device=DEV)
+    x = flat[offset : offset + n * n].view(n, n)
+    xd = x.double().cpu().numpy()
+    for leaf in (16, 32, 64, 128, 256):
+        bd = sp.bdim(n, leaf)
+        pad = np.zeros((bd * leaf, bd * leaf))
+        pad[:n, :n] = xd
+        want = np.sqrt((pad**2).reshape(bd, leaf, bd, leaf).sum(axis=(1, 3)))
+        assert np.allclose(sp.norms(x, leaf).cpu().numpy(), want, rtol=1e-11, atol=0.0), leaf
