@@ -9,6 +9,7 @@
 #include <mutex>
 
 #include "spamm.h"
+#include "spamm_noalloc.h"
 #include "dma.h"
 #include "host.h"
 #include "internal.h"
@@ -52,7 +53,9 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 }  // namespace
 
-Layout make_layout(const Geom& g) {
+namespace {
+// lean: ragged sizes without the regions that only speed them up
+Layout layout_of(const Geom& g, bool lean) {
     Layout L{};
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -75,15 +78,14 @@ Layout make_layout(const Geom& g) {
     L.mprefix = take(sizeof(int32_t) * (nm + 1));
     L.mitems = take(sizeof(uint32_t) * nm * size_t(g.bdim));
     // leaf 128 on the LDS-DMA kernel: two items per kept pair, their prefix
-    const bool l128 = g.leaf == 128 && g.n % 128 == 0 && g.bdim <= spamm::kLeaf128MaxBdim;
+    const bool l128 = g.leaf == 128 && !lean && g.n >= 4 && g.bdim <= spamm::kLeaf128MaxBdim;
     L.leaf128_dma = l128;
     L.items128 = take(l128 ? sizeof(uint32_t) * 2 * size_t(g.ntiles) * size_t(g.bdim) : 0);
     L.uprefix128 = take(l128 ? sizeof(int32_t) * size_t(g.ntiles + 1) : 0);
     L.bounds = take(sizeof(int64_t) * 4 * spamm::kSplitMaxGroups);
-    // partial sums of shared macro tiles (LDS-DMA kernel: leaf 64 or 128, N a
-    // multiple of 128), two slots per workgroup, at most one workgroup per
-    // macro tile
-    const bool dma = (g.leaf == 64 && g.n % 128 == 0) || l128;
+    // partial sums of shared macro tiles (LDS-DMA kernel: leaf 64 or 128), two
+    // slots per workgroup, at most one workgroup per macro tile
+    const bool dma = (g.leaf == 64 && !lean) || l128;
     const size_t macros = l128 ? size_t(g.ntiles) : nm;
     const size_t groups =
         macros < size_t(spamm::kSplitMaxGroups) ? (macros + 7) / 8 * 8 : size_t(spamm::kSplitMaxGroups);
@@ -95,6 +97,20 @@ Layout make_layout(const Geom& g) {
     L.partials = take(sizeof(double) * 1024);
     L.total = o;
     return L;
+}
+}  // namespace
+
+// The LDS-DMA kernel's regions (up to 32 MiB of partial sums, leaf 128's item
+// list) are left out for a ragged size that fits the static scratch of
+// spamm_multiply_noalloc only without them: its macro tiles are then not
+// shared between workgroups (leaf 64), or it takes the single-tile kernel
+// (leaf 128).  The choice is by size alone, so that every workspace of a size
+// takes the same route.
+Layout make_layout(const Geom& g) {
+    const Layout full = layout_of(g, false);
+    if (g.n % 128 == 0 || full.total <= size_t(SPAMM_NOALLOC_SCRATCH_BYTES)) return full;
+    const Layout lean = layout_of(g, true);
+    return lean.total <= size_t(SPAMM_NOALLOC_SCRATCH_BYTES) ? lean : full;
 }
 
 bool overlaps(const void* p, size_t pbytes, const void* q, size_t qbytes) {
@@ -305,7 +321,10 @@ spamm_status enqueue_multiply(const Geom& g, const float* a, const float* b, con
                               const int32_t* klist, float* c, void* ws, hipStream_t s) {
     const bool vec = (g.n % 4) == 0 && aligned16(a) && aligned16(b);
     const Layout L = make_layout(g);
-    if (L.leaf128_dma && vec)
+    if (g.n < 4 && g.leaf >= 64)  // one tile, smaller than the 16-byte copies of the LDS-DMA kernel: any leaf is one tile
+        return hip_check(spamm::launch_multiply_leaf16(a, b, c, g.n, g.bdim, offsets, klist, vec, s),
+                         "multiply kernel");
+    if (L.leaf128_dma)
         return hip_check(spamm::launch_leaf128_multiply(a, b, c, g.n, g.bdim, at<int32_t>(ws, L.uprefix128),
                                                         at<uint32_t>(ws, L.items128), at<int64_t>(ws, L.bounds),
                                                         at<float>(ws, L.fix_slots), device_cus(), s),

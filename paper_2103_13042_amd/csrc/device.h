@@ -18,6 +18,13 @@ __device__ __forceinline__ T* global_ptr(T* p) {
     return (T*)(__attribute__((address_space(1))) T*)reinterpret_cast<uintptr_t>(p);
 }
 
+// v, as a value the compiler knows nothing about (what is computed from it is
+// neither shared with other code nor moved out of a loop)
+__device__ __forceinline__ int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // whether a launch gated on the plan's pair count runs (PairGate, internal.h)
 template <typename Gate>
 __device__ __forceinline__ bool gate_open(const Gate& g) {

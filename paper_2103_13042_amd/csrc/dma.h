@@ -58,6 +58,12 @@ __device__ __forceinline__ void wait_copies(int stores) {
     }
 }
 
+// 16 bytes per lane from src (4-byte aligned) to dst + 16 * lane in LDS; dst is
+// the same in every lane
+__device__ __forceinline__ void copy_to_lds(const float* src, char* dst) {
+    __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+
 // The copy-completion waits above count this kernel's own memory operations;
 // a register spill would add scratch accesses to that count, and in any
 // multiply kernel it would put slow scratch traffic in the inner loop.  Every
@@ -75,14 +81,14 @@ static hipError_t check_no_scratch(K kernel, int* state) {
 }
 
 
-// Modelled cost of the macro tiles before m (row-major), bdim = 2 mb even:
-// kStoreCost per tile + kItemCost per union k (uprefix) + kKeptCost per kept
-// pair, the pairs of the tiles before m read off the plan's offsets (all tile
-// rows above the macro row, and the first 2J tiles of its two tile rows).
+// Modelled cost of the macro tiles before m (row-major): kStoreCost per tile +
+// kItemCost per union k (uprefix) + kKeptCost per kept pair, the pairs of the
+// tiles before m read off the plan's offsets (all tile rows above the macro
+// row, and the first 2J tiles of its two tile rows; with bdim odd the last
+// macro row has one).
 // offsets == nullptr: every item feeds all four quarters (leaf-128 tiles).
-__device__ inline int64_t macro_cost_before(int64_t m, int64_t mb, const int32_t* __restrict__ uprefix,
+__device__ inline int64_t macro_cost_before(int64_t m, int64_t mb, int64_t bdim, const int32_t* __restrict__ uprefix,
                                             const int32_t* __restrict__ offsets) {
-    const int64_t bdim = 2 * mb;
     int64_t kept;
     if (offsets == nullptr) {
         kept = 4 * int64_t(uprefix[m]);
@@ -90,7 +96,8 @@ __device__ inline int64_t macro_cost_before(int64_t m, int64_t mb, const int32_t
         kept = offsets[bdim * bdim];
     } else {
         const int64_t I = m / mb, J = m - (m / mb) * mb, r0 = 2 * I * bdim;
-        kept = int64_t(offsets[r0 + 2 * J]) + offsets[r0 + bdim + 2 * J] - offsets[r0 + bdim];
+        kept = int64_t(offsets[r0 + 2 * J]);
+        if (2 * I + 1 < bdim) kept += int64_t(offsets[r0 + bdim + 2 * J]) - offsets[r0 + bdim];
     }
     return kStoreCost * m + kItemCost * int64_t(uprefix[m]) + kKeptCost * kept;
 }
@@ -100,31 +107,33 @@ __device__ inline int64_t macro_cost_before(int64_t m, int64_t mb, const int32_t
 // reaches gg * total / G (the store of a macro tile counted before its items),
 // as (macro tile m, item index p) with uprefix[m] <= p < uprefix[m + 1], or
 // (m, uprefix[m]) at a clean macro-tile start (the end is (nm, uprefix[nm])).
+// whole: the boundary at the start of that macro tile (no shared tiles).
 struct SplitBound {
     int64_t m, p;
 };
 
-__device__ inline SplitBound split_bound(int64_t gg, int64_t G, int64_t mb, const int32_t* __restrict__ uprefix,
-                                         const int32_t* __restrict__ offsets, const uint32_t* __restrict__ items) {
+__device__ inline SplitBound split_bound(int64_t gg, int64_t G, int64_t mb, int64_t bdim, bool whole,
+                                         const int32_t* __restrict__ uprefix, const int32_t* __restrict__ offsets,
+                                         const uint32_t* __restrict__ items) {
     const int lane = threadIdx.x & 63;
     const int64_t nm = mb * mb;
     if (gg <= 0) return {0, 0};
     if (gg >= G) return {nm, int64_t(uprefix[nm])};
-    const int64_t T = gg * macro_cost_before(nm, mb, uprefix, offsets) / G;
+    const int64_t T = gg * macro_cost_before(nm, mb, bdim, uprefix, offsets) / G;
     // largest m < nm with cost_before(m) <= T: 64-ary search, invariant
     // cost_before(lo) <= T and the answer in [lo, hi)
     int64_t lo = 0, hi = nm;
     while (hi - lo > 1) {
         const int64_t step = (hi - lo + 63) / 64;
         const int64_t c = lo + step * (lane + 1);
-        const bool le = lane < 63 && c < hi && macro_cost_before(c, mb, uprefix, offsets) <= T;
+        const bool le = lane < 63 && c < hi && macro_cost_before(c, mb, bdim, uprefix, offsets) <= T;
         const int cnt = __popcll(__ballot(le));  // monotone: lanes 0 .. cnt-1
         lo += step * cnt;
         hi = (lo + step < hi) ? lo + step : hi;
     }
     const int64_t m = lo, u0 = uprefix[m], u1 = uprefix[m + 1];
-    int64_t c0 = macro_cost_before(m, mb, uprefix, offsets) + kStoreCost;  // cost before item u0
-    if (c0 >= T) return {m, u0};
+    int64_t c0 = macro_cost_before(m, mb, bdim, uprefix, offsets) + kStoreCost;  // cost before item u0
+    if (whole || c0 >= T) return {m, u0};
     for (int64_t base = u0; base < u1; base += 64) {
         const int64_t i = base + lane;
         const int cst = i < u1 ? kItemCost + kKeptCost * __popc(items[i] & 15u) : 0;

@@ -84,8 +84,10 @@ hipError_t launch_small_multiply(const float* a, const float* b, float* c, int64
                                  const double* na, const double* nb, int64_t ld, double tau, int64_t* pairs,
                                  hipStream_t s);
 
-// Multiply: persistent, cost-balanced multiply of the kept pairs into C
-// (leaf 32, 64, 128; leaf 16 goes to launch_multiply_leaf16).
+// Multiply on single output tiles: persistent, cost-balanced multiply of the
+// kept pairs into C (leaf 128 where the LDS-DMA kernel does not run: more than
+// kLeaf128MaxBdim tiles per side, or no room for its item list; leaf 16 goes
+// to launch_multiply_leaf16).
 // pair_scratch holds bdim^3 int32 (each group's packed (tile, k) pairs).
 hipError_t launch_multiply(const float* a, const float* b, float* c, int64_t n, int32_t leaf, int64_t bdim,
                            const int32_t* offsets, const int32_t* klist, int32_t* pair_scratch, bool vec,
@@ -100,11 +102,12 @@ hipError_t launch_multiply_leaf16(const float* a, const float* b, float* c, int6
 // per-macro-tile k bitmaps into words [mb*mb*4*nwords], union sizes into
 // ucount [mb*mb], their exclusive prefix into uprefix [mb*mb + 1], and the
 // union k lists as packed items into items [<= mb*mb*bdim].  Multiply: the
-// persistent kernel over that schedule; the leaf-64 LDS-DMA kernel (which
+// persistent kernel over that schedule; the leaf-64 LDS-DMA kernel (n >= 4; it
 // also reads the plan's offsets for its cost model) writes four records per
 // workgroup to bounds [4 * kSplitMaxGroups] and the partial sums of macro
 // tiles shared between workgroups to fix_slots [kSplitMaxGroups * 2 * 128 *
-// 128], which a second kernel adds into C.
+// 128], which a second kernel adds into C; with fix_slots null no macro tile is
+// shared.
 struct MacroSchedule {
     uint64_t* words;
     int32_t *ucount, *uprefix;
@@ -117,8 +120,7 @@ hipError_t launch_macro_schedule(const int32_t* offsets, const int32_t* klist, i
 hipError_t launch_macro_multiply(const float* a, const float* b, float* c, int64_t n, int32_t leaf, int64_t bdim,
                                  const int32_t* offsets, const MacroSchedule& ms, bool vec, int num_cus,
                                  hipStream_t s);
-// Leaf 128 with N a multiple of 128 (bdim <= kLeaf128MaxBdim) on the LDS-DMA
-// kernel: two items per kept pair (uprefix [bdim*bdim + 1], items
+// Leaf 128 (4 <= n, bdim <= kLeaf128MaxBdim) on the LDS-DMA kernel: two items per kept pair (uprefix [bdim*bdim + 1], items
 // [2 * pairs]), then the multiply and fixup kernels with one macro tile per
 // output tile.
 constexpr int64_t kLeaf128MaxBdim = 512;  // item fields: tile index < 512, k half < 1024

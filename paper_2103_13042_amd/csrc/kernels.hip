@@ -540,8 +540,8 @@ hipError_t launch_plan_fill(const uint64_t* masks, const int32_t* counts, const 
 // Tile loads are unconditional (out-of-range lanes read a valid address and
 // select zero) so the wait before storing item it+1 leaves item it+2's loads
 // outstanding.  Wave w computes
-// the (w>>1, w&1) quadrant of the output tile with FP32 MFMA: 32x32x2 for
-// quadrants of 32 or 64, 16x16x4 for quadrants of 16.  In MFMA step s, lane
+// the (w>>1, w&1) quadrant of the output tile with FP32 MFMA (32x32x2).
+// In MFMA step s, lane
 // group g takes k = g*(KC/G) + s, so a lane reads 4 consecutive A operands
 // with one 16-byte LDS load; B rows are XOR-swizzled by lane group so the G
 // groups read disjoint LDS banks.  Tiles are finished in ascending k and written
@@ -560,18 +560,11 @@ constexpr int kRing = 512;  // packed pairs held in LDS (a power of two)
 #ifndef SPAMM_OCC64
 #define SPAMM_OCC64 2
 #endif
-#ifndef SPAMM_OCC32
-#define SPAMM_OCC32 2
-#endif
 #ifndef SPAMM_OCC128
 #define SPAMM_OCC128 1
 #endif
 template <int LEAF>
 struct MulCfg;
-template <>
-struct MulCfg<32> {
-    static constexpr int MF = 16, KC = 32, OCC = SPAMM_OCC32;
-};
 template <>
 struct MulCfg<64> {
     static constexpr int MF = 32, KC = SPAMM_KC64, OCC = SPAMM_OCC64;
@@ -616,16 +609,6 @@ struct Mfma<32> {
     static __device__ __forceinline__ int row(int r, int l) { return 8 * (r >> 2) + 4 * (l >> 5) + (r & 3); }
     static __device__ __forceinline__ int col(int, int l) { return l & 31; }
 };
-template <>
-struct Mfma<16> {
-    typedef f4 acc_t;
-    static __device__ __forceinline__ acc_t step(float a, float b, acc_t c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ int row(int r, int l) { return 4 * (l >> 4) + r; }
-    static __device__ __forceinline__ int col(int, int l) { return l & 15; }
-};
-
 // First tile of logical group g: smallest t with (kPairCost*off[t] + t) * G >= g * total.
 __device__ __forceinline__ int64_t partition_start(const int32_t* __restrict__ off, int64_t nt, int64_t g,
                                                    int64_t groups, int64_t total) {
@@ -894,8 +877,6 @@ hipError_t launch_multiply(const float* a, const float* b, float* c, int64_t n, 
                            int num_cus, hipStream_t s) {
     switch (leaf) {
         case 16: return launch_multiply_leaf16(a, b, c, n, bdim, offsets, klist, vec, s);
-        case 32: return launch_mul<32>(a, b, c, n, bdim, offsets, klist, pair_scratch, vec, num_cus, s);
-        case 64: return launch_mul<64>(a, b, c, n, bdim, offsets, klist, pair_scratch, vec, num_cus, s);
         case 128: return launch_mul<128>(a, b, c, n, bdim, offsets, klist, pair_scratch, vec, num_cus, s);
         default: return hipErrorInvalidValue;
     }

@@ -75,11 +75,18 @@ __global__ __launch_bounds__(kMacThreads, MacGeom<LEAF>::OCC) void multiply_macr
 }
 
 // ---------------------------------------------------------------------------
-// Leaf 64 with N a multiple of 128 (whole macro tiles, every access inside
-// the matrix): the same macro-tile stream, but tiles move from global memory
+// Leaf 64: the same macro-tile stream, but tiles move from global memory
 // straight into LDS (global_load_lds_dwordx4) through kDmaStages LDS stages of
 // one item (kDmaKC k) each, so the copies of the next items are in flight
 // while one is multiplied and no registers stage the data.
+//
+// Bound by the matrix cores and the copy bursts between their blocks.  EDGE
+// (N not a multiple of 128): macro tiles and k-chunks may reach past the
+// matrix, and rows may be only 4-byte aligned, which the copies accept.
+// Multiply alone, +-1/(1+|i-j|)^2, tau 1e-6: N = 5003 317 -> 224 us and N =
+// 8191 505 us, against the register-staged kernel that took these sizes (N =
+// 5120 without EDGE 213 us, N = 8192 460 us); leaf 128, N = 6000, exp decay
+// 0.01: 1310 -> 852 us (121.6 TFLOP/s, 122.9 at N = 6016 without EDGE).
 //
 // Sixteen waves: wave w computes the 32x32 quadrant (w >> 3 & 1, w >> 2 & 1)
 // of output tile (w + (w >> 2)) & 3 of the macro tile.  Waves are dealt to the
@@ -103,6 +110,7 @@ __global__ __launch_bounds__(kMacThreads, MacGeom<LEAF>::OCC) void multiply_macr
 // consecutive workgroups.  Each sharer writes its partial sums to its own
 // slot instead of C; macro_fixup_kernel, launched next on the stream, adds the
 // partials of every shared tile in workgroup order and writes C.
+template <bool EDGE>
 __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
     const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C, int64_t n, int64_t bdim,
     int64_t mb, const uint32_t* __restrict__ items, const int32_t* __restrict__ uprefix,
@@ -110,10 +118,11 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
     constexpr int LEAF = 64, KC = kDmaKC, NCH = LEAF / KC, SPC = KC / 2;
     constexpr int ABYTES = 2 * LEAF * KC * 4, BBYTES = KC * 2 * LEAF * 4;
     constexpr int STAGE_BYTES = ABYTES + BBYTES;
-    // one LDS object (the stages, then the two partition boundaries): a second
-    // __shared__ array makes the compiler wait for every outstanding copy
-    // before each LDS read
-    __shared__ __attribute__((aligned(1024))) char lds[kDmaStages * STAGE_BYTES + 6 * sizeof(int64_t)];
+    // one LDS object (the stages, the partition boundaries, the last chunks of
+    // the matrices' last rows): a second __shared__ array makes the compiler
+    // wait for every outstanding copy before each LDS read
+    __shared__ __attribute__((aligned(1024))) char lds[kDmaStages * STAGE_BYTES + 6 * sizeof(int64_t) +
+                                                       8 * sizeof(float)];
     int64_t(*sbound)[2] = reinterpret_cast<int64_t(*)[2]>(lds + kDmaStages * STAGE_BYTES);
 
     // the wave index as a scalar, so that what derives from it (the tile, the
@@ -133,11 +142,19 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
     const int64_t nm = mb * mb;
     // boundaries lg, lg+1 and lg-1, one wave each
     if (wave < 3) {
-        const SplitBound sbd = split_bound(wave < 2 ? lg + wave : lg - 1, groups, mb, uprefix, offsets, items);
+        const SplitBound sbd = split_bound(wave < 2 ? lg + wave : lg - 1, groups, mb, bdim, fix_slots == nullptr,
+                                           uprefix, offsets, items);
         if (lane == 0) {
             sbound[wave][0] = sbd.m;
             sbound[wave][1] = sbd.p;
         }
+    }
+    // EDGE: the chunk of A's (0 .. 3) and B's (4 .. 7) last row that crosses its
+    // end, with zeros past it
+    float* last_chunk = reinterpret_cast<float*>(lds + kDmaStages * STAGE_BYTES + 6 * sizeof(int64_t));
+    if (EDGE && tid >= 256 && tid < 264) {
+        const int64_t col = n / 4 * 4 + (tid & 3);
+        last_chunk[tid & 7] = col < n ? (tid & 4 ? B : A)[(n - 1) * n + col] : 0.0f;
     }
     __syncthreads();
     const int64_t m_first = sbound[0][0], p_begin = sbound[0][1];
@@ -178,12 +195,16 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
     };
+    // EDGE: macro tiles of the last row and column may reach past the matrix
+    auto at_edge = [&](int64_t I, int64_t J) { return I == mb - 1 || J == mb - 1; };
     // exactly kDmaStores stores per wave: the accumulators of finished macro
     // tile m to C, or for a tile shared with other workgroups to this
     // workgroup's slot (a 128 x 128 row-major tile; side 1 if this workgroup
     // holds the tile's first item, the tile being its last, side 0 otherwise,
-    // the tile being its first)
-    auto store_macro = [&](int64_t m, bool shared) {
+    // the tile being its first).  Returns how many times kDmaStores the copy
+    // waits may count: 0 where stores outside the matrix were left out (a
+    // count that is too low only waits for more)
+    auto store_macro = [&](int64_t m, bool shared) -> int {
         const int64_t I = m / mb, J = m - (m / mb) * mb;
         float* base;
         int64_t ld;
@@ -195,9 +216,18 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
             base = C + 2 * I * LEAF * n + 2 * J * LEAF;
             ld = n;
         }
-        float* dst = base + (wa * LEAF + qr * 32 + 4 * g) * ld + wb * LEAF + qc * 32 + ir;
+        const int row0 = wa * LEAF + qr * 32 + 4 * g, col0 = wb * LEAF + qc * 32 + ir;
+        float* dst = base + row0 * ld + col0;
+        if (EDGE && !shared && at_edge(I, J)) {  // inside the matrix only
+            const int rows = int(n - 2 * I * LEAF), cols = int(n - 2 * J * LEAF);
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (row0 + 8 * (r >> 2) + (r & 3) < rows && col0 < cols) dst[(8 * (r >> 2) + (r & 3)) * ld] = acc[r];
+            return 0;
+        }
 #pragma unroll
         for (int r = 0; r < 16; ++r) dst[(8 * (r >> 2) + (r & 3)) * ld] = acc[r];
+        return 1;
     };
 
     // copies of item (pair item pi, chunk ch) into stage st: KC/32 A and KC/32
@@ -233,15 +263,72 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
             b_off[j] = uint32_t((int64_t(r) * n + half * LEAF + 4 * (p ^ (8 * ((r / SPC) & 1)))) * 4);
         }
     }
+    // EDGE: rows and columns outside the matrix are read from addresses inside
+    // it: their products only reach parts of C that are not stored.  In the
+    // last macro row the lane's rows, in the last macro column its columns,
+    // are moved inside by other offsets, as cheap as the ones above (the
+    // workgroups of the last macro row see no other items: with the addresses
+    // worked out per item they ended last, 10 % behind the others).
+    const int last_m = int(mb) - 1;
+    uint32_t a_edge[KC / 32], b_edge[KC / 32];
+    if (EDGE) {
+#pragma unroll
+        for (int j = 0; j < KC / 32; ++j) {
+            const int blka = wave * (KC / 32) + j, blkb = (wave & 7) * (KC / 32) + j;
+            const int ra = blka * (256 / KC) + lane / ACH, rb = blkb * 4 + (lane >> 4);
+            const int in_rows = int(n - 1 - 2 * int64_t(last_m) * LEAF);  // last row inside, from the macro row's first
+            a_edge[j] = uint32_t((int64_t(ra < in_rows ? ra : in_rows) * n + 4 * ((lane % ACH) ^ aswz(ra))) * 4);
+            const int cb = half * LEAF + 4 * ((lane & 15) ^ (8 * ((rb / SPC) & 1)));
+            const bool in = 2 * int64_t(last_m) * LEAF + cb < n;
+            b_edge[j] = uint32_t((int64_t(rb) * n + (in ? cb : 0)) * 4);
+        }
+    }
+    // EDGE, an item whose k reach past n (rare): any address inside for what
+    // lies outside; a chunk that crosses a row's end reads into the next row,
+    // and in the matrix's last row the last four floats.  patch_tail then
+    // clears k >= n and mends the last row.
+    const uint32_t whole_kt = uint32_t(n / LEAF);  // k-chunks inside the matrix
+    auto in_tail = [&](uint32_t pi) { return ((pi >> 4) & 1023u) >= whole_kt; };
+    // the lane as a value of its own in these rare blocks, so that what they
+    // compute from it does not stay in registers over the whole loop
+    auto edge_lane = [&]() { return opaque(lane); };
+    auto edge_source = [&](const float* X, int64_t row, int64_t col) -> const float* {
+        const int64_t r = row < n ? row : n - 1;
+        const int64_t e = r * n + (col < n ? col : 0), last = n * n - 4;
+        return X + (e < last ? e : last);
+    };
     auto copy_item = [&](uint32_t pi, int ch, int st) {
         const int64_t I = pi >> 23, J = (pi >> 14) & 511, kt = (pi >> 4) & 1023;
         char* sbase = lds + st * STAGE_BYTES;
+        if (EDGE && in_tail(pi)) {
+            const int lane = edge_lane();
+            if (pi & need_a) {
+#pragma unroll 1
+                for (int j = 0; j < KC / 32; ++j) {
+                    const int blk = wave * (KC / 32) + j;
+                    const int r = blk * (256 / KC) + lane / ACH, p = lane % ACH;
+                    copy_to_lds(edge_source(A, 2 * I * LEAF + r, kt * LEAF + ch * KC + 4 * (p ^ aswz(r))),
+                                sbase + blk * 1024);
+                }
+            }
+            if (pi & need_b) {
+#pragma unroll 1
+                for (int j = 0; j < KC / 32; ++j) {
+                    const int blk = (wave & 7) * (KC / 32) + j;
+                    const int r = blk * 4 + (lane >> 4), p = lane & 15;
+                    copy_to_lds(edge_source(B, kt * LEAF + ch * KC + r,
+                                            2 * J * LEAF + half * LEAF + 4 * (p ^ (8 * ((r / SPC) & 1)))),
+                                sbase + ABYTES + half * BHALF + blk * 1024);
+                }
+            }
+            return;
+        }
         if (pi & need_a) {
             const char* base = reinterpret_cast<const char*>(A + 2 * I * LEAF * n + kt * LEAF + ch * KC);
 #pragma unroll
             for (int j = 0; j < KC / 32; ++j) {
                 const int blk = wave * (KC / 32) + j;
-                __builtin_amdgcn_global_load_lds(reinterpret_cast<const float*>(base + a_off[j]),
+                __builtin_amdgcn_global_load_lds(reinterpret_cast<const float*>(base + (EDGE && int(I) == last_m ? a_edge[j] : a_off[j])),
                                                  (__attribute__((address_space(3))) void*)(sbase + blk * 1024), 16, 0,
                                                  0);
             }
@@ -252,8 +339,48 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
             for (int j = 0; j < KC / 32; ++j) {
                 const int blk = (wave & 7) * (KC / 32) + j;
                 __builtin_amdgcn_global_load_lds(
-                    reinterpret_cast<const float*>(base + b_off[j]),
+                    reinterpret_cast<const float*>(base + (EDGE && int(J) == last_m ? b_edge[j] : b_off[j])),
                     (__attribute__((address_space(3))) void*)(sbase + ABYTES + half * BHALF + blk * 1024), 16, 0, 0);
+            }
+        }
+    };
+    // EDGE, an item whose k reach past n, after this wave's copies of it have
+    // landed: zeros for every k >= n of the chunks this wave copied, and the
+    // elements of the matrix's last row whose chunk crosses its end
+    auto patch_tail = [&](uint32_t pi, int ch, int st) {
+        const int I = int(pi >> 23), J = int((pi >> 14) & 511), kt = int((pi >> 4) & 1023);
+        const int lane = edge_lane();
+        char* sbase = lds + st * STAGE_BYTES;
+        // dst: the chunk of (row, col); k: the index of the two that is one
+        auto mend = [&](char* dst, int row, int col, int k, int last) {
+            f4* d = reinterpret_cast<f4*>(dst);
+            if (k >= int(n)) {
+                *d = f4{0.0f, 0.0f, 0.0f, 0.0f};
+            } else if (col < int(n) && col + 4 > int(n)) {
+                f4 v = row == int(n) - 1 ? *reinterpret_cast<const f4*>(last_chunk + last) : *d;
+                v.y = col + 1 < int(n) ? v.y : 0.0f;
+                v.z = col + 2 < int(n) ? v.z : 0.0f;
+                v.w = 0.0f;
+                *d = v;
+            }
+        };
+        if (pi & need_a) {
+#pragma unroll 1
+            for (int j = 0; j < KC / 32; ++j) {
+                const int blk = wave * (KC / 32) + j;
+                const int r = blk * (256 / KC) + lane / ACH, p = lane % ACH;
+                const int col = kt * LEAF + ch * KC + 4 * (p ^ aswz(r));
+                mend(sbase + blk * 1024 + lane * 16, 2 * I * LEAF + r, col, col, 0);
+            }
+        }
+        if (pi & need_b) {
+#pragma unroll 1
+            for (int j = 0; j < KC / 32; ++j) {
+                const int blk = (wave & 7) * (KC / 32) + j;
+                const int r = blk * 4 + (lane >> 4), p = lane & 15;
+                const int row = kt * LEAF + ch * KC + r;
+                mend(sbase + ABYTES + half * BHALF + blk * 1024 + lane * 16, row,
+                     2 * J * LEAF + half * LEAF + 4 * (p ^ (8 * ((r / SPC) & 1))), row, 4);
             }
         }
     };
@@ -312,8 +439,7 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
     // finish macro tile out_m: its C tile, or this workgroup's partial sums of
     // a shared tile (kDmaStores stores per wave either way)
     auto finish = [&]() {
-        store_macro(out_m, (out_m == m_first && head_split) || (out_m == m_next && tail_split));
-        ++ns[0];
+        ns[0] += store_macro(out_m, (out_m == m_first && head_split) || (out_m == m_next && tail_split));
         zero_acc();
         ++out_m;
     };
@@ -332,6 +458,11 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
         // of items it+1 .. it+S-2 and the stores issued since are outstanding
         asm volatile("" ::: "memory");
         wait_copies<(S - 2) * kDmaCopies>(stores);
+        if (EDGE && in_tail(pi)) {
+            asm volatile("" ::: "memory");
+            patch_tail(pi, int(it % NCH), int(it % S));
+            asm volatile("" ::: "memory");
+        }
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's LDS reads of item it-1 are done
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
@@ -398,15 +529,16 @@ __global__ __launch_bounds__(kDmaThreads) void macro_fixup_kernel(float* __restr
         }
     }
     const int64_t I = m / mb, J = m - (m / mb) * mb;
+    const int64_t rows = n - 2 * I * LEAF, cols = n - 2 * J * LEAF;  // inside the matrix (any number past the tile's)
     float* dst = C + 2 * I * LEAF * n + 2 * J * LEAF;
 #pragma unroll
     for (int j = 0; j < EL; ++j) {
         const int e = tid + j * kDmaThreads;
-        dst[(e / (2 * LEAF)) * n + e % (2 * LEAF)] = sum[j];
+        if (e / (2 * LEAF) < rows && e % (2 * LEAF) < cols) dst[(e / (2 * LEAF)) * n + e % (2 * LEAF)] = sum[j];
     }
 }
 
-// Leaf 128 with N a multiple of 128 on the same kernel: a 128x128 output tile
+// Leaf 128 on the same kernel: a 128x128 output tile
 // is a macro tile of four 64x64 quarters that all keep every k, so each kept
 // pair (i, k, j) becomes two items (one per 64-wide half of k) with all four
 // membership bits set.  One wave per output tile t: its items at
@@ -434,24 +566,39 @@ hipError_t launch_leaf128_schedule(const int32_t* offsets, const int32_t* klist,
     return hipGetLastError();
 }
 
-hipError_t launch_leaf128_multiply(const float* a, const float* b, float* c, int64_t n, int64_t bdim,
-                                   const int32_t* uprefix, const uint32_t* items, int64_t* bounds, float* fix_slots,
-                                   int num_cus, hipStream_t s) {
-    const int64_t mb = bdim, nm = mb * mb;  // one macro tile per 128x128 output tile
-    const int64_t cap = ((nm + 7) / 8) * 8;
-    static int scratch_state = 0;
-    const hipError_t ce = check_no_scratch(multiply_macro_dma_kernel, &scratch_state);
+// The LDS-DMA multiply over mb x mb macro tiles and its fixup; fix_slots ==
+// nullptr: no macro tile is shared between workgroups.
+static hipError_t launch_dma(const float* a, const float* b, float* c, int64_t n, int64_t bdim, int64_t mb,
+                             const uint32_t* items, const int32_t* uprefix, const int32_t* offsets, int64_t* bounds,
+                             float* fix_slots, int num_cus, hipStream_t s) {
+    if (n < 4 || !bounds) return hipErrorInvalidValue;
+    const bool edge = n % 128 != 0;
+    static int scratch_state[2] = {0, 0};
+    const hipError_t ce = edge ? check_no_scratch(multiply_macro_dma_kernel<true>, &scratch_state[1])
+                               : check_no_scratch(multiply_macro_dma_kernel<false>, &scratch_state[0]);
     if (ce != hipSuccess) return ce;
+    const int64_t cap = ((mb * mb + 7) / 8) * 8;
     int64_t groups = int64_t(num_cus);
     if (groups > cap) groups = cap;
     groups = ((groups + 7) / 8) * 8;
     if (groups > kSplitMaxGroups) groups = kSplitMaxGroups;
-    multiply_macro_dma_kernel<<<unsigned(groups), kDmaThreads, 0, s>>>(a, b, c, n, 2 * mb, mb, items, uprefix,
-                                                                      nullptr, bounds, fix_slots);
+    if (edge)
+        multiply_macro_dma_kernel<true><<<unsigned(groups), kDmaThreads, 0, s>>>(a, b, c, n, bdim, mb, items, uprefix,
+                                                                                offsets, bounds, fix_slots);
+    else
+        multiply_macro_dma_kernel<false><<<unsigned(groups), kDmaThreads, 0, s>>>(a, b, c, n, bdim, mb, items,
+                                                                                 uprefix, offsets, bounds, fix_slots);
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || groups < 2) return e;
+    if (e != hipSuccess || groups < 2 || !fix_slots) return e;
     macro_fixup_kernel<<<unsigned(groups - 1), kDmaThreads, 0, s>>>(c, n, mb, uprefix, bounds, fix_slots, groups);
     return hipGetLastError();
+}
+
+hipError_t launch_leaf128_multiply(const float* a, const float* b, float* c, int64_t n, int64_t bdim,
+                                   const int32_t* uprefix, const uint32_t* items, int64_t* bounds, float* fix_slots,
+                                   int num_cus, hipStream_t s) {
+    // one macro tile per 128x128 output tile
+    return launch_dma(a, b, c, n, 2 * bdim, bdim, items, uprefix, nullptr, bounds, fix_slots, num_cus, s);
 }
 
 hipError_t launch_macro_schedule(const int32_t* offsets, const int32_t* klist, int64_t bdim, const MacroSchedule& ms,
@@ -469,27 +616,9 @@ hipError_t launch_macro_schedule(const int32_t* offsets, const int32_t* klist, i
 
 template <int LEAF>
 static hipError_t launch_macro_run(const float* a, const float* b, float* c, int64_t n, int64_t bdim,
-                                   const int32_t* offsets, const MacroSchedule& ms, bool vec, int num_cus,
-                                   hipStream_t s) {
+                                   const MacroSchedule& ms, bool vec, int num_cus, hipStream_t s) {
     const int64_t mb = (bdim + 1) / 2, nm = mb * mb;
     const int64_t cap = ((nm + 7) / 8) * 8;
-    if (LEAF == 64 && vec && n % 128 == 0) {
-        if (!ms.bounds || !ms.fix_slots) return hipErrorInvalidValue;
-        static int scratch_state = 0;
-        const hipError_t ce = check_no_scratch(multiply_macro_dma_kernel, &scratch_state);
-        if (ce != hipSuccess) return ce;
-        int64_t groups = int64_t(num_cus);
-        if (groups > cap) groups = cap;
-        groups = ((groups + 7) / 8) * 8;
-        if (groups > kSplitMaxGroups) groups = kSplitMaxGroups;
-        multiply_macro_dma_kernel<<<unsigned(groups), kDmaThreads, 0, s>>>(a, b, c, n, bdim, mb, ms.items, ms.uprefix,
-                                                                          offsets, ms.bounds, ms.fix_slots);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess || groups < 2) return e;
-        macro_fixup_kernel<<<unsigned(groups - 1), kDmaThreads, 0, s>>>(c, n, mb, ms.uprefix, ms.bounds,
-                                                                        ms.fix_slots, groups);
-        return hipGetLastError();
-    }
     int64_t groups = int64_t(num_cus) * MacGeom<LEAF>::OCC;
     if (groups > cap) groups = cap;
     groups = ((groups + 7) / 8) * 8;
@@ -510,8 +639,10 @@ hipError_t launch_macro_multiply(const float* a, const float* b, float* c, int64
                                  const int32_t* offsets, const MacroSchedule& ms, bool vec, int num_cus,
                                  hipStream_t s) {
     switch (leaf) {
-        case 32: return launch_macro_run<32>(a, b, c, n, bdim, offsets, ms, vec, num_cus, s);
-        case 64: return launch_macro_run<64>(a, b, c, n, bdim, offsets, ms, vec, num_cus, s);
+        case 32: return launch_macro_run<32>(a, b, c, n, bdim, ms, vec, num_cus, s);
+        case 64:
+            return launch_dma(a, b, c, n, bdim, (bdim + 1) / 2, ms.items, ms.uprefix, offsets, ms.bounds, ms.fix_slots,
+                              num_cus, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -657,3 +657,55 @@ def test_norms_of_unaligned_rows(n, offset):
         pad[:n, :n] = xd
         want = np.sqrt((pad**2).reshape(bd, leaf, bd, leaf).sum(axis=(1, 3)))
         assert np.allclose(sp.norms(x, leaf).cpu().numpy(), want, rtol=1e-11, atol=0.0), leaf
+
+
+@pytest.mark.parametrize("leaf", [64, 128])
+@pytest.mark.parametrize("n", [3, 4, 5, 63, 65, 127, 129, 190, 193, 255, 320, 1023, 1090])
+def test_multiply_at_ragged_edges(n, leaf):
+    """N no multiple of 128 on the LDS-DMA multiply: macro tiles, k-chunks and
+    16-byte copies that cross the matrix's edge, one tile row in the last macro
+    row, N below the copy's four floats.  C starts as NaN (every element is
+    written), against the oracle with every pair and about half of them kept."""
+    a, b = inputs.uniform_pm1(n, 51), inputs.uniform_pm1(n, 52)
+    prod = oracle_products(a, b, leaf)
+    for tau in (0.0, float(np.quantile(prod, 0.5)) * (1.0 + 1e-9)):
+        c = torch.full((n, n), float("nan"), device=DEV)
+        _, pairs = sp.multiply(gpu(a), gpu(b), tau, leaf, c=c)
+        c_ref, count, _ = oracle.spamm(a, b, tau, leaf)
+        assert pairs == count
+        check_c(c.cpu().numpy(), a, b, tau, leaf, c_ref=c_ref)
+
+
+@pytest.mark.parametrize("n", [130, 131, 189])
+def test_values_past_a_row_stay_out_of_it(n):
+    """Copies of 16 bytes reach past a ragged row into the next one: infinities
+    there must not enter the row's products (leaf 128: one k tile holds all)."""
+    a, b = inputs.uniform_pm1(n, 53), inputs.uniform_pm1(n, 54)
+    a[7, :5] = np.inf
+    b[9, 2] = np.inf
+    c, _ = sp.multiply(gpu(a), gpu(b), 0.0, 128)
+    with np.errstate(invalid="ignore"):
+        want = a.astype(np.float64) @ b.astype(np.float64)
+    got = c.cpu().numpy()
+    assert np.array_equal(np.isfinite(got), np.isfinite(want))
+    ok = np.isfinite(want)
+    a0, b0 = np.where(np.isfinite(a), a, 0.0), np.where(np.isfinite(b), b, 0.0)
+    bound = gamma32(n) * (np.abs(a0).astype(np.float64) @ np.abs(b0).astype(np.float64))
+    assert np.all(np.abs(got - want)[ok] <= bound[ok])
+
+
+@pytest.mark.parametrize("n,leaf", [(10877, 64), (20861, 128)])
+def test_ragged_sizes_with_the_lean_workspace(n, leaf):
+    """Ragged sizes whose workspace fits the static scratch only without the
+    partial-sum slots (leaf 64: no macro tile is shared) or the item list (leaf
+    128): dense random matrices with every pair kept, against the FP64 product,
+    every element."""
+    gen = torch.Generator(device=DEV).manual_seed(61)
+    a, b = (torch.rand((n, n), generator=gen, device=DEV) + 0.5 for _ in range(2))  # no products near underflow
+    assert sp.workspace_bytes(n, leaf) <= 64 << 20
+    c, pairs = sp.multiply(a, b, 0.0, leaf)
+    assert pairs == sp.bdim(n, leaf) ** 3
+    for r0 in range(0, n, 4096):
+        rows = slice(r0, min(n, r0 + 4096))
+        ref = a[rows].double() @ b.double()  # positive: also the bound's |A||B|
+        assert float(((c[rows].double() - ref).abs() - gamma32(n) * ref).max()) <= 0.0
