@@ -173,14 +173,14 @@ spamm_status spamm_prepare_schedule(const float* a, const float* b, int64_t n, d
  *   c      [n*n] FP32 device output, overwritten.
  *   pairs  one int64 in device memory (may be NULL): number of multiplied
  *          leaf-tile pairs, i.e. the valid ratio of section 3.5.2 times bdim^3.
- * Small products (leaf 32, at most 64 tiles per side, n a multiple of 4, a and
- * b 16-byte aligned) take two launches instead: the leaf norm pass, then one
- * kernel that applies the threshold test of Algorithm 1 to the leaf norms and
- * multiplies the kept pairs.  The pairs are those of the plan; C differs from
- * spamm_prepare + spamm_execute only in the order of the FP32 additions (the
- * k-range of an output tile is split four ways and the parts are added in a
- * fixed order, so repeated calls agree bitwise); the workspace then holds the
- * leaf norms but no pyramid or plan.
+ * Small products (n from 4 to 2048 at leaf 16 and 32, to 1728 at leaf 64 and
+ * 128) take two launches instead: the leaf norm pass, then one kernel that
+ * applies the threshold test of Algorithm 1 to the leaf norms and multiplies
+ * the kept pairs.  The pairs are those of the plan; C differs from
+ * spamm_prepare + spamm_execute only in the order of the FP32 additions (above
+ * leaf 16 the k-range of an output tile is split four ways and the parts are
+ * added in a fixed order, so repeated calls agree bitwise); the workspace then
+ * holds the leaf norms but no pyramid or plan.
  * Errors as spamm_pyramid, spamm_plan and spamm_execute. */
 spamm_status spamm_multiply(const float* a, const float* b, int64_t n, double tau, int32_t leaf, float* c,
                             int64_t* pairs, void* workspace, size_t workspace_bytes, void* stream);

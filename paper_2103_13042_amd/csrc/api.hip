@@ -563,10 +563,11 @@ spamm_status enqueue_small(const Geom& g, const float* a, const float* b, double
         nj.sumsq[m] = at<double>(ws, L.spyr[m]) + leaf_level;
         nj.norms[m] = at<double>(ws, L.pyr[m]) + leaf_level;
     }
-    spamm_status st = hip_check(spamm::launch_leaf_norms(nj, 2, g.n, g.leaf, true, s), "leaf norm kernel");
+    const bool vec = (g.n % 4) == 0 && aligned16(a) && aligned16(b);
+    spamm_status st = hip_check(spamm::launch_leaf_norms(nj, 2, g.n, g.leaf, vec, s), "leaf norm kernel");
     if (st != SPAMM_OK) return st;
-    return hip_check(spamm::launch_small_multiply(a, b, c, g.n, g.bdim, nj.norms[0], nj.norms[1], g.side, tau, pairs,
-                                                  s),
+    return hip_check(spamm::launch_small_multiply(a, b, c, g.n, g.leaf, vec, g.bdim, nj.norms[0], nj.norms[1], g.side,
+                                                  tau, pairs, s),
                      "small multiply kernel");
 }
 }  // namespace
@@ -583,7 +584,7 @@ spamm_status spamm_multiply(const float* a, const float* b, int64_t n, double ta
     if ((st = check_workspace(g, workspace, workspace_bytes)) != SPAMM_OK) return st;
     const Layout L = make_layout(g);
     int64_t* np = pairs ? pairs : at<int64_t>(workspace, L.pairs);
-    if (g.leaf == 32 && g.bdim <= spamm::kSmallMaxBdim && g.n % 4 == 0 && aligned16(a) && aligned16(b))
+    if (spamm::small_product(g.n, g.leaf))
         return enqueue_small(g, a, b, tau, c, np, workspace, static_cast<hipStream_t>(stream));
     int32_t* offsets = at<int32_t>(workspace, L.offsets);
     int32_t* klist = at<int32_t>(workspace, L.klist);

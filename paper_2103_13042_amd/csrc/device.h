@@ -7,6 +7,9 @@ namespace spamm {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f16v __attribute__((ext_vector_type(16)));
+// four floats read with one 16-byte load from a 4-byte aligned address
+// (global loads accept it)
+typedef float f4_dw __attribute__((ext_vector_type(4), aligned(4)));
 
 // p as a pointer into global memory.  A pointer read from memory (a
 // descriptor array) carries no address space, so the compiler emits flat

@@ -75,14 +75,21 @@ inline int64_t plan_macro_clear_words(int64_t bdim) { return (bdim + 1) / 2 + 1;
 hipError_t launch_plan_macro(const double* norms_a, const double* norms_b, int64_t side, int64_t bdim, double tau,
                              const PlanMacroOut& o, hipStream_t s);
 
-// Small products (leaf 32, bdim <= kSmallMaxBdim, n % 4 == 0, a and b 16-byte
-// aligned): the threshold test on the leaf norms na / nb (row stride ld) and
-// the multiply of the kept pairs in one launch; adds the number of kept pairs
-// to *pairs, which must be zero before (the norm pass clears it).
-constexpr int64_t kSmallMaxBdim = 64;
-hipError_t launch_small_multiply(const float* a, const float* b, float* c, int64_t n, int64_t bdim,
-                                 const double* na, const double* nb, int64_t ld, double tau, int64_t* pairs,
-                                 hipStream_t s);
+// Small products (small_product: by n and leaf): the threshold test on the
+// leaf norms na / nb (row stride ld) and the multiply of the kept pairs in one
+// launch; adds the number of kept pairs to *pairs, which must be zero before
+// (the norm pass clears it).  vec: n % 4 == 0 and a, b 16-byte aligned.
+//
+// Leaf 16 and 32: n <= 2048, the 64 entries of 32 k that one wave's lanes hold.
+// Leaf 64 and 128: n <= 1728, three rounds of 64x64 blocks on 256 CUs; above,
+// the general path's 128x128 macro tiles win on dense products (one call, leaf
+// 64: dense n = 1024 35 against 90 us, 1700 136 against 147, 1792 177 against
+// 153; exp decay 0.05, tau 1e-6: 1024 23 against 53, 1792 40 against 48).
+constexpr int64_t kSmallFineMaxN = 2048, kSmallCoarseMaxN = 1728;
+bool small_product(int64_t n, int32_t leaf);
+hipError_t launch_small_multiply(const float* a, const float* b, float* c, int64_t n, int32_t leaf, bool vec,
+                                 int64_t bdim, const double* na, const double* nb, int64_t ld, double tau,
+                                 int64_t* pairs, hipStream_t s);
 
 // Multiply on single output tiles: persistent, cost-balanced multiply of the
 // kept pairs into C (leaf 128 where the LDS-DMA kernel does not run: more than

@@ -130,10 +130,10 @@ __global__ __launch_bounds__(kNormThreads) void leaf_sumsq_kernel(NormJob job, i
 // threads per strip x 1024-column chunk, four row groups of LEAF/4 rows whose
 // loads are all in flight at once; the four partial sums of a column group
 // are added in row-group order through LDS, then across the tile's threads.
-// Rows 16-byte aligned (n % 4 == 0, x 16-byte aligned).
+// Rows at 4-byte alignment (VEC false, n >= 4) as in leaf_sumsq_strip.
 constexpr int kNormSmallThreads = 1024;
 
-template <int LEAF>
+template <int LEAF, bool VEC>
 __global__ __launch_bounds__(kNormSmallThreads) void leaf_sumsq_small_kernel(NormJob job, int64_t n, int64_t bdim) {
     constexpr int G = LEAF / 4;           // threads per tile (4 columns each)
     constexpr int RPG = LEAF / 4;         // rows per row group
@@ -147,10 +147,16 @@ __global__ __launch_bounds__(kNormSmallThreads) void leaf_sumsq_small_kernel(Nor
     double acc = 0.0;
     if (col < n) {
         f4 v[RPG];
+        const int back = VEC || col + 4 <= n ? 0 : int(col + 4 - n);  // columns that the thread before holds
 #pragma unroll
         for (int r = 0; r < RPG; ++r) {
             const int64_t row = r0 + r;
-            v[r] = row < n ? *reinterpret_cast<const f4*>(x + row * n + col) : f4{0.0f, 0.0f, 0.0f, 0.0f};
+            v[r] = row < n ? load_row<VEC, false>(x + row * n + col - back) : f4{0.0f, 0.0f, 0.0f, 0.0f};
+            if (!VEC) {
+                v[r].x = back > 0 ? 0.0f : v[r].x;
+                v[r].y = back > 1 ? 0.0f : v[r].y;
+                v[r].z = back > 2 ? 0.0f : v[r].z;
+            }
         }
         double a0 = 0.0, a1 = 0.0;
 #pragma unroll
@@ -212,8 +218,11 @@ static hipError_t launch_leaf_fixed(const NormJob& job, int nmat, int64_t n, int
     const bool nt = 4.0 * double(n) * double(n) * nmat > kInfinityCacheBytes;
     if constexpr (LEAF == 16 || LEAF == 32 || LEAF == 64) {
         // fewer blocks than CUs: the four-row-group form keeps more loads in flight
-        if (vec && int64_t(grid.x) * grid.y * grid.z < kSmallNormBlocks) {
-            leaf_sumsq_small_kernel<LEAF><<<grid, kNormSmallThreads, 0, s>>>(job, n, bdim);
+        if (n >= 4 && int64_t(grid.x) * grid.y * grid.z < kSmallNormBlocks) {
+            if (vec)
+                leaf_sumsq_small_kernel<LEAF, true><<<grid, kNormSmallThreads, 0, s>>>(job, n, bdim);
+            else
+                leaf_sumsq_small_kernel<LEAF, false><<<grid, kNormSmallThreads, 0, s>>>(job, n, bdim);
             return hipGetLastError();
         }
     }

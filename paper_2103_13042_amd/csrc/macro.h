@@ -74,10 +74,6 @@ __device__ __forceinline__ void macro_items_wave(const uint64_t* __restrict__ wo
     }
 }
 
-// four floats read with one 16-byte load from a 4-byte aligned address
-// (global loads accept it)
-typedef float f4_dw __attribute__((ext_vector_type(4), aligned(4)));
-
 template <int LEAF>
 struct MacGeom {
     static constexpr int KC = 32;                 // k per pipeline stage

@@ -709,3 +709,30 @@ def test_ragged_sizes_with_the_lean_workspace(n, leaf):
         rows = slice(r0, min(n, r0 + 4096))
         ref = a[rows].double() @ b.double()  # positive: also the bound's |A||B|
         assert float(((c[rows].double() - ref).abs() - gamma32(n) * ref).max()) <= 0.0
+
+
+@pytest.mark.parametrize("leaf", [16, 32, 64, 128])
+@pytest.mark.parametrize("n,offset", [(4, 0), (5, 0), (31, 0), (33, 0), (64, 1), (65, 0), (127, 0), (200, 0), (319, 0),
+                                      (320, 0), (321, 0), (322, 0), (323, 3), (640, 0), (1021, 0)])
+def test_small_products_at_edges(n, offset, leaf):
+    """The two-launch path at every leaf: n around the entries of 32, the blocks
+    of 64 and the last size of the strip kernel, rows and matrices at 4-byte
+    alignment, half and all of the pairs kept.  Pairs equal the oracle's, C is
+    within the FP32 accumulation bound and written everywhere, bitwise the same
+    on a second call; infinities stay in their row and column."""
+    a, b = inputs.uniform_pm1(n, 71), inputs.uniform_pm1(n, 72)
+    prod = oracle_products(a, b, leaf)
+    ga, gb = _offset_view(a, offset), _offset_view(b, offset)
+    for tau in (0.0, float(np.quantile(prod, 0.5)) * (1.0 + 1e-9)):
+        c_ref, count, _ = oracle.spamm(a, b, tau, leaf)
+        c = torch.full((n, n), float("nan"), device=DEV)
+        _, pairs = sp.multiply(ga, gb, tau, leaf, c=c)
+        assert pairs == count
+        check_c(c.cpu().numpy(), a, b, tau, leaf, c_ref=c_ref)
+        assert torch.equal(sp.multiply(ga, gb, tau, leaf)[0], c)
+    row, col = n // 2, n // 3
+    ga[row, 0], gb[n - 1, col] = math.inf, math.inf
+    c2 = sp.multiply(ga, gb, 0.0, leaf)[0].cpu().numpy()
+    clean = np.ones((n, n), dtype=bool)
+    clean[row, :] = clean[:, col] = False
+    assert np.all(np.isfinite(c2[clean]))
