@@ -63,7 +63,7 @@ def multiply_kernel(n: int, leaf: int, precision: str = "fp32", staged: bool = F
         return "multiply_macro_dma_kernel + macro_fixup_kernel", [CSRC / "multiply_macro.hip", CSRC / "macro.h",
                                                                   *heads]
     if leaf == 32:
-        return f"multiply_macro_kernel<{leaf}", [CSRC / "multiply_macro.hip", CSRC / "macro.h", *heads]
+        return "multiply_block_kernel<32", [CSRC / "multiply_block.hip", CSRC / "block.h", *heads]
     return f"multiply_kernel<{leaf}", [CSRC / "kernels.hip", CSRC / "device.h"]
 
 

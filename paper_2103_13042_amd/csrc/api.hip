@@ -321,7 +321,7 @@ spamm_status enqueue_multiply(const Geom& g, const float* a, const float* b, con
                               const int32_t* klist, float* c, void* ws, hipStream_t s) {
     const bool vec = (g.n % 4) == 0 && aligned16(a) && aligned16(b);
     const Layout L = make_layout(g);
-    if (g.n < 4 && g.leaf >= 64)  // one tile, smaller than the 16-byte copies of the LDS-DMA kernel: any leaf is one tile
+    if (g.n < 4 && g.leaf >= 32)  // one tile, smaller than the 16-byte copies of the LDS kernels: any leaf is one tile
         return hip_check(spamm::launch_multiply_leaf16(a, b, c, g.n, g.bdim, offsets, klist, vec, s),
                          "multiply kernel");
     if (L.leaf128_dma)
@@ -329,9 +329,13 @@ spamm_status enqueue_multiply(const Geom& g, const float* a, const float* b, con
                                                         at<uint32_t>(ws, L.items128), at<int64_t>(ws, L.bounds),
                                                         at<float>(ws, L.fix_slots), device_cus(), s),
                          "leaf-128 multiply kernels");
-    if (g.leaf == 32 || g.leaf == 64)
-        return hip_check(spamm::launch_macro_multiply(a, b, c, g.n, g.leaf, g.bdim, offsets, macro_schedule(L, ws),
-                                                      vec, device_cus(), s),
+    if (g.leaf == 32)
+        return hip_check(spamm::launch_block_plan32(a, b, c, g.n, g.bdim, at<uint32_t>(ws, L.mitems),
+                                                    at<int32_t>(ws, L.mprefix), s),
+                         "block multiply kernel");
+    if (g.leaf == 64)
+        return hip_check(spamm::launch_macro_multiply(a, b, c, g.n, g.bdim, offsets, macro_schedule(L, ws),
+                                                      device_cus(), s),
                          "macro multiply kernel");
     return hip_check(spamm::launch_multiply(a, b, c, g.n, g.leaf, g.bdim, offsets, klist,
                                             at<int32_t>(ws, L.pair_scratch), vec, device_cus(), s),
@@ -548,9 +552,9 @@ spamm_status spamm_prepare_schedule(const float* a, const float* b, int64_t n, d
 }
 
 namespace {
-// Small products: the leaf norm pass (which also clears the pair counter),
-// then the threshold test and the multiply in one launch.
-spamm_status enqueue_small(const Geom& g, const float* a, const float* b, double tau, float* c, int64_t* pairs,
+// The leaf norm pass (which also clears the pair counter), then the threshold
+// test and the multiply in one launch.
+spamm_status enqueue_direct(const Geom& g, const float* a, const float* b, double tau, float* c, int64_t* pairs,
                            void* ws, hipStream_t s) {
     const Layout L = make_layout(g);
     const int64_t leaf_level = spamm::level_offset(g.lv);
@@ -566,9 +570,13 @@ spamm_status enqueue_small(const Geom& g, const float* a, const float* b, double
     const bool vec = (g.n % 4) == 0 && aligned16(a) && aligned16(b);
     spamm_status st = hip_check(spamm::launch_leaf_norms(nj, 2, g.n, g.leaf, vec, s), "leaf norm kernel");
     if (st != SPAMM_OK) return st;
-    return hip_check(spamm::launch_small_multiply(a, b, c, g.n, g.leaf, vec, g.bdim, nj.norms[0], nj.norms[1], g.side,
-                                                  tau, pairs, s),
-                     "small multiply kernel");
+    if (g.n <= spamm::kSmallMaxN)
+        return hip_check(spamm::launch_small_multiply(a, b, c, g.n, g.leaf, vec, g.bdim, nj.norms[0], nj.norms[1],
+                                                      g.side, tau, pairs, s),
+                         "small multiply kernel");
+    return hip_check(spamm::launch_block_test(a, b, c, g.n, g.leaf, g.bdim, nj.norms[0], nj.norms[1], g.side, tau,
+                                              pairs, s),
+                     "block multiply kernel");
 }
 }  // namespace
 
@@ -584,8 +592,8 @@ spamm_status spamm_multiply(const float* a, const float* b, int64_t n, double ta
     if ((st = check_workspace(g, workspace, workspace_bytes)) != SPAMM_OK) return st;
     const Layout L = make_layout(g);
     int64_t* np = pairs ? pairs : at<int64_t>(workspace, L.pairs);
-    if (spamm::small_product(g.n, g.leaf))
-        return enqueue_small(g, a, b, tau, c, np, workspace, static_cast<hipStream_t>(stream));
+    if (spamm::block_product(g.n, g.leaf))
+        return enqueue_direct(g, a, b, tau, c, np, workspace, static_cast<hipStream_t>(stream));
     int32_t* offsets = at<int32_t>(workspace, L.offsets);
     int32_t* klist = at<int32_t>(workspace, L.klist);
     hipStream_t s = static_cast<hipStream_t>(stream);

@@ -75,21 +75,38 @@ inline int64_t plan_macro_clear_words(int64_t bdim) { return (bdim + 1) / 2 + 1;
 hipError_t launch_plan_macro(const double* norms_a, const double* norms_b, int64_t side, int64_t bdim, double tau,
                              const PlanMacroOut& o, hipStream_t s);
 
-// Small products (small_product: by n and leaf): the threshold test on the
-// leaf norms na / nb (row stride ld) and the multiply of the kept pairs in one
-// launch; adds the number of kept pairs to *pairs, which must be zero before
-// (the norm pass clears it).  vec: n % 4 == 0 and a, b 16-byte aligned.
-//
-// Leaf 16 and 32: n <= 2048, the 64 entries of 32 k that one wave's lanes hold.
-// Leaf 64 and 128: n <= 1728, three rounds of 64x64 blocks on 256 CUs; above,
-// the general path's 128x128 macro tiles win on dense products (one call, leaf
-// 64: dense n = 1024 35 against 90 us, 1700 136 against 147, 1792 177 against
-// 153; exp decay 0.05, tau 1e-6: 1024 23 against 53, 1792 40 against 48).
-constexpr int64_t kSmallFineMaxN = 2048, kSmallCoarseMaxN = 1728;
-bool small_product(int64_t n, int32_t leaf);
+// The smallest products (4 <= n <= kSmallMaxN, leaf 16 to 128): the threshold
+// test on the leaf norms na / nb (row stride ld) and the multiply of the kept
+// pairs in one launch; adds the number of kept pairs to *pairs, which must be
+// zero before (the norm pass clears it).  vec: n % 4 == 0 and a, b 16-byte
+// aligned.
+constexpr int64_t kSmallMaxN = 320;
 hipError_t launch_small_multiply(const float* a, const float* b, float* c, int64_t n, int32_t leaf, bool vec,
                                  int64_t bdim, const double* na, const double* nb, int64_t ld, double tau,
                                  int64_t* pairs, hipStream_t s);
+
+// One 64x64 block of C per workgroup (multiply_block.hip; n >= 4).  test: the
+// block tests the leaf norms itself, as launch_small_multiply (*pairs zero
+// before).  plan32: leaf 32, the items and prefix of a plan's macro-tile
+// schedule.
+//
+// block_product: where the one-call path takes it.  Leaf 16 and 32: any n (to
+// the tile grid's 1024 per side).  Leaf 64 and 128: n <= 5120; against the
+// general path's plan, 128x128 macro tiles and fixup (one call, leaf 64) it
+// saves two launches and their work list: exp decay 0.05, tau 1e-6, n = 2047 37
+// against 52 us, 5003 112 against 127, 8192 220 against 212; where most pairs
+// are kept the macro tiles' halved operand traffic wins from about n = 2200:
+// decay 0.01, n = 2047 159 against 161, 2500 273 against 238, 5003 669 against
+// 645, 8192 1190 against 1155.
+constexpr int64_t kBlockCoarseMaxN = 5120;
+inline bool block_product(int64_t n, int32_t leaf) {
+    return n >= 4 && (leaf == 16 || leaf == 32 || ((leaf == 64 || leaf == 128) && n <= kBlockCoarseMaxN));
+}
+hipError_t launch_block_test(const float* a, const float* b, float* c, int64_t n, int32_t leaf, int64_t bdim,
+                             const double* na, const double* nb, int64_t ld, double tau, int64_t* pairs,
+                             hipStream_t s);
+hipError_t launch_block_plan32(const float* a, const float* b, float* c, int64_t n, int64_t bdim,
+                               const uint32_t* items, const int32_t* uprefix, hipStream_t s);
 
 // Multiply on single output tiles: persistent, cost-balanced multiply of the
 // kept pairs into C (leaf 128 where the LDS-DMA kernel does not run: more than
@@ -105,13 +122,13 @@ hipError_t launch_multiply(const float* a, const float* b, float* c, int64_t n, 
 hipError_t launch_multiply_leaf16(const float* a, const float* b, float* c, int64_t n, int64_t bdim,
                                   const int32_t* offsets, const int32_t* klist, bool vec, hipStream_t s);
 
-// Multiply on 2x2 macro tiles (leaf 32 and 64), in two steps.  Schedule:
+// Multiply on 2x2 macro tiles, in two steps.  Schedule (leaf 32 and 64):
 // per-macro-tile k bitmaps into words [mb*mb*4*nwords], union sizes into
 // ucount [mb*mb], their exclusive prefix into uprefix [mb*mb + 1], and the
-// union k lists as packed items into items [<= mb*mb*bdim].  Multiply: the
-// persistent kernel over that schedule; the leaf-64 LDS-DMA kernel (n >= 4; it
-// also reads the plan's offsets for its cost model) writes four records per
-// workgroup to bounds [4 * kSplitMaxGroups] and the partial sums of macro
+// union k lists as packed items into items [<= mb*mb*bdim].  Multiply (leaf
+// 64, n >= 4; leaf 32 is launch_block_plan32): the persistent LDS-DMA kernel
+// over that schedule, which also reads the plan's offsets for its cost model,
+// writes four records per workgroup to bounds [4 * kSplitMaxGroups] and the partial sums of macro
 // tiles shared between workgroups to fix_slots [kSplitMaxGroups * 2 * 128 *
 // 128], which a second kernel adds into C; with fix_slots null no macro tile is
 // shared.
@@ -124,9 +141,8 @@ struct MacroSchedule {
 };
 hipError_t launch_macro_schedule(const int32_t* offsets, const int32_t* klist, int64_t bdim, const MacroSchedule& ms,
                                  hipStream_t s);
-hipError_t launch_macro_multiply(const float* a, const float* b, float* c, int64_t n, int32_t leaf, int64_t bdim,
-                                 const int32_t* offsets, const MacroSchedule& ms, bool vec, int num_cus,
-                                 hipStream_t s);
+hipError_t launch_macro_multiply(const float* a, const float* b, float* c, int64_t n, int64_t bdim,
+                                 const int32_t* offsets, const MacroSchedule& ms, int num_cus, hipStream_t s);
 // Leaf 128 (4 <= n, bdim <= kLeaf128MaxBdim) on the LDS-DMA kernel: two items per kept pair (uprefix [bdim*bdim + 1], items
 // [2 * pairs]), then the multiply and fixup kernels with one macro tile per
 // output tile.

@@ -1,0 +1,304 @@
+// Multiply of the kept leaf pairs, one 64x64 block (I, J) of C per workgroup of
+// four waves, wave q on the 32x32 quadrant (q >> 1, q & 1), at any leaf.
+//
+// k is walked in entries of 32.  An entry's four operand tiles (rows 2I + {0, 1}
+// of A, columns 2J + {0, 1} of B, in tiles of 32) are copied straight into LDS,
+// one tile per wave, into one of two stages while the entry before is
+// multiplied; a tile that no kept product reads is not copied.  The waves meet
+// once per entry; four workgroups per CU keep every SIMD supplied with waves of
+// four different blocks, so one block's copies and barriers hide behind the
+// others' MFMAs, and blocks of unequal length need no plan of the work split:
+// the hardware hands out the next one.
+//
+// The entries come either from the leaf norms, the block testing its own
+// products as Algorithm 2's blocks do (multiply_block_kernel<LEAF, true>, the
+// one-call path: no plan launch), or from the items of a plan and schedule,
+// whose macro tiles at leaf 32 are these blocks (<32, false>).  Pairs and their
+// order are the same, ascending k per output tile, at leaf 16 with the MFMA
+// steps of the leaf-16 kernel: at leaf 16 and 32 C is bitwise the same either
+// way.
+//
+// Bound by the matrix cores while the CUs are full: at N = 4096, the matrix
+// 0.1 / (|i-j|^0.1 + 1) at leaf 32 with 15 % of the pairs kept, they are busy 70 %
+// of the CUs' busy cycles (16 KiB of operands per 4 x 1024 cycles of MFMA work,
+// a third of them past L2), and the launch ends with 5 % of the CUs' time idle.
+// One call there 302 -> 236 us (register-staged 2x2 macro tiles in a static
+// split of whole tiles, after a plan launch); exp decay 0.05, tau 1e-6, leaf 32:
+// N = 2048 66 -> 34 us, 8192 287 -> 206; leaf 16: N = 2048 69 -> 36, 8192 601 ->
+// 297; leaf 64: N = 2047 117 -> 36.
+//
+// Sizes that are no multiple of 32, rows at 4-byte alignment: rows and columns
+// past the matrix are read from addresses inside it (they only reach parts of C
+// that are not stored), a chunk across a row's end reads into the next row.
+// Only the last entry, whose k reach past n, is loaded through registers with
+// zeros; it comes last, after the copies.
+#include <hip/hip_runtime.h>
+
+#include "block.h"
+#include "device.h"
+#include "dma.h"
+#include "internal.h"
+
+namespace spamm {
+
+namespace {
+constexpr int kBlockThreads = 256;
+constexpr int kBlockOcc = 4;         // workgroups per CU: 36 KiB of LDS each
+constexpr int kBlockEntries = 1024;  // k entries of a row of tiles (leaf 32: 1024 tiles, leaf 16: 512 pairs)
+
+// Blocks are dealt to the XCDs (workgroups congruent mod 8) by strips of two
+// block rows, so that every XCD gets rows from all over the matrix; the rows
+// left over, fewer than 16, are dealt block by block, so that every XCD gets as
+// many blocks.  Row I's blocks are taken outwards from the diagonal, the
+// longest of decaying matrices first, in rounds of kBlockRun columns over all
+// strips of the XCD: the longest blocks of the whole matrix start first and the
+// short ones fill the end (strip after strip the CUs idled 15 % of the launch
+// at n = 4096), and the run keeps neighbours that share rows of A in L2.
+constexpr int kBlockRun = 8;
+
+struct BlockAt {
+    int I, J;
+    bool valid;
+};
+
+__device__ __forceinline__ BlockAt block_at(int bid, int nb) {
+    const int xcd = bid & 7, idx = bid >> 3;
+    const int dealt = nb / 16 * 16, left = nb - dealt;  // rows in whole rounds of strips
+    const int first = (left * nb + 7) / 8;              // blocks of an XCD in the rows left over
+    int I, step;
+    if (idx < first) {
+        const int r = idx * 8 + xcd;
+        if (r >= left * nb) return {0, 0, false};
+        I = dealt + r % left;
+        step = r / left;
+    } else {
+        const int rows = dealt / 8, r = idx - first;  // rows > 0: idx < first otherwise
+        const int run = r / (rows * kBlockRun), in = r - run * rows * kBlockRun;
+        const int wide = nb - run * kBlockRun < kBlockRun ? nb - run * kBlockRun : kBlockRun;  // columns of this run
+        const int strip = in / (2 * wide), of = in - strip * 2 * wide;
+        I = 2 * (strip * 8 + xcd) + (of & 1);
+        step = run * kBlockRun + (of >> 1);
+    }
+    // columns I, I - 1, I + 1, I - 2, ... while both sides last, then the rest in order
+    const int near = I < nb - 1 - I ? I : nb - 1 - I;
+    int J;
+    if (step <= 2 * near)
+        J = (step & 1) ? I - (step + 1) / 2 : I + step / 2;
+    else
+        J = I < nb - 1 - I ? step : nb - 1 - step;
+    return {I, J, true};
+}
+}  // namespace
+
+static unsigned block_grid(int nb) {
+    const int dealt = nb / 16 * 16;
+    return unsigned((((nb - dealt) * nb + 7) / 8 + dealt / 8 * nb) * 8);
+}
+
+template <int LEAF, bool TEST>
+__global__ __launch_bounds__(kBlockThreads, kBlockOcc) void multiply_block_kernel(
+    const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C, int64_t n, int bdim, int nb,
+    const double* __restrict__ na, const double* __restrict__ nbm, int64_t ld, double tau,
+    unsigned long long* __restrict__ pairs, const uint32_t* __restrict__ items, const int32_t* __restrict__ uprefix) {
+    constexpr int STAGE = 4 * kOpTile;
+    // one LDS object (stages, then the list): see the copies' waits in dma.h
+    constexpr int LIST = TEST ? kBlockEntries : 0, MASKS = TEST && LEAF == 16 ? kBlockEntries / 2 : 0;
+    __shared__ __attribute__((aligned(1024))) float lds[2 * STAGE + LIST + MASKS + 8];
+    uint32_t* list = reinterpret_cast<uint32_t*>(lds + 2 * STAGE);
+    uint32_t* masks = list + LIST;  // leaf 16: the 32 products of a list entry
+    int* wsum = reinterpret_cast<int*>(masks + MASKS);
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const BlockAt at = block_at(blockIdx.x, nb);
+    if (!at.valid) return;
+    const int I = at.I, J = at.J;
+    const int whole = int(n) / 32;  // entries inside the matrix
+
+    // ---- the block's entries: list[e] = k << 4 | quadrants (leaf 16: and masks[e])
+    int count = 0;
+    const uint32_t* plan = nullptr;
+    if constexpr (TEST) {
+        int kept = 0;
+        const int entries = LEAF == 16 ? (bdim + 1) / 2 : (int(n) + 31) / 32;
+        for (int e0 = 0; e0 < entries; e0 += kBlockThreads) {
+            const int e = e0 + tid;
+            uint32_t mem = 0, quads = 0;
+            if constexpr (LEAF >= 64) {
+                constexpr int R = LEAF / 64, S = LEAF / 32;  // blocks and entries per leaf tile side
+                const int k = e / S < bdim ? e / S : bdim - 1;
+                if (e < entries && na[(I / R) * ld + k] * nbm[k * ld + J / R] >= tau) {
+                    kept += I % R == 0 && J % R == 0 && e % S == 0 ? 1 : 0;
+                    mem = quads = (I * 64 + 32 < int(n) ? 0xFu : 0x3u) & (J * 64 + 32 < int(n) ? 0xFu : 0x5u);
+                }
+            } else {
+                constexpr int T = 64 / LEAF, H = 32 / LEAF;  // leaf tiles per block side and per entry
+                double nav[T][H], nbv[H][T];
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+#pragma unroll
+                    for (int h = 0; h < H; ++h) {
+                        const int ti = T * I + t < bdim ? T * I + t : bdim - 1;
+                        const int tj = T * J + t < bdim ? T * J + t : bdim - 1;
+                        const int k = H * e + h < bdim ? H * e + h : bdim - 1;
+                        nav[t][h] = na[ti * ld + k];
+                        nbv[h][t] = nbm[k * ld + tj];
+                    }
+#pragma unroll
+                for (int i = 0; i < T; ++i)
+#pragma unroll
+                    for (int j = 0; j < T; ++j)
+#pragma unroll
+                        for (int h = 0; h < H; ++h) {
+                            const bool in = H * e + h < bdim && T * I + i < bdim && T * J + j < bdim;
+                            const int q = LEAF == 32 ? 2 * i + j : 2 * (i >> 1) + (j >> 1);
+                            const int bit = LEAF == 32 ? q : 8 * q + 4 * (i & 1) + 2 * (j & 1) + h;
+                            if (in && nav[i][h] * nbv[h][j] >= tau) {
+                                mem |= 1u << bit;
+                                quads |= 1u << q;
+                            }
+                        }
+                kept += __popc(mem);
+            }
+            const uint64_t bal = __ballot(mem != 0);
+            if (lane == 0) wsum[wave] = __popcll(bal);
+            __syncthreads();
+            int pos = count + __popcll(bal & (lane == 0 ? 0ull : (~0ull >> (64 - lane))));
+#pragma unroll
+            for (int w = 0; w < kBlockThreads / 64; ++w) {
+                if (w < wave) pos += wsum[w];
+                count += wsum[w];
+            }
+            if (mem) {
+                list[pos] = uint32_t(e) << 4 | quads;
+                if constexpr (LEAF == 16) masks[pos] = mem;
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) kept += __shfl_xor(kept, o);
+        if (lane == 0) wsum[wave] = kept;
+        __syncthreads();
+        if (tid == 0) {
+            const int total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+            if (total) atomicAdd(pairs, static_cast<unsigned long long>(total));
+        }
+    } else {
+        const int64_t m = int64_t(I) * nb + J;
+        plan = items + uprefix[m];
+        count = uprefix[m + 1] - uprefix[m];
+    }
+    count = __builtin_amdgcn_readfirstlane(count);
+    auto entry = [&](int e) -> uint32_t {  // k << 4 | quadrants
+        if constexpr (TEST)
+            return uint32_t(__builtin_amdgcn_readfirstlane(int(list[e])));
+        else
+            return plan[e] & 0x3FFFu;
+    };
+    const bool tail = count > 0 && int(entry(count - 1) >> 4) >= whole;
+    const int full = tail ? count - 1 : count;
+
+    // ---- this wave's operand tile: chunk 64 j + lane of it is row 8 j + lane / 8,
+    // position lane % 8; rows of A and columns of B past the matrix moved inside
+    const OpTile of(A, B, I, J, wave);
+    const bool is_a = wave < 2;
+    const uint32_t need = wave == 0 ? 3u : wave == 1 ? 12u : wave == 2 ? 5u : 10u;
+    uint32_t off[4];  // byte offsets from the entry's base
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int r = 8 * j + (lane >> 3), p = lane & 7;
+        if (is_a) {
+            const int row = of.row0 + r < int(n) ? r : int(n) - 1 - of.row0;
+            off[j] = uint32_t((int64_t(row) * n + 4 * (p ^ (r & 7))) * 4);
+        } else {
+            const int k = LEAF == 16 ? r ^ ((r >> 3) & 1) : r ^ ((r >> 4) & 1);  // the row stored at r (b_at)
+            const int c = LEAF == 16 ? p ^ (4 * ((k >> 2) & 1)) : p;
+            const bool in = of.col0 + 4 * c < int(n);
+            off[j] = uint32_t((int64_t(k) * n + (in ? 4 * c : 0)) * 4);
+        }
+    }
+    const bool outside = is_a ? of.row0 >= int(n) : of.col0 >= int(n);  // nothing of the tile inside: never kept
+    const char* base = reinterpret_cast<const char*>(of.X + (outside ? 0 : (is_a ? int64_t(of.row0) * n : of.col0)));
+    const int64_t step = is_a ? 128 : 128 * n;  // bytes from an entry's tile to the next
+    auto copy = [&](uint32_t pk, int st) {
+        if (!(pk & need)) return;
+        const char* src = base + int64_t(pk >> 4) * step;
+        char* dst = reinterpret_cast<char*>(lds + st * STAGE + wave * kOpTile);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) copy_to_lds(reinterpret_cast<const float*>(src + off[j]), dst + 1024 * j);
+    };
+
+    BlockAcc<LEAF> acc;
+    acc.zero();
+    const int run = n <= 2048 ? 2 : 4;
+    uint32_t cur = full > 0 ? entry(0) : 0u;
+    if (full > 0) copy(cur, 0);
+    for (int e = 0; e < full; ++e) {
+        const uint32_t next = e + 1 < full ? entry(e + 1) : 0u;
+        uint32_t mask = cur;
+        if constexpr (LEAF == 16) mask = uint32_t(__builtin_amdgcn_readfirstlane(int(masks[e])));
+        asm volatile("" ::: "memory");
+        wait_vmcnt<0>();  // this wave's copies of entry e have landed
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (e + 1 < full) copy(next, (e + 1) & 1);  // the stage entry e - 1 used
+        // a wave with MFMAs to issue goes ahead of those that copy or wait
+        __builtin_amdgcn_s_setprio(1);
+        acc.multiply(lds + (e & 1) * STAGE, mask, e, run, wave, lane);
+        __builtin_amdgcn_s_setprio(0);
+        cur = next;
+    }
+    if (tail) {
+        const uint32_t pk = entry(count - 1);
+        uint32_t mask = pk;
+        if constexpr (LEAF == 16) mask = masks[count - 1];
+        float* t = lds + (full & 1) * STAGE + wave * kOpTile;  // the stage entry full - 2 used
+        OpChunk<false> x[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j].load(of, n, int(pk >> 4), 64 * j + lane, (pk & need) != 0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) op_commit<LEAF>(t, wave, 64 * j + lane, x[j].value());
+        __syncthreads();
+        acc.multiply(lds + (full & 1) * STAGE, mask, full, run, wave, lane);
+    }
+    acc.store(C, n, I, J, wave, lane);
+}
+
+namespace {
+template <int LEAF, bool TEST>
+hipError_t launch_block_of(const float* a, const float* b, float* c, int64_t n, int64_t bdim, const double* na,
+                           const double* nb, int64_t ld, double tau, int64_t* pairs, const uint32_t* items,
+                           const int32_t* uprefix, hipStream_t s) {
+    static int scratch_state = 0;
+    const hipError_t ce = check_no_scratch(multiply_block_kernel<LEAF, TEST>, &scratch_state);
+    if (ce != hipSuccess) return ce;
+    const int blocks = int((n + 63) / 64);
+    multiply_block_kernel<LEAF, TEST><<<block_grid(blocks), kBlockThreads, 0, s>>>(
+        a, b, c, n, int(bdim), blocks, na, nb, ld, tau, reinterpret_cast<unsigned long long*>(pairs), items, uprefix);
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_block_test(const float* a, const float* b, float* c, int64_t n, int32_t leaf, int64_t bdim,
+                             const double* na, const double* nb, int64_t ld, double tau, int64_t* pairs,
+                             hipStream_t s) {
+    if (n < 4 || bdim != (n + leaf - 1) / leaf || (n + 31) / 32 > (leaf == 16 ? kBlockEntries / 2 : kBlockEntries))
+        return hipErrorInvalidValue;
+    if (leaf == 16)
+        return launch_block_of<16, true>(a, b, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, s);
+    if (leaf == 32)
+        return launch_block_of<32, true>(a, b, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, s);
+    if (leaf == 64)
+        return launch_block_of<64, true>(a, b, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, s);
+    if (leaf == 128)
+        return launch_block_of<128, true>(a, b, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, s);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_block_plan32(const float* a, const float* b, float* c, int64_t n, int64_t bdim,
+                               const uint32_t* items, const int32_t* uprefix, hipStream_t s) {
+    if (n < 4 || bdim != (n + 31) / 32) return hipErrorInvalidValue;
+    return launch_block_of<32, false>(a, b, c, n, bdim, nullptr, nullptr, 0, 0.0, nullptr, items, uprefix, s);
+}
+
+}  // namespace spamm

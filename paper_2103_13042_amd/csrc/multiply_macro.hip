@@ -1,22 +1,19 @@
 // Multiply of the kept leaf pairs on 2x2 blocks of output tiles ("macro
-// tiles"), for leaf 32 and 64.
+// tiles") at leaf 64 (and 128), and the schedule of such blocks at leaf 32 and
+// 64.
 //
 // A macro tile (I, J) covers output tiles (2I+a, 2J+b), a, b in {0, 1}.  Its
 // k-stream is the union of the four tiles' k-lists in ascending order; for each
 // k the workgroup stages A[2I..2I+1, k] and B[k, 2J..2J+1] once and every wave
-// (a, b) whose own tile keeps that k multiplies its 64x64 (or 32x32) part.  One
-// staged A/B pair thus feeds up to four leaf products, which halves the bytes
-// per flop against one tile per workgroup for banded pair patterns, and every
-// barrier is amortised over twice the MFMA work.
+// whose own tile keeps that k multiplies its part.  One staged A/B pair thus
+// feeds up to four leaf products, which halves the bytes per flop against one
+// tile per workgroup for banded pair patterns, and every barrier is amortised
+// over twice the MFMA work.
 //
-// Work units: a persistent grid of G workgroups splits the macro tiles into
-// contiguous row-major ranges of equal cost (kUnionCost per union k plus
-// kMacroWrite per macro tile, from the prefix of union sizes), XCD-aware as in
-// the single-tile kernel; the leaf-64 LDS-DMA kernel below splits at item
-// granularity instead (see its comment).  The schedule step lists, for every
-// macro tile in order, its union k values with the 4-bit membership of the
-// four tiles (packed items); a workgroup streams its contiguous slice of that
-// list with scalar loads, a few items ahead of the one it multiplies.
+// The schedule step lists, for every macro tile in order, its union k values
+// with the 4-bit membership of the four tiles (packed items); a workgroup
+// streams its contiguous slice of that list with scalar loads, a few items
+// ahead of the one it multiplies.
 #include <hip/hip_runtime.h>
 
 #include "device.h"
@@ -47,36 +44,8 @@ __global__ __launch_bounds__(256) void macro_items_kernel(const uint64_t* __rest
     macro_items_wave(words, uprefix, mb, nw, items, m);
 }
 
-// A persistent grid over the macro tiles, split into contiguous ranges of
-// equal cost (kUnionCost per union k, kMacroWrite per macro tile).
-template <int LEAF, bool VEC>
-__global__ __launch_bounds__(kMacThreads, MacGeom<LEAF>::OCC) void multiply_macro_kernel(
-    const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C, int64_t n, int64_t bdim,
-    int64_t mb, const uint32_t* __restrict__ items, const int32_t* __restrict__ uprefix) {
-    __shared__ __attribute__((aligned(16))) float lds[2 * MacGeom<LEAF>::STAGE];
-    const int64_t groups = gridDim.x;
-    const int64_t bid = blockIdx.x;
-    const int64_t lg = (bid & 7) * (groups >> 3) + (bid >> 3);
-    const int64_t nm = mb * mb;
-    const int64_t total = int64_t(kUnionCost) * uprefix[nm] + int64_t(kMacroWrite) * nm;
-    auto start_of = [&](int64_t gg) {
-        const int64_t target = gg * total;
-        int64_t lo = 0, hi = nm;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            if ((int64_t(kUnionCost) * uprefix[mid] + int64_t(kMacroWrite) * mid) * groups >= target)
-                hi = mid;
-            else
-                lo = mid + 1;
-        }
-        return lo;
-    };
-    macro_range<LEAF, VEC>(A, B, C, n, bdim, mb, items, uprefix, start_of(lg), start_of(lg + 1), lds);
-}
-
 // ---------------------------------------------------------------------------
-// Leaf 64: the same macro-tile stream, but tiles move from global memory
-// straight into LDS (global_load_lds_dwordx4) through kDmaStages LDS stages of
+// Leaf 64: tiles move from global memory straight into LDS (global_load_lds_dwordx4) through kDmaStages LDS stages of
 // one item (kDmaKC k) each, so the copies of the next items are in flight
 // while one is multiplied and no registers stage the data.
 //
@@ -614,37 +583,10 @@ hipError_t launch_macro_schedule(const int32_t* offsets, const int32_t* klist, i
     return hipGetLastError();
 }
 
-template <int LEAF>
-static hipError_t launch_macro_run(const float* a, const float* b, float* c, int64_t n, int64_t bdim,
-                                   const MacroSchedule& ms, bool vec, int num_cus, hipStream_t s) {
-    const int64_t mb = (bdim + 1) / 2, nm = mb * mb;
-    const int64_t cap = ((nm + 7) / 8) * 8;
-    int64_t groups = int64_t(num_cus) * MacGeom<LEAF>::OCC;
-    if (groups > cap) groups = cap;
-    groups = ((groups + 7) / 8) * 8;
-    static int scratch_state[2] = {0, 0};
-    const hipError_t ce = vec ? check_no_scratch(multiply_macro_kernel<LEAF, true>, &scratch_state[1])
-                              : check_no_scratch(multiply_macro_kernel<LEAF, false>, &scratch_state[0]);
-    if (ce != hipSuccess) return ce;
-    if (vec)
-        multiply_macro_kernel<LEAF, true>
-            <<<unsigned(groups), kMacThreads, 0, s>>>(a, b, c, n, bdim, mb, ms.items, ms.uprefix);
-    else
-        multiply_macro_kernel<LEAF, false>
-            <<<unsigned(groups), kMacThreads, 0, s>>>(a, b, c, n, bdim, mb, ms.items, ms.uprefix);
-    return hipGetLastError();
-}
-
-hipError_t launch_macro_multiply(const float* a, const float* b, float* c, int64_t n, int32_t leaf, int64_t bdim,
-                                 const int32_t* offsets, const MacroSchedule& ms, bool vec, int num_cus,
-                                 hipStream_t s) {
-    switch (leaf) {
-        case 32: return launch_macro_run<32>(a, b, c, n, bdim, ms, vec, num_cus, s);
-        case 64:
-            return launch_dma(a, b, c, n, bdim, (bdim + 1) / 2, ms.items, ms.uprefix, offsets, ms.bounds, ms.fix_slots,
-                              num_cus, s);
-        default: return hipErrorInvalidValue;
-    }
+hipError_t launch_macro_multiply(const float* a, const float* b, float* c, int64_t n, int64_t bdim,
+                                 const int32_t* offsets, const MacroSchedule& ms, int num_cus, hipStream_t s) {
+    return launch_dma(a, b, c, n, bdim, (bdim + 1) / 2, ms.items, ms.uprefix, offsets, ms.bounds, ms.fix_slots, num_cus,
+                      s);
 }
 
 }  // namespace spamm

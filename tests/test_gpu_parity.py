@@ -736,3 +736,25 @@ def test_small_products_at_edges(n, offset, leaf):
     clean = np.ones((n, n), dtype=bool)
     clean[row, :] = clean[:, col] = False
     assert np.all(np.isfinite(c2[clean]))
+
+
+@pytest.mark.parametrize("leaf", [16, 32, 64, 128])
+@pytest.mark.parametrize("n,offset", [(352, 0), (1025, 0), (1100, 1), (2081, 0)])
+def test_block_multiply_matches_oracle_and_staged_path(n, offset, leaf):
+    """The one-call path above n = 320 (a block of C per workgroup, testing its
+    own products): k past the last whole entry of 32, block rows left over from
+    the strips dealt to the XCDs, unaligned matrices.  Pairs equal the oracle's,
+    C within the FP32 accumulation bound; leaf 16 and 32 bitwise the staged
+    path's C."""
+    a, b = inputs.exp_decay(n, 0.02, 81), inputs.exp_decay(n, 0.03, 82)
+    prod = oracle_products(a, b, leaf)
+    tau = float(np.quantile(prod, 0.6)) * (1.0 + 1e-9)
+    c_ref, count, _ = oracle.spamm(a, b, tau, leaf)
+    ga, gb = _offset_view(a, offset), _offset_view(b, offset)
+    c = torch.full((n, n), float("nan"), device=DEV)
+    _, pairs = sp.multiply(ga, gb, tau, leaf, c=c)
+    assert pairs == count
+    check_c(c.cpu().numpy(), a, b, tau, leaf, c_ref=c_ref)
+    if leaf <= 32:
+        offsets, klist, _ = sp.prepare(ga, gb, tau, leaf)
+        assert torch.equal(sp.execute(ga, gb, leaf, offsets, klist), c)
