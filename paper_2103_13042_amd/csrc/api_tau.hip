@@ -5,11 +5,11 @@
 
 #include <cfloat>
 #include <cmath>
-#include <cstring>
 #include <limits>
 
 #include "host.h"
 #include "internal.h"
+#include "search.h"
 #include "spamm_tau.h"
 
 using namespace spamm_host;
@@ -17,13 +17,6 @@ using namespace spamm_host;
 namespace {
 
 constexpr double kInf = std::numeric_limits<double>::infinity();
-
-double bits_to_double(unsigned long long u) {
-    double d;
-    static_assert(sizeof(d) == sizeof(u), "64-bit double");
-    std::memcpy(&d, &u, sizeof(d));
-    return d;
-}
 
 // The device-side pieces of one (A, B) problem that the search uses.
 struct Probe {
@@ -34,23 +27,75 @@ struct Probe {
     float* e;
     void* ws;
     hipStream_t s;
+    // regions of the workspace that the norm queries and the error evaluations
+    // borrow; none holds a pyramid or a plan that a caller may have passed
+    double *rows_b, *cols_a, *ksums, *partials, *sums;
+    int32_t* counts;
+    spamm::StepAnswer* answer;
+    int64_t blocks;
 
-    // (smallest norm product >= lo, or +inf; largest norm product)
-    spamm_status bounds(double lo, double* snap, double* pmax) const {
+    void bind() {
         const Layout L = make_layout(g);
-        auto* d = at<unsigned long long>(ws, L.scalars) + 1;
-        spamm_status st = hip_check(spamm::launch_product_bounds(pa, pb, g.bdim, g.lv, lo, d, s), "bounds kernel");
+        rows_b = at<double>(ws, L.spyr[0]);
+        cols_a = at<double>(ws, L.spyr[1]);
+        ksums = at<double>(ws, L.partials);
+        partials = at<double>(ws, L.masks);
+        answer = at<spamm::StepAnswer>(ws, L.offsets);
+        const int64_t nb = (g.n + 63) / 64;
+        blocks = nb * nb;
+        // per 64x64 block of C: a double, an int32 (the k-list regions hold
+        // bdim^3 int32, too little only for the smallest grids)
+        sums = at<double>(ws, nb <= 32 ? L.bounds : L.klist);
+        counts = at<int32_t>(ws, L.pair_scratch);
+    }
+
+    // E is formed block by block with no plan where the kernel's list allows
+    bool by_blocks() const { return g.n >= 4 && g.n <= spamm::kBandMaxN; }
+
+    spamm_status sort() const {
+        return hip_check(spamm::launch_norms_sort(pa, pb, g.bdim, g.lv, rows_b, cols_a, ksums, nullptr, {}, s),
+                         "norm sort kernel");
+    }
+
+    // E at tau from the E of band.base (launch_block_dropped)
+    spamm_status dropped(double tau, spamm::BandJob band) const {
+        const int64_t leaf_level = spamm::level_offset(g.lv);
+        band.sums = sums;
+        band.counts = counts;
+        return hip_check(spamm::launch_block_dropped(a, b, e, g.n, g.leaf, g.bdim, pa + leaf_level, pb + leaf_level,
+                                                     g.side, tau, band, s),
+                         "error kernel");
+    }
+
+    // the answers of the last queries (q.count of them, 0: none) and error
+    // evaluation (evaluated), read back
+    spamm_status read(const spamm::StepQuery& q, bool evaluated, spamm::StepAnswer* h) const {
+        spamm_status st = SPAMM_OK;
+        if (q.count > 0 && (st = hip_check(spamm::launch_norm_query(rows_b, cols_a, g.bdim, q, partials, s),
+                                           "norm query kernel")) != SPAMM_OK)
+            return st;
+        st = hip_check(spamm::launch_step_answer(partials, g.bdim, q.count, sums, counts, evaluated ? blocks : 0, answer,
+                                                 s),
+                       "answer kernel");
         if (st != SPAMM_OK) return st;
-        unsigned long long h[2];
-        if ((st = hip_check(hipMemcpyAsync(h, d, sizeof(h), hipMemcpyDeviceToHost, s), "copy")) != SPAMM_OK) return st;
-        if ((st = hip_check(hipStreamSynchronize(s), "synchronize")) != SPAMM_OK) return st;
-        *snap = bits_to_double(h[0]);
-        if (pmax) *pmax = bits_to_double(h[1]);
-        return SPAMM_OK;
+        if ((st = hip_check(hipMemcpyAsync(h, answer, sizeof(*h), hipMemcpyDeviceToHost, s), "copy")) != SPAMM_OK)
+            return st;
+        return hip_check(hipStreamSynchronize(s), "synchronize");
     }
 
     // relative error at tau, and the number of dropped triples
-    spamm_status error(double tau, double* err, int64_t* dropped) const {
+    spamm_status error(double tau, double* err, int64_t* count) const {
+        if (by_blocks()) {
+            spamm::BandJob band;
+            band.store = 1;
+            spamm_status st = dropped(tau, band);
+            if (st != SPAMM_OK) return st;
+            spamm::StepAnswer h;
+            if ((st = read(spamm::StepQuery{}, true, &h)) != SPAMM_OK) return st;
+            *err = std::sqrt(h.sumsq / ab_sumsq);
+            if (count) *count = h.dropped;
+            return SPAMM_OK;
+        }
         const Layout L = make_layout(g);
         int32_t* offsets = at<int32_t>(ws, L.offsets);
         int32_t* klist = at<int32_t>(ws, L.klist);
@@ -59,7 +104,8 @@ struct Probe {
         spamm_status st = enqueue_plan(g, pa, pb, tau, true, offsets, klist, d_pairs, ws, s);
         if (st != SPAMM_OK) return st;
         if ((st = enqueue_execute(g, a, b, offsets, klist, e, ws, s)) != SPAMM_OK) return st;
-        st = hip_check(spamm::launch_sumsq(e, g.n * g.n, at<double>(ws, L.partials), d_sum, s), "sumsq kernels");
+        // the sum's partials go where the search keeps sums it no longer needs
+        st = hip_check(spamm::launch_sumsq(e, g.n * g.n, ksums, d_sum, s), "sumsq kernels");
         if (st != SPAMM_OK) return st;
         double esq = 0.0;
         int64_t cnt = 0;
@@ -70,7 +116,7 @@ struct Probe {
             return st;
         if ((st = hip_check(hipStreamSynchronize(s), "synchronize")) != SPAMM_OK) return st;
         *err = std::sqrt(esq / ab_sumsq);
-        if (dropped) *dropped = cnt;
+        if (count) *count = cnt;
         return SPAMM_OK;
     }
 
@@ -92,6 +138,92 @@ struct Probe {
     }
 };
 
+// The search's view of a Probe: thresholds snapped up to norm products, and
+// errors at products.  An evaluation carries along the queries that the search
+// asks next whichever way it turns out, so that a step of the bisection costs
+// one synchronisation; the E of the largest passing product is kept in e, and
+// an evaluation adds to it only the products between the two thresholds.
+class Search {
+public:
+    struct Snap {
+        double x, least;  // the smallest norm product >= x (+inf: none)
+        int64_t kept;     // how many products are >= x
+    };
+
+    Search(const Probe& p, double target) : p_(p), target_(target) {}
+
+    spamm_status start(double x, Snap* out, double* most) {
+        spamm_status st = p_.sort();
+        if (st != SPAMM_OK) return st;
+        return ask(&x, 1, nullptr, out, most);
+    }
+
+    spamm_status snap(double x, Snap* out) {
+        for (const Snap& k : known_)
+            if (k.x == x) {
+                *out = k;
+                return SPAMM_OK;
+            }
+        return ask(&x, 1, nullptr, out, nullptr);
+    }
+
+    // error at the product t, with the queries that may follow
+    spamm_status eval(double t, const double* next, int count, bool* pass, double* err) {
+        spamm_status st;
+        if (!p_.by_blocks()) {
+            st = p_.error(t, err, nullptr);
+        } else {
+            if (pending_) {  // the product evaluated last passed: its E becomes the base
+                spamm::BandJob keep = base_;
+                keep.store = 1;
+                if ((st = p_.dropped(passed_, keep)) != SPAMM_OK) return st;
+                base_.base = passed_;
+                base_.has_base = 1;
+                pending_ = false;
+            }
+            if ((st = p_.dropped(t, base_)) != SPAMM_OK) return st;
+            double esq = 0.0;
+            st = ask(next, count, &esq, nullptr, nullptr);
+            *err = std::sqrt(esq / p_.ab_sumsq);
+        }
+        if (st != SPAMM_OK) return st;
+        *pass = *err <= target_;
+        if (*pass) {
+            pending_ = true;
+            passed_ = t;
+        }
+        return SPAMM_OK;
+    }
+
+private:
+    // queries (those > 0 and finite) and, with esq, the evaluation just enqueued
+    spamm_status ask(const double* x, int count, double* esq, Snap* first, double* most) {
+        spamm::StepQuery q{};
+        for (int c = 0; c < count; ++c)
+            if (x[c] > 0.0 && (!std::isinf(x[c]) || first)) q.x[q.count++] = x[c];
+        spamm::StepAnswer h;
+        const spamm_status st = p_.read(q, esq != nullptr, &h);
+        if (st != SPAMM_OK) return st;
+        for (int c = 0; c < q.count; ++c) {
+            known_[at_] = {q.x[c], h.least[c], h.kept[c]};
+            if (c == 0 && first) *first = known_[at_];
+            at_ = (at_ + 1) % kKnown;
+        }
+        if (most) *most = h.most;
+        if (esq) *esq = h.sumsq;
+        return SPAMM_OK;
+    }
+
+    static constexpr int kKnown = 12;
+    const Probe& p_;
+    double target_;
+    Snap known_[kKnown] = {};
+    int at_ = 0;
+    spamm::BandJob base_;
+    bool pending_ = false;
+    double passed_ = 0.0;
+};
+
 spamm_status make_probe(const float* a, const float* b, int64_t n, int32_t leaf, const double* pa, const double* pb,
                         double ab_sumsq, float* e, void* ws, size_t ws_bytes, void* stream, Probe* p) {
     if (!make_geom(n, leaf, &p->g)) return fail(SPAMM_EINVAL, "bad size n=%lld leaf=%d", (long long)n, leaf);
@@ -110,6 +242,7 @@ spamm_status make_probe(const float* a, const float* b, int64_t n, int32_t leaf,
     p->e = e;
     p->ws = ws;
     p->s = static_cast<hipStream_t>(stream);
+    p->bind();
     return SPAMM_OK;
 }
 
@@ -208,89 +341,95 @@ spamm_status spamm_search_tau_for_error(const float* a, const float* b, int64_t 
     if (std::isnan(tau_guess)) return fail(SPAMM_EINVAL, "tau_guess is NaN");
 
     int evals = 0;
-    double pmin = 0.0, pmax = 0.0;
-    if ((st = p.bounds(DBL_TRUE_MIN, &pmin, &pmax)) != SPAMM_OK) return st;
+    double pmax = 0.0;
+    Search find(p, target);
+    Search::Snap low{};
+    if ((st = find.start(DBL_TRUE_MIN, &low, &pmax)) != SPAMM_OK) return st;
+    const double pmin = low.least;
     double lo = 0.0, lo_err = 0.0;  // passing threshold (a product) and its error
+    int64_t kept = low.kept;
     if (std::isinf(pmin)) {
         // every norm product is zero: SpAMM is exactly AB for every tau, and
         // the largest product is 0
         lo = 0.0;
+        if ((st = p.kept(lo, &kept)) != SPAMM_OK) return st;
     } else {
         // invariant: lo is a product with error <= target (the smallest positive
         // product keeps every nonzero pair: error 0); hi is a threshold whose
         // error exceeds the target, +inf standing for "above every product"
         lo = pmin;
         double hi = kInf;
-        auto snap = [&](double x, double* out) { return p.bounds(x, out, nullptr); };
-        auto eval = [&](double t, bool* pass, double* e) -> spamm_status {
-            spamm_status r = p.error(t, e, nullptr);
+        bool pass = false, bracket = true;
+        double e = 0.0;
+        Search::Snap c{};
+        auto middle = [&](double l, double h) { return std::isinf(h) ? pmax : std::sqrt(l) * std::sqrt(h); };
+        auto eval = [&]() -> spamm_status {  // at c, with what may be asked next
+            const double next[3] = {std::nextafter(c.least, kInf), bracket ? c.least * 4.0 : middle(c.least, hi),
+                                    bracket ? c.least / 4.0 : middle(lo, c.least)};
+            const spamm_status r = find.eval(c.least, next, 3, &pass, &e);
             ++evals;
-            *pass = *e <= target;
             return r;
         };
-        bool pass = false;
-        double e = 0.0, c = 0.0;
+        auto accept = [&]() {
+            lo = c.least;
+            lo_err = e;
+            kept = c.kept;
+        };
         if (tau_guess > 0.0 && evals < max_evals) {
             const double g0 = tau_guess < pmin ? pmin : (tau_guess > pmax ? pmax : tau_guess);
-            if ((st = snap(g0, &c)) != SPAMM_OK) return st;
-            if ((st = eval(c, &pass, &e)) != SPAMM_OK) return st;
+            if ((st = find.snap(g0, &c)) != SPAMM_OK) return st;
+            if ((st = eval()) != SPAMM_OK) return st;
             if (pass) {
-                lo = c;
-                lo_err = e;
+                accept();
                 while (evals < max_evals) {  // grow upwards
                     const double up = lo * 4.0;
                     if (up > pmax) break;
-                    if ((st = snap(up, &c)) != SPAMM_OK) return st;
-                    if ((st = eval(c, &pass, &e)) != SPAMM_OK) return st;
+                    if ((st = find.snap(up, &c)) != SPAMM_OK) return st;
+                    if ((st = eval()) != SPAMM_OK) return st;
                     if (!pass) {
-                        hi = c;
+                        hi = c.least;
                         break;
                     }
-                    lo = c;
-                    lo_err = e;
+                    accept();
                 }
             } else {
-                hi = c;
+                hi = c.least;
                 while (evals < max_evals) {  // grow downwards
                     const double down = hi / 4.0;
                     if (down <= pmin) break;
-                    if ((st = snap(down, &c)) != SPAMM_OK) return st;
-                    if (c >= hi) {  // no product in [down, hi): same mask as hi
+                    if ((st = find.snap(down, &c)) != SPAMM_OK) return st;
+                    if (c.least >= hi) {  // no product in [down, hi): same mask as hi
                         hi = down;
                         continue;
                     }
-                    if ((st = eval(c, &pass, &e)) != SPAMM_OK) return st;
+                    if ((st = eval()) != SPAMM_OK) return st;
                     if (pass) {
-                        lo = c;
-                        lo_err = e;
+                        accept();
                         break;
                     }
-                    hi = c;
+                    hi = c.least;
                 }
             }
         }
+        bracket = false;
         for (int guard = 0; evals < max_evals && guard < 8192; ++guard) {
-            double next = 0.0;  // the smallest product above lo
-            if ((st = snap(std::nextafter(lo, kInf), &next)) != SPAMM_OK) return st;
-            if (next >= hi) break;  // lo is the largest passing product
-            double mid = std::isinf(hi) ? pmax : std::sqrt(lo) * std::sqrt(hi);
-            if (!(mid > lo)) mid = next;
-            if ((st = snap(mid, &c)) != SPAMM_OK) return st;
-            if (c >= hi) {  // no product in [mid, hi): mid fails like hi
+            Search::Snap next{};  // the smallest product above lo
+            if ((st = find.snap(std::nextafter(lo, kInf), &next)) != SPAMM_OK) return st;
+            if (next.least >= hi) break;  // lo is the largest passing product
+            double mid = middle(lo, hi);
+            if (!(mid > lo)) mid = next.least;
+            if ((st = find.snap(mid, &c)) != SPAMM_OK) return st;
+            if (c.least >= hi) {  // no product in [mid, hi): mid fails like hi
                 hi = mid;
                 continue;
             }
-            if ((st = eval(c, &pass, &e)) != SPAMM_OK) return st;
-            if (pass) {
-                lo = c;
-                lo_err = e;
-            } else {
-                hi = c;
-            }
+            if ((st = eval()) != SPAMM_OK) return st;
+            if (pass)
+                accept();
+            else
+                hi = c.least;
         }
     }
-    int64_t kept = 0;
-    if ((st = p.kept(lo, &kept)) != SPAMM_OK) return st;
     *tau_out = lo;
     if (err_out) *err_out = lo_err;
     if (pairs_out) *pairs_out = kept;

@@ -140,14 +140,16 @@ struct BlockAcc {
             }
         }
     }
-    __device__ __forceinline__ void store(float* __restrict__ C, int64_t n, int I, int J, int q, int lane) const {
+    // f(element of the matrix, its sum) for every element of the quadrant inside it
+    template <typename F>
+    __device__ __forceinline__ void each(int64_t n, int I, int J, int q, int lane, F f) const {
         const int64_t row0 = 64 * int64_t(I) + 32 * (q >> 1) + 4 * (lane >> 5);
         const int64_t col = 64 * int64_t(J) + 32 * (q & 1) + (lane & 31);
         if (col >= n) return;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int64_t row = row0 + 8 * (r >> 2) + (r & 3);
-            if (row < n) C[row * n + col] = total[r] + acc[r];
+            if (row < n) f(row * n + col, total[r] + acc[r]);
         }
     }
 };
@@ -166,7 +168,8 @@ struct BlockAcc<16> {
         for (int x = 0; x < 4; ++x)
             op_multiply16(acc[x], t, 2 * (q >> 1) + (x >> 1), 2 * (q & 1) + (x & 1), (keep >> (2 * x)) & 3u, lane);
     }
-    __device__ __forceinline__ void store(float* __restrict__ C, int64_t n, int I, int J, int q, int lane) const {
+    template <typename F>
+    __device__ __forceinline__ void each(int64_t n, int I, int J, int q, int lane, F f) const {
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
             const int64_t row0 = 64 * int64_t(I) + 32 * (q >> 1) + 16 * (x >> 1) + 4 * (lane >> 4);
@@ -174,7 +177,7 @@ struct BlockAcc<16> {
             if (col >= n) continue;
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                if (row0 + v < n) C[(row0 + v) * n + col] = acc[x][v];
+                if (row0 + v < n) f((row0 + v) * n + col, acc[x][v]);
         }
     }
 };

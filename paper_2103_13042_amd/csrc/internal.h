@@ -107,6 +107,22 @@ hipError_t launch_block_test(const float* a, const float* b, float* c, int64_t n
                              hipStream_t s);
 hipError_t launch_block_plan32(const float* a, const float* b, float* c, int64_t n, int64_t bdim,
                                const uint32_t* items, const int32_t* uprefix, hipStream_t s);
+// dropped: e plus the products dropped at tau (norm product not >= tau) but not
+// at band.base; per block of C the FP64 sum of squares of the result and the
+// number of products added.  Without a base e counts as zero and every
+// product dropped at tau is added.  4 <= n <= kBandMaxN (the entries that a
+// block's list holds).
+struct BandJob {
+    double base = 0.0;
+    int has_base = 0;
+    int store = 0;              // whether e receives the result
+    double* sums = nullptr;     // [ceil(n / 64)^2]
+    int32_t* counts = nullptr;  // [ceil(n / 64)^2]
+};
+constexpr int64_t kBandMaxN = 65536;
+hipError_t launch_block_dropped(const float* a, const float* b, float* e, int64_t n, int32_t leaf, int64_t bdim,
+                                const double* na, const double* nb, int64_t ld, double tau, const BandJob& band,
+                                hipStream_t s);
 
 // Multiply on single output tiles: persistent, cost-balanced multiply of the
 // kept pairs into C (leaf 128 where the LDS-DMA kernel does not run: more than
@@ -189,10 +205,6 @@ struct MlpLayout {
 
 hipError_t launch_tau_features(const double* pyr_a, const double* pyr_b, int64_t bdim, int lv, float log_target,
                                float* out, hipStream_t s);
-// out[0] = smallest norm product >= lo (+inf bits if none), out[1] = largest
-// product, as double bit patterns.
-hipError_t launch_product_bounds(const double* pyr_a, const double* pyr_b, int64_t bdim, int lv, double lo,
-                                 unsigned long long* out, hipStream_t s);
 // *out = sum of x[q]^2 in FP64; partials holds kSumBlocks doubles.
 hipError_t launch_sumsq(const float* x, int64_t count, double* partials, double* out, hipStream_t s);
 hipError_t launch_mlp_forward(const float* params, const float* x, int batch, float* acts, float* y, hipStream_t s);

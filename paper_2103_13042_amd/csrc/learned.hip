@@ -59,58 +59,6 @@ hipError_t launch_tau_features(const double* pyr_a, const double* pyr_b, int64_t
 }
 
 // --------------------------------------------------------------------------
-// Norm product bounds over the real bdim^3 triples, with products formed as in
-// the plan (fl64(nA[i,k] * nB[k,j])):  out[0] = the smallest product >= lo,
-// out[1] = the largest product, both as the bit patterns of non-negative
-// doubles (which order like unsigned integers), +inf bits when no product is
-// >= lo.  out must hold the initial values {+inf bits, 0} (bounds_init).
-
-__global__ void bounds_init_kernel(unsigned long long* out) {
-    if (threadIdx.x == 0) {
-        out[0] = 0x7FF0000000000000ull;
-        out[1] = 0ull;
-    }
-}
-
-constexpr int kBoundThreads = 256;
-
-__global__ __launch_bounds__(kBoundThreads) void product_bounds_kernel(const double* __restrict__ pyr_a,
-                                                                       const double* __restrict__ pyr_b, int64_t bdim,
-                                                                       int lv, double lo,
-                                                                       unsigned long long* __restrict__ out) {
-    const int64_t side = int64_t(1) << lv;
-    const double* la = pyr_a + level_offset(lv);
-    const double* lb = pyr_b + level_offset(lv);
-    const int64_t i = blockIdx.x;
-    double vmin = INFINITY, vmax = 0.0;
-    const int64_t kj = bdim * bdim;
-    for (int64_t e = threadIdx.x; e < kj; e += kBoundThreads) {
-        const int64_t k = e / bdim, j = e - k * bdim;
-        const double p = la[i * side + k] * lb[k * side + j];
-        if (p >= lo && p < vmin) vmin = p;
-        if (p > vmax) vmax = p;
-    }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        vmin = fmin(vmin, __shfl_xor(vmin, o));
-        vmax = fmax(vmax, __shfl_xor(vmax, o));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        atomicMin(&out[0], static_cast<unsigned long long>(__double_as_longlong(vmin)));
-        atomicMax(&out[1], static_cast<unsigned long long>(__double_as_longlong(vmax)));
-    }
-}
-
-hipError_t launch_product_bounds(const double* pyr_a, const double* pyr_b, int64_t bdim, int lv, double lo,
-                                 unsigned long long* out, hipStream_t s) {
-    bounds_init_kernel<<<1, 64, 0, s>>>(out);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    product_bounds_kernel<<<unsigned(bdim), kBoundThreads, 0, s>>>(pyr_a, pyr_b, bdim, lv, lo, out);
-    return hipGetLastError();
-}
-
-// --------------------------------------------------------------------------
 // Sum of squares of an FP32 array in FP64 (squares are exact in FP64): a fixed
 // grid of kSumBlocks blocks writes one partial each, then one block adds them
 // in a fixed tree order.

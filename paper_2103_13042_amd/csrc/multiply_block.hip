@@ -11,9 +11,9 @@
 // the hardware hands out the next one.
 //
 // The entries come either from the leaf norms, the block testing its own
-// products as Algorithm 2's blocks do (multiply_block_kernel<LEAF, true>, the
-// one-call path: no plan launch), or from the items of a plan and schedule,
-// whose macro tiles at leaf 32 are these blocks (<32, false>).  Pairs and their
+// products as Algorithm 2's blocks do (kKept, the one-call path: no plan
+// launch; kDropped, the error searches below), or from the items of a plan and
+// schedule, whose macro tiles at leaf 32 are these blocks (kPlanned).  Pairs and their
 // order are the same, ascending k per output tile, at leaf 16 with the MFMA
 // steps of the leaf-16 kernel: at leaf 16 and 32 C is bitwise the same either
 // way.
@@ -32,6 +32,12 @@
 // that are not stored), a chunk across a row's end reads into the next row.
 // Only the last entry, whose k reach past n, is loaded through registers with
 // zeros; it comes last, after the copies.
+// kDropped forms the error of a threshold search, E = the sum of the products
+// dropped at tau, in one launch: C holds the E of a lower threshold `base`, the
+// block adds the products dropped at tau but not at base, sums the squares of
+// what that gives, and stores it only if asked to.  The products between two
+// thresholds of a bisection are ever fewer, where E from nothing multiplies
+// most of the matrix each time.
 #include <hip/hip_runtime.h>
 
 #include "block.h"
@@ -44,7 +50,8 @@ namespace spamm {
 namespace {
 constexpr int kBlockThreads = 256;
 constexpr int kBlockOcc = 4;         // workgroups per CU: 36 KiB of LDS each
-constexpr int kBlockEntries = 1024;  // k entries of a row of tiles (leaf 32: 1024 tiles, leaf 16: 512 pairs)
+constexpr int kBlockEntries = 2048;  // k entries that the list holds (leaf 16: half of them)
+constexpr int kKept = 0, kPlanned = 1, kDropped = 2;  // where a block's entries come from
 
 // Blocks are dealt to the XCDs (workgroups congruent mod 8) by strips of two
 // block rows, so that every XCD gets rows from all over the matrix; the rows
@@ -95,18 +102,21 @@ static unsigned block_grid(int nb) {
     return unsigned((((nb - dealt) * nb + 7) / 8 + dealt / 8 * nb) * 8);
 }
 
-template <int LEAF, bool TEST>
+template <int LEAF, int FROM>
 __global__ __launch_bounds__(kBlockThreads, kBlockOcc) void multiply_block_kernel(
     const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C, int64_t n, int bdim, int nb,
     const double* __restrict__ na, const double* __restrict__ nbm, int64_t ld, double tau,
-    unsigned long long* __restrict__ pairs, const uint32_t* __restrict__ items, const int32_t* __restrict__ uprefix) {
+    unsigned long long* __restrict__ pairs, const uint32_t* __restrict__ items, const int32_t* __restrict__ uprefix,
+    BandJob band) {
+    constexpr bool TEST = FROM != kPlanned;
     constexpr int STAGE = 4 * kOpTile;
-    // one LDS object (stages, then the list): see the copies' waits in dma.h
-    constexpr int LIST = TEST ? kBlockEntries : 0, MASKS = TEST && LEAF == 16 ? kBlockEntries / 2 : 0;
+    // one LDS object (stages, then the list, in floats): see the copies' waits in dma.h
+    constexpr int LIST = !TEST ? 0 : LEAF == 16 ? kBlockEntries / 4 : kBlockEntries / 2;
+    constexpr int MASKS = TEST && LEAF == 16 ? kBlockEntries / 4 : 0;
     __shared__ __attribute__((aligned(1024))) float lds[2 * STAGE + LIST + MASKS + 8];
-    uint32_t* list = reinterpret_cast<uint32_t*>(lds + 2 * STAGE);
-    uint32_t* masks = list + LIST;  // leaf 16: the 32 products of a list entry
-    int* wsum = reinterpret_cast<int*>(masks + MASKS);
+    uint16_t* list = reinterpret_cast<uint16_t*>(lds + 2 * STAGE);
+    uint32_t* masks = reinterpret_cast<uint32_t*>(lds + 2 * STAGE + LIST);  // leaf 16: the 32 products of a list entry
+    int* wsum = reinterpret_cast<int*>(lds + 2 * STAGE + LIST + MASKS);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const BlockAt at = block_at(blockIdx.x, nb);
@@ -117,6 +127,12 @@ __global__ __launch_bounds__(kBlockThreads, kBlockOcc) void multiply_block_kerne
     // ---- the block's entries: list[e] = k << 4 | quadrants (leaf 16: and masks[e])
     int count = 0;
     const uint32_t* plan = nullptr;
+    auto chosen = [&](double p) {
+        if constexpr (FROM == kDropped)
+            return !(p >= tau) && (!band.has_base || p >= band.base);
+        else
+            return p >= tau;
+    };
     if constexpr (TEST) {
         int kept = 0;
         const int entries = LEAF == 16 ? (bdim + 1) / 2 : (int(n) + 31) / 32;
@@ -126,7 +142,7 @@ __global__ __launch_bounds__(kBlockThreads, kBlockOcc) void multiply_block_kerne
             if constexpr (LEAF >= 64) {
                 constexpr int R = LEAF / 64, S = LEAF / 32;  // blocks and entries per leaf tile side
                 const int k = e / S < bdim ? e / S : bdim - 1;
-                if (e < entries && na[(I / R) * ld + k] * nbm[k * ld + J / R] >= tau) {
+                if (e < entries && chosen(na[(I / R) * ld + k] * nbm[k * ld + J / R])) {
                     kept += I % R == 0 && J % R == 0 && e % S == 0 ? 1 : 0;
                     mem = quads = (I * 64 + 32 < int(n) ? 0xFu : 0x3u) & (J * 64 + 32 < int(n) ? 0xFu : 0x5u);
                 }
@@ -152,7 +168,7 @@ __global__ __launch_bounds__(kBlockThreads, kBlockOcc) void multiply_block_kerne
                             const bool in = H * e + h < bdim && T * I + i < bdim && T * J + j < bdim;
                             const int q = LEAF == 32 ? 2 * i + j : 2 * (i >> 1) + (j >> 1);
                             const int bit = LEAF == 32 ? q : 8 * q + 4 * (i & 1) + 2 * (j & 1) + h;
-                            if (in && nav[i][h] * nbv[h][j] >= tau) {
+                            if (in && chosen(nav[i][h] * nbv[h][j])) {
                                 mem |= 1u << bit;
                                 quads |= 1u << q;
                             }
@@ -169,7 +185,7 @@ __global__ __launch_bounds__(kBlockThreads, kBlockOcc) void multiply_block_kerne
                 count += wsum[w];
             }
             if (mem) {
-                list[pos] = uint32_t(e) << 4 | quads;
+                list[pos] = uint16_t(e << 4 | quads);
                 if constexpr (LEAF == 16) masks[pos] = mem;
             }
             __syncthreads();
@@ -180,7 +196,10 @@ __global__ __launch_bounds__(kBlockThreads, kBlockOcc) void multiply_block_kerne
         __syncthreads();
         if (tid == 0) {
             const int total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-            if (total) atomicAdd(pairs, static_cast<unsigned long long>(total));
+            if constexpr (FROM == kDropped)
+                band.counts[I * nb + J] = total;
+            else if (total)
+                atomicAdd(pairs, static_cast<unsigned long long>(total));
         }
     } else {
         const int64_t m = int64_t(I) * nb + J;
@@ -261,44 +280,78 @@ __global__ __launch_bounds__(kBlockThreads, kBlockOcc) void multiply_block_kerne
         __syncthreads();
         acc.multiply(lds + (full & 1) * STAGE, mask, full, run, wave, lane);
     }
-    acc.store(C, n, I, J, wave, lane);
+    if constexpr (FROM == kDropped) {
+        double sq = 0.0;
+        acc.each(n, I, J, wave, lane, [&](int64_t at, float v) {
+            const float x = band.has_base ? C[at] + v : v;
+            if (band.store) C[at] = x;
+            sq += double(x) * double(x);
+        });
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) sq += __shfl_xor(sq, o);
+        __syncthreads();  // the list is no longer read
+        double* red = reinterpret_cast<double*>(lds + 2 * STAGE);
+        if (lane == 0) red[wave] = sq;
+        __syncthreads();
+        if (tid == 0) band.sums[I * nb + J] = (red[0] + red[1]) + (red[2] + red[3]);
+    } else {
+        acc.each(n, I, J, wave, lane, [&](int64_t at, float v) { C[at] = v; });
+    }
 }
 
 namespace {
-template <int LEAF, bool TEST>
+template <int LEAF, int FROM>
 hipError_t launch_block_of(const float* a, const float* b, float* c, int64_t n, int64_t bdim, const double* na,
                            const double* nb, int64_t ld, double tau, int64_t* pairs, const uint32_t* items,
-                           const int32_t* uprefix, hipStream_t s) {
+                           const int32_t* uprefix, const BandJob& band, hipStream_t s) {
+    if (n < 4 || bdim != (n + LEAF - 1) / LEAF) return hipErrorInvalidValue;
+    if (FROM != kPlanned && (n + 31) / 32 > (LEAF == 16 ? kBlockEntries / 4 : kBlockEntries))
+        return hipErrorInvalidValue;
     static int scratch_state = 0;
-    const hipError_t ce = check_no_scratch(multiply_block_kernel<LEAF, TEST>, &scratch_state);
+    const hipError_t ce = check_no_scratch(multiply_block_kernel<LEAF, FROM>, &scratch_state);
     if (ce != hipSuccess) return ce;
     const int blocks = int((n + 63) / 64);
-    multiply_block_kernel<LEAF, TEST><<<block_grid(blocks), kBlockThreads, 0, s>>>(
-        a, b, c, n, int(bdim), blocks, na, nb, ld, tau, reinterpret_cast<unsigned long long*>(pairs), items, uprefix);
+    multiply_block_kernel<LEAF, FROM><<<block_grid(blocks), kBlockThreads, 0, s>>>(
+        a, b, c, n, int(bdim), blocks, na, nb, ld, tau, reinterpret_cast<unsigned long long*>(pairs), items, uprefix,
+        band);
     return hipGetLastError();
+}
+
+template <int FROM>
+hipError_t launch_block_leaf(const float* a, const float* b, float* c, int64_t n, int32_t leaf, int64_t bdim,
+                             const double* na, const double* nb, int64_t ld, double tau, int64_t* pairs,
+                             const BandJob& band, hipStream_t s) {
+    switch (leaf) {
+        case 16:
+            return launch_block_of<16, FROM>(a, b, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, band, s);
+        case 32:
+            return launch_block_of<32, FROM>(a, b, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, band, s);
+        case 64:
+            return launch_block_of<64, FROM>(a, b, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, band, s);
+        case 128:
+            return launch_block_of<128, FROM>(a, b, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, band, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 }  // namespace
 
 hipError_t launch_block_test(const float* a, const float* b, float* c, int64_t n, int32_t leaf, int64_t bdim,
                              const double* na, const double* nb, int64_t ld, double tau, int64_t* pairs,
                              hipStream_t s) {
-    if (n < 4 || bdim != (n + leaf - 1) / leaf || (n + 31) / 32 > (leaf == 16 ? kBlockEntries / 2 : kBlockEntries))
-        return hipErrorInvalidValue;
-    if (leaf == 16)
-        return launch_block_of<16, true>(a, b, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, s);
-    if (leaf == 32)
-        return launch_block_of<32, true>(a, b, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, s);
-    if (leaf == 64)
-        return launch_block_of<64, true>(a, b, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, s);
-    if (leaf == 128)
-        return launch_block_of<128, true>(a, b, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, s);
-    return hipErrorInvalidValue;
+    return launch_block_leaf<kKept>(a, b, c, n, leaf, bdim, na, nb, ld, tau, pairs, BandJob{}, s);
 }
 
 hipError_t launch_block_plan32(const float* a, const float* b, float* c, int64_t n, int64_t bdim,
                                const uint32_t* items, const int32_t* uprefix, hipStream_t s) {
-    if (n < 4 || bdim != (n + 31) / 32) return hipErrorInvalidValue;
-    return launch_block_of<32, false>(a, b, c, n, bdim, nullptr, nullptr, 0, 0.0, nullptr, items, uprefix, s);
+    return launch_block_of<32, kPlanned>(a, b, c, n, bdim, nullptr, nullptr, 0, 0.0, nullptr, items, uprefix,
+                                         BandJob{}, s);
+}
+
+hipError_t launch_block_dropped(const float* a, const float* b, float* e, int64_t n, int32_t leaf, int64_t bdim,
+                                const double* na, const double* nb, int64_t ld, double tau, const BandJob& band,
+                                hipStream_t s) {
+    if (!band.sums || !band.counts) return hipErrorInvalidValue;
+    return launch_block_leaf<kDropped>(a, b, e, n, leaf, bdim, na, nb, ld, tau, nullptr, band, s);
 }
 
 }  // namespace spamm

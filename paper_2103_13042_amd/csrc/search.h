@@ -94,4 +94,26 @@ hipError_t launch_ratio_probe(const double* rows_b, const double* cols_a, const 
 // The state after `rounds` rounds, into states[rounds & 1].
 hipError_t launch_ratio_finish(int64_t bdim, SearchState* states, int32_t* const* counts, int rounds, hipStream_t s);
 
+// One question and its answer per step of the search for an error target.
+constexpr int kQueries = 3;
+struct StepAnswer {
+    double sumsq;               // of E at the threshold evaluated
+    double least[kQueries];     // smallest norm product >= x[q], +inf if none
+    double most;                // largest norm product, at least 0
+    int64_t dropped;            // products added to E
+    int64_t kept[kQueries];     // norm products >= x[q]
+};
+struct StepQuery {
+    double x[kQueries];  // each > 0
+    int count;
+};
+// partials: bdim entries of kQueryPartial doubles (launch_norms_sort's arrays
+// as input); the sums and counts of launch_block_dropped over `blocks` blocks
+// (0: none).  The answer is one StepAnswer in device memory.
+constexpr int kQueryPartial = 2 * kQueries + 1;
+hipError_t launch_norm_query(const double* rows_b, const double* cols_a, int64_t bdim, const StepQuery& q,
+                             double* partials, hipStream_t s);
+hipError_t launch_step_answer(const double* partials, int64_t bdim, int queries, const double* sums,
+                              const int32_t* counts, int64_t blocks, StepAnswer* out, hipStream_t s);
+
 }  // namespace spamm

@@ -218,6 +218,150 @@ __global__ __launch_bounds__(kProbeThreads) void ratio_finish_kernel(int bdim, S
     if (threadIdx.x == 0) states[rounds & 1] = st;
 }
 
+// Block k: over the products of this k, per threshold x the smallest one >= x
+// and how many there are, and the largest product.  x > 0, so a zero norm of A
+// has no product to give (0, or NaN against infinity).
+__global__ __launch_bounds__(kProbeThreads) void norm_query_kernel(const double* __restrict__ rows_b,
+                                                                   const double* __restrict__ cols_a, int bdim,
+                                                                   StepQuery q, double* __restrict__ partials) {
+    __shared__ double s[kSortMax];
+    __shared__ double red[kProbeThreads / 64][kQueryPartial];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int64_t k = blockIdx.x;
+    for (int j = tid; j < bdim; j += kProbeThreads) s[j] = rows_b[k * bdim + j];
+    __syncthreads();
+    int step0 = 1;
+    while (2 * step0 <= bdim) step0 *= 2;
+    double least[kQueries], most = 0.0, kept[kQueries];  // counts below 2^20 are exact in FP64
+#pragma unroll
+    for (int c = 0; c < kQueries; ++c) {
+        least[c] = INFINITY;
+        kept[c] = 0.0;
+    }
+    for (int i = tid; i < bdim; i += kProbeThreads) {
+        const double a = cols_a[k * bdim + i];
+        const double top = a * s[bdim - 1];
+        if (top > most) most = top;
+#pragma unroll
+        for (int c = 0; c < kQueries; ++c) {
+            if (c >= q.count) break;
+            const int at = first_kept(s, bdim, step0, a, q.x[c]);
+            if (at < bdim) {
+                least[c] = fmin(least[c], a * s[at]);
+                kept[c] += double(bdim - at);
+            }
+        }
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        most = fmax(most, __shfl_xor(most, o));
+#pragma unroll
+        for (int c = 0; c < kQueries; ++c) {
+            least[c] = fmin(least[c], __shfl_xor(least[c], o));
+            kept[c] += __shfl_xor(kept[c], o);
+        }
+    }
+    if (lane == 0) {
+#pragma unroll
+        for (int c = 0; c < kQueries; ++c) {
+            red[tid >> 6][c] = least[c];
+            red[tid >> 6][kQueries + c] = kept[c];
+        }
+        red[tid >> 6][2 * kQueries] = most;
+    }
+    __syncthreads();
+    if (tid < kQueryPartial) {
+        double v = red[0][tid];
+        for (int w = 1; w < kProbeThreads / 64; ++w)
+            v = tid < kQueries ? fmin(v, red[w][tid]) : tid < 2 * kQueries ? v + red[w][tid] : fmax(v, red[w][tid]);
+        partials[k * kQueryPartial + tid] = v;
+    }
+}
+
+// One block: the partials of a query and of an error evaluation, each in a
+// fixed order.
+__global__ __launch_bounds__(1024) void step_answer_kernel(const double* __restrict__ partials, int bdim, int queries,
+                                                           const double* __restrict__ sums,
+                                                           const int32_t* __restrict__ counts, int64_t blocks,
+                                                           StepAnswer* __restrict__ out) {
+    __shared__ double red[16][kQueryPartial + 1];
+    __shared__ long long redn[16][kQueries + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    double least[kQueries], most = 0.0, sq = 0.0;
+    long long kept[kQueries], dropped = 0;
+#pragma unroll
+    for (int c = 0; c < kQueries; ++c) {
+        least[c] = INFINITY;
+        kept[c] = 0;
+    }
+    if (queries > 0)
+        for (int k = tid; k < bdim; k += 1024) {
+            const double* p = partials + int64_t(k) * kQueryPartial;
+#pragma unroll
+            for (int c = 0; c < kQueries; ++c) {
+                least[c] = fmin(least[c], p[c]);
+                kept[c] += static_cast<long long>(p[kQueries + c]);
+            }
+            most = fmax(most, p[2 * kQueries]);
+        }
+    for (int64_t b = tid; b < blocks; b += 1024) {
+        sq += sums[b];
+        dropped += counts[b];
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        most = fmax(most, __shfl_xor(most, o));
+        sq += __shfl_xor(sq, o);
+        dropped += __shfl_xor(dropped, o);
+#pragma unroll
+        for (int c = 0; c < kQueries; ++c) {
+            least[c] = fmin(least[c], __shfl_xor(least[c], o));
+            kept[c] += __shfl_xor(kept[c], o);
+        }
+    }
+    if (lane == 0) {
+#pragma unroll
+        for (int c = 0; c < kQueries; ++c) {
+            red[wave][c] = least[c];
+            redn[wave][c] = kept[c];
+        }
+        red[wave][kQueries] = most;
+        red[wave][kQueries + 1] = sq;
+        redn[wave][kQueries] = dropped;
+    }
+    __syncthreads();
+    if (tid != 0) return;
+    for (int w = 1; w < 16; ++w) {
+        for (int c = 0; c < kQueries; ++c) {
+            red[0][c] = fmin(red[0][c], red[w][c]);
+            redn[0][c] += redn[w][c];
+        }
+        red[0][kQueries] = fmax(red[0][kQueries], red[w][kQueries]);
+        red[0][kQueries + 1] += red[w][kQueries + 1];
+        redn[0][kQueries] += redn[w][kQueries];
+    }
+    for (int c = 0; c < kQueries; ++c) {
+        out->least[c] = red[0][c];
+        out->kept[c] = redn[0][c];
+    }
+    out->most = red[0][kQueries];
+    out->sumsq = red[0][kQueries + 1];
+    out->dropped = redn[0][kQueries];
+}
+
+hipError_t launch_norm_query(const double* rows_b, const double* cols_a, int64_t bdim, const StepQuery& q,
+                             double* partials, hipStream_t s) {
+    if (q.count < 1 || q.count > kQueries || bdim < 1 || bdim > kSortMax) return hipErrorInvalidValue;
+    norm_query_kernel<<<unsigned(bdim), kProbeThreads, 0, s>>>(rows_b, cols_a, int(bdim), q, partials);
+    return hipGetLastError();
+}
+
+hipError_t launch_step_answer(const double* partials, int64_t bdim, int queries, const double* sums,
+                              const int32_t* counts, int64_t blocks, StepAnswer* out, hipStream_t s) {
+    step_answer_kernel<<<1, 1024, 0, s>>>(partials, int(bdim), queries, sums, counts, blocks, out);
+    return hipGetLastError();
+}
+
 hipError_t launch_norms_sort(const double* pyr_a, const double* pyr_b, int64_t bdim, int lv, double* rows_b,
                              double* cols_a, double* ksums, SearchState* state, const SearchState& init,
                              hipStream_t s) {

@@ -218,3 +218,34 @@ def test_forward_and_gradient_at_batch_edges(batch):
     got, ref = learned.unpack(g.cpu().numpy().astype(np.float64)), learned.unpack(g_ref)
     for name in ref:
         assert np.max(np.abs(got[name] - ref[name])) <= 1e-4 * max(np.max(np.abs(ref[name])), 1e-30), name
+
+
+@pytest.mark.parametrize("n,leaf,guess", [(300, 16, 0.0), (321, 128, 1e-3), (1001, 32, 1e-9), (1500, 64, 0.0), (3, 64, 0.0)])
+def test_search_result_sits_at_the_target(n, leaf, guess):
+    """The threshold returned against FP64 errors formed with torch: its error
+    is within the target and is the one returned, the next norm product's is
+    not, and the count is the plain count (ragged and unaligned sizes, grids
+    that are no power of two, guesses on both sides).  1e-5: FP32 sums of the
+    dropped products, as for error_for_tau above."""
+    a, b = inputs.exp_decay_torch(n, 0.1, 31, DEV), inputs.exp_decay_torch(n, 0.15, 32, DEV)
+    pa, pb = sp.pyramid(a, leaf), sp.pyramid(b, leaf)
+    bd, target = sp.bdim(n, leaf), 1e-3
+    na = sp.pyramid_levels(pa, n, leaf)[-1][:bd, :bd]
+    nb = sp.pyramid_levels(pb, n, leaf)[-1][:bd, :bd]
+    prods = na[:, :, None] * nb[None, :, :]
+    ab = a.double() @ b.double()
+
+    def error(tau):
+        e = torch.zeros_like(ab)
+        for k in range(bd):
+            ks = slice(k * leaf, min(n, (k + 1) * leaf))
+            drop = (prods[:, k, :] < tau).repeat_interleave(leaf, 0)[:n].repeat_interleave(leaf, 1)[:, :n]
+            e += (a[:, ks].double() @ b[ks].double()) * drop
+        return float(e.norm() / ab.norm())
+
+    tau, err, pairs, evals = sp.search_tau_for_error(a, b, leaf, target, pa, pb, float(ab.square().sum()), guess=guess)
+    assert pairs == int((prods >= tau).sum()) and bool((prods == tau).any())
+    assert err <= target and err == pytest.approx(error(tau), rel=1e-5, abs=1e-12)
+    above = prods[prods > tau]
+    if above.numel():
+        assert error(float(above.min())) > target * (1.0 - 1e-5)
