@@ -321,7 +321,7 @@ spamm_status enqueue_multiply(const Geom& g, const float* a, const float* b, con
                               const int32_t* klist, float* c, void* ws, hipStream_t s) {
     const bool vec = (g.n % 4) == 0 && aligned16(a) && aligned16(b);
     const Layout L = make_layout(g);
-    if (g.n < 4 && g.leaf >= 32)  // one tile, smaller than the 16-byte copies of the LDS kernels: any leaf is one tile
+    if (g.n < 4 && g.leaf >= 64)  // one tile, smaller than the 16-byte copies of the LDS-DMA kernel: any leaf is one tile
         return hip_check(spamm::launch_multiply_leaf16(a, b, c, g.n, g.bdim, offsets, klist, vec, s),
                          "multiply kernel");
     if (L.leaf128_dma)

@@ -49,9 +49,6 @@ struct Probe {
         counts = at<int32_t>(ws, L.pair_scratch);
     }
 
-    // E is formed block by block with no plan where the kernel's list allows
-    bool by_blocks() const { return g.n >= 4 && g.n <= spamm::kBandMaxN; }
-
     spamm_status sort() const {
         return hip_check(spamm::launch_norms_sort(pa, pb, g.bdim, g.lv, rows_b, cols_a, ksums, nullptr, {}, s),
                          "norm sort kernel");
@@ -85,38 +82,14 @@ struct Probe {
 
     // relative error at tau, and the number of dropped triples
     spamm_status error(double tau, double* err, int64_t* count) const {
-        if (by_blocks()) {
-            spamm::BandJob band;
-            band.store = 1;
-            spamm_status st = dropped(tau, band);
-            if (st != SPAMM_OK) return st;
-            spamm::StepAnswer h;
-            if ((st = read(spamm::StepQuery{}, true, &h)) != SPAMM_OK) return st;
-            *err = std::sqrt(h.sumsq / ab_sumsq);
-            if (count) *count = h.dropped;
-            return SPAMM_OK;
-        }
-        const Layout L = make_layout(g);
-        int32_t* offsets = at<int32_t>(ws, L.offsets);
-        int32_t* klist = at<int32_t>(ws, L.klist);
-        int64_t* d_pairs = at<int64_t>(ws, L.pairs);
-        double* d_sum = at<double>(ws, L.scalars);
-        spamm_status st = enqueue_plan(g, pa, pb, tau, true, offsets, klist, d_pairs, ws, s);
+        spamm::BandJob band;
+        band.store = 1;
+        spamm_status st = dropped(tau, band);
         if (st != SPAMM_OK) return st;
-        if ((st = enqueue_execute(g, a, b, offsets, klist, e, ws, s)) != SPAMM_OK) return st;
-        // the sum's partials go where the search keeps sums it no longer needs
-        st = hip_check(spamm::launch_sumsq(e, g.n * g.n, ksums, d_sum, s), "sumsq kernels");
-        if (st != SPAMM_OK) return st;
-        double esq = 0.0;
-        int64_t cnt = 0;
-        if ((st = hip_check(hipMemcpyAsync(&esq, d_sum, sizeof(esq), hipMemcpyDeviceToHost, s), "copy")) != SPAMM_OK)
-            return st;
-        if ((st = hip_check(hipMemcpyAsync(&cnt, d_pairs, sizeof(cnt), hipMemcpyDeviceToHost, s), "copy")) !=
-            SPAMM_OK)
-            return st;
-        if ((st = hip_check(hipStreamSynchronize(s), "synchronize")) != SPAMM_OK) return st;
-        *err = std::sqrt(esq / ab_sumsq);
-        if (count) *count = cnt;
+        spamm::StepAnswer h;
+        if ((st = read(spamm::StepQuery{}, true, &h)) != SPAMM_OK) return st;
+        *err = std::sqrt(h.sumsq / ab_sumsq);
+        if (count) *count = h.dropped;
         return SPAMM_OK;
     }
 
@@ -170,23 +143,18 @@ public:
     // error at the product t, with the queries that may follow
     spamm_status eval(double t, const double* next, int count, bool* pass, double* err) {
         spamm_status st;
-        if (!p_.by_blocks()) {
-            st = p_.error(t, err, nullptr);
-        } else {
-            if (pending_) {  // the product evaluated last passed: its E becomes the base
-                spamm::BandJob keep = base_;
-                keep.store = 1;
-                if ((st = p_.dropped(passed_, keep)) != SPAMM_OK) return st;
-                base_.base = passed_;
-                base_.has_base = 1;
-                pending_ = false;
-            }
-            if ((st = p_.dropped(t, base_)) != SPAMM_OK) return st;
-            double esq = 0.0;
-            st = ask(next, count, &esq, nullptr, nullptr);
-            *err = std::sqrt(esq / p_.ab_sumsq);
+        if (pending_) {  // the product evaluated last passed: its E becomes the base
+            spamm::BandJob keep = base_;
+            keep.store = 1;
+            if ((st = p_.dropped(passed_, keep)) != SPAMM_OK) return st;
+            base_.base = passed_;
+            base_.has_base = 1;
+            pending_ = false;
         }
-        if (st != SPAMM_OK) return st;
+        if ((st = p_.dropped(t, base_)) != SPAMM_OK) return st;
+        double esq = 0.0;
+        if ((st = ask(next, count, &esq, nullptr, nullptr)) != SPAMM_OK) return st;
+        *err = std::sqrt(esq / p_.ab_sumsq);
         *pass = *err <= target_;
         if (*pass) {
             pending_ = true;

@@ -1,0 +1,114 @@
+// Batched products: two stages over all products of a batch, the leaf norms and
+// the multiply of 64x64 blocks that test their own products (one launch per
+// leaf class present), with the single-product device code.  A workgroup finds
+// its product by a 64-ary search over the prefix of the stage's work, one read
+// per lane; a binary search is a chain of reads as long as a small block's work.
+// Products are taken largest first, so that the longest blocks start early.
+//
+// A batch of 48 products (n log-uniform in 256 .. 4096, exp decay, leaf 64): 577
+// us with plan, cost and fill launches and the products in persistent
+// single-tile ranges; see the figures at the kernels.
+#include <hip/hip_runtime.h>
+
+#include "block_multiply.h"
+#include "device.h"
+#include "internal.h"
+#include "norms.h"
+
+namespace spamm {
+
+namespace {
+// the last p with base[p] <= x (base ascending, base[0] = 0); the whole wave
+// calls it with the same x
+__device__ __forceinline__ int batch_find(const int64_t* __restrict__ base, int count, int64_t x) {
+    const int lane = threadIdx.x & 63;
+    int lo = 0, len = count;
+    while (len > 1) {
+        const int step = (len + 63) / 64, at = lo + step * lane;
+        const bool le = at < lo + len && base[at] <= x;
+        const int cnt = __popcll(__ballot(le));  // monotone: lanes 0 .. cnt - 1
+        const int end = lo + len;
+        lo += step * (cnt - 1);
+        len = end - lo < step ? end - lo : step;
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
+}
+
+template <int LEAF>
+__device__ __forceinline__ void batch_strip(const float* x, double* norms, int64_t n, int64_t bdim, bool vec,
+                                            int64_t b) {
+    const int64_t chunks = (n + kNormCols - 1) / kNormCols;
+    if (vec)
+        leaf_sumsq_strip<LEAF, true>(x, n, bdim, b / chunks, b % chunks, nullptr, norms, bdim);
+    else
+        leaf_sumsq_strip<LEAF, false>(x, n, bdim, b / chunks, b % chunks, nullptr, norms, bdim);
+}
+}  // namespace
+
+// One block per (tile row, 1024-column chunk) of A (blockIdx.y = 0) or B (1);
+// a product's first block clears its pair counter.
+__global__ __launch_bounds__(kNormThreads) void batch_norms_kernel(const BatchProduct* __restrict__ P,
+                                                                   const int64_t* __restrict__ strip_base, int count) {
+    const int64_t bg = blockIdx.x;
+    const int p = batch_find(strip_base, count, bg);
+    const BatchProduct q = P[p];
+    const int64_t b = bg - strip_base[p];
+    const bool second = blockIdx.y != 0;
+    if (b == 0 && !second && threadIdx.x == 0) *global_ptr(q.pairs) = 0;
+    const float* x = global_ptr(second ? q.b : q.a);
+    double* norms = global_ptr(second ? q.norms[1] : q.norms[0]);
+    switch (q.leaf) {
+        case 32: batch_strip<32>(x, norms, q.n, q.bdim, q.vec != 0, b); break;
+        case 64: batch_strip<64>(x, norms, q.n, q.bdim, q.vec != 0, b); break;
+        default: batch_strip<128>(x, norms, q.n, q.bdim, q.vec != 0, b); break;
+    }
+}
+
+// Products [0, count) of one leaf class, block_base their first blocks.
+template <int LEAF>
+__global__ __launch_bounds__(kBlockThreads, kBlockOcc) void multiply_batch_kernel(
+    const BatchProduct* __restrict__ P, const int64_t* __restrict__ block_base, int count) {
+    const int p = batch_find(block_base, count, blockIdx.x);
+    const BatchProduct q = P[p];
+    block_multiply<LEAF, kKept>(global_ptr(q.a), global_ptr(q.b), global_ptr(q.c), q.n, int(q.bdim),
+                                int((q.n + 63) / 64), global_ptr(q.norms[0]), global_ptr(q.norms[1]), q.bdim, q.tau,
+                                reinterpret_cast<unsigned long long*>(global_ptr(q.pairs)), nullptr, nullptr,
+                                BandJob{}, int(blockIdx.x - block_base[p]));
+}
+
+int64_t batch_strips(int64_t n, int64_t bdim) { return bdim * ((n + kNormCols - 1) / kNormCols); }
+
+int64_t batch_blocks(int64_t n) { return block_grid(int((n + 63) / 64)); }
+
+hipError_t launch_batch(const BatchProduct* prods, const int64_t* strip_base, const int64_t* block_base,
+                        const int32_t* class_count, const int64_t* class_blocks, int64_t strips, int32_t count,
+                        hipStream_t s) {
+    if (strips < 1 || strips > 0x7FFFFFFF) return hipErrorInvalidValue;
+    batch_norms_kernel<<<dim3{unsigned(strips), 2u, 1u}, kNormThreads, 0, s>>>(prods, strip_base, count);
+    hipError_t e = hipGetLastError();
+    static int scratch_state[3] = {0, 0, 0};
+    if (e != hipSuccess || (e = check_no_scratch(multiply_batch_kernel<32>, &scratch_state[0])) != hipSuccess ||
+        (e = check_no_scratch(multiply_batch_kernel<64>, &scratch_state[1])) != hipSuccess ||
+        (e = check_no_scratch(multiply_batch_kernel<128>, &scratch_state[2])) != hipSuccess)
+        return e;
+    int32_t first = 0;
+    for (int cls = 0; cls < kBatchClasses; ++cls) {
+        const int32_t members = class_count[cls];
+        if (members == 0) continue;
+        if (class_blocks[cls] > 0x7FFFFFFF) return hipErrorInvalidValue;
+        const unsigned grid = unsigned(class_blocks[cls]);
+        const BatchProduct* p = prods + first;
+        const int64_t* base = block_base + first;
+        if (cls == 0)
+            multiply_batch_kernel<32><<<grid, kBlockThreads, 0, s>>>(p, base, members);
+        else if (cls == 1)
+            multiply_batch_kernel<64><<<grid, kBlockThreads, 0, s>>>(p, base, members);
+        else
+            multiply_batch_kernel<128><<<grid, kBlockThreads, 0, s>>>(p, base, members);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        first += members;
+    }
+    return hipSuccess;
+}
+
+}  // namespace spamm

@@ -30,8 +30,8 @@ struct OpTile {
 
 // Chunk e (0 .. 255) of an operand tile of entry k: row e / 8, columns 4 (e % 8)
 // .. + 3.  load() issues the load (of any address inside the matrix if the
-// chunk lies outside or is not wanted; n >= 4); value() puts its floats in
-// place, zeros outside the matrix, and is called when the chunk is needed.
+// chunk lies outside or is not wanted); value() puts its floats in place, zeros
+// outside the matrix, and is called when the chunk is needed.
 template <bool VEC>
 struct OpChunk {
     f4 x;
@@ -42,10 +42,18 @@ struct OpChunk {
         const bool in = want && row < int(n) && col < int(n);
         back = in ? over : 4;
         const float* p = t.X + (in ? int64_t(row) * n + col - over : 0);
-        if constexpr (VEC)
+        if constexpr (VEC) {
             x = *reinterpret_cast<const f4*>(p);
-        else
+        } else if (n >= 4) {
             x = *reinterpret_cast<const f4_dw*>(p);
+        } else {  // no four floats in a row of the matrix
+            const float* q = t.X + (in ? int64_t(row) * n : 0);
+            x = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (e < int(n)) x[e] = q[e];
+            back = in ? 0 : 4;
+        }
     }
     __device__ __forceinline__ f4 value() const {
         f4 v;

@@ -75,7 +75,7 @@ inline int64_t plan_macro_clear_words(int64_t bdim) { return (bdim + 1) / 2 + 1;
 hipError_t launch_plan_macro(const double* norms_a, const double* norms_b, int64_t side, int64_t bdim, double tau,
                              const PlanMacroOut& o, hipStream_t s);
 
-// The smallest products (4 <= n <= kSmallMaxN, leaf 16 to 128): the threshold
+// The smallest products (n <= kSmallMaxN, leaf 16 to 128): the threshold
 // test on the leaf norms na / nb (row stride ld) and the multiply of the kept
 // pairs in one launch; adds the number of kept pairs to *pairs, which must be
 // zero before (the norm pass clears it).  vec: n % 4 == 0 and a, b 16-byte
@@ -85,7 +85,7 @@ hipError_t launch_small_multiply(const float* a, const float* b, float* c, int64
                                  int64_t bdim, const double* na, const double* nb, int64_t ld, double tau,
                                  int64_t* pairs, hipStream_t s);
 
-// One 64x64 block of C per workgroup (multiply_block.hip; n >= 4).  test: the
+// One 64x64 block of C per workgroup (multiply_block.hip).  test: the
 // block tests the leaf norms itself, as launch_small_multiply (*pairs zero
 // before).  plan32: leaf 32, the items and prefix of a plan's macro-tile
 // schedule.
@@ -100,7 +100,7 @@ hipError_t launch_small_multiply(const float* a, const float* b, float* c, int64
 // 645, 8192 1190 against 1155.
 constexpr int64_t kBlockCoarseMaxN = 5120;
 inline bool block_product(int64_t n, int32_t leaf) {
-    return n >= 4 && (leaf == 16 || leaf == 32 || ((leaf == 64 || leaf == 128) && n <= kBlockCoarseMaxN));
+    return leaf == 16 || leaf == 32 || ((leaf == 64 || leaf == 128) && n <= kBlockCoarseMaxN);
 }
 hipError_t launch_block_test(const float* a, const float* b, float* c, int64_t n, int32_t leaf, int64_t bdim,
                              const double* na, const double* nb, int64_t ld, double tau, int64_t* pairs,
@@ -110,8 +110,7 @@ hipError_t launch_block_plan32(const float* a, const float* b, float* c, int64_t
 // dropped: e plus the products dropped at tau (norm product not >= tau) but not
 // at band.base; per block of C the FP64 sum of squares of the result and the
 // number of products added.  Without a base e counts as zero and every
-// product dropped at tau is added.  4 <= n <= kBandMaxN (the entries that a
-// block's list holds).
+// product dropped at tau is added.
 struct BandJob {
     double base = 0.0;
     int has_base = 0;
@@ -119,7 +118,6 @@ struct BandJob {
     double* sums = nullptr;     // [ceil(n / 64)^2]
     int32_t* counts = nullptr;  // [ceil(n / 64)^2]
 };
-constexpr int64_t kBandMaxN = 65536;
 hipError_t launch_block_dropped(const float* a, const float* b, float* e, int64_t n, int32_t leaf, int64_t bdim,
                                 const double* na, const double* nb, int64_t ld, double tau, const BandJob& band,
                                 hipStream_t s);
@@ -256,49 +254,31 @@ hipError_t launch_lowp_multiply(const SplitLayout& L, float* c, int64_t n, int64
                                 hipStream_t s);
 
 // --------------------------------------------------------------------------
-// Batched products (kernels.hip): one descriptor per product in device memory.
+// Batched products (batch.hip): one descriptor per product in device memory.
 
 struct BatchProduct {
     const float* a;
     const float* b;
     float* c;
-    double* spyr[2];  // sums of squares (scratch) of A, B
-    double* pyr[2];   // norm pyramids of A, B
-    uint64_t* masks;
-    int32_t* counts;
-    int32_t* bsums;
-    int32_t* boffs;
-    int32_t* offsets;
-    int32_t* klist;
-    int32_t* pair_scratch;
-    int64_t* pairs;  // this product's slot of the caller's pairs array
+    double* norms[2];  // leaf norms of A, B [bdim][bdim]
+    int64_t* pairs;    // this product's slot of the caller's pairs array
     int64_t n, bdim;
-    int32_t leaf, lv, nw, vec;
+    int32_t leaf, vec;
     double tau;
-    int64_t tile_base;  // prefix of bdim^2 over the batch's products with nw > 1
-    int64_t mask_base;  // prefix of nw * bdim over the batch's products with nw > 1
-    int64_t norm_base;  // prefix of bdim * ceil(n / 1024) (norm-pass strips) over the batch
-    int64_t cost_base;  // written on the device: prefix of multiply cost within its leaf class
-    // macro-tile schedule (leaf 32 and 64; mb = 0 for leaf 128): k bitmaps,
-    // union sizes, their prefix, packed items, as in the single-product path
-    uint64_t* mwords;
-    int32_t* mcount;
-    int32_t* mprefix;
-    uint32_t* mitems;
-    int64_t mb;          // macro tiles per side
-    int64_t macro_base;  // prefix of mb^2 over the batch
 };
 
 // leaf classes of the batched multiply: 32, 64, 128
 constexpr int kBatchClasses = 3;
 
-// members: product indices grouped by class (class_count[c] entries each, in
-// class order); class_total receives each class's total multiply cost.
-// total_tiles and total_mask_blocks count the products with nw > 1 only;
-// small_count is the number of products with nw = 1.
-hipError_t launch_batch(const BatchProduct* prods, int32_t count, const int32_t* members,
-                        const int32_t* class_count_host, int64_t* class_total, int64_t total_tiles,
-                        int64_t total_mask_blocks, int64_t total_strips, int64_t total_macros, int32_t small_count,
-                        int num_cus, hipStream_t s);
+// work of a product: norm-pass blocks per matrix, workgroups of the multiply
+int64_t batch_strips(int64_t n, int64_t bdim);
+int64_t batch_blocks(int64_t n);
+
+// prods: class after class (class_count each).  strip_base, block_base [count]:
+// the prefix of batch_strips over the batch, of batch_blocks within each class;
+// strips and class_blocks: the totals.
+hipError_t launch_batch(const BatchProduct* prods, const int64_t* strip_base, const int64_t* block_base,
+                        const int32_t* class_count, const int64_t* class_blocks, int64_t strips, int32_t count,
+                        hipStream_t s);
 
 }  // namespace spamm

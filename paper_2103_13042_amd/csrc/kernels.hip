@@ -13,98 +13,12 @@
 #include "device.h"
 #include "dma.h"
 #include "internal.h"
-#include "macro.h"
+#include "norms.h"
 
 namespace spamm {
 
 // --------------------------------------------------------------------------
-// Leaf norms.  A block of 256 threads reads a strip of `leaf` rows by 1024
-// columns; each thread owns 4 adjacent columns and sums their squares down the
-// strip in FP64 (an FP32 square is exact in FP64), then the leaf/4 threads of
-// one tile combine their sums with an xor butterfly.  Rows are read as whole
-// 4 KiB segments per block, so the pass streams HBM at full coalescing.
-
-constexpr int kNormThreads = 256;
-constexpr int kNormCols = kNormThreads * 4;
-
-// NT: nontemporal loads, for a pass whose input is larger than the
-// infinity cache: A and B are read once here, and keeping them out of the
-// caches leaves room for the multiply's tiles (measured on the N = 8192 step:
-// norm pass 112 -> 90 us, multiply unchanged).  Below that size the multiply
-// profits from what the pass leaves in the cache (batch of small products:
-// 2 % slower with NT).  ALIGNED: the address is a multiple of 16, else of 4.
-template <bool ALIGNED, bool NT>
-__device__ __forceinline__ f4 load_row(const float* p) {
-    if constexpr (ALIGNED) {
-        const f4* q = reinterpret_cast<const f4*>(p);
-        if constexpr (NT)
-            return __builtin_nontemporal_load(q);
-        else
-            return *q;
-    } else {
-        const f4_dw* q = reinterpret_cast<const f4_dw*>(p);
-        if constexpr (NT)
-            return __builtin_nontemporal_load(q);
-        else
-            return *q;
-    }
-}
-
-// strip `strip` (tile row) x column chunk `chunk` of x; tile (strip, tj) goes to
-// sumsq / norms[strip * ld + tj] (either may be null)
-//
-// Rows that are not 16-byte aligned (VEC false: n % 4 != 0, or x itself only
-// 4-byte aligned) are read by the same 16-byte loads at 4-byte alignment,
-// which global loads accept.  The thread whose four columns cross the
-// matrix's edge reads the row's last four instead and drops the ones that its
-// neighbour holds, so no lane runs a loop of its own (one 64-row column of
-// 4-byte loads by that thread took as long as the strip: n = 5003, leaf 64,
-// one matrix 42 -> 20 us, as fast as n = 5000).
-template <int LEAF, bool VEC, bool NT = false>
-__device__ __forceinline__ void leaf_sumsq_strip(const float* __restrict__ x, int64_t n, int64_t bdim, int64_t strip,
-                                                 int64_t chunk, double* sumsq, double* norms, int64_t ld) {
-    constexpr int G = LEAF / 4;  // threads per tile
-    const int64_t r0 = strip * LEAF;
-    const int64_t r1 = r0 + LEAF < n ? r0 + LEAF : n;
-    const int t = threadIdx.x;
-    const int64_t col = chunk * kNormCols + 4 * t;  // columns 4t .. 4t+3 of the chunk
-    double acc0 = 0.0, acc1 = 0.0;
-    if (!VEC && n < 4) {  // no four columns to read
-        for (int64_t r = r0; r < r1; ++r)
-            for (int64_t c = col; c < n; ++c) acc0 += double(x[r * n + c]) * double(x[r * n + c]);
-    } else if (col < n) {
-        const int back = VEC || col + 4 <= n ? 0 : int(col + 4 - n);  // columns that the thread before holds
-        const float* p = x + r0 * n + col - back;
-        auto add = [&](f4 v) {
-            if (!VEC) {
-                v.x = back > 0 ? 0.0f : v.x;
-                v.y = back > 1 ? 0.0f : v.y;
-                v.z = back > 2 ? 0.0f : v.z;
-            }
-            acc0 += double(v.x) * double(v.x) + double(v.y) * double(v.y);
-            acc1 += double(v.z) * double(v.z) + double(v.w) * double(v.w);
-        };
-        int64_t r = r0;
-#pragma unroll 4
-        for (; r + 1 < r1; r += 2) {
-            const f4 v = load_row<VEC, NT>(p);
-            const f4 w = load_row<VEC, NT>(p + n);
-            p += 2 * n;
-            add(v);
-            add(w);
-        }
-        if (r < r1) add(load_row<VEC, NT>(p));
-    }
-    double s = acc0 + acc1;
-#pragma unroll
-    for (int off = 1; off < G; off <<= 1) s += __shfl_xor(s, off);
-    const int64_t tj = col / LEAF;
-    if ((t % G) == 0 && tj < bdim) {
-        const int64_t i = strip * ld + tj;
-        if (sumsq) sumsq[i] = s;
-        if (norms) norms[i] = sqrt(s);
-    }
-}
+// Leaf norms (norms.h).
 
 // words the first block of a norm pass sets to zero (a pair counter, the
 // look-back state of the plan that follows)
@@ -889,492 +803,6 @@ hipError_t launch_multiply(const float* a, const float* b, float* c, int64_t n, 
         case 128: return launch_mul<128>(a, b, c, n, bdim, offsets, klist, pair_scratch, vec, num_cus, s);
         default: return hipErrorInvalidValue;
     }
-}
-
-// --------------------------------------------------------------------------
-// Batched products.  Every stage of the path runs as one launch over all
-// products (the multiply as one persistent launch per leaf class present): a
-// block finds its product by binary search over the prefix of its work in the
-// descriptor array, then runs the single-product code on it.
-
-// product i's descriptor with every pointer in it marked as global memory
-__device__ __forceinline__ BatchProduct product_at(const BatchProduct* __restrict__ P, int64_t i) {
-    BatchProduct q = P[i];
-    q.a = global_ptr(q.a);
-    q.b = global_ptr(q.b);
-    q.c = global_ptr(q.c);
-    for (int m = 0; m < 2; ++m) {
-        q.spyr[m] = global_ptr(q.spyr[m]);
-        q.pyr[m] = global_ptr(q.pyr[m]);
-    }
-    q.masks = global_ptr(q.masks);
-    q.counts = global_ptr(q.counts);
-    q.bsums = global_ptr(q.bsums);
-    q.boffs = global_ptr(q.boffs);
-    q.offsets = global_ptr(q.offsets);
-    q.klist = global_ptr(q.klist);
-    q.pair_scratch = global_ptr(q.pair_scratch);
-    q.pairs = global_ptr(q.pairs);
-    q.mwords = global_ptr(q.mwords);
-    q.mcount = global_ptr(q.mcount);
-    q.mprefix = global_ptr(q.mprefix);
-    q.mitems = global_ptr(q.mitems);
-    return q;
-}
-
-constexpr int kFindTile = 0, kFindMask = 1, kFindNorm = 2;
-
-__device__ __forceinline__ int32_t batch_find(const BatchProduct* __restrict__ P, int32_t count, int64_t x,
-                                              int which) {
-    int32_t lo = 0, hi = count - 1;  // last p with base(p) <= x
-    while (lo < hi) {
-        const int32_t mid = (lo + hi + 1) >> 1;
-        const int64_t base = which == kFindMask ? P[mid].mask_base
-                             : which == kFindNorm ? P[mid].norm_base
-                                                  : P[mid].tile_base;
-        if (base <= x)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo;
-}
-
-// leaf norms: one block per (tile row, 1024-column chunk) of A (blockIdx.y = 0)
-// or B (1), as in the single-product pass
-template <int LEAF>
-__device__ __forceinline__ void batch_strip(const BatchProduct& q, int m, int64_t b) {
-    const int64_t chunks = (q.n + kNormCols - 1) / kNormCols;
-    const int64_t side = int64_t(1) << q.lv, at = level_offset(q.lv);
-    const float* x = m == 0 ? q.a : q.b;
-    double* sp = (m == 0 ? q.spyr[0] : q.spyr[1]) + at;  // selected, not indexed: q stays in registers
-    double* np = (m == 0 ? q.pyr[0] : q.pyr[1]) + at;
-    // chunks fastest here: with the products' strips in strips-fastest order
-    // the batch's pass took 1134 against 1086 us
-    if (q.vec)
-        leaf_sumsq_strip<LEAF, true>(x, q.n, q.bdim, b / chunks, b % chunks, sp, np, side);
-    else
-        leaf_sumsq_strip<LEAF, false>(x, q.n, q.bdim, b / chunks, b % chunks, sp, np, side);
-}
-
-__global__ __launch_bounds__(kNormThreads) void batch_norms_kernel(const BatchProduct* __restrict__ P, int32_t count,
-                                                                   int64_t total_strips) {
-    const int m = blockIdx.y;
-    for (int64_t bg = blockIdx.x; bg < total_strips; bg += gridDim.x) {
-        const BatchProduct q = product_at(P, batch_find(P, count, bg, kFindNorm));
-        const int64_t b = bg - q.norm_base;
-        switch (q.leaf) {
-            case 32: batch_strip<32>(q, m, b); break;
-            case 64: batch_strip<64>(q, m, b); break;
-            default: batch_strip<128>(q, m, b); break;
-        }
-    }
-}
-
-// The pyramid, mask, scan and fill launches plan the products with more than
-// 64 tiles per side (the others have no mask blocks and no tiles in the
-// prefixes; the two small-plan launches below plan them).
-__global__ __launch_bounds__(kPyrThreads) void batch_pyramid_kernel(const BatchProduct* __restrict__ P) {
-    const BatchProduct q = product_at(P, blockIdx.x);
-    if (q.nw == 1) return;
-    const bool b = blockIdx.y != 0;
-    pyramid_build(b ? q.spyr[1] : q.spyr[0], b ? q.pyr[1] : q.pyr[0], q.bdim, q.lv);
-}
-
-__global__ __launch_bounds__(kPlanThreads) void batch_plan_mask_kernel(const BatchProduct* __restrict__ P,
-                                                                       int32_t count, int64_t total_blocks) {
-    for (int64_t bg = blockIdx.x; bg < total_blocks; bg += gridDim.x) {
-        const BatchProduct q = product_at(P, batch_find(P, count, bg, kFindMask));
-        const int64_t b = bg - q.mask_base;
-        plan_mask_block<true, false>(q.pyr[0], q.pyr[1], q.bdim, q.lv, q.tau, q.masks, q.counts, q.bsums, b % q.nw,
-                                     b / q.nw);
-        __syncthreads();
-    }
-}
-
-__global__ __launch_bounds__(kScanThreads) void batch_plan_scan_kernel(const BatchProduct* __restrict__ P) {
-    const BatchProduct q = product_at(P, blockIdx.x);
-    if (q.nw == 1) return;
-    plan_scan_block(q.bsums, q.bdim * q.nw, q.boffs, q.offsets, q.bdim * q.bdim, q.pairs);
-}
-
-// Each wave takes kFillRun consecutive tiles of the batch: one search for the
-// product of the first, then a forward walk over the products (in base order;
-// the last of several products with the same base is the one owning the work).
-constexpr int kFillRun = 8;
-__global__ __launch_bounds__(256) void batch_plan_fill_kernel(const BatchProduct* __restrict__ P, int32_t count,
-                                                              int64_t total_tiles) {
-    for (int64_t t0 = (int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6)) * kFillRun; t0 < total_tiles;
-         t0 += int64_t(gridDim.x) * 4 * kFillRun) {
-        int32_t p = batch_find(P, count, t0, kFindTile);
-        const int64_t t1 = t0 + kFillRun < total_tiles ? t0 + kFillRun : total_tiles;
-        for (int64_t tg = t0; tg < t1; ++tg) {
-            while (p + 1 < count && P[p + 1].tile_base <= tg) ++p;
-            const BatchProduct q = product_at(P, p);
-            plan_fill_wave(q.masks, q.counts, q.boffs, q.bdim, q.offsets, q.klist, tg - q.tile_base);
-        }
-    }
-}
-
-// Products with at most 64 tiles per side (one k word per tile) are planned
-// by two launches over (product, group of 16 tile rows), in place of the
-// pyramid, mask, scan and fill launches above, which then cover only the
-// larger products.  The node tests there only skip work (a node norm bounds
-// every leaf norm below it, and rounding is monotone), so the kept set is the
-// same.  The test launch: wave w of group g takes tile row i = 16 g + w, B's
-// leaf norms staged in LDS transposed (one tile's k column is a contiguous
-// read), one ballot per tile, and writes the row's bitmaps and its pair count.
-// The fill launch: each row's offset is the sum of the counts of the rows
-// above it; then the row's tiles write their k in ascending order.
-constexpr int kSmallPlanThreads = 1024;
-constexpr int kSmallPlanRows = kSmallPlanThreads / 64;  // tile rows per workgroup
-constexpr int kSmallPlanGroups = 64 / kSmallPlanRows;    // workgroups per product
-constexpr int kSmallPlanPitch = 65;                      // doubles per row of the transposed B norms
-
-__global__ __launch_bounds__(kSmallPlanThreads) void batch_plan_small_test_kernel(const BatchProduct* __restrict__ P) {
-    __shared__ double sbt[64 * kSmallPlanPitch];
-    const BatchProduct q = product_at(P, blockIdx.x);
-    const int bdim = int(q.bdim);
-    if (q.nw != 1 || int(blockIdx.y) * kSmallPlanRows >= bdim) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lv = q.lv, side = 1 << lv;
-    const double tau = q.tau;
-    const double* la = q.pyr[0] + level_offset(lv);
-    const double* lb = q.pyr[1] + level_offset(lv);
-    for (int e = tid; e < side * side; e += kSmallPlanThreads)
-        sbt[(e & (side - 1)) * kSmallPlanPitch + (e >> lv)] = lb[e];
-    __syncthreads();
-    const int i = int(blockIdx.y) * kSmallPlanRows + wave;
-    if (i >= bdim) return;
-    const double a = lane < bdim ? la[i * side + lane] : 0.0;
-    const bool live = lane < bdim;
-    uint64_t mask = 0;
-    for (int j0 = 0; j0 < bdim; j0 += 8) {
-        double bv[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) bv[u] = sbt[((j0 + u) & 63) * kSmallPlanPitch + lane];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            if (j0 + u < bdim) {
-                const double p = a * bv[u];
-                const uint64_t m = __ballot(live && p >= tau);
-                if (lane == j0 + u) mask = m;
-            }
-        }
-    }
-    int32_t c = __popcll(mask);
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o);
-    if (live) q.masks[i * bdim + lane] = mask;
-    if (lane == 0) q.bsums[i] = c;
-}
-
-__global__ __launch_bounds__(kSmallPlanThreads) void batch_plan_small_fill_kernel(const BatchProduct* __restrict__ P) {
-    const BatchProduct q = product_at(P, blockIdx.x);
-    const int bdim = int(q.bdim);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int i = int(blockIdx.y) * kSmallPlanRows + wave;
-    if (q.nw != 1 || i >= bdim) return;
-    const int32_t rs = lane < bdim ? q.bsums[lane] : 0;
-    int32_t before = lane < i ? rs : 0;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o);
-    const bool live = lane < bdim;
-    const uint64_t mask = live ? q.masks[i * bdim + lane] : 0ull;
-    const int32_t c = __popcll(mask);
-    int32_t incl = c;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int32_t up = __shfl_up(incl, o);
-        if (lane >= o) incl += up;
-    }
-    const int32_t base = before + incl - c;
-    if (live) q.offsets[i * bdim + lane] = base;
-    if (i == 0) {
-        int32_t total = rs;
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) total += __shfl_xor(total, o);
-        if (lane == 0) {
-            q.offsets[bdim * bdim] = total;
-            *q.pairs = total;
-        }
-    }
-    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    const uint32_t mlo = uint32_t(mask), mhi = uint32_t(mask >> 32);
-    for (int j = 0; j < bdim; ++j) {
-        const uint64_t m = uint64_t(uint32_t(__builtin_amdgcn_readlane(int(mlo), j))) |
-                           (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(mhi), j))) << 32);
-        const int32_t at = __builtin_amdgcn_readlane(base, j);
-        if ((m >> lane) & 1ull) q.klist[at + __popcll(m & below)] = lane;
-    }
-}
-
-// per class, the prefix of multiply cost (kPairCost per kept pair + 1 per
-// tile, as in the single-product partition) over its members, in order
-// Macro-tile schedule of the leaf-32 and leaf-64 products: one wave per macro
-// tile of the batch (prefix macro_base), as macro_words_kernel /
-// macro_items_kernel do for one product, and one block per product for the
-// prefix of union sizes.
-__device__ __forceinline__ int32_t batch_find_macro(const BatchProduct* __restrict__ P, int32_t count, int64_t x) {
-    int32_t lo = 0, hi = count - 1;  // last p with macro_base(p) <= x
-    while (lo < hi) {
-        const int32_t mid = (lo + hi + 1) >> 1;
-        if (P[mid].macro_base <= x)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo;
-}
-
-constexpr int kMacroRun = 4;  // consecutive macro tiles per wave (one search, then a walk)
-__global__ __launch_bounds__(256) void batch_macro_words_kernel(const BatchProduct* __restrict__ P, int32_t count,
-                                                                int64_t total_macros) {
-    __shared__ unsigned long long sw[4][4][16];  // [wave][tile][word]
-    const int wave = threadIdx.x >> 6;
-    for (int64_t m0 = (int64_t(blockIdx.x) * 4 + wave) * kMacroRun; m0 < total_macros;
-         m0 += int64_t(gridDim.x) * 4 * kMacroRun) {
-        int32_t p = batch_find_macro(P, count, m0);
-        const int64_t m1 = m0 + kMacroRun < total_macros ? m0 + kMacroRun : total_macros;
-        for (int64_t gm = m0; gm < m1; ++gm) {
-            while (p + 1 < count && P[p + 1].macro_base <= gm) ++p;
-            const BatchProduct q = product_at(P, p);
-            macro_words_wave(q.offsets, q.klist, q.bdim, q.mb, q.nw, q.mwords, q.mcount, gm - q.macro_base,
-                             sw[wave]);
-        }
-    }
-}
-
-__global__ __launch_bounds__(kScanThreads) void batch_macro_scan_kernel(const BatchProduct* __restrict__ P) {
-    const BatchProduct q = product_at(P, blockIdx.x);
-    if (q.mb == 0) return;
-    const int64_t nm = q.mb * q.mb;
-    plan_scan_block(q.mcount, nm, q.mprefix, q.mprefix, nm, nullptr);
-}
-
-__global__ __launch_bounds__(256) void batch_macro_items_kernel(const BatchProduct* __restrict__ P, int32_t count,
-                                                                int64_t total_macros) {
-    const int wave = threadIdx.x >> 6;
-    for (int64_t m0 = (int64_t(blockIdx.x) * 4 + wave) * kMacroRun; m0 < total_macros;
-         m0 += int64_t(gridDim.x) * 4 * kMacroRun) {
-        int32_t p = batch_find_macro(P, count, m0);
-        const int64_t m1 = m0 + kMacroRun < total_macros ? m0 + kMacroRun : total_macros;
-        for (int64_t gm = m0; gm < m1; ++gm) {
-            while (p + 1 < count && P[p + 1].macro_base <= gm) ++p;
-            const BatchProduct q = product_at(P, p);
-            macro_items_wave(q.mwords, q.mprefix, q.mb, q.nw, q.mitems, gm - q.macro_base);
-        }
-    }
-}
-
-// Cost prefix of each leaf class over its products: leaf 32 runs on macro
-// tiles (kUnionCost per union k + kMacroWrite per macro tile, as the
-// single-product macro kernel), leaf 64 and 128 on single tiles (kPairCost
-// per pair + 1 per tile).  One workgroup; each class's members (contiguous in
-// `members`) are scanned in chunks of kCostThreads.
-constexpr int kCostThreads = 1024;
-__global__ __launch_bounds__(kCostThreads) void batch_cost_kernel(BatchProduct* __restrict__ P,
-                                                                  const int32_t* __restrict__ members, int32_t c0,
-                                                                  int32_t c1, int32_t c2,
-                                                                  int64_t* __restrict__ class_total) {
-    __shared__ int64_t wsum[kCostThreads / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int32_t cnt[kBatchClasses] = {c0, c1, c2};
-    int32_t first = 0;
-    for (int c = 0; c < kBatchClasses; ++c) {
-        int64_t carry = 0;
-        for (int32_t start = 0; start < cnt[c]; start += kCostThreads) {
-            const int32_t k = start + tid;
-            int64_t cost = 0;
-            const int32_t idx = k < cnt[c] ? members[first + k] : -1;
-            if (idx >= 0) {
-                const BatchProduct q = product_at(P, idx);
-                if (q.mb > 0) {
-                    const int64_t nm = q.mb * q.mb;
-                    cost = int64_t(kUnionCost) * q.mprefix[nm] + int64_t(kMacroWrite) * nm;
-                } else {
-                    cost = int64_t(kPairCost) * (*q.pairs) + q.bdim * q.bdim;
-                }
-            }
-            int64_t incl = cost;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int64_t up = __shfl_up(incl, o);
-                if (lane >= o) incl += up;
-            }
-            if (lane == 63) wsum[wave] = incl;
-            __syncthreads();
-            int64_t before = carry;
-            for (int w = 0; w < wave; ++w) before += wsum[w];
-            if (idx >= 0) P[idx].cost_base = before + incl - cost;
-            int64_t chunk = 0;
-            for (int w = 0; w < kCostThreads / 64; ++w) chunk += wsum[w];
-            __syncthreads();
-            carry += chunk;
-        }
-        if (tid == 0) class_total[c] = carry;
-        first += cnt[c];
-    }
-}
-
-// first macro tile m of product q whose cost position reaches g * total / groups
-__device__ __forceinline__ int64_t batch_macro_partition(const BatchProduct& q, int64_t g, int64_t groups,
-                                                         int64_t total) {
-    const int64_t target = g * total, nm = q.mb * q.mb;
-    int64_t lo = 0, hi = nm;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if ((q.cost_base + int64_t(kUnionCost) * q.mprefix[mid] + int64_t(kMacroWrite) * mid) * groups >= target)
-            hi = mid;
-        else
-            lo = mid + 1;
-    }
-    return lo;
-}
-
-// Leaf 32 and 64: a persistent grid over the class's macro tiles (all its
-// products in turn), each workgroup a contiguous range of equal cost.  Three
-// workgroups per CU: the kernel holds both the aligned and the unaligned form
-// of the macro-tile multiply, and at four per CU (128 registers per lane) it
-// spilled to scratch.
-constexpr int kBatchMacOcc = 3;
-
-template <int LEAF>
-__global__ __launch_bounds__(kMacThreads, kBatchMacOcc) void multiply_batch_macro_kernel(
-    const BatchProduct* __restrict__ P, const int32_t* __restrict__ members, int32_t nmem,
-    const int64_t* __restrict__ class_total, int cls) {
-    __shared__ __attribute__((aligned(16))) float lds[2 * MacGeom<LEAF>::STAGE];
-    const int64_t groups = gridDim.x;
-    const int64_t bid = blockIdx.x;
-    const int64_t lg = (bid & 7) * (groups >> 3) + (bid >> 3);
-    const int64_t total = class_total[cls];
-    int32_t lo = 0, hi = nmem - 1;  // last member with cost_base * groups <= lg * total
-    while (lo < hi) {
-        const int32_t mid = (lo + hi + 1) >> 1;
-        if (P[members[mid]].cost_base * groups <= lg * total)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    for (int32_t k = lo; k < nmem; ++k) {
-        const BatchProduct q = product_at(P, members[k]);
-        if (q.cost_base * groups >= (lg + 1) * total) break;
-        const int64_t m0 = batch_macro_partition(q, lg, groups, total);
-        const int64_t m1 = batch_macro_partition(q, lg + 1, groups, total);
-        if (m0 >= m1) continue;
-        if (q.vec)
-            macro_range<LEAF, true>(q.a, q.b, q.c, q.n, q.bdim, q.mb, q.mitems, q.mprefix, m0, m1, lds);
-        else
-            macro_range<LEAF, false>(q.a, q.b, q.c, q.n, q.bdim, q.mb, q.mitems, q.mprefix, m0, m1, lds);
-        __syncthreads();
-    }
-}
-
-// first tile t of product q whose cost position reaches target / groups
-__device__ __forceinline__ int64_t batch_partition(const BatchProduct& q, int64_t g, int64_t groups, int64_t total) {
-    const int64_t target = g * total, nt = q.bdim * q.bdim;
-    int64_t lo = 0, hi = nt;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if ((q.cost_base + int64_t(kPairCost) * q.offsets[mid] + mid) * groups >= target)
-            hi = mid;
-        else
-            lo = mid + 1;
-    }
-    return lo;
-}
-
-template <int LEAF>
-__global__ __launch_bounds__(kMulThreads, MulCfg<LEAF>::OCC) void multiply_batch_kernel(
-    const BatchProduct* __restrict__ P, const int32_t* __restrict__ members, int32_t nmem,
-    const int64_t* __restrict__ class_total, int cls) {
-    __shared__ __attribute__((aligned(16))) float lds[2 * MulGeom<LEAF>::STAGE];
-    __shared__ int32_t ring[kRing];
-    const int64_t groups = gridDim.x;
-    const int64_t bid = blockIdx.x;
-    const int64_t lg = (bid & 7) * (groups >> 3) + (bid >> 3);
-    const int64_t total = class_total[cls];
-    // members whose cost range meets [lg, lg + 1) * total / groups
-    int32_t lo = 0, hi = nmem - 1;  // last member with cost_base * groups <= lg * total
-    while (lo < hi) {
-        const int32_t mid = (lo + hi + 1) >> 1;
-        if (P[members[mid]].cost_base * groups <= lg * total)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    for (int32_t k = lo; k < nmem; ++k) {
-        const BatchProduct q = product_at(P, members[k]);
-        if (q.cost_base * groups >= (lg + 1) * total) break;
-        const int64_t t0 = batch_partition(q, lg, groups, total), t1 = batch_partition(q, lg + 1, groups, total);
-        if (t0 >= t1) continue;
-        if (q.vec)
-            mul_range<LEAF, true>(q.a, q.b, q.c, q.n, q.bdim, q.offsets, q.klist, q.pair_scratch, t0, t1, lds, ring);
-        else
-            mul_range<LEAF, false>(q.a, q.b, q.c, q.n, q.bdim, q.offsets, q.klist, q.pair_scratch, t0, t1, lds,
-                                   ring);
-        __syncthreads();
-    }
-}
-
-hipError_t launch_batch(const BatchProduct* prods, int32_t count, const int32_t* members,
-                        const int32_t* class_count_host, int64_t* class_total, int64_t total_tiles,
-                        int64_t total_mask_blocks, int64_t total_strips, int64_t total_macros, int32_t small_count,
-                        int num_cus, hipStream_t s) {
-    auto blocks = [](int64_t work, int64_t cap) { return unsigned(work < cap ? (work > 0 ? work : 1) : cap); };
-    batch_norms_kernel<<<dim3{blocks(total_strips, 1 << 20), 2u, 1u}, kNormThreads, 0, s>>>(prods, count,
-                                                                                           total_strips);
-    if (total_mask_blocks > 0) {
-        batch_pyramid_kernel<<<dim3{unsigned(count), 2u, 1u}, kPyrThreads, 0, s>>>(prods);
-        batch_plan_mask_kernel<<<blocks(total_mask_blocks, 1 << 20), kPlanThreads, 0, s>>>(prods, count,
-                                                                                           total_mask_blocks);
-        batch_plan_scan_kernel<<<unsigned(count), kScanThreads, 0, s>>>(prods);
-        batch_plan_fill_kernel<<<blocks((total_tiles + 4 * kFillRun - 1) / (4 * kFillRun), 1 << 20), 256, 0, s>>>(
-            prods, count, total_tiles);
-    }
-    if (small_count > 0) {
-        const dim3 grid{unsigned(count), unsigned(kSmallPlanGroups), 1u};
-        batch_plan_small_test_kernel<<<grid, kSmallPlanThreads, 0, s>>>(prods);
-        batch_plan_small_fill_kernel<<<grid, kSmallPlanThreads, 0, s>>>(prods);
-    }
-    if (total_macros > 0) {
-        const unsigned mblocks = blocks((total_macros + 4 * kMacroRun - 1) / (4 * kMacroRun), 1 << 20);
-        batch_macro_words_kernel<<<mblocks, 256, 0, s>>>(prods, count, total_macros);
-        batch_macro_scan_kernel<<<unsigned(count), kScanThreads, 0, s>>>(prods);
-        batch_macro_items_kernel<<<mblocks, 256, 0, s>>>(prods, count, total_macros);
-    }
-    batch_cost_kernel<<<1, kCostThreads, 0, s>>>(const_cast<BatchProduct*>(prods), members, class_count_host[0],
-                                       class_count_host[1], class_count_host[2], class_total);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    static int scratch_state[3] = {0, 0, 0};
-    if ((e = check_no_scratch(multiply_batch_macro_kernel<32>, &scratch_state[0])) != hipSuccess ||
-        (e = check_no_scratch(multiply_batch_kernel<64>, &scratch_state[1])) != hipSuccess ||
-        (e = check_no_scratch(multiply_batch_kernel<128>, &scratch_state[2])) != hipSuccess)
-        return e;
-    int32_t first = 0;
-    for (int c = 0; c < kBatchClasses; ++c) {
-        const int32_t nmem = class_count_host[c];
-        if (nmem > 0) {
-            const unsigned groups = unsigned(num_cus * (c == 1 ? MulCfg<64>::OCC : MulCfg<128>::OCC));
-            switch (c) {
-                case 0:
-                    multiply_batch_macro_kernel<32><<<unsigned(num_cus * kBatchMacOcc), kMacThreads, 0, s>>>(
-                        prods, members + first, nmem, class_total, c);
-                    break;
-                case 1:
-                    multiply_batch_kernel<64><<<groups, kMulThreads, 0, s>>>(prods, members + first, nmem,
-                                                                             class_total, c);
-                    break;
-                default:
-                    multiply_batch_kernel<128><<<groups, kMulThreads, 0, s>>>(prods, members + first, nmem,
-                                                                              class_total, c);
-                    break;
-            }
-        }
-        first += nmem;
-    }
-    return hipGetLastError();
 }
 
 }  // namespace spamm

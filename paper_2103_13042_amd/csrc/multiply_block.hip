@@ -40,67 +40,9 @@
 // most of the matrix each time.
 #include <hip/hip_runtime.h>
 
-#include "block.h"
-#include "device.h"
-#include "dma.h"
-#include "internal.h"
+#include "block_multiply.h"
 
 namespace spamm {
-
-namespace {
-constexpr int kBlockThreads = 256;
-constexpr int kBlockOcc = 4;         // workgroups per CU: 36 KiB of LDS each
-constexpr int kBlockEntries = 2048;  // k entries that the list holds (leaf 16: half of them)
-constexpr int kKept = 0, kPlanned = 1, kDropped = 2;  // where a block's entries come from
-
-// Blocks are dealt to the XCDs (workgroups congruent mod 8) by strips of two
-// block rows, so that every XCD gets rows from all over the matrix; the rows
-// left over, fewer than 16, are dealt block by block, so that every XCD gets as
-// many blocks.  Row I's blocks are taken outwards from the diagonal, the
-// longest of decaying matrices first, in rounds of kBlockRun columns over all
-// strips of the XCD: the longest blocks of the whole matrix start first and the
-// short ones fill the end (strip after strip the CUs idled 15 % of the launch
-// at n = 4096), and the run keeps neighbours that share rows of A in L2.
-constexpr int kBlockRun = 8;
-
-struct BlockAt {
-    int I, J;
-    bool valid;
-};
-
-__device__ __forceinline__ BlockAt block_at(int bid, int nb) {
-    const int xcd = bid & 7, idx = bid >> 3;
-    const int dealt = nb / 16 * 16, left = nb - dealt;  // rows in whole rounds of strips
-    const int first = (left * nb + 7) / 8;              // blocks of an XCD in the rows left over
-    int I, step;
-    if (idx < first) {
-        const int r = idx * 8 + xcd;
-        if (r >= left * nb) return {0, 0, false};
-        I = dealt + r % left;
-        step = r / left;
-    } else {
-        const int rows = dealt / 8, r = idx - first;  // rows > 0: idx < first otherwise
-        const int run = r / (rows * kBlockRun), in = r - run * rows * kBlockRun;
-        const int wide = nb - run * kBlockRun < kBlockRun ? nb - run * kBlockRun : kBlockRun;  // columns of this run
-        const int strip = in / (2 * wide), of = in - strip * 2 * wide;
-        I = 2 * (strip * 8 + xcd) + (of & 1);
-        step = run * kBlockRun + (of >> 1);
-    }
-    // columns I, I - 1, I + 1, I - 2, ... while both sides last, then the rest in order
-    const int near = I < nb - 1 - I ? I : nb - 1 - I;
-    int J;
-    if (step <= 2 * near)
-        J = (step & 1) ? I - (step + 1) / 2 : I + step / 2;
-    else
-        J = I < nb - 1 - I ? step : nb - 1 - step;
-    return {I, J, true};
-}
-}  // namespace
-
-static unsigned block_grid(int nb) {
-    const int dealt = nb / 16 * 16;
-    return unsigned((((nb - dealt) * nb + 7) / 8 + dealt / 8 * nb) * 8);
-}
 
 template <int LEAF, int FROM>
 __global__ __launch_bounds__(kBlockThreads, kBlockOcc) void multiply_block_kernel(
@@ -108,195 +50,7 @@ __global__ __launch_bounds__(kBlockThreads, kBlockOcc) void multiply_block_kerne
     const double* __restrict__ na, const double* __restrict__ nbm, int64_t ld, double tau,
     unsigned long long* __restrict__ pairs, const uint32_t* __restrict__ items, const int32_t* __restrict__ uprefix,
     BandJob band) {
-    constexpr bool TEST = FROM != kPlanned;
-    constexpr int STAGE = 4 * kOpTile;
-    // one LDS object (stages, then the list, in floats): see the copies' waits in dma.h
-    constexpr int LIST = !TEST ? 0 : LEAF == 16 ? kBlockEntries / 4 : kBlockEntries / 2;
-    constexpr int MASKS = TEST && LEAF == 16 ? kBlockEntries / 4 : 0;
-    __shared__ __attribute__((aligned(1024))) float lds[2 * STAGE + LIST + MASKS + 8];
-    uint16_t* list = reinterpret_cast<uint16_t*>(lds + 2 * STAGE);
-    uint32_t* masks = reinterpret_cast<uint32_t*>(lds + 2 * STAGE + LIST);  // leaf 16: the 32 products of a list entry
-    int* wsum = reinterpret_cast<int*>(lds + 2 * STAGE + LIST + MASKS);
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const BlockAt at = block_at(blockIdx.x, nb);
-    if (!at.valid) return;
-    const int I = at.I, J = at.J;
-    const int whole = int(n) / 32;  // entries inside the matrix
-
-    // ---- the block's entries: list[e] = k << 4 | quadrants (leaf 16: and masks[e])
-    int count = 0;
-    const uint32_t* plan = nullptr;
-    auto chosen = [&](double p) {
-        if constexpr (FROM == kDropped)
-            return !(p >= tau) && (!band.has_base || p >= band.base);
-        else
-            return p >= tau;
-    };
-    if constexpr (TEST) {
-        int kept = 0;
-        const int entries = LEAF == 16 ? (bdim + 1) / 2 : (int(n) + 31) / 32;
-        for (int e0 = 0; e0 < entries; e0 += kBlockThreads) {
-            const int e = e0 + tid;
-            uint32_t mem = 0, quads = 0;
-            if constexpr (LEAF >= 64) {
-                constexpr int R = LEAF / 64, S = LEAF / 32;  // blocks and entries per leaf tile side
-                const int k = e / S < bdim ? e / S : bdim - 1;
-                if (e < entries && chosen(na[(I / R) * ld + k] * nbm[k * ld + J / R])) {
-                    kept += I % R == 0 && J % R == 0 && e % S == 0 ? 1 : 0;
-                    mem = quads = (I * 64 + 32 < int(n) ? 0xFu : 0x3u) & (J * 64 + 32 < int(n) ? 0xFu : 0x5u);
-                }
-            } else {
-                constexpr int T = 64 / LEAF, H = 32 / LEAF;  // leaf tiles per block side and per entry
-                double nav[T][H], nbv[H][T];
-#pragma unroll
-                for (int t = 0; t < T; ++t)
-#pragma unroll
-                    for (int h = 0; h < H; ++h) {
-                        const int ti = T * I + t < bdim ? T * I + t : bdim - 1;
-                        const int tj = T * J + t < bdim ? T * J + t : bdim - 1;
-                        const int k = H * e + h < bdim ? H * e + h : bdim - 1;
-                        nav[t][h] = na[ti * ld + k];
-                        nbv[h][t] = nbm[k * ld + tj];
-                    }
-#pragma unroll
-                for (int i = 0; i < T; ++i)
-#pragma unroll
-                    for (int j = 0; j < T; ++j)
-#pragma unroll
-                        for (int h = 0; h < H; ++h) {
-                            const bool in = H * e + h < bdim && T * I + i < bdim && T * J + j < bdim;
-                            const int q = LEAF == 32 ? 2 * i + j : 2 * (i >> 1) + (j >> 1);
-                            const int bit = LEAF == 32 ? q : 8 * q + 4 * (i & 1) + 2 * (j & 1) + h;
-                            if (in && chosen(nav[i][h] * nbv[h][j])) {
-                                mem |= 1u << bit;
-                                quads |= 1u << q;
-                            }
-                        }
-                kept += __popc(mem);
-            }
-            const uint64_t bal = __ballot(mem != 0);
-            if (lane == 0) wsum[wave] = __popcll(bal);
-            __syncthreads();
-            int pos = count + __popcll(bal & (lane == 0 ? 0ull : (~0ull >> (64 - lane))));
-#pragma unroll
-            for (int w = 0; w < kBlockThreads / 64; ++w) {
-                if (w < wave) pos += wsum[w];
-                count += wsum[w];
-            }
-            if (mem) {
-                list[pos] = uint16_t(e << 4 | quads);
-                if constexpr (LEAF == 16) masks[pos] = mem;
-            }
-            __syncthreads();
-        }
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) kept += __shfl_xor(kept, o);
-        if (lane == 0) wsum[wave] = kept;
-        __syncthreads();
-        if (tid == 0) {
-            const int total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-            if constexpr (FROM == kDropped)
-                band.counts[I * nb + J] = total;
-            else if (total)
-                atomicAdd(pairs, static_cast<unsigned long long>(total));
-        }
-    } else {
-        const int64_t m = int64_t(I) * nb + J;
-        plan = items + uprefix[m];
-        count = uprefix[m + 1] - uprefix[m];
-    }
-    count = __builtin_amdgcn_readfirstlane(count);
-    auto entry = [&](int e) -> uint32_t {  // k << 4 | quadrants
-        if constexpr (TEST)
-            return uint32_t(__builtin_amdgcn_readfirstlane(int(list[e])));
-        else
-            return plan[e] & 0x3FFFu;
-    };
-    const bool tail = count > 0 && int(entry(count - 1) >> 4) >= whole;
-    const int full = tail ? count - 1 : count;
-
-    // ---- this wave's operand tile: chunk 64 j + lane of it is row 8 j + lane / 8,
-    // position lane % 8; rows of A and columns of B past the matrix moved inside
-    const OpTile of(A, B, I, J, wave);
-    const bool is_a = wave < 2;
-    const uint32_t need = wave == 0 ? 3u : wave == 1 ? 12u : wave == 2 ? 5u : 10u;
-    uint32_t off[4];  // byte offsets from the entry's base
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int r = 8 * j + (lane >> 3), p = lane & 7;
-        if (is_a) {
-            const int row = of.row0 + r < int(n) ? r : int(n) - 1 - of.row0;
-            off[j] = uint32_t((int64_t(row) * n + 4 * (p ^ (r & 7))) * 4);
-        } else {
-            const int k = LEAF == 16 ? r ^ ((r >> 3) & 1) : r ^ ((r >> 4) & 1);  // the row stored at r (b_at)
-            const int c = LEAF == 16 ? p ^ (4 * ((k >> 2) & 1)) : p;
-            const bool in = of.col0 + 4 * c < int(n);
-            off[j] = uint32_t((int64_t(k) * n + (in ? 4 * c : 0)) * 4);
-        }
-    }
-    const bool outside = is_a ? of.row0 >= int(n) : of.col0 >= int(n);  // nothing of the tile inside: never kept
-    const char* base = reinterpret_cast<const char*>(of.X + (outside ? 0 : (is_a ? int64_t(of.row0) * n : of.col0)));
-    const int64_t step = is_a ? 128 : 128 * n;  // bytes from an entry's tile to the next
-    auto copy = [&](uint32_t pk, int st) {
-        if (!(pk & need)) return;
-        const char* src = base + int64_t(pk >> 4) * step;
-        char* dst = reinterpret_cast<char*>(lds + st * STAGE + wave * kOpTile);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) copy_to_lds(reinterpret_cast<const float*>(src + off[j]), dst + 1024 * j);
-    };
-
-    BlockAcc<LEAF> acc;
-    acc.zero();
-    const int run = n <= 2048 ? 2 : 4;
-    uint32_t cur = full > 0 ? entry(0) : 0u;
-    if (full > 0) copy(cur, 0);
-    for (int e = 0; e < full; ++e) {
-        const uint32_t next = e + 1 < full ? entry(e + 1) : 0u;
-        uint32_t mask = cur;
-        if constexpr (LEAF == 16) mask = uint32_t(__builtin_amdgcn_readfirstlane(int(masks[e])));
-        asm volatile("" ::: "memory");
-        wait_vmcnt<0>();  // this wave's copies of entry e have landed
-        __builtin_amdgcn_s_waitcnt(0xC07F);
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        if (e + 1 < full) copy(next, (e + 1) & 1);  // the stage entry e - 1 used
-        // a wave with MFMAs to issue goes ahead of those that copy or wait
-        __builtin_amdgcn_s_setprio(1);
-        acc.multiply(lds + (e & 1) * STAGE, mask, e, run, wave, lane);
-        __builtin_amdgcn_s_setprio(0);
-        cur = next;
-    }
-    if (tail) {
-        const uint32_t pk = entry(count - 1);
-        uint32_t mask = pk;
-        if constexpr (LEAF == 16) mask = masks[count - 1];
-        float* t = lds + (full & 1) * STAGE + wave * kOpTile;  // the stage entry full - 2 used
-        OpChunk<false> x[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) x[j].load(of, n, int(pk >> 4), 64 * j + lane, (pk & need) != 0);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) op_commit<LEAF>(t, wave, 64 * j + lane, x[j].value());
-        __syncthreads();
-        acc.multiply(lds + (full & 1) * STAGE, mask, full, run, wave, lane);
-    }
-    if constexpr (FROM == kDropped) {
-        double sq = 0.0;
-        acc.each(n, I, J, wave, lane, [&](int64_t at, float v) {
-            const float x = band.has_base ? C[at] + v : v;
-            if (band.store) C[at] = x;
-            sq += double(x) * double(x);
-        });
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) sq += __shfl_xor(sq, o);
-        __syncthreads();  // the list is no longer read
-        double* red = reinterpret_cast<double*>(lds + 2 * STAGE);
-        if (lane == 0) red[wave] = sq;
-        __syncthreads();
-        if (tid == 0) band.sums[I * nb + J] = (red[0] + red[1]) + (red[2] + red[3]);
-    } else {
-        acc.each(n, I, J, wave, lane, [&](int64_t at, float v) { C[at] = v; });
-    }
+    block_multiply<LEAF, FROM>(A, B, C, n, bdim, nb, na, nbm, ld, tau, pairs, items, uprefix, band, int(blockIdx.x));
 }
 
 namespace {
@@ -304,9 +58,7 @@ template <int LEAF, int FROM>
 hipError_t launch_block_of(const float* a, const float* b, float* c, int64_t n, int64_t bdim, const double* na,
                            const double* nb, int64_t ld, double tau, int64_t* pairs, const uint32_t* items,
                            const int32_t* uprefix, const BandJob& band, hipStream_t s) {
-    if (n < 4 || bdim != (n + LEAF - 1) / LEAF) return hipErrorInvalidValue;
-    if (FROM != kPlanned && (n + 31) / 32 > (LEAF == 16 ? kBlockEntries / 4 : kBlockEntries))
-        return hipErrorInvalidValue;
+    if (n < 1 || bdim != (n + LEAF - 1) / LEAF || bdim > 1024) return hipErrorInvalidValue;
     static int scratch_state = 0;
     const hipError_t ce = check_no_scratch(multiply_block_kernel<LEAF, FROM>, &scratch_state);
     if (ce != hipSuccess) return ce;

@@ -236,7 +236,7 @@ hipError_t launch_small_multiply(const float* a, const float* b, float* c, int64
                                  int64_t bdim, const double* na, const double* nb, int64_t ld, double tau,
                                  int64_t* pairs, hipStream_t s) {
     static_assert(kSmallMaxN <= 32 * kStripEntries, "every operand tile of a block in LDS");
-    if (n < 4 || n > kSmallMaxN || bdim != (n + leaf - 1) / leaf || (vec && n % 4 != 0)) return hipErrorInvalidValue;
+    if (n < 1 || n > kSmallMaxN || bdim != (n + leaf - 1) / leaf || (vec && n % 4 != 0)) return hipErrorInvalidValue;
     switch (leaf) {
         case 16: return launch_strip<16>(a, b, c, n, vec, bdim, na, nb, ld, tau, pairs, s);
         case 32: return launch_strip<32>(a, b, c, n, vec, bdim, na, nb, ld, tau, pairs, s);
