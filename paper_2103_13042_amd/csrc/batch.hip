@@ -64,13 +64,18 @@ __global__ __launch_bounds__(kNormThreads) void batch_norms_kernel(const BatchPr
     }
 }
 
-// Products [0, count) of one leaf class, block_base their first blocks.
-template <int LEAF>
-__global__ __launch_bounds__(kBlockThreads, kBlockOcc) void multiply_batch_kernel(
+// Products [0, count) of one leaf class, block_base their first blocks.  Two
+// stages of operand tiles up to so many blocks (kTwoStageMaxN's reasons; 24
+// products of 499 .. 1996, 6,700 blocks: 146 against 147 us, 48 of 256 .. 4096,
+// 33,000 blocks: 475 against 462).
+constexpr int64_t kTwoStageMaxBlocks = 8192;
+
+template <int LEAF, int STAGES>
+__global__ __launch_bounds__(kBlockThreads, block_occ(STAGES)) void multiply_batch_kernel(
     const BatchProduct* __restrict__ P, const int64_t* __restrict__ block_base, int count) {
     const int p = batch_find(block_base, count, blockIdx.x);
     const BatchProduct q = P[p];
-    block_multiply<LEAF, kKept>(global_ptr(q.a), global_ptr(q.b), global_ptr(q.c), q.n, int(q.bdim),
+    block_multiply<LEAF, kKept, STAGES>(global_ptr(q.a), global_ptr(q.b), global_ptr(q.c), q.n, int(q.bdim),
                                 int((q.n + 63) / 64), global_ptr(q.norms[0]), global_ptr(q.norms[1]), q.bdim, q.tau,
                                 reinterpret_cast<unsigned long long*>(global_ptr(q.pairs)), nullptr, nullptr,
                                 BandJob{}, int(blockIdx.x - block_base[p]));
@@ -80,35 +85,41 @@ int64_t batch_strips(int64_t n, int64_t bdim) { return bdim * ((n + kNormCols - 
 
 int64_t batch_blocks(int64_t n) { return block_grid(int((n + 63) / 64)); }
 
+namespace {
+template <int LEAF>
+hipError_t launch_class(const BatchProduct* p, const int64_t* base, int32_t members, int64_t blocks, hipStream_t s) {
+    if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+    const bool two = blocks <= kTwoStageMaxBlocks;
+    static int scratch_state[2] = {0, 0};
+    const hipError_t e = two ? check_no_scratch(multiply_batch_kernel<LEAF, 2>, &scratch_state[1])
+                             : check_no_scratch(multiply_batch_kernel<LEAF, 1>, &scratch_state[0]);
+    if (e != hipSuccess) return e;
+    if (two)
+        multiply_batch_kernel<LEAF, 2><<<unsigned(blocks), kBlockThreads, 0, s>>>(p, base, members);
+    else
+        multiply_batch_kernel<LEAF, 1><<<unsigned(blocks), kBlockThreads, 0, s>>>(p, base, members);
+    return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_batch(const BatchProduct* prods, const int64_t* strip_base, const int64_t* block_base,
                         const int32_t* class_count, const int64_t* class_blocks, int64_t strips, int32_t count,
                         hipStream_t s) {
     if (strips < 1 || strips > 0x7FFFFFFF) return hipErrorInvalidValue;
     batch_norms_kernel<<<dim3{unsigned(strips), 2u, 1u}, kNormThreads, 0, s>>>(prods, strip_base, count);
     hipError_t e = hipGetLastError();
-    static int scratch_state[3] = {0, 0, 0};
-    if (e != hipSuccess || (e = check_no_scratch(multiply_batch_kernel<32>, &scratch_state[0])) != hipSuccess ||
-        (e = check_no_scratch(multiply_batch_kernel<64>, &scratch_state[1])) != hipSuccess ||
-        (e = check_no_scratch(multiply_batch_kernel<128>, &scratch_state[2])) != hipSuccess)
-        return e;
     int32_t first = 0;
-    for (int cls = 0; cls < kBatchClasses; ++cls) {
+    for (int cls = 0; cls < kBatchClasses && e == hipSuccess; ++cls) {
         const int32_t members = class_count[cls];
         if (members == 0) continue;
-        if (class_blocks[cls] > 0x7FFFFFFF) return hipErrorInvalidValue;
-        const unsigned grid = unsigned(class_blocks[cls]);
         const BatchProduct* p = prods + first;
         const int64_t* base = block_base + first;
-        if (cls == 0)
-            multiply_batch_kernel<32><<<grid, kBlockThreads, 0, s>>>(p, base, members);
-        else if (cls == 1)
-            multiply_batch_kernel<64><<<grid, kBlockThreads, 0, s>>>(p, base, members);
-        else
-            multiply_batch_kernel<128><<<grid, kBlockThreads, 0, s>>>(p, base, members);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        e = cls == 0   ? launch_class<32>(p, base, members, class_blocks[cls], s)
+            : cls == 1 ? launch_class<64>(p, base, members, class_blocks[cls], s)
+                       : launch_class<128>(p, base, members, class_blocks[cls], s);
         first += members;
     }
-    return hipSuccess;
+    return e;
 }
 
 }  // namespace spamm

@@ -12,7 +12,15 @@
 namespace spamm {
 
 constexpr int kBlockThreads = 256;
-constexpr int kBlockOcc = 4;         // workgroups per CU: 36 KiB of LDS each
+// Stages of operand tiles in LDS.  Two (36 KiB a workgroup, four per CU) copy an
+// entry while the one before is multiplied; one (20 KiB, six per CU) waits for
+// every copy but has half as many blocks again to hide it and the blocks'
+// prologues.  With several rounds of blocks to run the latter is faster (one
+// call, leaf 32: the 0.1 / (|i-j|^0.1 + 1) matrix at N = 8192 1451 -> 1406 us,
+// exp decay 0.05 203 -> 192; leaf 16, N = 4096, decay 0.01 496 -> 460), with few
+// blocks the former (leaf 32, N = 1000, decay 0.01: 38 against 45 us).
+constexpr int block_occ(int stages) { return stages == 1 ? 5 : 4; }  // registers for so many at least
+constexpr int64_t kTwoStageMaxN = 2048;                              // 1024 blocks: one round of four per CU
 constexpr int kBlockEntries = 2048;  // k entries that the list holds (leaf 16, with its masks: a quarter)
 constexpr int kKept = 0, kPlanned = 1, kDropped = 2;  // where a block's entries come from
 
@@ -65,7 +73,7 @@ static inline unsigned block_grid(int nb) {
 
 // The multiply of block `bid` (block_at) of one product by the calling
 // workgroup; nothing if the grid has no such block.
-template <int LEAF, int FROM>
+template <int LEAF, int FROM, int STAGES>
 __device__ __forceinline__ void block_multiply(const float* A, const float* B, float* C, int64_t n, int bdim, int nb,
                                                const double* na, const double* nbm, int64_t ld, double tau,
                                                unsigned long long* pairs, const uint32_t* items,
@@ -75,10 +83,10 @@ __device__ __forceinline__ void block_multiply(const float* A, const float* B, f
     // one LDS object (stages, then the list, in floats): see the copies' waits in dma.h
     constexpr int LIST = !TEST ? 0 : LEAF == 16 ? kBlockEntries / 4 : kBlockEntries / 2;
     constexpr int MASKS = TEST && LEAF == 16 ? kBlockEntries / 4 : 0;
-    __shared__ __attribute__((aligned(1024))) float lds[2 * STAGE + LIST + MASKS + 8];
-    uint16_t* list = reinterpret_cast<uint16_t*>(lds + 2 * STAGE);
-    uint32_t* masks = reinterpret_cast<uint32_t*>(lds + 2 * STAGE + LIST);  // leaf 16: the 32 products of a list entry
-    int* wsum = reinterpret_cast<int*>(lds + 2 * STAGE + LIST + MASKS);
+    __shared__ __attribute__((aligned(1024))) float lds[STAGES * STAGE + LIST + MASKS + 8];
+    uint16_t* list = reinterpret_cast<uint16_t*>(lds + STAGES * STAGE);
+    uint32_t* masks = reinterpret_cast<uint32_t*>(lds + STAGES * STAGE + LIST);  // leaf 16: the 32 products of a list entry
+    int* wsum = reinterpret_cast<int*>(lds + STAGES * STAGE + LIST + MASKS);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const BlockAt at = block_at(bid, nb);
@@ -216,25 +224,32 @@ __device__ __forceinline__ void block_multiply(const float* A, const float* B, f
             __builtin_amdgcn_s_waitcnt(0xC07F);
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
-            if (e + 1 < full) copy(next, (e + 1) & 1);  // the stage entry e - 1 used
+            if (STAGES == 2 && e + 1 < full) copy(next, (e + 1) & 1);  // the stage entry e - 1 used
             // a wave with MFMAs to issue goes ahead of those that copy or wait
             __builtin_amdgcn_s_setprio(1);
-            acc.multiply(lds + (e & 1) * STAGE, mask, e, run, wave, lane);
+            acc.multiply(lds + (e & (STAGES - 1)) * STAGE, mask, e, run, wave, lane);
             __builtin_amdgcn_s_setprio(0);
+            if (STAGES == 1 && e + 1 < count) {  // every wave is done with the stage
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_waitcnt(0xC07F);
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                if (e + 1 < full) copy(next, 0);
+            }
             cur = next;
         }
         if (tail) {
             const uint32_t pk = entry(count - 1);
             uint32_t mask = pk;
             if constexpr (LEAF == 16) mask = masks[count - 1];
-            float* t = lds + (full & 1) * STAGE + wave * kOpTile;  // the stage entry full - 2 used
+            float* t = lds + (full & (STAGES - 1)) * STAGE + wave * kOpTile;  // a stage that no wave reads any more
             OpChunk<false> x[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) x[j].load(of, n, int(pk >> 4), 64 * j + lane, (pk & need) != 0);
 #pragma unroll
             for (int j = 0; j < 4; ++j) op_commit<LEAF>(t, wave, 64 * j + lane, x[j].value());
             __syncthreads();
-            acc.multiply(lds + (full & 1) * STAGE, mask, full, run, wave, lane);
+            acc.multiply(lds + (full & (STAGES - 1)) * STAGE, mask, full, run, wave, lane);
         }
         if (LEAF == 128) __syncthreads();  // the list and the stages are used again
     }
@@ -262,7 +277,7 @@ __device__ __forceinline__ void block_multiply(const float* A, const float* B, f
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) sq += __shfl_xor(sq, o);
         __syncthreads();  // the list is no longer read
-        double* red = reinterpret_cast<double*>(lds + 2 * STAGE);
+        double* red = reinterpret_cast<double*>(lds + STAGES * STAGE);
         if (lane == 0) red[wave] = sq;
         __syncthreads();
         if (tid == 0) band.sums[I * nb + J] = (red[0] + red[1]) + (red[2] + red[3]);

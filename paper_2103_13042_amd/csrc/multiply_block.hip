@@ -3,12 +3,13 @@
 //
 // k is walked in entries of 32.  An entry's four operand tiles (rows 2I + {0, 1}
 // of A, columns 2J + {0, 1} of B, in tiles of 32) are copied straight into LDS,
-// one tile per wave, into one of two stages while the entry before is
-// multiplied; a tile that no kept product reads is not copied.  The waves meet
-// once per entry; four workgroups per CU keep every SIMD supplied with waves of
-// four different blocks, so one block's copies and barriers hide behind the
-// others' MFMAs, and blocks of unequal length need no plan of the work split:
-// the hardware hands out the next one.
+// one tile per wave; a tile that no kept product reads is not copied.  With two
+// stages this goes on while the entry before is multiplied and the waves meet
+// once per entry, with one (the larger grids, kTwoStageMaxN) an entry is copied,
+// then multiplied.  Four or six workgroups per CU keep every SIMD supplied with
+// waves of as many different blocks, so one block's copies and barriers hide
+// behind the others' MFMAs, and blocks of unequal length need no plan of the
+// work split: the hardware hands out the next one.
 //
 // The entries come either from the leaf norms, the block testing its own
 // products as Algorithm 2's blocks do (kKept, the one-call path: no plan
@@ -22,9 +23,9 @@
 // 0.1 / (|i-j|^0.1 + 1) at leaf 32 with 15 % of the pairs kept, they are busy 70 %
 // of the CUs' busy cycles (16 KiB of operands per 4 x 1024 cycles of MFMA work,
 // a third of them past L2), and the launch ends with 5 % of the CUs' time idle.
-// One call there 302 -> 236 us (register-staged 2x2 macro tiles in a static
+// One call there 302 -> 231 us (register-staged 2x2 macro tiles in a static
 // split of whole tiles, after a plan launch); exp decay 0.05, tau 1e-6, leaf 32:
-// N = 2048 66 -> 34 us, 8192 287 -> 206; leaf 16: N = 2048 69 -> 36, 8192 601 ->
+// N = 2048 66 -> 33 us, 8192 287 -> 190; leaf 16: N = 2048 69 -> 34, 8192 601 ->
 // 297; leaf 64: N = 2047 117 -> 36.
 //
 // Sizes that are no multiple of 32, rows at 4-byte alignment: rows and columns
@@ -44,13 +45,13 @@
 
 namespace spamm {
 
-template <int LEAF, int FROM>
-__global__ __launch_bounds__(kBlockThreads, kBlockOcc) void multiply_block_kernel(
+template <int LEAF, int FROM, int STAGES>
+__global__ __launch_bounds__(kBlockThreads, block_occ(STAGES)) void multiply_block_kernel(
     const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C, int64_t n, int bdim, int nb,
     const double* __restrict__ na, const double* __restrict__ nbm, int64_t ld, double tau,
     unsigned long long* __restrict__ pairs, const uint32_t* __restrict__ items, const int32_t* __restrict__ uprefix,
     BandJob band) {
-    block_multiply<LEAF, FROM>(A, B, C, n, bdim, nb, na, nbm, ld, tau, pairs, items, uprefix, band, int(blockIdx.x));
+    block_multiply<LEAF, FROM, STAGES>(A, B, C, n, bdim, nb, na, nbm, ld, tau, pairs, items, uprefix, band, int(blockIdx.x));
 }
 
 namespace {
@@ -59,13 +60,19 @@ hipError_t launch_block_of(const float* a, const float* b, float* c, int64_t n, 
                            const double* nb, int64_t ld, double tau, int64_t* pairs, const uint32_t* items,
                            const int32_t* uprefix, const BandJob& band, hipStream_t s) {
     if (n < 1 || bdim != (n + LEAF - 1) / LEAF || bdim > 1024) return hipErrorInvalidValue;
-    static int scratch_state = 0;
-    const hipError_t ce = check_no_scratch(multiply_block_kernel<LEAF, FROM>, &scratch_state);
+    const bool two = n <= kTwoStageMaxN;
+    static int scratch_state[2] = {0, 0};
+    const hipError_t ce = two ? check_no_scratch(multiply_block_kernel<LEAF, FROM, 2>, &scratch_state[1])
+                              : check_no_scratch(multiply_block_kernel<LEAF, FROM, 1>, &scratch_state[0]);
     if (ce != hipSuccess) return ce;
     const int blocks = int((n + 63) / 64);
-    multiply_block_kernel<LEAF, FROM><<<block_grid(blocks), kBlockThreads, 0, s>>>(
-        a, b, c, n, int(bdim), blocks, na, nb, ld, tau, reinterpret_cast<unsigned long long*>(pairs), items, uprefix,
-        band);
+    auto* count = reinterpret_cast<unsigned long long*>(pairs);
+    if (two)
+        multiply_block_kernel<LEAF, FROM, 2><<<block_grid(blocks), kBlockThreads, 0, s>>>(
+            a, b, c, n, int(bdim), blocks, na, nb, ld, tau, count, items, uprefix, band);
+    else
+        multiply_block_kernel<LEAF, FROM, 1><<<block_grid(blocks), kBlockThreads, 0, s>>>(
+            a, b, c, n, int(bdim), blocks, na, nb, ld, tau, count, items, uprefix, band);
     return hipGetLastError();
 }
 

@@ -739,7 +739,7 @@ def test_small_products_at_edges(n, offset, leaf):
 
 
 @pytest.mark.parametrize("leaf", [16, 32, 64, 128])
-@pytest.mark.parametrize("n,offset", [(352, 0), (1025, 0), (1100, 1), (2081, 0)])
+@pytest.mark.parametrize("n,offset", [(352, 0), (1025, 0), (1100, 1), (2081, 0), (2112, 3)])
 def test_block_multiply_matches_oracle_and_staged_path(n, offset, leaf):
     """The one-call path above n = 320 (a block of C per workgroup, testing its
     own products): k past the last whole entry of 32, block rows left over from
