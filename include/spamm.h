@@ -233,8 +233,8 @@ spamm_status spamm_split_scales(const double* pyr_a, const double* pyr_b, int64_
                                 size_t header_bytes, void* stream);
 
 /* F16X3 products straight from the FP32 inputs, after spamm_schedule on the
- * same plan and workspace: one kernel stages FP32 tiles of A and B and splits
- * them into hi and lo in registers with the exponents of `header`
+ * same plan and workspace: one kernel loads FP32 tiles of A and B and splits
+ * them into hi and lo with the exponents of `header`
  * (spamm_split_scales), so C is bitwise the C of spamm_split +
  * spamm_execute_split_scheduled without the split pass over A and B.  a, b:
  * device, 16-byte aligned.  Errors as spamm_execute_split_scheduled (EINVAL
@@ -245,8 +245,8 @@ spamm_status spamm_execute_f16x3_scheduled(const float* a, const float* b, int64
 
 /* BF16 products (section 3.3's reduced-precision leaf products, FP32
  * accumulation) straight from the FP32 inputs, after spamm_prepare and
- * spamm_schedule on the same plan and workspace: one kernel stages FP32 tiles
- * of A and B and rounds them to BF16 (nearest-even) in registers, so C is
+ * spamm_schedule on the same plan and workspace: one kernel loads FP32 tiles
+ * of A and B and rounds them to BF16 (nearest-even), so C is
  * bitwise the C of spamm_split + spamm_execute_split_scheduled with
  * SPAMM_PREC_BF16, without the split pass over A and B.  a, b: device, 16-byte
  * aligned; c overwritten.  Errors as spamm_execute_split_scheduled. */
@@ -255,8 +255,7 @@ spamm_status spamm_execute_bf16_scheduled(const float* a, const float* b, int64_
                                           size_t workspace_bytes, void* stream);
 
 /* spamm_prepare followed by spamm_split_scales on the pyramids it leaves in
- * the workspace (the first stage of the F16X3 path of
- * spamm_multiply_precision).  Errors as spamm_prepare and spamm_split_scales
+ * the workspace.  Errors as spamm_prepare and spamm_split_scales
  * (EINVAL also for a header overlapping a or b). */
 spamm_status spamm_prepare_scales(const float* a, const float* b, int64_t n, double tau, int32_t leaf,
                                   int32_t* offsets, int32_t* klist, int64_t klist_capacity, int64_t* pairs,
@@ -265,10 +264,7 @@ spamm_status spamm_prepare_scales(const float* a, const float* b, int64_t n, dou
 
 /* spamm_prepare_schedule followed by spamm_split_scales on the leaf norms it
  * leaves in the workspace: the plan, the multiply schedule and the FP16 hi+lo
- * scale exponents, so that spamm_execute_f16x3_scheduled can follow directly
- * (the first stage of the in-register F16X3 path of spamm_multiply_precision,
- * which uses the one-launch plan and schedule where spamm_prepare_schedule
- * does).  Arguments as spamm_prepare_scales; the same offsets, k-lists, pairs
+ * scale exponents, so that spamm_execute_f16x3_scheduled can follow directly.  Arguments as spamm_prepare_scales; the same offsets, k-lists, pairs
  * and header.  The header (256-byte aligned, at least 256 bytes, not
  * overlapping a or b: else EINVAL or ENOSPACE) is checked before anything is
  * enqueued.  Other errors as spamm_prepare_schedule. */
@@ -278,27 +274,23 @@ spamm_status spamm_prepare_schedule_scales(const float* a, const float* b, int64
                                            size_t workspace_bytes, void* stream);
 
 /* spamm_prepare followed by spamm_split on the pyramids it leaves in the
- * workspace (the first half of spamm_multiply_precision).  Errors as
+ * workspace.  Errors as
  * spamm_prepare and spamm_split. */
 spamm_status spamm_prepare_split(const float* a, const float* b, int64_t n, double tau, int32_t leaf,
                                  int32_t precision, int32_t* offsets, int32_t* klist, int64_t klist_capacity,
                                  int64_t* pairs, void* split, size_t split_bytes, void* workspace,
                                  size_t workspace_bytes, void* stream);
 
-/* The whole path with reduced-precision products.  F16X3:
- * spamm_prepare_schedule_scales into the first 256 bytes of `split`, then
- * either the planes and the split multiply (spamm_split's planes,
- * spamm_execute_split_scheduled) or the in-register split
- * (spamm_execute_f16x3_scheduled), picked on the device from the plan's pair
- * count: the planes when it keeps at least 45 pairs per output tile on
- * average.  With split_bytes below spamm_split_bytes (at least 256), always
- * in registers and the planes are not written.  BF16: the same with
- * spamm_prepare_schedule (no scales) and spamm_execute_bf16_scheduled, the planes from
- * 16 pairs per tile; split may be NULL (then always in registers).  Either
- * way C is bitwise the C of the split path.  SPAMM_PREC_FP32 is
- * spamm_multiply (split unused, may be NULL).  Errors as spamm_multiply and
+/* The whole path with reduced-precision products: leaf norms, F16X3: the scale
+ * exponents into the first 256 bytes of `split` (spamm_split_scales), and one
+ * multiply launch that tests the products on the norms and converts A and B as
+ * it loads them; no plan is formed and the planes of `split` are not written.
+ * C is bitwise the C of spamm_prepare + spamm_split + spamm_execute_split.
+ * F16X3 needs split_bytes >= 256, for BF16 split may be NULL.  SPAMM_PREC_FP32
+ * is spamm_multiply (split unused, may be NULL).  Errors as spamm_multiply and
  * spamm_split (F16X3: EINVAL for a header that is null, not 256-byte aligned
- * or overlapping a, b or c; ENOSPACE below 256 bytes). */
+ * or overlapping a, b or c; ENOSPACE below 256 bytes; a buffer of
+ * spamm_split_bytes or more must not overlap them either). */
 spamm_status spamm_multiply_precision(const float* a, const float* b, int64_t n, double tau, int32_t leaf,
                                       int32_t precision, float* c, int64_t* pairs, void* split, size_t split_bytes,
                                       void* workspace, size_t workspace_bytes, void* stream);

@@ -351,18 +351,6 @@ spamm_status enqueue_execute(const Geom& g, const float* a, const float* b, cons
 
 namespace {
 constexpr size_t kSplitHeaderBytes = 256;  // scale exponents and largest leaf norms
-// F16X3 whole path: split A and B once when the plan keeps at least this many
-// pairs per output tile on average, else split in registers.  The split pass
-// reads and writes A and B once more (1 ms at N = 16384); the in-register
-// split redoes the conversions in every wave that reads an operand, work that
-// grows with the kept pairs.  Whole steps measured at N = 16384 on
-// exponential decay cross near 50 pairs per tile (in registers 5.84 against
-// 6.26 ms at 30 pairs per tile, planes 13.40 against 13.74 ms at 74).
-constexpr int64_t kF16x3StagedPairsPerTile = 45;
-// BF16: the in-register rounding reads the FP32 tiles (twice the bytes of the
-// planes); the same measurement crosses near 19 pairs per tile (in registers
-// 1.46 against 1.91 ms at 8 pairs per tile, planes 3.30 against 3.77 ms at 30).
-constexpr int64_t kBf16StagedPairsPerTile = 16;
 size_t plane_bytes(int64_t n) { return (size_t(n) * size_t(n) * 2 + 255) / 256 * 256; }
 int split_planes(int32_t precision) { return precision == spamm::kPrecF16x3 ? 4 : 2; }
 
@@ -554,8 +542,9 @@ spamm_status spamm_prepare_schedule(const float* a, const float* b, int64_t n, d
 namespace {
 // The leaf norm pass (which also clears the pair counter), then the threshold
 // test and the multiply in one launch.
-spamm_status enqueue_direct(const Geom& g, const float* a, const float* b, double tau, float* c, int64_t* pairs,
-                           void* ws, hipStream_t s) {
+// The leaf norms of a and b into the workspace pyramids (norms[2]), *pairs = 0.
+spamm_status enqueue_leaf_norms(const Geom& g, const float* a, const float* b, int64_t* pairs, double** norms,
+                                void* ws, hipStream_t s) {
     const Layout L = make_layout(g);
     const int64_t leaf_level = spamm::level_offset(g.lv);
     spamm::NormJob nj{};
@@ -565,17 +554,24 @@ spamm_status enqueue_direct(const Geom& g, const float* a, const float* b, doubl
     for (int m = 0; m < 2; ++m) {
         nj.x[m] = xs[m];
         nj.sumsq[m] = at<double>(ws, L.spyr[m]) + leaf_level;
-        nj.norms[m] = at<double>(ws, L.pyr[m]) + leaf_level;
+        nj.norms[m] = norms[m] = at<double>(ws, L.pyr[m]) + leaf_level;
     }
     const bool vec = (g.n % 4) == 0 && aligned16(a) && aligned16(b);
-    spamm_status st = hip_check(spamm::launch_leaf_norms(nj, 2, g.n, g.leaf, vec, s), "leaf norm kernel");
+    return hip_check(spamm::launch_leaf_norms(nj, 2, g.n, g.leaf, vec, s), "leaf norm kernel");
+}
+
+spamm_status enqueue_direct(const Geom& g, const float* a, const float* b, double tau, float* c, int64_t* pairs,
+                           void* ws, hipStream_t s) {
+    double* norms[2];
+    const spamm_status st = enqueue_leaf_norms(g, a, b, pairs, norms, ws, s);
     if (st != SPAMM_OK) return st;
+    const bool vec = (g.n % 4) == 0 && aligned16(a) && aligned16(b);
     if (g.n <= spamm::kSmallMaxN)
-        return hip_check(spamm::launch_small_multiply(a, b, c, g.n, g.leaf, vec, g.bdim, nj.norms[0], nj.norms[1],
+        return hip_check(spamm::launch_small_multiply(a, b, c, g.n, g.leaf, vec, g.bdim, norms[0], norms[1],
                                                       g.side, tau, pairs, s),
                          "small multiply kernel");
-    return hip_check(spamm::launch_block_test(a, b, c, g.n, g.leaf, g.bdim, nj.norms[0], nj.norms[1], g.side, tau,
-                                              pairs, s),
+    return hip_check(spamm::launch_block_test(a, b, c, g.n, g.leaf, g.bdim, norms[0], norms[1], g.side, tau, pairs,
+                                              s),
                      "block multiply kernel");
 }
 }  // namespace
@@ -643,7 +639,7 @@ spamm_status spamm_execute_split_scheduled(const void* split, int64_t n, int32_t
     const Layout L = make_layout(g);
     return hip_check(spamm::launch_lowp_multiply(split_layout(const_cast<void*>(split), n, precision), c, n, g.bdim,
                                                  precision, at<uint32_t>(workspace, L.mitems),
-                                                 at<int32_t>(workspace, L.mprefix), device_cus(), spamm::PairGate{},
+                                                 at<int32_t>(workspace, L.mprefix), device_cus(),
                                                  static_cast<hipStream_t>(stream)),
                      "reduced-precision multiply kernel");
 }
@@ -688,10 +684,9 @@ spamm_status spamm_execute_f16x3_scheduled(const float* a, const float* b, int64
     if (overlaps(c, sizeof(float) * size_t(n) * size_t(n), header, kSplitHeaderBytes))
         return fail(SPAMM_EINVAL, "c overlaps the header");
     const Layout L = make_layout(g);
-    return hip_check(spamm::launch_fused_multiply(a, b, spamm::kPrecF16x3, static_cast<const int32_t*>(header), c, n,
-                                                  g.bdim, at<uint32_t>(workspace, L.mitems),
-                                                  at<int32_t>(workspace, L.mprefix), device_cus(), spamm::PairGate{},
-                                                  static_cast<hipStream_t>(stream)),
+    return hip_check(spamm::launch_convert_plan(a, b, spamm::kPrecF16x3, static_cast<const int32_t*>(header), c, n,
+                                                g.bdim, at<uint32_t>(workspace, L.mitems),
+                                                at<int32_t>(workspace, L.mprefix), static_cast<hipStream_t>(stream)),
                      "fused f16x3 multiply kernel");
 }
 
@@ -708,10 +703,9 @@ spamm_status spamm_execute_bf16_scheduled(const float* a, const float* b, int64_
     if ((st = check_workspace(g, workspace, workspace_bytes)) != SPAMM_OK) return st;
     if (!aligned16(a) || !aligned16(b)) return fail(SPAMM_EINVAL, "a and b need 16-byte alignment");
     const Layout L = make_layout(g);
-    return hip_check(spamm::launch_fused_multiply(a, b, spamm::kPrecBf16, nullptr, c, n, g.bdim,
-                                                  at<uint32_t>(workspace, L.mitems),
-                                                  at<int32_t>(workspace, L.mprefix), device_cus(), spamm::PairGate{},
-                                                  static_cast<hipStream_t>(stream)),
+    return hip_check(spamm::launch_convert_plan(a, b, spamm::kPrecBf16, nullptr, c, n, g.bdim,
+                                                at<uint32_t>(workspace, L.mitems),
+                                                at<int32_t>(workspace, L.mprefix), static_cast<hipStream_t>(stream)),
                      "fused bf16 multiply kernel");
 }
 
@@ -790,15 +784,7 @@ spamm_status spamm_multiply_precision(const float* a, const float* b, int64_t n,
     if ((st = check_tau(tau)) != SPAMM_OK) return st;
     if ((st = check_workspace(g, workspace, workspace_bytes)) != SPAMM_OK) return st;
     const Layout L = make_layout(g);
-    int32_t* offsets = at<int32_t>(workspace, L.offsets);
-    int32_t* klist = at<int32_t>(workspace, L.klist);
     int64_t* np = pairs ? pairs : at<int64_t>(workspace, L.pairs);
-    // With room for the planes the device picks, from the plan's pair count,
-    // between converting A and B once and multiplying the planes (many pairs:
-    // each tile feeds many products) and converting the FP32 tiles in
-    // registers inside the multiply (few pairs: the split pass would cost more
-    // than the conversions).  With less room (F16X3: only the 256-byte header
-    // of scale exponents), always in registers.  Both give bitwise the same C.
     const bool f16 = precision == spamm::kPrecF16x3;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (!aligned16(a) || !aligned16(b)) return fail(SPAMM_EINVAL, "a and b need 16-byte alignment");
@@ -819,31 +805,16 @@ spamm_status spamm_multiply_precision(const float* a, const float* b, int64_t n,
             overlaps(split, kSplitHeaderBytes, c, mbytes))
             return fail(SPAMM_EINVAL, "header overlaps a, b or c");
     }
-    // norms, pyramids, then the plan and the multiply schedule in one launch
-    if ((st = enqueue_prepare(g, a, b, tau, offsets, klist, np, workspace, s, true)) != SPAMM_OK) return st;
-    const spamm::SplitLayout SL = split_layout(split, n, precision);
+    double* norms[2];
+    if ((st = enqueue_leaf_norms(g, a, b, np, norms, workspace, s)) != SPAMM_OK) return st;
+    int32_t* exps = f16 ? static_cast<int32_t*>(split) : nullptr;
     if (f16 && (st = hip_check(spamm::launch_split_scales(g.bdim, g.lv, at<double>(workspace, L.pyr[0]),
-                                                          at<double>(workspace, L.pyr[1]), SL.exps, s),
-                               "scale kernels")) != SPAMM_OK)
+                                                          at<double>(workspace, L.pyr[1]), exps, s),
+                               "scale kernel")) != SPAMM_OK)
         return st;
-    const int64_t per_tile = f16 ? kF16x3StagedPairsPerTile : kBf16StagedPairsPerTile;
-    spamm::PairGate staged{np, per_tile * g.bdim * g.bdim, 1}, fused{};
-    if (planes) {
-        fused = staged;
-        fused.when_at_least = 0;
-        if ((st = hip_check(spamm::launch_split_planes(a, b, n, precision, SL, staged, s), "split kernels")) !=
-            SPAMM_OK)
-            return st;
-    }
-    if (planes &&
-        (st = hip_check(spamm::launch_lowp_multiply(SL, c, n, g.bdim, precision, at<uint32_t>(workspace, L.mitems),
-                                                    at<int32_t>(workspace, L.mprefix), device_cus(), staged, s),
-                        "reduced-precision multiply kernel")) != SPAMM_OK)
-        return st;
-    return hip_check(spamm::launch_fused_multiply(a, b, precision, f16 ? SL.exps : nullptr, c, n, g.bdim,
-                                                  at<uint32_t>(workspace, L.mitems),
-                                                  at<int32_t>(workspace, L.mprefix), device_cus(), fused, s),
-                     "reduced-precision multiply kernel (in-register conversion)");
+    return hip_check(spamm::launch_convert_test(a, b, precision, exps, c, n, g.bdim, norms[0], norms[1], g.side, tau,
+                                                np, s),
+                     "reduced-precision multiply kernel (FP32 inputs)");
 }
 
 spamm_status spamm_search_valid_ratio(const double* pyr_a, const double* pyr_b, int64_t n, int32_t leaf,

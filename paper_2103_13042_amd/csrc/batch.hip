@@ -83,7 +83,7 @@ __global__ __launch_bounds__(kBlockThreads, block_occ(STAGES)) void multiply_bat
 
 int64_t batch_strips(int64_t n, int64_t bdim) { return bdim * ((n + kNormCols - 1) / kNormCols); }
 
-int64_t batch_blocks(int64_t n) { return block_grid(int((n + 63) / 64)); }
+int64_t batch_blocks(int64_t n) { return block_grid(int((n + 63) / 64), kBlockOrder); }
 
 namespace {
 template <int LEAF>

@@ -24,52 +24,68 @@ constexpr int64_t kTwoStageMaxN = 2048;                              // 1024 blo
 constexpr int kBlockEntries = 2048;  // k entries that the list holds (leaf 16, with its masks: a quarter)
 constexpr int kKept = 0, kPlanned = 1, kDropped = 2;  // where a block's entries come from
 
-// Blocks are dealt to the XCDs (workgroups congruent mod 8) by strips of two
-// block rows, so that every XCD gets rows from all over the matrix; the rows
-// left over, fewer than 16, are dealt block by block, so that every XCD gets as
-// many blocks.  Row I's blocks are taken outwards from the diagonal, the
-// longest of decaying matrices first, in rounds of kBlockRun columns over all
-// strips of the XCD: the longest blocks of the whole matrix start first and the
-// short ones fill the end (strip after strip the CUs idled 15 % of the launch
-// at n = 4096), and the run keeps neighbours that share rows of A in L2.
-constexpr int kBlockRun = 8;
+// Blocks are dealt to the XCDs (workgroups congruent mod 8) by strips of H block
+// rows, so that every XCD gets rows from all over the matrix; the rows left
+// over, fewer than 8 H, are dealt block by block, so that every XCD gets as many
+// blocks, unless they are nearly a round of strips.  A strip's blocks are taken
+// outwards from the diagonal, the longest of decaying matrices first, in rounds
+// of `run` columns over all strips of the XCD: the longest blocks of the whole
+// matrix start first and the short ones fill the end (strip after strip the CUs
+// idled 15 % of the launch at n = 4096), and the run keeps neighbours that share
+// rows of A and columns of B in L2.
+struct BlockOrder {
+    int H, run;
+};
 
 struct BlockAt {
     int I, J;
     bool valid;
 };
 
-__device__ __forceinline__ BlockAt block_at(int bid, int nb) {
+// rows in whole rounds of strips, a nearly whole last round included (its rows
+// past the matrix have no blocks)
+__host__ __device__ __forceinline__ int dealt_rows(int nb, int H) {
+    return (nb + H) / (8 * H) * (8 * H);
+}
+
+__device__ __forceinline__ BlockAt block_at(int bid, int nb, BlockOrder order) {
+    const int H = order.H;
     const int xcd = bid & 7, idx = bid >> 3;
-    const int dealt = nb / 16 * 16, left = nb - dealt;  // rows in whole rounds of strips
-    const int first = (left * nb + 7) / 8;              // blocks of an XCD in the rows left over
-    int I, step;
-    if (idx < first) {
-        const int r = idx * 8 + xcd;
+    const int dealt = dealt_rows(nb, H), left = nb > dealt ? nb - dealt : 0;
+    const int rows = dealt / 8;  // of an XCD's strips, whose blocks come first
+    int I, mid, step;
+    if (idx >= rows * nb) {
+        const int r = (idx - rows * nb) * 8 + xcd;
         if (r >= left * nb) return {0, 0, false};
-        I = dealt + r % left;
+        I = mid = dealt + r % left;
         step = r / left;
     } else {
-        const int rows = dealt / 8, r = idx - first;  // rows > 0: idx < first otherwise
-        const int run = r / (rows * kBlockRun), in = r - run * rows * kBlockRun;
-        const int wide = nb - run * kBlockRun < kBlockRun ? nb - run * kBlockRun : kBlockRun;  // columns of this run
-        const int strip = in / (2 * wide), of = in - strip * 2 * wide;
-        I = 2 * (strip * 8 + xcd) + (of & 1);
-        step = run * kBlockRun + (of >> 1);
+        const int col0 = idx / (rows * order.run) * order.run, in = idx - col0 * rows;  // rows > 0 here
+        const int wide = nb - col0 < order.run ? nb - col0 : order.run;                 // columns of this run
+        const int strip = in / (H * wide), of = in - strip * H * wide;
+        const int row0 = H * (strip * 8 + xcd);
+        I = row0 + of % H;
+        if (I >= nb) return {0, 0, false};
+        mid = row0 + H / 2 < nb ? row0 + H / 2 : nb - 1;
+        step = col0 + of / H;
     }
-    // columns I, I - 1, I + 1, I - 2, ... while both sides last, then the rest in order
-    const int near = I < nb - 1 - I ? I : nb - 1 - I;
+    // columns mid, mid - 1, mid + 1, mid - 2, ... while both sides last, then the rest in order
+    const int near = mid < nb - 1 - mid ? mid : nb - 1 - mid;
     int J;
     if (step <= 2 * near)
-        J = (step & 1) ? I - (step + 1) / 2 : I + step / 2;
+        J = (step & 1) ? mid - (step + 1) / 2 : mid + step / 2;
     else
-        J = I < nb - 1 - I ? step : nb - 1 - step;
+        J = mid < nb - 1 - mid ? step : nb - 1 - step;
     return {I, J, true};
 }
-static inline unsigned block_grid(int nb) {
-    const int dealt = nb / 16 * 16;
-    return unsigned((((nb - dealt) * nb + 7) / 8 + dealt / 8 * nb) * 8);
+static inline unsigned block_grid(int nb, BlockOrder order) {
+    const int H = order.H;
+    const int dealt = dealt_rows(nb, H), left = nb > dealt ? nb - dealt : 0;
+    return unsigned(((left * nb + 7) / 8 + dealt / 8 * nb) * 8);
 }
+// Of the FP32 blocks, whose kernel is bound by the matrix cores (strips of up to
+// 8 rows measured the same, with fewer than two strips per XCD 6 % slower).
+constexpr BlockOrder kBlockOrder{2, 8};
 
 // The multiply of block `bid` (block_at) of one product by the calling
 // workgroup; nothing if the grid has no such block.
@@ -89,7 +105,7 @@ __device__ __forceinline__ void block_multiply(const float* A, const float* B, f
     int* wsum = reinterpret_cast<int*>(lds + STAGES * STAGE + LIST + MASKS);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const BlockAt at = block_at(bid, nb);
+    const BlockAt at = block_at(bid, nb, kBlockOrder);
     if (!at.valid) return;
     const int I = at.I, J = at.J;
     const int whole = int(n) / 32;  // entries inside the matrix

@@ -28,10 +28,4 @@ __device__ __forceinline__ int opaque(int v) {
     return v;
 }
 
-// whether a launch gated on the plan's pair count runs (PairGate, internal.h)
-template <typename Gate>
-__device__ __forceinline__ bool gate_open(const Gate& g) {
-    return g.pairs == nullptr || ((*g.pairs >= g.threshold) == (g.when_at_least != 0));
-}
-
 }  // namespace spamm

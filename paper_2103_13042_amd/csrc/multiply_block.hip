@@ -68,10 +68,10 @@ hipError_t launch_block_of(const float* a, const float* b, float* c, int64_t n, 
     const int blocks = int((n + 63) / 64);
     auto* count = reinterpret_cast<unsigned long long*>(pairs);
     if (two)
-        multiply_block_kernel<LEAF, FROM, 2><<<block_grid(blocks), kBlockThreads, 0, s>>>(
+        multiply_block_kernel<LEAF, FROM, 2><<<block_grid(blocks, kBlockOrder), kBlockThreads, 0, s>>>(
             a, b, c, n, int(bdim), blocks, na, nb, ld, tau, count, items, uprefix, band);
     else
-        multiply_block_kernel<LEAF, FROM, 1><<<block_grid(blocks), kBlockThreads, 0, s>>>(
+        multiply_block_kernel<LEAF, FROM, 1><<<block_grid(blocks, kBlockOrder), kBlockThreads, 0, s>>>(
             a, b, c, n, int(bdim), blocks, na, nb, ld, tau, count, items, uprefix, band);
     return hipGetLastError();
 }

@@ -18,37 +18,37 @@
 
 namespace spamm {
 
-// e per matrix from the leaf level of its pyramid: the largest leaf norm of A
-// and of B (grid-wide maximum of non-negative doubles through their bit
-// patterns, which order like unsigned integers), then e from it.
-__global__ void split_scale_init_kernel(unsigned long long* __restrict__ mx) {
-    if (threadIdx.x < 2) mx[threadIdx.x] = 0ull;
-}
+// Of one matrix per block: the largest leaf norm, from the leaf level of its
+// pyramid, and e from it.  One launch: two more around it, to clear a maximum in
+// memory and to read it, cost more (14 us of gaps and launches at bdim 256)
+// than two blocks instead of 128 (6 us against 5 there).
+constexpr int kScaleThreads = 1024;
 
-__global__ __launch_bounds__(256) void split_max_kernel(const double* __restrict__ pyr_a,
-                                                        const double* __restrict__ pyr_b, int64_t bdim, int lv,
-                                                        unsigned long long* __restrict__ mx) {
+__global__ __launch_bounds__(kScaleThreads) void split_scale_kernel(const double* __restrict__ pyr_a,
+                                                                    const double* __restrict__ pyr_b, int64_t bdim,
+                                                                    int lv, int32_t* __restrict__ exps,
+                                                                    double* __restrict__ mx) {
     const int64_t side = int64_t(1) << lv;
-    const int m = blockIdx.y;
+    const int m = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const double* leaf = (m == 0 ? pyr_a : pyr_b) + level_offset(lv);
     double v = 0.0;
-    for (int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x; t < bdim * bdim; t += int64_t(gridDim.x) * 256)
-        v = fmax(v, leaf[(t / bdim) * side + t % bdim]);
+    for (int64_t i = wave; i < bdim; i += kScaleThreads / 64)
+        for (int64_t j = lane; j < bdim; j += 64) v = fmax(v, leaf[i * side + j]);
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-    if ((threadIdx.x & 63) == 0) atomicMax(&mx[m], static_cast<unsigned long long>(__double_as_longlong(v)));
-}
-
-__global__ void split_scale_kernel(const unsigned long long* __restrict__ mx, int32_t* __restrict__ exps) {
-    if (threadIdx.x < 2) {
-        const double m = __longlong_as_double(static_cast<long long>(mx[threadIdx.x]));
+    __shared__ double part[kScaleThreads / 64];
+    if (lane == 0) part[wave] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kScaleThreads / 64; ++w) v = fmax(v, part[w]);
+        mx[m] = v;
         int e = 0;
-        if (m > 0.0) {
+        if (v > 0.0) {
             int x = 0;
-            const double f = frexp(m, &x);  // m = f 2^x, f in [0.5, 1)
+            const double f = frexp(v, &x);  // v = f 2^x, f in [0.5, 1)
             e = 15 - (f == 0.5 ? x - 1 : x);
         }
-        exps[threadIdx.x] = e;
+        exps[m] = e;
     }
 }
 
@@ -78,8 +78,7 @@ struct Conv<kPrecF16x3> {
 template <int MODE>
 __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict__ x, int64_t count,
                                                          const int32_t* __restrict__ exps, uint16_t* __restrict__ hi,
-                                                         uint16_t* __restrict__ lo, PairGate gate) {
-    if (!gate_open(gate)) return;
+                                                         uint16_t* __restrict__ lo) {
     const float s = MODE == kPrecF16x3 ? ldexpf(1.0f, exps[0]) : 1.0f;
     const int64_t n4 = count / 4;
     const f4* x4 = reinterpret_cast<const f4*>(x);
@@ -102,9 +101,7 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
 template <int MODE>
 __global__ __launch_bounds__(256) void split_transpose_kernel(const float* __restrict__ x, int64_t n,
                                                               const int32_t* __restrict__ exps,
-                                                              uint16_t* __restrict__ hi, uint16_t* __restrict__ lo,
-                                                              PairGate gate) {
-    if (!gate_open(gate)) return;
+                                                              uint16_t* __restrict__ hi, uint16_t* __restrict__ lo) {
     __shared__ float t[64][65];
     const float s = MODE == kPrecF16x3 ? ldexpf(1.0f, exps[1]) : 1.0f;
     const int64_t r0 = int64_t(blockIdx.y) * 64, c0 = int64_t(blockIdx.x) * 64;
@@ -147,26 +144,22 @@ __global__ __launch_bounds__(256) void split_transpose_kernel(const float* __res
 hipError_t launch_split_scales(int64_t bdim, int lv, const double* pyr_a, const double* pyr_b, int32_t* header,
                                hipStream_t s) {
     // the header holds exps[2] (bytes 0..7) and the two maxima (bytes 8..23)
-    unsigned long long* mx = reinterpret_cast<unsigned long long*>(header + 2);
-    split_scale_init_kernel<<<1, 64, 0, s>>>(mx);
-    const int64_t tiles = bdim * bdim;
-    const unsigned blocks = unsigned(tiles < 64 * 256 ? (tiles + 255) / 256 : 64);
-    split_max_kernel<<<dim3{blocks, 2u, 1u}, 256, 0, s>>>(pyr_a, pyr_b, bdim, lv, mx);
-    split_scale_kernel<<<1, 64, 0, s>>>(mx, header);
+    split_scale_kernel<<<2, kScaleThreads, 0, s>>>(pyr_a, pyr_b, bdim, lv, header,
+                                                   reinterpret_cast<double*>(header + 2));
     return hipGetLastError();
 }
 
 hipError_t launch_split_planes(const float* a, const float* b, int64_t n, int precision, const SplitLayout& L,
-                               const PairGate& gate, hipStream_t s) {
+                               hipStream_t s) {
     const int64_t n4 = n * n / 4;
     const unsigned rows_grid = unsigned(n4 < 2048 * 256 ? (n4 + 255) / 256 : 2048);
     const dim3 tgrid{unsigned(n / 64), unsigned(n / 64), 1u};
     if (precision == kPrecBf16) {
-        split_rows_kernel<kPrecBf16><<<rows_grid, 256, 0, s>>>(a, n * n, L.exps, L.a_hi, nullptr, gate);
-        split_transpose_kernel<kPrecBf16><<<tgrid, 256, 0, s>>>(b, n, L.exps, L.bt_hi, nullptr, gate);
+        split_rows_kernel<kPrecBf16><<<rows_grid, 256, 0, s>>>(a, n * n, L.exps, L.a_hi, nullptr);
+        split_transpose_kernel<kPrecBf16><<<tgrid, 256, 0, s>>>(b, n, L.exps, L.bt_hi, nullptr);
     } else {
-        split_rows_kernel<kPrecF16x3><<<rows_grid, 256, 0, s>>>(a, n * n, L.exps, L.a_hi, L.a_lo, gate);
-        split_transpose_kernel<kPrecF16x3><<<tgrid, 256, 0, s>>>(b, n, L.exps, L.bt_hi, L.bt_lo, gate);
+        split_rows_kernel<kPrecF16x3><<<rows_grid, 256, 0, s>>>(a, n * n, L.exps, L.a_hi, L.a_lo);
+        split_transpose_kernel<kPrecF16x3><<<tgrid, 256, 0, s>>>(b, n, L.exps, L.bt_hi, L.bt_lo);
     }
     return hipGetLastError();
 }
@@ -175,7 +168,7 @@ hipError_t launch_split(const float* a, const float* b, int64_t n, int64_t bdim,
                         const double* pyr_b, int precision, const SplitLayout& L, hipStream_t s) {
     hipError_t e = launch_split_scales(bdim, lv, pyr_a, pyr_b, L.exps, s);
     if (e != hipSuccess) return e;
-    return launch_split_planes(a, b, n, precision, L, PairGate{}, s);
+    return launch_split_planes(a, b, n, precision, L, s);
 }
 
 }  // namespace spamm

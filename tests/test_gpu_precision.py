@@ -144,6 +144,33 @@ def test_staged_split_path_equals_fused(precision, kind):
         assert torch.equal(sp.execute_bf16(ga, gb, leaf, offsets, klist, ws=ws), c1)
 
 
+@pytest.mark.parametrize("precision", ["bf16", "f16x3"])
+@pytest.mark.parametrize("n", [128, 1536, 1664, 2048, 2176, 3968])
+def test_products_from_fp32_inputs_equal_the_split_path(precision, n):
+    """Both sides of the sizes where a workgroup goes from one leaf tile to 2x2
+    (bf16 1536, f16x3 2048), a single macro tile, macro rows that fill no round of
+    strips (13, 17, 31): the one-call path, the product from a plan and the
+    split path give bitwise the same C and the same pairs; c is written
+    everywhere, at 4-byte alignment too."""
+    leaf, tau = 64, 1e-4
+    a, b = inputs.exp_decay(n, 0.02, 5), inputs.exp_decay(n, 0.03, 6)
+    a[: n // 2] *= np.float32(-(2.0**-9))
+    ga, gb = gpu(a), gpu(b)
+    ws = sp.workspace(n, leaf, DEV)
+    header = torch.zeros(256, dtype=torch.uint8, device=DEV)
+    offsets, klist, pairs = sp.prepare_scales(ga, gb, tau, leaf, header, ws=ws)
+    buf = sp.split(ga, gb, leaf, precision, sp.pyramid(ga, leaf), sp.pyramid(gb, leaf))
+    want = sp.execute_split(buf, n, leaf, precision, offsets, klist, ws=ws)
+    c = torch.full((n * n + 1,), float("nan"), device=DEV)[1:].view(n, n)
+    _, count = sp.multiply_precision(ga, gb, tau, leaf, precision, c=c)
+    assert count == int(pairs.item())
+    assert torch.equal(c, want)
+    sp.schedule(offsets, klist, n, leaf, ws=ws)
+    planned = (sp.execute_f16x3(ga, gb, leaf, header, offsets, klist, ws=ws) if precision == "f16x3"
+               else sp.execute_bf16(ga, gb, leaf, offsets, klist, ws=ws))
+    assert torch.equal(planned, want)
+
+
 @pytest.mark.parametrize("n,kind", [(1024, "exp"), (1024, "signed"), (640, "exp")])
 def test_prepare_schedule_scales_equals_the_staged_calls(n, kind):
     """spamm_prepare_schedule_scales (one-launch plan and schedule, then the
