@@ -45,17 +45,25 @@ __global__ __launch_bounds__(256) void macro_items_kernel(const uint64_t* __rest
 }
 
 // ---------------------------------------------------------------------------
-// Leaf 64: tiles move from global memory straight into LDS (global_load_lds_dwordx4) through kDmaStages LDS stages of
-// one item (kDmaKC k) each, so the copies of the next items are in flight
-// while one is multiplied and no registers stage the data.
+// Leaf 64: tiles move from global memory straight into LDS
+// (global_load_lds_dwordx4) through two LDS stages of one item (64 k) each, so
+// the copies of the next item are in flight while one is multiplied and no
+// registers stage the data.
 //
-// Bound by the matrix cores and the copy bursts between their blocks.  EDGE
-// (N not a multiple of 128): macro tiles and k-chunks may reach past the
-// matrix, and rows may be only 4-byte aligned, which the copies accept.
-// Multiply alone, +-1/(1+|i-j|)^2, tau 1e-6: N = 5003 317 -> 224 us and N =
-// 8191 505 us, against the register-staged kernel that took these sizes (N =
-// 5120 without EDGE 213 us, N = 8192 460 us); leaf 128, N = 6000, exp decay
-// 0.01: 1310 -> 852 us (121.6 TFLOP/s, 122.9 at N = 6016 without EDGE).
+// Bound by the matrix cores: every pair of N = 8192 kept runs at 142 TFLOP/s,
+// MFMAs alone at 155.  Vector instructions take the FP32 MFMAs' issue time and
+// all waves' first LDS reads come at once after an item's barrier, so the loop
+// has next to none of the former (scalar bases and counters, addresses as
+// constants of the stage) and the latter are small; with 64-bit vector adds
+// for the copies, stage-dependent read addresses and twice the first reads it
+// ran at 127.  Banded patterns add items that few of the four tiles keep.
+// Multiply alone, +-1/(1+|i-j|)^2, tau 1e-6, N = 8192: 466 -> 440 us, leaf 128
+// 842 -> 790; exp decay 0.01, tau 1e-6: 1058 -> 964, leaf 128 1237 -> 1127.
+//
+// EDGE (N not a multiple of 128): macro tiles and k-chunks may reach past the
+// matrix, and rows may be only 4-byte aligned, which the copies accept.  One
+// call, leaf 128, N = 6000, exp decay 0.01: 1379 (register-staged, the kernel
+// that took these sizes) -> 925 -> 882 us.
 //
 // Sixteen waves: wave w computes the 32x32 quadrant (w >> 3 & 1, w >> 2 & 1)
 // of output tile (w + (w >> 2)) & 3 of the macro tile.  Waves are dealt to the
@@ -84,7 +92,8 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
     const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C, int64_t n, int64_t bdim,
     int64_t mb, const uint32_t* __restrict__ items, const int32_t* __restrict__ uprefix,
     const int32_t* __restrict__ offsets, int64_t* __restrict__ bounds, float* __restrict__ fix_slots) {
-    constexpr int LEAF = 64, KC = kDmaKC, NCH = LEAF / KC, SPC = KC / 2;
+    constexpr int LEAF = 64, KC = kDmaKC, SPC = KC / 2;
+    static_assert(KC == LEAF && kDmaStages == 2, "an item is one stage, its parity the stage");
     constexpr int ABYTES = 2 * LEAF * KC * 4, BBYTES = KC * 2 * LEAF * 4;
     constexpr int STAGE_BYTES = ABYTES + BBYTES;
     // one LDS object (the stages, the partition boundaries, the last chunks of
@@ -93,6 +102,9 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
     __shared__ __attribute__((aligned(1024))) char lds[kDmaStages * STAGE_BYTES + 6 * sizeof(int64_t) +
                                                        8 * sizeof(float)];
     int64_t(*sbound)[2] = reinterpret_cast<int64_t(*)[2]>(lds + kDmaStages * STAGE_BYTES);
+    // the A stages, then the B stages: an operand's stages are less than 64 KiB apart
+    auto a_stage = [&](int st) { return lds + st * ABYTES; };
+    auto b_stage = [&](int st) { return lds + kDmaStages * ABYTES + st * BBYTES; };
 
     // the wave index as a scalar, so that what derives from it (the tile, the
     // copy half and its membership tests) stays in scalar registers
@@ -149,9 +161,8 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
     // this group's slice of the item list (wave-uniform); past the end the
     // last item repeats (a harmless reload)
     const uint32_t* ip = items + p_begin;
-    const int64_t npairs = p_end - p_begin;
-    const int64_t nitems = npairs * NCH;
-    int64_t pp = 0;
+    const int32_t npairs = int32_t(p_end - p_begin);
+    int32_t pp = 0;
     uint32_t last = 0;
     auto produce = [&]() -> uint32_t {
         if (pp < npairs) last = ip[pp];
@@ -208,7 +219,6 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
     // so an item kept by one tile moves half the bytes.  The copy waits count
     // only the stores issued after a wave's copies, which holds for any number
     // of copies per wave with two stages.
-    static_assert(kDmaStages == 2, "copies per wave vary with the item");
     constexpr int ACH = KC / 4;  // 16-byte chunks per A row
     constexpr int BHALF = KC * LEAF * 4;  // bytes of one B column half
     auto aswz = [](int r) { return KC == 32 ? ((r >> 1) & 7) : (r & 15); };
@@ -217,7 +227,11 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
     // each copy's address: the item's part (uniform: a scalar base) plus the
     // lane's part, the same for every item (a 32-bit byte offset computed
     // once: row r of the copy's block times n, plus its swizzled chunk), so
-    // the copies of an item cost no per-lane address arithmetic
+    // the copies of an item cost no per-lane address arithmetic (the offset is
+    // opaque where it is used: an extension to 64 bits outside the loop would
+    // cost each copy a 64-bit vector add, and vector instructions take the FP32
+    // MFMAs' issue time, 3 to 4 cycles each: 155 TFLOP/s of them alone, 130 with
+    // 4 additions per MFMA)
     uint32_t a_off[KC / 32], b_off[KC / 32];
 #pragma unroll
     for (int j = 0; j < KC / 32; ++j) {
@@ -266,9 +280,8 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
         const int64_t e = r * n + (col < n ? col : 0), last = n * n - 4;
         return X + (e < last ? e : last);
     };
-    auto copy_item = [&](uint32_t pi, int ch, int st) {
+    auto copy_item = [&](uint32_t pi, int st) {
         const int64_t I = pi >> 23, J = (pi >> 14) & 511, kt = (pi >> 4) & 1023;
-        char* sbase = lds + st * STAGE_BYTES;
         if (EDGE && in_tail(pi)) {
             const int lane = edge_lane();
             if (pi & need_a) {
@@ -276,8 +289,8 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
                 for (int j = 0; j < KC / 32; ++j) {
                     const int blk = wave * (KC / 32) + j;
                     const int r = blk * (256 / KC) + lane / ACH, p = lane % ACH;
-                    copy_to_lds(edge_source(A, 2 * I * LEAF + r, kt * LEAF + ch * KC + 4 * (p ^ aswz(r))),
-                                sbase + blk * 1024);
+                    copy_to_lds(edge_source(A, 2 * I * LEAF + r, kt * LEAF + 4 * (p ^ aswz(r))),
+                                a_stage(st) + blk * 1024);
                 }
             }
             if (pi & need_b) {
@@ -285,41 +298,40 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
                 for (int j = 0; j < KC / 32; ++j) {
                     const int blk = (wave & 7) * (KC / 32) + j;
                     const int r = blk * 4 + (lane >> 4), p = lane & 15;
-                    copy_to_lds(edge_source(B, kt * LEAF + ch * KC + r,
+                    copy_to_lds(edge_source(B, kt * LEAF + r,
                                             2 * J * LEAF + half * LEAF + 4 * (p ^ (8 * ((r / SPC) & 1)))),
-                                sbase + ABYTES + half * BHALF + blk * 1024);
+                                b_stage(st) + half * BHALF + blk * 1024);
                 }
             }
             return;
         }
         if (pi & need_a) {
-            const char* base = reinterpret_cast<const char*>(A + 2 * I * LEAF * n + kt * LEAF + ch * KC);
+            const char* base = reinterpret_cast<const char*>(A + 2 * I * LEAF * n + kt * LEAF);
 #pragma unroll
             for (int j = 0; j < KC / 32; ++j) {
                 const int blk = wave * (KC / 32) + j;
-                __builtin_amdgcn_global_load_lds(reinterpret_cast<const float*>(base + (EDGE && int(I) == last_m ? a_edge[j] : a_off[j])),
-                                                 (__attribute__((address_space(3))) void*)(sbase + blk * 1024), 16, 0,
-                                                 0);
+                asm volatile("" : "+v"(a_off[j]));  // see a_off
+                const uint32_t off = EDGE && int(I) == last_m ? a_edge[j] : a_off[j];
+                copy_to_lds(reinterpret_cast<const float*>(base + off), a_stage(st) + blk * 1024);
             }
         }
         if (pi & need_b) {
-            const char* base = reinterpret_cast<const char*>(B + (kt * LEAF + ch * KC) * n + 2 * J * LEAF);
+            const char* base = reinterpret_cast<const char*>(B + (kt * LEAF) * n + 2 * J * LEAF);
 #pragma unroll
             for (int j = 0; j < KC / 32; ++j) {
                 const int blk = (wave & 7) * (KC / 32) + j;
-                __builtin_amdgcn_global_load_lds(
-                    reinterpret_cast<const float*>(base + (EDGE && int(J) == last_m ? b_edge[j] : b_off[j])),
-                    (__attribute__((address_space(3))) void*)(sbase + ABYTES + half * BHALF + blk * 1024), 16, 0, 0);
+                asm volatile("" : "+v"(b_off[j]));
+                const uint32_t off = EDGE && int(J) == last_m ? b_edge[j] : b_off[j];
+                copy_to_lds(reinterpret_cast<const float*>(base + off), b_stage(st) + half * BHALF + blk * 1024);
             }
         }
     };
     // EDGE, an item whose k reach past n, after this wave's copies of it have
     // landed: zeros for every k >= n of the chunks this wave copied, and the
     // elements of the matrix's last row whose chunk crosses its end
-    auto patch_tail = [&](uint32_t pi, int ch, int st) {
+    auto patch_tail = [&](uint32_t pi, int st) {
         const int I = int(pi >> 23), J = int((pi >> 14) & 511), kt = int((pi >> 4) & 1023);
         const int lane = edge_lane();
-        char* sbase = lds + st * STAGE_BYTES;
         // dst: the chunk of (row, col); k: the index of the two that is one
         auto mend = [&](char* dst, int row, int col, int k, int last) {
             f4* d = reinterpret_cast<f4*>(dst);
@@ -338,8 +350,8 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
             for (int j = 0; j < KC / 32; ++j) {
                 const int blk = wave * (KC / 32) + j;
                 const int r = blk * (256 / KC) + lane / ACH, p = lane % ACH;
-                const int col = kt * LEAF + ch * KC + 4 * (p ^ aswz(r));
-                mend(sbase + blk * 1024 + lane * 16, 2 * I * LEAF + r, col, col, 0);
+                const int col = kt * LEAF + 4 * (p ^ aswz(r));
+                mend(a_stage(st) + blk * 1024 + lane * 16, 2 * I * LEAF + r, col, col, 0);
             }
         }
         if (pi & need_b) {
@@ -347,34 +359,37 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
             for (int j = 0; j < KC / 32; ++j) {
                 const int blk = (wave & 7) * (KC / 32) + j;
                 const int r = blk * 4 + (lane >> 4), p = lane & 15;
-                const int row = kt * LEAF + ch * KC + r;
-                mend(sbase + ABYTES + half * BHALF + blk * 1024 + lane * 16, row,
+                const int row = kt * LEAF + r;
+                mend(b_stage(st) + half * BHALF + blk * 1024 + lane * 16, row,
                      2 * J * LEAF + half * LEAF + 4 * (p ^ (8 * ((r / SPC) & 1))), row, 4);
             }
         }
     };
     // operands are read in groups of GRP MFMA steps, one group ahead of the
-    // MFMAs that use them, so the LDS latency hides behind MFMA work
-    constexpr int GRP = 8, NGRP = SPC / GRP;
+    // MFMAs that use them, so the LDS latency hides behind MFMA work; small
+    // groups, as all 16 waves read their first ones at once after the barrier.
+    // The stage is a constant, so that every address is one of a_chunk, b_col
+    // plus an offset in the instruction.
+    constexpr int GRP = 4, NGRP = SPC / GRP;
     static_assert(SPC % GRP == 0, "operand groups");
-    auto compute = [&](int st) {
-        const char* sa = lds + st * STAGE_BYTES;
-        const char* sb = sa + ABYTES;
-        const int r = wa * 64 + qr * 32 + ir;
-        const int cc = qc * 32 + ir;  // column within tile column wb's half of B
-        const char* brow = sb + wb * BHALF + ((cc >> 2) ^ (8 * g)) * 16 + (cc & 3) * 4;
+    const int a_row = wa * 64 + qr * 32 + ir, cc = qc * 32 + ir;  // cc: column within tile column wb's half of B
+    int a_chunk[SPC / 4];  // opaque: else a base and eight offsets, added for every read
+#pragma unroll
+    for (int q = 0; q < SPC / 4; ++q)
+        a_chunk[q] = opaque(a_row * (KC * 4) + ((g * (SPC / 4) + q) ^ aswz(a_row)) * 16);
+    const char* b_col = b_stage(0) + wb * BHALF + g * SPC * (LEAF * 4) + ((cc >> 2) ^ (8 * g)) * 16 + (cc & 3) * 4;
+    auto compute = [&](auto stage) {
+        constexpr int st = decltype(stage)::value;
         f4 av[2][GRP / 4];
         float bv[2][GRP];
         auto load = [&](int grp, int buf) {
 #pragma unroll
             for (int q = 0; q < GRP / 4; ++q) {
-                const int c = (g * (SPC / 4) + grp * (GRP / 4) + q) ^ aswz(r);
-                av[buf][q] = *reinterpret_cast<const f4*>(sa + r * (KC * 4) + c * 16);
+                av[buf][q] = *reinterpret_cast<const f4*>(a_stage(st) + a_chunk[grp * (GRP / 4) + q]);
             }
 #pragma unroll
             for (int u = 0; u < GRP; ++u) {
-                const int kr = g * SPC + grp * GRP + u;
-                bv[buf][u] = *reinterpret_cast<const float*>(brow + kr * (LEAF * 4));
+                bv[buf][u] = *reinterpret_cast<const float*>(b_col + st * BBYTES + (grp * GRP + u) * (LEAF * 4));
             }
         };
         // a wave in its MFMA block goes first in its SIMD's issue arbitration,
@@ -393,63 +408,45 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_macro_dma_kernel(
         __builtin_amdgcn_s_setprio(0);
     };
 
-    // pair items of item it (f[0]) and of the next pairs; item it + S - 1 lies
-    // at most S - 1 pairs ahead
-    constexpr int S = kDmaStages;
-    uint32_t f[S];
-#pragma unroll
-    for (int i = 0; i < S; ++i) f[i] = produce();
-#pragma unroll
-    for (int i = 0; i < S - 1; ++i) copy_item(f[i / NCH], i % NCH, i);
-    int64_t out_m = m_begin;
-    int ns[S];  // macro tiles stored in the last S-1 steps (ns[0]: this step)
-#pragma unroll
-    for (int i = 0; i < S; ++i) ns[i] = 0;
+    uint32_t cur = produce(), next = produce();
+    copy_item(cur, 0);
+    int32_t out_m = int32_t(m_begin);
     // finish macro tile out_m: its C tile, or this workgroup's partial sums of
-    // a shared tile (kDmaStores stores per wave either way)
-    auto finish = [&]() {
-        ns[0] += store_macro(out_m, (out_m == m_first && head_split) || (out_m == m_next && tail_split));
+    // a shared tile
+    auto finish = [&]() -> int {
+        const int stored = store_macro(out_m, (out_m == m_first && head_split) || (out_m == m_next && tail_split));
         zero_acc();
         ++out_m;
+        return stored;
     };
     zero_acc();
-    for (int64_t it = 0; it < nitems; ++it) {
-        const uint32_t pi = f[0];
-        const int64_t m_it = int64_t(pi >> 23) * mb + ((pi >> 14) & 511);
-#pragma unroll
-        for (int i = S - 1; i > 0; --i) ns[i] = ns[i - 1];
-        ns[0] = 0;
-        while (out_m < m_it) finish();
+    // item `cur` from stage st, its parity
+    auto step = [&](auto st) {
+        const uint32_t pi = cur;
+        const int32_t m_it = int32_t(pi >> 23) * int32_t(mb) + int32_t((pi >> 14) & 511);
         int stores = 0;
-#pragma unroll
-        for (int i = 0; i < S - 1; ++i) stores += ns[i];
-        // this wave's copies of item it are complete once at most the copies
-        // of items it+1 .. it+S-2 and the stores issued since are outstanding
+        while (out_m < m_it) stores += finish();
+        // this wave's copies of the item are complete once at most the stores
+        // issued since are outstanding
         asm volatile("" ::: "memory");
-        wait_copies<(S - 2) * kDmaCopies>(stores);
+        wait_copies<0>(stores);
         if (EDGE && in_tail(pi)) {
             asm volatile("" ::: "memory");
-            patch_tail(pi, int(it % NCH), int(it % S));
+            patch_tail(pi, st);
             asm volatile("" ::: "memory");
         }
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's LDS reads of item it-1 are done
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's LDS reads of the item before are done
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        {   // item it+S-1 -> the stage item it-1 used
-            const int64_t il = it + S - 1;
-            const int ahead = int((it % NCH + S - 1) / NCH);  // pairs ahead of item it's pair
-            uint32_t pl = f[0];
-#pragma unroll
-            for (int i = 1; i < S; ++i)
-                if (ahead == i) pl = f[i];
-            copy_item(pl, int(il % NCH), int(il % S));
-        }
-        if ((pi >> tile) & 1) compute(int(it % S));
-        if ((it + 1) % NCH == 0) {
-#pragma unroll
-            for (int i = 0; i < S - 1; ++i) f[i] = f[i + 1];
-            f[S - 1] = produce();
-        }
+        copy_item(next, 1 - st);  // the next item -> the stage that the one before used
+        if ((pi >> tile) & 1) compute(st);
+        cur = next;
+        next = produce();
+    };
+    for (int32_t it = 0; it < npairs; it += 2) {
+        step(std::integral_constant<int, 0>{});
+        if (it + 1 == npairs) break;
+        step(std::integral_constant<int, 1>{});
     }
     while (out_m < m_end) finish();
     __builtin_amdgcn_s_waitcnt(0);  // no copy into LDS may outlive the workgroup
