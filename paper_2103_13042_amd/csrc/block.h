@@ -91,7 +91,8 @@ __device__ __forceinline__ void op_commit(float* t, int role, int e, f4 v) {
 
 // acc += quadrant (q >> 1, q & 1) of the entry whose four operand tiles are at t
 // (leaf 32 and up): lane (ir, g) supplies k = 16 g + u of MFMA step u, A[ir][16g
-// + u] and B[16g + u][ir]
+// + u] and B[16g + u][ir].  FIRST: acc = instead of acc +=.
+template <bool FIRST = false>
 __device__ __forceinline__ void op_multiply(f16v& acc, const float* t, int q, int lane) {
     const int ir = lane & 31, g = lane >> 5;
     const float* ta = t + (q >> 1) * kOpTile;
@@ -103,7 +104,8 @@ __device__ __forceinline__ void op_multiply(f16v& acc, const float* t, int q, in
     for (int v = 0; v < 4; ++v) av[v] = *reinterpret_cast<const f4*>(ta + a_at(ir, 4 * g + v));
 #pragma unroll
     for (int u = 0; u < 16; ++u)
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[u >> 2][u & 3], (u & 1 ? tb1 : tb0)[u * 32], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[u >> 2][u & 3], (u & 1 ? tb1 : tb0)[u * 32],
+                                                   FIRST && u == 0 ? f16v{} : acc, 0, 0, 0);
 }
 
 // acc += output tile (a, b) of the block (leaf 16) for the halves of the entry
@@ -135,18 +137,31 @@ struct BlockAcc {
     f16v acc, total;
     __device__ __forceinline__ void zero() {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = total[r] = 0.0f;
+        for (int r = 0; r < 16; ++r) total[r] = 0.0f;
     }
-    // e: the entry's index in the list
+    // e: the entry's index in the list.  A run starts without clearing the
+    // accumulators: vector instructions take the MFMAs' issue time, 3 to 4
+    // cycles each of the 64 of an MFMA (this and the copies' addresses: N = 4096
+    // paper matrix 231 -> 220 us, exp decay 0.01 at leaf 64 496 -> 476).
     __device__ __forceinline__ void multiply(const float* t, uint32_t quads, int e, int run, int q, int lane) {
-        if ((quads >> q) & 1) op_multiply(acc, t, q, lane);
-        if (((e + 1) & (run - 1)) == 0) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                total[r] += acc[r];
-                acc[r] = 0.0f;
-            }
+        const bool kept = (quads >> q) & 1;
+        if ((e & (run - 1)) == 0) {
+            if (kept)
+                op_multiply<true>(acc, t, q, lane);
+            else
+                acc = f16v{};
+        } else if (kept) {
+            op_multiply(acc, t, q, lane);
         }
+        if (((e + 1) & (run - 1)) == 0) add();
+    }
+    // after the last of `count` entries
+    __device__ __forceinline__ void finish(int count, int run) {
+        if (count & (run - 1)) add();
+    }
+    __device__ __forceinline__ void add() {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) total[r] += acc[r];
     }
     // f(element of the matrix, its sum) for every element of the quadrant inside it
     template <typename F>
@@ -157,7 +172,7 @@ struct BlockAcc {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int64_t row = row0 + 8 * (r >> 2) + (r & 3);
-            if (row < n) f(row * n + col, total[r] + acc[r]);
+            if (row < n) f(row * n + col, total[r]);
         }
     }
 };
@@ -176,6 +191,7 @@ struct BlockAcc<16> {
         for (int x = 0; x < 4; ++x)
             op_multiply16(acc[x], t, 2 * (q >> 1) + (x >> 1), 2 * (q & 1) + (x & 1), (keep >> (2 * x)) & 3u, lane);
     }
+    __device__ __forceinline__ void finish(int, int) {}
     template <typename F>
     __device__ __forceinline__ void each(int64_t n, int I, int J, int q, int lane, F f) const {
 #pragma unroll

@@ -147,7 +147,10 @@ __device__ __forceinline__ void block_multiply(const float* A, const float* B, f
         const char* src = base + int64_t(pk >> 4) * step;
         char* dst = reinterpret_cast<char*>(lds + st * STAGE + wave * kOpTile);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) copy_to_lds(reinterpret_cast<const float*>(src + off[j]), dst + 1024 * j);
+        for (int j = 0; j < 4; ++j) {
+            asm volatile("" : "+v"(off[j]));  // else extended to 64 bits outside the loop, a vector add a copy
+            copy_to_lds(reinterpret_cast<const float*>(src + off[j]), dst + 1024 * j);
+        }
     };
 
     BlockAcc<LEAF> acc;
@@ -267,6 +270,7 @@ __device__ __forceinline__ void block_multiply(const float* A, const float* B, f
             __syncthreads();
             acc.multiply(lds + (full & (STAGES - 1)) * STAGE, mask, full, run, wave, lane);
         }
+        acc.finish(count, run);
         if (LEAF == 128) __syncthreads();  // the list and the stages are used again
     }
     if constexpr (TEST) {

@@ -23,10 +23,10 @@
 // 0.1 / (|i-j|^0.1 + 1) at leaf 32 with 15 % of the pairs kept, they are busy 70 %
 // of the CUs' busy cycles (16 KiB of operands per 4 x 1024 cycles of MFMA work,
 // a third of them past L2), and the launch ends with 5 % of the CUs' time idle.
-// One call there 302 -> 231 us (register-staged 2x2 macro tiles in a static
+// One call there 302 -> 220 us (register-staged 2x2 macro tiles in a static
 // split of whole tiles, after a plan launch); exp decay 0.05, tau 1e-6, leaf 32:
-// N = 2048 66 -> 33 us, 8192 287 -> 190; leaf 16: N = 2048 69 -> 34, 8192 601 ->
-// 297; leaf 64: N = 2047 117 -> 36.
+// N = 2048 66 -> 33 us, 8192 287 -> 191; leaf 16: N = 2048 69 -> 33, 8192 601 ->
+// 290; leaf 64: N = 2047 117 -> 36.
 //
 // Sizes that are no multiple of 32, rows at 4-byte alignment: rows and columns
 // past the matrix are read from addresses inside it (they only reach parts of C
