@@ -27,6 +27,7 @@ struct BatchPlan {
     std::vector<size_t> base;  // per product region offset
     std::vector<Geom> geom;
     int64_t strips = 0;
+    double bytes = 0.0;  // of all inputs
     int32_t class_count[spamm::kBatchClasses] = {0, 0, 0};
     int64_t class_blocks[spamm::kBatchClasses] = {0, 0, 0};
 };
@@ -51,6 +52,7 @@ spamm_status plan_batch(int32_t count, const int64_t* n, const int32_t* leaf, Ba
         bp->base[size_t(p)] = o;
         o += 2 * norm_bytes(g);
         bp->strips += spamm::batch_strips(g.n, g.bdim);
+        bp->bytes += 8.0 * double(g.n) * double(g.n);
         bp->class_blocks[leaf_class(leaf[p])] += spamm::batch_blocks(g.n);
         ++bp->class_count[leaf_class(leaf[p])];
     }
@@ -149,7 +151,7 @@ spamm_status spamm_batch_run(int32_t count, const int64_t* n, const int32_t* lea
     return hip_check(spamm::launch_batch(reinterpret_cast<const spamm::BatchProduct*>(ws),
                                          reinterpret_cast<const int64_t*>(ws + bp.strips_at),
                                          reinterpret_cast<const int64_t*>(ws + bp.blocks_at), bp.class_count,
-                                         bp.class_blocks, bp.strips, count, static_cast<hipStream_t>(stream)),
+                                         bp.class_blocks, bp.strips, bp.bytes, count, static_cast<hipStream_t>(stream)),
                      "batch kernels");
 }
 

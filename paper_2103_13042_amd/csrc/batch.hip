@@ -7,7 +7,7 @@
 //
 // A batch of 48 products (n log-uniform in 256 .. 4096, exp decay, leaf 64): 577
 // us with plan, cost and fill launches and the products in persistent
-// single-tile ranges; see the figures at the kernels.
+// single-tile ranges, 418 so.
 #include <hip/hip_runtime.h>
 
 #include "block_multiply.h"
@@ -34,19 +34,25 @@ __device__ __forceinline__ int batch_find(const int64_t* __restrict__ base, int 
     return __builtin_amdgcn_readfirstlane(lo);
 }
 
-template <int LEAF>
+template <int LEAF, bool NT>
 __device__ __forceinline__ void batch_strip(const float* x, double* norms, int64_t n, int64_t bdim, bool vec,
                                             int64_t b) {
-    const int64_t chunks = (n + kNormCols - 1) / kNormCols;
     if (vec)
-        leaf_sumsq_strip<LEAF, true>(x, n, bdim, b / chunks, b % chunks, nullptr, norms, bdim);
+        leaf_sumsq_strip<LEAF, true, NT>(x, n, bdim, b % bdim, b / bdim, nullptr, norms, bdim);
     else
-        leaf_sumsq_strip<LEAF, false>(x, n, bdim, b / chunks, b % chunks, nullptr, norms, bdim);
+        leaf_sumsq_strip<LEAF, false, NT>(x, n, bdim, b % bdim, b / bdim, nullptr, norms, bdim);
 }
 }  // namespace
 
-// One block per (tile row, 1024-column chunk) of A (blockIdx.y = 0) or B (1);
-// a product's first block clears its pair counter.
+// One block per (tile row, 1024-column chunk) of A (blockIdx.y = 0) or B (1),
+// tile rows fastest (as leaf_sumsq_kernel); a product's first block clears its
+// pair counter.  NT: inputs of kBatchStreamBytes and more are read past the
+// last-level cache, whose lines the multiply then finds free for its own reads
+// and C (the 48 products of 1 GB in all: 460 -> 418 us a run; of 260 MB, which
+// stay cached, 139 us against 148).
+constexpr double kBatchStreamBytes = 512.0 * 1024 * 1024;
+
+template <bool NT>
 __global__ __launch_bounds__(kNormThreads) void batch_norms_kernel(const BatchProduct* __restrict__ P,
                                                                    const int64_t* __restrict__ strip_base, int count) {
     const int64_t bg = blockIdx.x;
@@ -58,9 +64,9 @@ __global__ __launch_bounds__(kNormThreads) void batch_norms_kernel(const BatchPr
     const float* x = global_ptr(second ? q.b : q.a);
     double* norms = global_ptr(second ? q.norms[1] : q.norms[0]);
     switch (q.leaf) {
-        case 32: batch_strip<32>(x, norms, q.n, q.bdim, q.vec != 0, b); break;
-        case 64: batch_strip<64>(x, norms, q.n, q.bdim, q.vec != 0, b); break;
-        default: batch_strip<128>(x, norms, q.n, q.bdim, q.vec != 0, b); break;
+        case 32: batch_strip<32, NT>(x, norms, q.n, q.bdim, q.vec != 0, b); break;
+        case 64: batch_strip<64, NT>(x, norms, q.n, q.bdim, q.vec != 0, b); break;
+        default: batch_strip<128, NT>(x, norms, q.n, q.bdim, q.vec != 0, b); break;
     }
 }
 
@@ -103,10 +109,14 @@ hipError_t launch_class(const BatchProduct* p, const int64_t* base, int32_t memb
 }  // namespace
 
 hipError_t launch_batch(const BatchProduct* prods, const int64_t* strip_base, const int64_t* block_base,
-                        const int32_t* class_count, const int64_t* class_blocks, int64_t strips, int32_t count,
-                        hipStream_t s) {
+                        const int32_t* class_count, const int64_t* class_blocks, int64_t strips, double bytes,
+                        int32_t count, hipStream_t s) {
     if (strips < 1 || strips > 0x7FFFFFFF) return hipErrorInvalidValue;
-    batch_norms_kernel<<<dim3{unsigned(strips), 2u, 1u}, kNormThreads, 0, s>>>(prods, strip_base, count);
+    const dim3 grid{unsigned(strips), 2u, 1u};
+    if (bytes > kBatchStreamBytes)
+        batch_norms_kernel<true><<<grid, kNormThreads, 0, s>>>(prods, strip_base, count);
+    else
+        batch_norms_kernel<false><<<grid, kNormThreads, 0, s>>>(prods, strip_base, count);
     hipError_t e = hipGetLastError();
     int32_t first = 0;
     for (int cls = 0; cls < kBatchClasses && e == hipSuccess; ++cls) {

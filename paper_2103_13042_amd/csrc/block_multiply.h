@@ -156,6 +156,7 @@ __device__ __forceinline__ void block_multiply(const float* A, const float* B, f
     BlockAcc<LEAF> acc;
     acc.zero();
     const int run = n <= 2048 ? 2 : 4;
+    bool none = true;  // no entry so far
     // one segment, but for leaf 128 beyond n = 65536
     for (int seg = 0; seg == 0 || (LEAF == 128 && seg < entries); seg += CAPACITY) {
         // ---- the entries of this segment: list[e] = k << 4 | quadrants (leaf 16: and masks[e])
@@ -223,6 +224,7 @@ __device__ __forceinline__ void block_multiply(const float* A, const float* B, f
             count = uprefix[m + 1] - uprefix[m];
         }
         count = __builtin_amdgcn_readfirstlane(count);
+        none = none && count == 0;
         auto entry = [&](int e) -> uint32_t {  // k << 4 | quadrants
             if constexpr (TEST)
                 return uint32_t(__builtin_amdgcn_readfirstlane(int(list[e])));
@@ -286,6 +288,20 @@ __device__ __forceinline__ void block_multiply(const float* A, const float* B, f
             else if (total)
                 atomicAdd(pairs, static_cast<unsigned long long>(total));
         }
+    }
+    if (FROM != kDropped && none) {  // 16 bytes a store, the accumulators' layout has 4
+        const int row = 64 * I + (tid >> 4), col = 64 * J + 4 * (tid & 15);
+        if (col + 4 <= int(n)) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (row + 16 * u < int(n))
+                    *reinterpret_cast<f4_dw*>(C + int64_t(row + 16 * u) * n + col) = f4{0, 0, 0, 0};
+        } else {
+            for (int u = 0; u < 4; ++u)
+                for (int c = col; c < int(n); ++c)
+                    if (row + 16 * u < int(n)) C[int64_t(row + 16 * u) * n + c] = 0.0f;
+        }
+        return;
     }
     if constexpr (FROM == kDropped) {
         double sq = 0.0;

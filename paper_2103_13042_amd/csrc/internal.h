@@ -266,9 +266,9 @@ int64_t batch_blocks(int64_t n);
 
 // prods: class after class (class_count each).  strip_base, block_base [count]:
 // the prefix of batch_strips over the batch, of batch_blocks within each class;
-// strips and class_blocks: the totals.
+// strips and class_blocks: the totals; bytes: of all inputs.
 hipError_t launch_batch(const BatchProduct* prods, const int64_t* strip_base, const int64_t* block_base,
-                        const int32_t* class_count, const int64_t* class_blocks, int64_t strips, int32_t count,
+                        const int32_t* class_count, const int64_t* class_blocks, int64_t strips, double bytes, int32_t count,
                         hipStream_t s);
 
 }  // namespace spamm

@@ -739,6 +739,19 @@ def test_small_products_at_edges(n, offset, leaf):
 
 
 @pytest.mark.parametrize("leaf", [16, 32, 64, 128])
+@pytest.mark.parametrize("n,offset", [(352, 0), (1027, 0), (2117, 1)])
+def test_blocks_without_products_are_zeros(n, offset, leaf):
+    """No pair kept: every element of C written as zero, none outside it, in
+    whole blocks and in those that reach past the matrix."""
+    a, b = _offset_view(inputs.uniform_pm1(n, 83), offset), _offset_view(inputs.uniform_pm1(n, 84), offset)
+    buf = torch.full((n * n + 4,), 7.0, device=DEV)
+    c = buf[2 : 2 + n * n].view(n, n)
+    _, pairs = sp.multiply(a, b, 1e30, leaf, c=c)
+    assert pairs == 0 and not c.any()
+    assert bool((buf[:2] == 7.0).all()) and bool((buf[-2:] == 7.0).all())
+
+
+@pytest.mark.parametrize("leaf", [16, 32, 64, 128])
 @pytest.mark.parametrize("n,offset", [(352, 0), (1025, 0), (1100, 1), (2081, 0), (2112, 3)])
 def test_block_multiply_matches_oracle_and_staged_path(n, offset, leaf):
     """The one-call path above n = 320 (a block of C per workgroup, testing its
