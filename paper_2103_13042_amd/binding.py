@@ -134,20 +134,29 @@ LIBRARY_WORKSPACE = "library"
 # -- marshalling helpers ----------------------------------------------------
 
 
-def _stream(dev: torch.device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+# A small product takes the GPU about as long as its call takes the host, so
+# these are kept cheap (N = 300 at leaf 32: 12.0 us a call with a stream object, a
+# pointer object per argument and the tensors' device objects, 8.6 so; 6.4 of
+# it the C call with its two launches).
 
 
-def _ptr(t: torch.Tensor | None) -> ctypes.c_void_p | None:
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+def _stream(dev: torch.device) -> int:
+    """The current stream of dev as the C ABI takes it (hipStream_t)."""
+    index = dev.index
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
+
+
+def _ptr(t: torch.Tensor | None) -> int | None:
+    return None if t is None else t.data_ptr()
 
 
 def _square_f32(x: torch.Tensor, name: str) -> int:
-    if not isinstance(x, torch.Tensor) or x.device.type != "cuda":
+    if not isinstance(x, torch.Tensor) or not x.is_cuda:
         raise TypeError(f"{name} must be a CUDA (HIP) tensor")
-    if x.dtype != torch.float32 or x.dim() != 2 or x.shape[0] != x.shape[1] or not x.is_contiguous():
+    shape = x.shape
+    if x.dtype != torch.float32 or len(shape) != 2 or shape[0] != shape[1] or not x.is_contiguous():
         raise ValueError(f"{name} must be a contiguous square float32 matrix")
-    return int(x.shape[0])
+    return shape[0]
 
 
 _WS: dict = {}
