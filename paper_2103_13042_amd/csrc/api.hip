@@ -565,11 +565,15 @@ spamm_status enqueue_direct(const Geom& g, const float* a, const float* b, doubl
     double* norms[2];
     const spamm_status st = enqueue_leaf_norms(g, a, b, pairs, norms, ws, s);
     if (st != SPAMM_OK) return st;
-    const bool vec = (g.n % 4) == 0 && aligned16(a) && aligned16(b);
-    if (g.n <= spamm::kSmallMaxN)
-        return hip_check(spamm::launch_small_multiply(a, b, c, g.n, g.leaf, vec, g.bdim, norms[0], norms[1],
-                                                      g.side, tau, pairs, s),
+    if (g.leaf >= 32 && g.n <= spamm::kTileMaxN)
+        return hip_check(spamm::launch_tile_multiply(a, b, c, g.n, g.leaf, norms[0], norms[1], g.side, tau, pairs, s),
+                         "tile multiply kernel");
+    if (g.leaf == 16 && g.n <= spamm::kSmallMaxN) {
+        const bool vec = (g.n % 4) == 0 && aligned16(a) && aligned16(b);
+        return hip_check(spamm::launch_small_multiply16(a, b, c, g.n, vec, g.bdim, norms[0], norms[1], g.side, tau,
+                                                        pairs, s),
                          "small multiply kernel");
+    }
     return hip_check(spamm::launch_block_test(a, b, c, g.n, g.leaf, g.bdim, norms[0], norms[1], g.side, tau, pairs,
                                               s),
                      "block multiply kernel");

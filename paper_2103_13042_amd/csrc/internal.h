@@ -75,23 +75,30 @@ inline int64_t plan_macro_clear_words(int64_t bdim) { return (bdim + 1) / 2 + 1;
 hipError_t launch_plan_macro(const double* norms_a, const double* norms_b, int64_t side, int64_t bdim, double tau,
                              const PlanMacroOut& o, hipStream_t s);
 
-// The smallest products (n <= kSmallMaxN, leaf 16 to 128): the threshold
-// test on the leaf norms na / nb (row stride ld) and the multiply of the kept
-// pairs in one launch; adds the number of kept pairs to *pairs, which must be
-// zero before (the norm pass clears it).  vec: n % 4 == 0 and a, b 16-byte
-// aligned.
+// Small products, n <= kTileMaxN at leaf 32, 64 and 128 (multiply_tile.hip), n <=
+// kSmallMaxN at leaf 16 (multiply_small.hip): the threshold test on the leaf
+// norms na / nb (row stride ld) and the multiply of the kept pairs in one
+// launch; adds the number of kept pairs to *pairs, which must be zero before
+// (the norm pass clears it).  vec: n % 4 == 0 and a, b 16-byte aligned.
+// kTileMaxN: a 32x32 tile of C per workgroup against a 64x64 block (one call,
+// exp decay 0.05 and 0.01, tau 1e-6, leaf 32: n = 352 12.1 and 12.1 us against 16.0
+// and 16.1; 1000 16.4 and 31.8 against 20.5 and 37.2; 1920 27.6 and 123 against 31
+// and 138; 2047 30.7 and 167 against 31.5 and 142; leaf 64 and 128 alike).
+constexpr int64_t kTileMaxN = 1920;
 constexpr int64_t kSmallMaxN = 320;
-hipError_t launch_small_multiply(const float* a, const float* b, float* c, int64_t n, int32_t leaf, bool vec,
-                                 int64_t bdim, const double* na, const double* nb, int64_t ld, double tau,
-                                 int64_t* pairs, hipStream_t s);
+hipError_t launch_tile_multiply(const float* a, const float* b, float* c, int64_t n, int32_t leaf, const double* na,
+                                const double* nb, int64_t ld, double tau, int64_t* pairs, hipStream_t s);
+hipError_t launch_small_multiply16(const float* a, const float* b, float* c, int64_t n, bool vec, int64_t bdim,
+                                   const double* na, const double* nb, int64_t ld, double tau, int64_t* pairs,
+                                   hipStream_t s);
 
 // One 64x64 block of C per workgroup (multiply_block.hip).  test: the
-// block tests the leaf norms itself, as launch_small_multiply (*pairs zero
+// block tests the leaf norms itself, as launch_tile_multiply (*pairs zero
 // before).  plan32: leaf 32, the items and prefix of a plan's macro-tile
 // schedule.
 //
-// block_product: where the one-call path takes it.  Leaf 16 and 32: any n (to
-// the tile grid's 1024 per side).  Leaf 64 and 128: n <= 5120; against the
+// block_product: where the one-call path takes it or, at small n, the kernels
+// above.  Leaf 16 and 32: any n (to the tile grid's 1024 per side).  Leaf 64 and 128: n <= 5120; against the
 // general path's plan, 128x128 macro tiles and fixup (one call, leaf 64) it
 // saves two launches and their work list: exp decay 0.05, tau 1e-6, n = 2047 37
 // against 52 us, 5003 112 against 127, 8192 220 against 212; where most pairs

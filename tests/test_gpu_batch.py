@@ -71,15 +71,17 @@ def test_batch_matches_oracle_and_single_products(batch):
 @pytest.mark.parametrize("n,leaf", [(640, 32), (641, 64), (671, 128)])
 def test_batch_of_many_blocks(n, leaf):
     """More than 8192 blocks of C in one leaf class, the form with one stage of
-    operand tiles: every product bitwise the single product's (two stages, the
-    same order of sums) with the same pairs."""
+    operand tiles: every product bitwise that of a batch of few blocks (two
+    stages, the same order of sums), with the single product's pairs."""
     mats = [[torch.from_numpy(m).to(DEV) for m in _mats(n, "exp", 50 + 2 * q)] for q in range(3)]
     single = [sp.multiply(a, b, 1e-6, leaf) for a, b in mats]
     order = [q % 3 for q in range(84)]
     bt = sp.Batch([mats[q][0] for q in order], [mats[q][1] for q in order], [leaf] * 84, [1e-6] * 84)
     bt.run()
     assert bt.pairs.cpu().tolist() == [single[q][1] for q in order]
-    assert all(torch.equal(bt.c[i], single[q][0]) for i, q in enumerate(order))
+    few = sp.Batch([m[0] for m in mats], [m[1] for m in mats], [leaf] * 3, [1e-6] * 3)
+    few.run()
+    assert all(torch.equal(bt.c[i], few.c[q]) for i, q in enumerate(order))
 
 
 def test_batch_reruns_are_bitwise_equal(batch):

@@ -738,6 +738,25 @@ def test_small_products_at_edges(n, offset, leaf):
     assert np.all(np.isfinite(c2[clean]))
 
 
+@pytest.mark.parametrize("leaf", [32, 64, 128])
+@pytest.mark.parametrize("n,offset", [(1, 0), (33, 1), (255, 0), (1000, 0), (1889, 3), (1920, 0), (1921, 0)])
+def test_tiles_at_both_ends_of_their_range(n, offset, leaf):
+    """A 32x32 tile of C per workgroup: one tile, fewer tile rows than XCDs, k
+    past the last whole entry, the last sizes of the range and the first beyond
+    it, at 16- and 4-byte alignment.  Pairs equal the oracle's, C within the FP32
+    accumulation bound, written everywhere and nothing outside it."""
+    a, b = inputs.exp_decay(n, 0.02, 91), inputs.exp_decay(n, 0.03, 92)
+    prod = oracle_products(a, b, leaf)
+    tau = float(np.quantile(prod, 0.5)) * (1.0 - 1e-9)
+    c_ref, count, _ = oracle.spamm(a, b, tau, leaf)
+    buf = torch.full((n * n + 4,), float("nan"), device=DEV)
+    c = buf[1 : 1 + n * n].view(n, n)
+    _, pairs = sp.multiply(_offset_view(a, offset), _offset_view(b, offset), tau, leaf, c=c)
+    assert pairs == count
+    check_c(c.cpu().numpy(), a, b, tau, leaf, c_ref=c_ref)
+    assert bool(buf[:1].isnan().all()) and bool(buf[-3:].isnan().all())
+
+
 @pytest.mark.parametrize("leaf", [16, 32, 64, 128])
 @pytest.mark.parametrize("n,offset", [(352, 0), (1027, 0), (2117, 1)])
 def test_blocks_without_products_are_zeros(n, offset, leaf):
@@ -757,8 +776,8 @@ def test_block_multiply_matches_oracle_and_staged_path(n, offset, leaf):
     """The one-call path above n = 320 (a block of C per workgroup, testing its
     own products): k past the last whole entry of 32, block rows left over from
     the strips dealt to the XCDs, unaligned matrices.  Pairs equal the oracle's,
-    C within the FP32 accumulation bound; leaf 16 and 32 bitwise the staged
-    path's C."""
+    C within the FP32 accumulation bound; leaf 16, and leaf 32 above the sizes
+    whose k four waves share (n = 1920), bitwise the staged path's C."""
     a, b = inputs.exp_decay(n, 0.02, 81), inputs.exp_decay(n, 0.03, 82)
     prod = oracle_products(a, b, leaf)
     tau = float(np.quantile(prod, 0.6)) * (1.0 + 1e-9)
@@ -768,6 +787,6 @@ def test_block_multiply_matches_oracle_and_staged_path(n, offset, leaf):
     _, pairs = sp.multiply(ga, gb, tau, leaf, c=c)
     assert pairs == count
     check_c(c.cpu().numpy(), a, b, tau, leaf, c_ref=c_ref)
-    if leaf <= 32:
+    if leaf == 16 or (leaf == 32 and n > 1920):
         offsets, klist, _ = sp.prepare(ga, gb, tau, leaf)
         assert torch.equal(sp.execute(ga, gb, leaf, offsets, klist), c)
