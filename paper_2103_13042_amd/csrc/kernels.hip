@@ -222,8 +222,72 @@ __global__ __launch_bounds__(kPyrThreads) void pyramid_kernel(PyramidJob job, in
     pyramid_build(job.spyr[blockIdx.x], job.pyr[blockIdx.x], bdim, lv);
 }
 
+// The six levels above the leaves under one node of level lv - 6 (blockIdx.x,
+// row-major), and the padding of its 64 x 64 leaves: the same sums as
+// pyramid_build's.
+constexpr int kSubtree = 6;
+
+__global__ __launch_bounds__(kPyrThreads) void pyramid_subtree_kernel(PyramidJob job, int64_t bdim, int lv) {
+    double* __restrict__ sp = job.spyr[blockIdx.y];
+    double* __restrict__ np = job.pyr[blockIdx.y];
+    const int64_t top = int64_t(1) << (lv - kSubtree), side = int64_t(1) << lv;
+    const int64_t bi = blockIdx.x / top, bj = blockIdx.x % top;
+    __shared__ double lvl[2][32 * 32];
+    {   // 32 x 32 nodes of level lv - 1, one per thread, from its four leaves
+        const int i = threadIdx.x >> 5, j = threadIdx.x & 31;
+        const int64_t li = bi * 64 + 2 * i, lj = bj * 64 + 2 * j, leaves = level_offset(lv);
+        double c[2][2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                const int64_t at = leaves + (li + u) * side + lj + v;
+                if (li + u < bdim && lj + v < bdim) {
+                    c[u][v] = sp[at];
+                } else {
+                    c[u][v] = 0.0;
+                    sp[at] = 0.0;
+                    np[at] = 0.0;
+                }
+            }
+        const double s = (c[0][0] + c[0][1]) + (c[1][0] + c[1][1]);
+        const int64_t at = level_offset(lv - 1) + (bi * 32 + i) * (side >> 1) + bj * 32 + j;
+        sp[at] = s;
+        np[at] = sqrt(s);
+        lvl[0][threadIdx.x] = s;
+    }
+#pragma unroll
+    for (int d = 2; d <= kSubtree; ++d) {
+        __syncthreads();
+        const int w = 64 >> d;  // nodes per side of level lv - d
+        const double* src = lvl[d & 1];
+        if (int(threadIdx.x) < w * w) {
+            const int i = threadIdx.x / w, j = threadIdx.x % w;
+            const double* c0 = src + 2 * i * 2 * w + 2 * j;
+            const double* c1 = c0 + 2 * w;
+            const double s = (c0[0] + c0[1]) + (c1[0] + c1[1]);
+            const int64_t at = level_offset(lv - d) + (bi * w + i) * (side >> d) + bj * w + j;
+            sp[at] = s;
+            np[at] = sqrt(s);
+            lvl[(d + 1) & 1][threadIdx.x] = s;
+        }
+    }
+}
+
+// From 128 leaves a side (rounded up) on the lower levels by subtrees, then the
+// levels above by one block per matrix.  One block alone is bound by its own
+// reads and writes: 9 us at 128 a side, 18 at 256, 95 at 512 with 256 of them
+// padding, 197 at 1024; the two launches take 6, 9, 9 and 10.
+constexpr int kSubtreeMinLevels = 7;
+
 hipError_t launch_pyramid(const PyramidJob& job, int nmat, int64_t bdim, int lv, hipStream_t s) {
-    pyramid_kernel<<<nmat, kPyrThreads, 0, s>>>(job, bdim, lv);
+    if (lv < kSubtreeMinLevels) {
+        pyramid_kernel<<<nmat, kPyrThreads, 0, s>>>(job, bdim, lv);
+        return hipGetLastError();
+    }
+    const int above = lv - kSubtree;
+    pyramid_subtree_kernel<<<dim3{1u << (2 * above), unsigned(nmat), 1u}, kPyrThreads, 0, s>>>(job, bdim, lv);
+    pyramid_kernel<<<nmat, kPyrThreads, 0, s>>>(job, int64_t(1) << above, above);
     return hipGetLastError();
 }
 

@@ -738,6 +738,23 @@ def test_small_products_at_edges(n, offset, leaf):
     assert np.all(np.isfinite(c2[clean]))
 
 
+@pytest.mark.parametrize("n,leaf", [(1024, 16), (1040, 16), (2049, 16), (2064, 32), (4112, 32)])
+def test_pyramid_in_two_launches(n, leaf):
+    """64 to 256 leaves a side, whole and with padding that ends inside a subtree
+    of 64 or leaves one empty: every level the square root of the sum of its
+    leaves' squares within FP64 rounding (at most 2 roundings of a sum a level, 9
+    levels), padding zero."""
+    x = gpu(inputs.uniform_pm1(n, 95))
+    b = sp.bdim(n, leaf)
+    levels = [p.cpu().numpy() for p in sp.pyramid_levels(sp.pyramid(x, leaf), n, leaf)]
+    assert np.array_equal(levels[-1][:b, :b], sp.norms(x, leaf).cpu().numpy())
+    assert not levels[-1][b:].any() and not levels[-1][:, b:].any()
+    exact = levels[-1].astype(np.longdouble) ** 2
+    for level in levels[-2::-1]:
+        exact = exact[0::2, 0::2] + exact[0::2, 1::2] + exact[1::2, 0::2] + exact[1::2, 1::2]
+        assert np.allclose(level, np.sqrt(exact).astype(np.float64), rtol=2 * 10 * 2.0**-52, atol=0.0)
+
+
 @pytest.mark.parametrize("leaf", [32, 64, 128])
 @pytest.mark.parametrize("n,offset", [(1, 0), (33, 1), (255, 0), (1000, 0), (1889, 3), (1920, 0), (1921, 0)])
 def test_tiles_at_both_ends_of_their_range(n, offset, leaf):
