@@ -541,26 +541,13 @@ constexpr int32_t kIdxMask = (1 << kIdxBits) - 1;
 constexpr int kRing = 512;  // packed pairs held in LDS (a power of two)
 
 // Tile shapes per leaf: MFMA edge, k per pipeline stage, workgroups per CU.
-#ifndef SPAMM_KC64
-#define SPAMM_KC64 64
-#endif
-#ifndef SPAMM_OCC64
-#define SPAMM_OCC64 2
-#endif
-#ifndef SPAMM_OCC128
-#define SPAMM_OCC128 1
-#endif
 template <int LEAF>
 struct MulCfg;
-template <>
-struct MulCfg<64> {
-    static constexpr int MF = 32, KC = SPAMM_KC64, OCC = SPAMM_OCC64;
-};
 template <>
 struct MulCfg<128> {
     // one workgroup per CU: at two (256 registers per lane) the kernel spilled
     // to scratch, also with 16 k per stage
-    static constexpr int MF = 32, KC = 32, OCC = SPAMM_OCC128;
+    static constexpr int MF = 32, KC = 32, OCC = 1;
 };
 
 template <int LEAF>

@@ -22,12 +22,14 @@
 // at different k); the matrix cores are busy 45 % of the time (F16X3; 15 % BF16).
 // Loads are 16 bytes a lane: B by 8-byte loads, which suit the transposition,
 // read L2 at 30 bytes a clock and CU against 52.
-// One call, F16X3: N = 16384, decay 0.01, tau 1e-6 2,000 -> 1,284 us (331 of it the
-// norms); 1024, 0.0126 122 -> 52; 4096, 0.0126 299 -> 158; 12800, 0.0126 1,090 ->
-// 754.  BF16: 16384 1,546 -> 1,181; 1024 85 -> 40; 2816, 0.0126 127 -> 112.  With
-// every pair kept, N = 8192: F16X3 3,650 -> 2,900, BF16 2,300 -> 2,262; BF16 at
-// N = 10112 and 10368 lost 7 and 11 % against planes converted first, which halve
-// the bytes of its loads.
+// One call, F16X3: N = 16384, decay 0.01, tau 1e-6 2,000 -> 1,261 us (314 of it the
+// norms); 1024, 0.0126 122 -> 46; 4096, 0.0126 299 -> 170; 12800, 0.0126 1,090 ->
+// 759.  BF16: 16384 1,546 -> 1,196; 1024 85 -> 36; 2816, 0.0126 127 -> 94.  With
+// every pair kept, N = 8192: F16X3 3,650 -> 2,620, BF16 2,300 -> 1,922; BF16 at N =
+// 10112 and 10368 was 7 and 11 % behind planes converted first, which halve the
+// bytes of its loads, before the loads took a scalar base (8192 then: 2,279).
+// hi and lo by mixed-precision FMAs, two instructions an element instead of three,
+// measured 2 to 10 % slower.
 #include <hip/hip_runtime.h>
 
 #include "block_multiply.h"
@@ -166,11 +168,11 @@ __global__ __launch_bounds__(kConvertThreads, 3) void multiply_convert_kernel(
     // columns of four k
     constexpr int AL = KC / 4, AR = kConvertThreads / AL;  // lanes per A row, rows per pass
     const int ar = tid / AL, aq = tid % AL;
-    const uint32_t a_off = uint32_t((int64_t(ar) * n + 4 * aq) * 4);
+    uint32_t a_off = uint32_t((int64_t(ar) * n + 4 * aq) * 4);
     // B: rows 4 bk .. + 3, columns 4 bc .. + 3 of the stage
     const int bk = (lane >> 3 & 1) + (T == 2 ? 2 * wave : 4 * wave + 2 * (lane >> 5));
     const int bc = (lane & 7) + (T == 2 ? lane >> 4 << 3 : (lane >> 4 & 1) << 3);
-    const uint32_t b_off = uint32_t((int64_t(4) * bk * n + 4 * bc) * 4);
+    uint32_t b_off = uint32_t((int64_t(4) * bk * n + 4 * bc) * 4);
     int a_at[4], b_at[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
@@ -182,6 +184,8 @@ __global__ __launch_bounds__(kConvertThreads, 3) void multiply_convert_kernel(
     auto load = [&](int k) {  // k: first of the stage
         const char* pa = reinterpret_cast<const char*>(A + int64_t(I) * R * n + k);
         const char* pb = reinterpret_cast<const char*>(B + int64_t(k) * n + J * R);
+        // opaque: else extended to 64 bits outside the loop, a vector add a load
+        asm volatile("" : "+v"(a_off), "+v"(b_off));
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
             xa[p] = *reinterpret_cast<const f4*>(pa + int64_t(p) * AR * n * 4 + a_off);

@@ -19,9 +19,9 @@
 namespace spamm {
 
 // Of one matrix per block: the largest leaf norm, from the leaf level of its
-// pyramid, and e from it.  One launch: two more around it, to clear a maximum in
-// memory and to read it, cost more (14 us of gaps and launches at bdim 256)
-// than two blocks instead of 128 (6 us against 5 there).
+// pyramid, and e from it.  One launch of two blocks, 12.8 us at bdim 256, bound
+// by one CU's loads: clearing a maximum in memory, 128 blocks and a last launch to
+// read it took 4.8 + 8.3 + 4.9 us and the gaps between them.
 constexpr int kScaleThreads = 1024;
 
 __global__ __launch_bounds__(kScaleThreads) void split_scale_kernel(const double* __restrict__ pyr_a,
@@ -32,8 +32,18 @@ __global__ __launch_bounds__(kScaleThreads) void split_scale_kernel(const double
     const int m = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const double* leaf = (m == 0 ? pyr_a : pyr_b) + level_offset(lv);
     double v = 0.0;
-    for (int64_t i = wave; i < bdim; i += kScaleThreads / 64)
-        for (int64_t j = lane; j < bdim; j += 64) v = fmax(v, leaf[i * side + j]);
+    constexpr int kRows = 16;  // of a wave, in flight at a time
+    for (int64_t j = lane; j < bdim; j += 64)
+        for (int64_t i0 = wave; i0 < bdim; i0 += kRows * (kScaleThreads / 64)) {
+            double x[kRows];
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                const int64_t i = i0 + u * (kScaleThreads / 64);
+                x[u] = i < bdim ? leaf[i * side + j] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) v = fmax(v, x[u]);
+        }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o));
     __shared__ double part[kScaleThreads / 64];
