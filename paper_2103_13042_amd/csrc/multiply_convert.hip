@@ -79,9 +79,7 @@ __device__ __forceinline__ int plane_at(int r, int c) {
 // 2,262), if they leave every XCD two strips and few rows over.
 template <int MODE>
 BlockOrder convert_order(int nb) {
-    const int dealt = dealt_rows(nb, 4);
-    const bool four = MODE == kPrecBf16 && nb >= 60 && (nb - dealt) * 8 <= nb;
-    return four ? BlockOrder{4, 24} : BlockOrder{2, 48};
+    return MODE == kPrecBf16 && nb >= 60 ? BlockOrder{4, 24} : BlockOrder{2, 48};
 }
 
 template <int MODE, int T, int FROM>
