@@ -9,7 +9,7 @@ spamm_prepare_schedule (leaf norms of A and B, then the plan for tau and the
 multiply schedule from one launch), then spamm_execute_scheduled (the MFMA
 multiply kernel of the kept pairs).  (Reduced precision: the same first stage,
 with the FP16 hi+lo scale exponents, spamm_prepare_schedule_scales, then the
-in-register multiply; with the split planes spamm_prepare_split,
+multiply from the FP32 inputs; with the split planes spamm_prepare_split,
 spamm_schedule, the planes' multiply.)  HIP events on the stream
 the library launches on bracket K steps run back to back (the step time),
 then K more steps with an event around each stage (the stage times; the
@@ -45,17 +45,13 @@ CSRC = ROOT / "paper_2103_13042_amd" / "csrc"
 CALIB_BYTES = 256 << 20  # device copy whose counter readings scale the HBM byte counters
 
 
-# the library's choice between the two forms of reduced-precision products:
-# split planes from this many kept pairs per output tile, else in registers
-LOWP_STAGED_PAIRS_PER_TILE = {"bf16": 16, "f16x3": 45}
-
-
 def multiply_kernel(n: int, leaf: int, precision: str = "fp32", staged: bool = False) -> tuple[str, list[Path]]:
     """Name and source files (kernel file and the headers it includes) of the
     multiply kernel the timed step launches."""
     heads = [CSRC / "device.h", CSRC / "dma.h"]
-    if precision != "fp32" and not staged:  # conversion in registers from the FP32 tiles
-        return f"multiply_fused_kernel<{ {'bf16': 1, 'f16x3': 2}[precision] }>", [CSRC / "multiply_lowp.hip", *heads]
+    if precision != "fp32" and not staged:  # FP32 tiles converted as they are loaded
+        return (f"multiply_convert_kernel<{ {'bf16': 1, 'f16x3': 2}[precision] }",
+                [CSRC / "multiply_convert.hip", CSRC / "block_multiply.h", *heads])
     if precision != "fp32":
         return f"multiply_lowp_kernel<{ {'bf16': 1, 'f16x3': 2}[precision] }>", [CSRC / "multiply_lowp.hip", *heads]
     if leaf == 64 or (leaf == 128 and n <= 128 * 512):
@@ -107,11 +103,11 @@ def parse_args():
     ap.add_argument("--precision", choices=["fp32", "bf16", "f16x3"], default="fp32",
                     help="leaf-product precision (the mask is always the FP32 inputs')")
     ap.add_argument("--form", choices=["auto", "planes", "registers"], default="auto",
-                    help="reduced precision: split planes or in-register conversion (auto: as the library picks, "
-                         "from the plan's pairs per output tile)")
+                    help="reduced precision: split planes, or conversion of the FP32 inputs in the multiply (auto, "
+                         "registers: the latter, as spamm_multiply_precision)")
     ap.add_argument("--one-call", action="store_true",
-                    help="time spamm_multiply as one call (fp32; leaf 32 with at most 64 tiles per side takes the "
-                         "two-launch small-product path)")
+                    help="time spamm_multiply as one call (fp32; leaf 16 and 32, and leaf 64 and 128 up to N = 5120, "
+                         "take two launches)")
     ap.add_argument("--sweep", default="1e-8,1e-4", help="other tau values timed briefly (empty: none)")
     ap.add_argument("--no-dense", action="store_true", help="skip the dense FP32 GEMM comparison")
     ap.add_argument("--no-cpu-baseline", action="store_true", help="skip timing the CPU oracle")
@@ -271,21 +267,17 @@ def main() -> int:
     # spamm_execute as its two launch steps, so that events on the stream the
     # library launches on (torch's current stream, passed by the binding)
     # bracket the multiply kernel alone.
-    # Reduced-precision products, as spamm_multiply_precision picks on the
-    # device (decided here once, from the pair count of a first pass): with at
-    # least 16 (BF16) or 45 (FP16 hi+lo) kept pairs per output tile on average
-    # the first stage also
+    # Reduced-precision products: the multiply converts the FP32 tiles as it
+    # loads them, as in spamm_multiply_precision (BF16: spamm_prepare_schedule,
+    # spamm_execute_bf16_scheduled; FP16 hi+lo: the first stage adds the scale
+    # exponents, spamm_prepare_schedule_scales, then
+    # spamm_execute_f16x3_scheduled); with --form planes the first stage also
     # writes the split operands (spamm_prepare_split) and the multiply reads
-    # them; below that the multiply converts the FP32 tiles in registers
-    # (BF16: spamm_prepare_schedule, spamm_execute_bf16_scheduled; FP16 hi+lo:
-    # the first stage adds the scale exponents, spamm_prepare_schedule_scales,
-    # then spamm_execute_f16x3_scheduled), as spamm_multiply_precision runs it.
+    # them.
     staged = False
     if prec != "fp32":
         sp.prepare(a, b, tau, leaf, bufs=bufs, ws=ws)
-        staged = int(bufs[2].item()) >= LOWP_STAGED_PAIRS_PER_TILE[prec] * (n // leaf) ** 2
-        if args.form != "auto":
-            staged = args.form == "planes"
+        staged = args.form == "planes"
         if staged:
             split_buf = sp.split_buffer(n, prec, dev)
 
@@ -366,8 +358,10 @@ def main() -> int:
 
     kname, ksrc = multiply_kernel(n, leaf, prec, staged)
     if one_call:
-        small = leaf == 32 and bd <= 64 and n % 4 == 0
-        kname = ("spamm_multiply: leaf norms + multiply_small_kernel" if small else "spamm_multiply (all launches)")
+        name = ("multiply_strip_kernel" if leaf == 16 and n <= 320 else
+                "multiply_tile_kernel" if leaf >= 32 and n <= 1920 else
+                "multiply_block_kernel" if leaf <= 32 or n <= 5120 else None)
+        kname = f"spamm_multiply: leaf norms + {name}" if name else "spamm_multiply (all launches)"
         ksrc = None
     workload = workload_name(n, leaf, tau, args.workload, args.alpha, prec)
     # The dense FP32 GEMM the speedup is quoted against.
@@ -585,8 +579,8 @@ def run_batch(args, torch, sp, inputs, dev) -> int:
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": f"batch of {len(specs)} products, n log-uniform in [256, 4096], exponential decay "
                                f"rates U[0.01, 0.5), tau={tau:g}, autotuned leaves",
-                   "form": "each stage one launch over the whole batch (about 11 launches, one persistent multiply "
-                           "per leaf class) captured in one graph and replayed; not one persistent launch",
+                   "form": "two stages over the whole batch (the norms, then blocks of C that test their own "
+                           "products, one launch per leaf class) captured in one graph and replayed",
                    "products": len(specs), "tau": tau, "leaves": hist, "pairs": int(sum(pairs)),
                    "dense_equiv_flop": dense_flop},
         "stages_ms": {"per_product_loop": round(loop_ms, 4), "batched_eager": round(eager_ms, 4),

@@ -177,7 +177,7 @@ spamm_status spamm_prepare_schedule(const float* a, const float* b, int64_t n, d
  * launches instead: the leaf norm pass, then one kernel that applies the
  * threshold test of Algorithm 1 to the leaf norms and multiplies the kept
  * pairs.  The pairs are those of the plan; C differs from spamm_prepare +
- * spamm_execute at most in the order of the FP32 additions (up to n = 320 the
+ * spamm_execute at most in the order of the FP32 additions (up to n = 1920 the
  * k-range of an output tile is split four ways above leaf 16 and the parts are
  * added in a fixed order; repeated calls agree bitwise); the workspace then
  * holds the leaf norms but no pyramid or plan.
@@ -296,11 +296,10 @@ spamm_status spamm_multiply_precision(const float* a, const float* b, int64_t n,
                                       void* workspace, size_t workspace_bytes, void* stream);
 
 /* Batches of independent products (each its own n, leaf and tau; the same
- * result as spamm_multiply on each, up to FP32 accumulation order).  Every
- * stage of the path is one launch over the whole batch: leaf norms, pyramids,
- * plan (mask, scan, fill), the per-class cost prefix, and one persistent
- * multiply launch per leaf class present (32, 64, 128) whose workgroups split
- * the class's total cost (section 3.5.1's balance, across products).
+ * result as spamm_multiply on each, up to FP32 accumulation order).  Two
+ * stages over the whole batch: the leaf norms, then blocks of C that apply the
+ * threshold test to the norms themselves and multiply the kept pairs, one
+ * launch per leaf class present (32, 64, 128), the largest products first.
  *
  * spamm_batch_workspace_bytes: device bytes for a batch (0 on bad arguments).
  * spamm_batch_setup: binds the batch to its matrices.  a, b, c: HOST arrays of

@@ -25,9 +25,9 @@
 // One call, F16X3: N = 16384, decay 0.01, tau 1e-6 2,000 -> 1,261 us (314 of it the
 // norms); 1024, 0.0126 122 -> 46; 4096, 0.0126 299 -> 170; 12800, 0.0126 1,090 ->
 // 759.  BF16: 16384 1,546 -> 1,196; 1024 85 -> 36; 2816, 0.0126 127 -> 94.  With
-// every pair kept, N = 8192: F16X3 3,650 -> 2,620, BF16 2,300 -> 1,922; BF16 at N =
-// 10112 and 10368 was 7 and 11 % behind planes converted first, which halve the
-// bytes of its loads, before the loads took a scalar base (8192 then: 2,279).
+// every pair kept, N = 8192: F16X3 3,650 -> 2,620, BF16 2,300 -> 1,890; BF16 at N =
+// 10112 and 10368 is 6 and 10 % behind planes converted first, which halve the
+// bytes of its loads, 10240 equal, 12288 5 % ahead.
 // hi and lo by mixed-precision FMAs, two instructions an element instead of three,
 // measured 2 to 10 % slower.
 #include <hip/hip_runtime.h>
@@ -73,10 +73,10 @@ __device__ __forceinline__ int plane_at(int r, int c) {
 // CUs hold at a time: these start together and stay near the same k, so the panels
 // that they share stay in L2.  Strips of two rows, whose rounds span the whole
 // band of a decaying matrix (F16X3, N = 16384, decay 0.01: 1,284 us, 1,343 at four
-// rows and 24 columns, 1,392 at eight and eight); BF16, whose loads weigh more, on
-// larger grids four, as rows two by two lose more where every pair is kept
-// (N = 16384, decay 0.01 1,238 against 1,181 us; N = 8192, all pairs 2,995 against
-// 2,262), if they leave every XCD two strips and few rows over.
+// rows and 24 columns, 1,392 at eight and eight); BF16, whose loads weigh more,
+// four rows on the grids that give every XCD about two strips (N = 16384, decay
+// 0.01 1,234 against 1,170 us; every pair kept, N = 8192 2,883 against 1,869, 10112
+// 5,840 against 4,527).
 template <int MODE>
 BlockOrder convert_order(int nb) {
     return MODE == kPrecBf16 && nb >= 60 ? BlockOrder{4, 24} : BlockOrder{2, 48};
