@@ -37,7 +37,6 @@ constexpr int kDmaStores = 16;  // per wave per macro tile
 #endif
 constexpr int kDmaKC = SPAMM_DMA_KC;          // k per item
 constexpr int kDmaStages = SPAMM_DMA_STAGES;  // LDS stages (items in flight + 1)
-constexpr int kDmaCopies = 2 * kDmaKC / 32;   // copies per wave per item
 static_assert(kDmaStages * (2 * 64 * kDmaKC * 4 * 2) <= 160 * 1024, "LDS budget");
 
 template <int N>

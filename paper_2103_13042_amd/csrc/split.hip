@@ -152,15 +152,15 @@ __global__ __launch_bounds__(256) void split_transpose_kernel(const float* __res
 }
 
 hipError_t launch_split_scales(int64_t bdim, int lv, const double* pyr_a, const double* pyr_b, int32_t* header,
-                               hipStream_t s) {
+                                      hipStream_t s) {
     // the header holds exps[2] (bytes 0..7) and the two maxima (bytes 8..23)
     split_scale_kernel<<<2, kScaleThreads, 0, s>>>(pyr_a, pyr_b, bdim, lv, header,
                                                    reinterpret_cast<double*>(header + 2));
     return hipGetLastError();
 }
 
-hipError_t launch_split_planes(const float* a, const float* b, int64_t n, int precision, const SplitLayout& L,
-                               hipStream_t s) {
+static hipError_t launch_split_planes(const float* a, const float* b, int64_t n, int precision, const SplitLayout& L,
+                                      hipStream_t s) {
     const int64_t n4 = n * n / 4;
     const unsigned rows_grid = unsigned(n4 < 2048 * 256 ? (n4 + 255) / 256 : 2048);
     const dim3 tgrid{unsigned(n / 64), unsigned(n / 64), 1u};
