@@ -113,6 +113,38 @@ Layout make_layout(const Geom& g) {
     return lean.total <= size_t(SPAMM_NOALLOC_SCRATCH_BYTES) ? lean : full;
 }
 
+bool search_regions(const Geom& g, SearchRegions* out) {
+    const Layout L = make_layout(g);
+    const size_t bdim = size_t(g.bdim), nb = size_t((g.n + 63) / 64);
+    const size_t starts[] = {L.spyr[0], L.spyr[1], L.pyr[0], L.pyr[1], L.counts, L.bsums, L.boffs, L.masks,
+                             L.offsets, L.klist, L.pair_scratch, L.mwords, L.mcount, L.mprefix, L.mitems,
+                             L.items128, L.uprefix128, L.bounds, L.fix_slots, L.pm_state, L.pairs, L.scalars,
+                             L.partials, L.total};
+    bool fits = true;
+    auto borrow = [&](size_t at, size_t bytes) {  // up to the next region's start
+        for (const size_t next : starts) fits = fits && (next <= at || at + bytes <= next);
+        return at;
+    };
+    SearchRegions R{};
+    R.blocks = int64_t(nb * nb);
+    const size_t norms = sizeof(double) * bdim * bdim;
+    R.rows_b = borrow(L.spyr[0], norms);
+    R.cols_a = borrow(L.spyr[1], norms);
+    R.ksums = borrow(L.partials, sizeof(double) * bdim);
+    const size_t probe = sizeof(int32_t) * bdim * spamm::kProbeStride;
+    R.count_even = borrow(L.klist, probe);
+    R.count_odd = borrow(L.pair_scratch, probe);
+    R.states = borrow(L.bounds, 2 * sizeof(spamm::SearchState));
+    R.partials = borrow(L.mwords, sizeof(double) * bdim * spamm::kQueryPartial);
+    R.answer = borrow(L.offsets, sizeof(spamm::StepAnswer));
+    // the k-list regions hold bdim^3 int32, too little for the sums only on
+    // the smallest grids
+    R.sums = borrow(nb <= 32 ? L.bounds : L.klist, sizeof(double) * nb * nb);
+    R.counts = borrow(L.pair_scratch, sizeof(int32_t) * nb * nb);
+    *out = R;
+    return fits;
+}
+
 bool overlaps(const void* p, size_t pbytes, const void* q, size_t qbytes) {
     const char* a = static_cast<const char*>(p);
     const char* b = static_cast<const char*>(q);
@@ -835,14 +867,13 @@ spamm_status spamm_search_valid_ratio(const double* pyr_a, const double* pyr_b, 
     if (st != SPAMM_OK) return st;
     if ((st = check_workspace(g, workspace, workspace_bytes)) != SPAMM_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const Layout L = make_layout(g);
-    // the norms sorted for counting, the counts and the state of the search, in
-    // regions of the workspace that hold no caller-visible pyramid or plan
-    double* rows_b = at<double>(workspace, L.spyr[0]);
-    double* cols_a = at<double>(workspace, L.spyr[1]);
-    double* ksums = at<double>(workspace, L.partials);
-    int32_t* counts[2] = {at<int32_t>(workspace, L.klist), at<int32_t>(workspace, L.pair_scratch)};
-    auto* states = at<spamm::SearchState>(workspace, L.bounds);
+    SearchRegions R;
+    if (!search_regions(g, &R)) return fail(SPAMM_ENOSPACE, "no room for the search in the workspace");
+    double* rows_b = at<double>(workspace, R.rows_b);
+    double* cols_a = at<double>(workspace, R.cols_a);
+    double* ksums = at<double>(workspace, R.ksums);
+    int32_t* counts[2] = {at<int32_t>(workspace, R.count_even), at<int32_t>(workspace, R.count_odd)};
+    auto* states = at<spamm::SearchState>(workspace, R.states);
     spamm::SearchState h{};
     h.target = target;
     h.tol = tol;

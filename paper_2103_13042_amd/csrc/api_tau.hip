@@ -27,26 +27,24 @@ struct Probe {
     float* e;
     void* ws;
     hipStream_t s;
-    // regions of the workspace that the norm queries and the error evaluations
-    // borrow; none holds a pyramid or a plan that a caller may have passed
+    // what the norm queries and the error evaluations keep in the workspace
     double *rows_b, *cols_a, *ksums, *partials, *sums;
     int32_t* counts;
     spamm::StepAnswer* answer;
     int64_t blocks;
 
-    void bind() {
-        const Layout L = make_layout(g);
-        rows_b = at<double>(ws, L.spyr[0]);
-        cols_a = at<double>(ws, L.spyr[1]);
-        ksums = at<double>(ws, L.partials);
-        partials = at<double>(ws, L.masks);
-        answer = at<spamm::StepAnswer>(ws, L.offsets);
-        const int64_t nb = (g.n + 63) / 64;
-        blocks = nb * nb;
-        // per 64x64 block of C: a double, an int32 (the k-list regions hold
-        // bdim^3 int32, too little only for the smallest grids)
-        sums = at<double>(ws, nb <= 32 ? L.bounds : L.klist);
-        counts = at<int32_t>(ws, L.pair_scratch);
+    spamm_status bind() {
+        SearchRegions R;
+        if (!search_regions(g, &R)) return fail(SPAMM_ENOSPACE, "no room for the search in the workspace");
+        rows_b = at<double>(ws, R.rows_b);
+        cols_a = at<double>(ws, R.cols_a);
+        ksums = at<double>(ws, R.ksums);
+        partials = at<double>(ws, R.partials);
+        answer = at<spamm::StepAnswer>(ws, R.answer);
+        blocks = R.blocks;
+        sums = at<double>(ws, R.sums);
+        counts = at<int32_t>(ws, R.counts);
+        return SPAMM_OK;
     }
 
     spamm_status sort() const {
@@ -210,8 +208,7 @@ spamm_status make_probe(const float* a, const float* b, int64_t n, int32_t leaf,
     p->e = e;
     p->ws = ws;
     p->s = static_cast<hipStream_t>(stream);
-    p->bind();
-    return SPAMM_OK;
+    return p->bind();
 }
 
 }  // namespace

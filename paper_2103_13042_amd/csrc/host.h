@@ -35,6 +35,21 @@ struct Layout {
 
 Layout make_layout(const Geom& g);
 
+// Regions that the threshold searches borrow; none of them holds a pyramid or
+// a plan that a caller may have passed, and none is used for two things at a
+// time.  The valid-ratio search has its counts in count_even / count_odd and
+// its states in states, the error search its norm queries' partials, its
+// answer, and per 64x64 block of C a sum of squares and a count.
+struct SearchRegions {
+    size_t rows_b, cols_a, ksums;
+    size_t count_even, count_odd, states;
+    size_t partials, answer, sums, counts;
+    int64_t blocks;  // 64x64 blocks of C
+};
+// false: a region is too small for what the searches keep there (then *out is
+// not to be used)
+bool search_regions(const Geom& g, SearchRegions* out);
+
 template <typename T>
 T* at(void* ws, size_t off) {
     return reinterpret_cast<T*>(static_cast<char*>(ws) + off);
