@@ -89,7 +89,15 @@ __global__ __launch_bounds__(kBlockThreads, block_occ(STAGES)) void multiply_bat
 
 int64_t batch_strips(int64_t n, int64_t bdim) { return bdim * ((n + kNormCols - 1) / kNormCols); }
 
-int64_t batch_blocks(int64_t n) { return block_grid(int((n + 63) / 64), kBlockOrder); }
+// A product of few block rows, all of them left over by block_at's strips, takes
+// its blocks in launch order: it needs no more workgroups than blocks (4096
+// products of n = 48, rounded up to one workgroup per XCD: 8 workgroups for 1
+// block, 277 us against 66).  A class's products go from the largest to the
+// smallest, so every product of whole strips still starts at a multiple of 8.
+int64_t batch_blocks(int64_t n) {
+    const int nb = int((n + 63) / 64);
+    return dealt_rows(nb, kBlockOrder.H) == 0 ? int64_t(nb) * nb : block_grid(nb, kBlockOrder);
+}
 
 namespace {
 template <int LEAF>
