@@ -98,16 +98,24 @@ hipError_t launch_small_multiply16(const float* a, const float* b, float* c, int
 // schedule.
 //
 // block_product: where the one-call path takes it or, at small n, the kernels
-// above.  Leaf 16 and 32: any n (to the tile grid's 1024 per side).  Leaf 64 and 128: n <= 5120; against the
-// general path's plan, 128x128 macro tiles and fixup (one call, leaf 64) it
-// saves two launches and their work list: exp decay 0.05, tau 1e-6, n = 2047 37
-// against 52 us, 5003 112 against 127, 8192 220 against 212; where most pairs
-// are kept the macro tiles' halved operand traffic wins from about n = 2200:
-// decay 0.01, n = 2047 159 against 161, 2500 273 against 238, 5003 669 against
-// 645, 8192 1190 against 1155.
-constexpr int64_t kBlockCoarseMaxN = 5120;
+// above.  Leaf 16 and 32: any n (to the tile grid's 1024 per side).  Leaf 64 and
+// 128 against the general path's plan, 128x128 macro tiles and fixup, which are two
+// launches and their work list more, but read half the operands and share the
+// work evenly, where blocks come in rounds of five a CU whose last is part empty.
+// Measured on one call, leaf 64, exp decay 0.05, 0.01 and 0.005 (leaf 128 alike):
+//  n <= 2048: blocks (2048: 32, 145, 152 us against 48, 144, 149);
+//  to 3968, a multiple of 128: macro tiles (2560: 55, 213, 279 against 43, 237, 322;
+//    3584: 69, 354, 647 against 65, 380, 718): the blocks gain on narrow bands, but
+//    lose up to a third on wide ones (2688, decay 0.0065: 301 against 397);
+//  to 5120: blocks (4096: 62, 467, 943 against 78, 428, 890; 5120: 96, 616, 1547
+//    against 119, 584, 1448), and below 4096 at ragged n, where macro tiles at the
+//    edge cost more (2500: 43, 237, 321 against 57, 226, 294; 3001: 46, 325, 471 against
+//    66, 296, 449).
+constexpr int64_t kBlockCoarseFullN = 2048, kBlockCoarseRoundsN = 4096, kBlockCoarseMaxN = 5120;
 inline bool block_product(int64_t n, int32_t leaf) {
-    return leaf == 16 || leaf == 32 || ((leaf == 64 || leaf == 128) && n <= kBlockCoarseMaxN);
+    if (leaf == 16 || leaf == 32) return true;
+    if (leaf != 64 && leaf != 128) return false;
+    return n <= kBlockCoarseFullN || (n <= kBlockCoarseMaxN && (n >= kBlockCoarseRoundsN || n % 128 != 0));
 }
 hipError_t launch_block_test(const float* a, const float* b, float* c, int64_t n, int32_t leaf, int64_t bdim,
                              const double* na, const double* nb, int64_t ld, double tau, int64_t* pairs,
