@@ -93,7 +93,7 @@ Layout layout_of(const Geom& g, bool lean) {
     L.fix_slots = take(L.fix_slot_bytes);
     L.pm_state = take(sizeof(int64_t) * size_t(spamm::plan_macro_clear_words(g.bdim)));
     L.pairs = take(sizeof(int64_t));
-    L.scalars = take(4 * sizeof(double));
+    L.form = take(sizeof(int32_t));
     L.partials = take(sizeof(double) * 1024);
     L.total = o;
     return L;
@@ -118,7 +118,7 @@ bool search_regions(const Geom& g, SearchRegions* out) {
     const size_t bdim = size_t(g.bdim), nb = size_t((g.n + 63) / 64);
     const size_t starts[] = {L.spyr[0], L.spyr[1], L.pyr[0], L.pyr[1], L.counts, L.bsums, L.boffs, L.masks,
                              L.offsets, L.klist, L.pair_scratch, L.mwords, L.mcount, L.mprefix, L.mitems,
-                             L.items128, L.uprefix128, L.bounds, L.fix_slots, L.pm_state, L.pairs, L.scalars,
+                             L.items128, L.uprefix128, L.bounds, L.fix_slots, L.pm_state, L.pairs, L.form,
                              L.partials, L.total};
     bool fits = true;
     auto borrow = [&](size_t at, size_t bytes) {  // up to the next region's start
@@ -610,6 +610,48 @@ spamm_status enqueue_direct(const Geom& g, const float* a, const float* b, doubl
                                               s),
                      "block multiply kernel");
 }
+
+// After the leaf norms: the choice of form and, where it falls on the planes, the
+// planes, the plan with its schedule and the multiply (*pairs is the plan's).
+spamm_status enqueue_planes(const Geom& g, const float* a, const float* b, spamm::FormChoice& choice,
+                            const spamm::SplitLayout& SL, float* c, int64_t* pairs, void* ws, hipStream_t s) {
+    const Layout L = make_layout(g);
+    const spamm::MacroSchedule ms = macro_schedule(L, ws);
+    const int32_t* run = choice.form;
+    int32_t* offsets = at<int32_t>(ws, L.offsets);
+    int32_t* klist = at<int32_t>(ws, L.klist);
+    int64_t* state = at<int64_t>(ws, L.pm_state);
+    choice.clear = state;
+    choice.clear_count = spamm::plan_macro_clear_words(g.bdim);
+    spamm_status st = hip_check(spamm::launch_split_choice(a, b, g.n, g.bdim, choice, SL, s), "split kernel");
+    if (st != SPAMM_OK) return st;
+    if (g.bdim <= spamm::kPlanMacroMaxBdim) {
+        const spamm::PlanMacroOut o{offsets, klist, pairs, ms.uprefix, ms.items,
+                                    reinterpret_cast<unsigned long long*>(state),
+                                    reinterpret_cast<unsigned int*>(state + (g.bdim + 1) / 2), run};
+        st = hip_check(spamm::launch_plan_macro(choice.na, choice.nb, g.side, g.bdim, choice.tau, o, s),
+                       "plan and schedule kernel");
+    } else {
+        uint64_t* masks = at<uint64_t>(ws, L.masks);
+        int32_t *counts = at<int32_t>(ws, L.counts), *bsums = at<int32_t>(ws, L.bsums),
+                *boffs = at<int32_t>(ws, L.boffs);
+        const spamm::PyramidJob pj{{at<double>(ws, L.spyr[0]), at<double>(ws, L.spyr[1])},
+                                   {at<double>(ws, L.pyr[0]), at<double>(ws, L.pyr[1])}};
+        hipError_t e = spamm::launch_pyramid(pj, 2, g.bdim, g.lv, s, run);
+        if (e == hipSuccess)
+            e = spamm::launch_plan_mask(pj.pyr[0], pj.pyr[1], g.bdim, g.lv, choice.tau, false, masks, counts, bsums, s,
+                                        run);
+        if (e == hipSuccess)
+            e = spamm::launch_plan_scan(bsums, g.bdim * g.nwords, boffs, offsets, g.ntiles, pairs, s, run);
+        if (e == hipSuccess) e = spamm::launch_plan_fill(masks, counts, boffs, g.bdim, offsets, klist, s, run);
+        if (e == hipSuccess) e = spamm::launch_macro_schedule(offsets, klist, g.bdim, ms, s, run);
+        st = hip_check(e, "plan and schedule kernels");
+    }
+    if (st != SPAMM_OK) return st;
+    return hip_check(spamm::launch_lowp_multiply(SL, c, g.n, g.bdim, spamm::kPrecBf16, ms.items, ms.uprefix,
+                                                 device_cus(), s, run),
+                     "reduced-precision multiply kernel");
+}
 }  // namespace
 
 spamm_status spamm_multiply(const float* a, const float* b, int64_t n, double tau, int32_t leaf, float* c,
@@ -843,13 +885,27 @@ spamm_status spamm_multiply_precision(const float* a, const float* b, int64_t n,
     }
     double* norms[2];
     if ((st = enqueue_leaf_norms(g, a, b, np, norms, workspace, s)) != SPAMM_OK) return st;
+    // BF16 with room for the planes (at the alignment that spamm_split asks for):
+    // the device picks between them and the FP32 inputs; both give the same C
+    const int32_t* form = nullptr;
+    spamm::FormChoice choice{};
+    if (!f16 && planes && (reinterpret_cast<uintptr_t>(split) & 255u) == 0 && spamm::bf16_choice(n, g.bdim, &choice)) {
+        choice.na = norms[0];
+        choice.nb = norms[1];
+        choice.ld = g.side;
+        choice.tau = tau;
+        choice.form = at<int32_t>(workspace, L.form);
+        if ((st = enqueue_planes(g, a, b, choice, split_layout(split, n, precision), c, np, workspace, s)) != SPAMM_OK)
+            return st;
+        form = choice.form;
+    }
     int32_t* exps = f16 ? static_cast<int32_t*>(split) : nullptr;
     if (f16 && (st = hip_check(spamm::launch_split_scales(g.bdim, g.lv, at<double>(workspace, L.pyr[0]),
                                                           at<double>(workspace, L.pyr[1]), exps, s),
                                "scale kernel")) != SPAMM_OK)
         return st;
     return hip_check(spamm::launch_convert_test(a, b, precision, exps, c, n, g.bdim, norms[0], norms[1], g.side, tau,
-                                                np, s),
+                                                np, form, s),
                      "reduced-precision multiply kernel (FP32 inputs)");
 }
 

@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstdint>
+
 namespace spamm {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
@@ -20,6 +22,10 @@ template <typename T>
 __device__ __forceinline__ T* global_ptr(T* p) {
     return (T*)(__attribute__((address_space(1))) T*)reinterpret_cast<uintptr_t>(p);
 }
+
+// A launch that runs only if *run is not zero (null: always), so that one stream
+// can hold both forms of a step and the device pick.
+__device__ __forceinline__ bool closed(const int32_t* run) { return run != nullptr && *run == 0; }
 
 // v, as a value the compiler knows nothing about (what is computed from it is
 // neither shared with other code nor moved out of a loop)

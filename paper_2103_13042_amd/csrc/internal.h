@@ -32,14 +32,19 @@ struct PyramidJob {
 // Norm pass: leaf sums of squares / norms of nmat matrices.
 hipError_t launch_leaf_norms(const NormJob& job, int nmat, int64_t n, int32_t leaf, bool vec, hipStream_t s);
 
+// Here and below, run: the launch does something only if *run (device memory) is
+// not zero; null: always.
+
 // Pyramid: bottom-up quadtree of sums of squares and norms for nmat matrices.
-hipError_t launch_pyramid(const PyramidJob& job, int nmat, int64_t bdim, int lv, hipStream_t s);
+hipError_t launch_pyramid(const PyramidJob& job, int nmat, int64_t bdim, int lv, hipStream_t s,
+                          const int32_t* run = nullptr);
 
 // Plan: per output tile, the ballot bitmap of kept k (words of 64) and its
 // count V; per block of 64 tiles (i, 64*jb ..) the sum of V (block b = i*nw + jb).
 // With `skipped` the bitmaps select the dropped triples instead.
 hipError_t launch_plan_mask(const double* pyr_a, const double* pyr_b, int64_t bdim, int lv, double tau, bool skipped,
-                            uint64_t* masks, int32_t* counts, int32_t* block_sums, hipStream_t s);
+                            uint64_t* masks, int32_t* counts, int32_t* block_sums, hipStream_t s,
+                            const int32_t* run = nullptr);
 // Plan counts only (no bitmaps): per block of 64 tiles the number of kept triples.
 hipError_t launch_plan_count(const double* pyr_a, const double* pyr_b, int64_t bdim, int lv, double tau,
                              int32_t* block_sums, hipStream_t s);
@@ -47,11 +52,12 @@ hipError_t launch_plan_count(const double* pyr_a, const double* pyr_b, int64_t b
 // offsets[T] and *pairs.  Each of the three outputs may be null; block_offsets
 // and offsets may be the same array (they are written at disjoint indices).
 hipError_t launch_plan_scan(const int32_t* block_sums, int64_t nblocks, int32_t* block_offsets, int32_t* offsets,
-                            int64_t ntiles, int64_t* pairs, hipStream_t s);
+                            int64_t ntiles, int64_t* pairs, hipStream_t s, const int32_t* run = nullptr);
 // Plan: per tile offset (block offset + prefix inside the block) and the
 // compaction of its bitmap into an ascending k-list.
 hipError_t launch_plan_fill(const uint64_t* masks, const int32_t* counts, const int32_t* block_offsets,
-                            int64_t bdim, int32_t* offsets, int32_t* klist, hipStream_t s);
+                            int64_t bdim, int32_t* offsets, int32_t* klist, hipStream_t s,
+                            const int32_t* run = nullptr);
 
 // Plan and macro-tile schedule in one launch (plan_macro.hip; leaf 32 and 64,
 // bdim <= kPlanMacroMaxBdim): the outputs of launch_plan_mask +
@@ -68,6 +74,7 @@ struct PlanMacroOut {
     uint32_t* items;
     unsigned long long* flags;
     unsigned int* ticket;
+    const int32_t* run;
 };
 inline int64_t plan_macro_clear_words(int64_t bdim) { return (bdim + 1) / 2 + 1; }
 // norms_a, norms_b: the leaf norms (row stride side); the pyramid above the
@@ -169,7 +176,7 @@ struct MacroSchedule {
     float* fix_slots;
 };
 hipError_t launch_macro_schedule(const int32_t* offsets, const int32_t* klist, int64_t bdim, const MacroSchedule& ms,
-                                 hipStream_t s);
+                                 hipStream_t s, const int32_t* run = nullptr);
 hipError_t launch_macro_multiply(const float* a, const float* b, float* c, int64_t n, int64_t bdim,
                                  const int32_t* offsets, const MacroSchedule& ms, int num_cus, hipStream_t s);
 // Leaf 128 (4 <= n, bdim <= kLeaf128MaxBdim) on the LDS-DMA kernel: two items per kept pair (uprefix [bdim*bdim + 1], items
@@ -249,14 +256,36 @@ hipError_t launch_split_scales(int64_t bdim, int lv, const double* pyr_a, const 
 // inputs (multiply_convert.hip), bitwise the same C as launch_split +
 // launch_lowp_multiply: with the products tested on the leaf norms (row stride
 // ld) and counted in *pairs, or from a plan's items.  exps: the split scale
-// exponents (F16X3 only; may be null for BF16).
+// exponents (F16X3 only; may be null for BF16).  planes (may be null): nothing is
+// done if *planes is not zero.
 hipError_t launch_convert_test(const float* a, const float* b, int precision, const int32_t* exps, float* c, int64_t n,
                                int64_t bdim, const double* na, const double* nb, int64_t ld, double tau,
-                               int64_t* pairs, hipStream_t s);
+                               int64_t* pairs, const int32_t* planes, hipStream_t s);
 hipError_t launch_convert_plan(const float* a, const float* b, int precision, const int32_t* exps, float* c, int64_t n,
                                int64_t bdim, const uint32_t* items, const int32_t* uprefix, hipStream_t s);
 hipError_t launch_lowp_multiply(const SplitLayout& L, float* c, int64_t n, int64_t bdim, int precision,
-                                const uint32_t* items, const int32_t* uprefix, int num_cus, hipStream_t s);
+                                const uint32_t* items, const int32_t* uprefix, int num_cus, hipStream_t s,
+                                const int32_t* run = nullptr);
+
+// BF16, one call, a caller with room for planes: which form multiplies is picked
+// on the device from the leaf norms na, nb (row stride ld).  The planes are
+// taken from `pairs` kept pairs per output tile on average (an estimate from 1024
+// products), unless every one is kept and full_fp32 is set.  launch_split_choice
+// writes *form (1: planes, 0: FP32 inputs), the planes if they are taken, and
+// zeros to clear_count words at clear.  bf16_choice: whether there is a choice
+// at this size, and its constants (multiply_convert.hip).
+struct FormChoice {
+    const double *na, *nb;
+    int64_t ld;
+    double tau;
+    int32_t pairs, full_fp32;
+    int32_t* form;
+    int64_t* clear;
+    int64_t clear_count;
+};
+bool bf16_choice(int64_t n, int64_t bdim, FormChoice* choice);
+hipError_t launch_split_choice(const float* a, const float* b, int64_t n, int64_t bdim, const FormChoice& choice,
+                               const SplitLayout& L, hipStream_t s);
 
 // --------------------------------------------------------------------------
 // Batched products (batch.hip): one descriptor per product in device memory.

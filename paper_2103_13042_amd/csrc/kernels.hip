@@ -218,7 +218,8 @@ __device__ __forceinline__ void pyramid_build(double* __restrict__ sp, double* _
     }
 }
 
-__global__ __launch_bounds__(kPyrThreads) void pyramid_kernel(PyramidJob job, int64_t bdim, int lv) {
+__global__ __launch_bounds__(kPyrThreads) void pyramid_kernel(PyramidJob job, int64_t bdim, int lv, const int32_t* run) {
+    if (closed(run)) return;
     pyramid_build(job.spyr[blockIdx.x], job.pyr[blockIdx.x], bdim, lv);
 }
 
@@ -227,7 +228,9 @@ __global__ __launch_bounds__(kPyrThreads) void pyramid_kernel(PyramidJob job, in
 // pyramid_build's.
 constexpr int kSubtree = 6;
 
-__global__ __launch_bounds__(kPyrThreads) void pyramid_subtree_kernel(PyramidJob job, int64_t bdim, int lv) {
+__global__ __launch_bounds__(kPyrThreads) void pyramid_subtree_kernel(PyramidJob job, int64_t bdim, int lv,
+                                                                      const int32_t* run) {
+    if (closed(run)) return;
     double* __restrict__ sp = job.spyr[blockIdx.y];
     double* __restrict__ np = job.pyr[blockIdx.y];
     const int64_t top = int64_t(1) << (lv - kSubtree), side = int64_t(1) << lv;
@@ -280,14 +283,14 @@ __global__ __launch_bounds__(kPyrThreads) void pyramid_subtree_kernel(PyramidJob
 // padding, 197 at 1024; the two launches take 6, 9, 9 and 10.
 constexpr int kSubtreeMinLevels = 7;
 
-hipError_t launch_pyramid(const PyramidJob& job, int nmat, int64_t bdim, int lv, hipStream_t s) {
+hipError_t launch_pyramid(const PyramidJob& job, int nmat, int64_t bdim, int lv, hipStream_t s, const int32_t* run) {
     if (lv < kSubtreeMinLevels) {
-        pyramid_kernel<<<nmat, kPyrThreads, 0, s>>>(job, bdim, lv);
+        pyramid_kernel<<<nmat, kPyrThreads, 0, s>>>(job, bdim, lv, run);
         return hipGetLastError();
     }
     const int above = lv - kSubtree;
-    pyramid_subtree_kernel<<<dim3{1u << (2 * above), unsigned(nmat), 1u}, kPyrThreads, 0, s>>>(job, bdim, lv);
-    pyramid_kernel<<<nmat, kPyrThreads, 0, s>>>(job, int64_t(1) << above, above);
+    pyramid_subtree_kernel<<<dim3{1u << (2 * above), unsigned(nmat), 1u}, kPyrThreads, 0, s>>>(job, bdim, lv, run);
+    pyramid_kernel<<<nmat, kPyrThreads, 0, s>>>(job, int64_t(1) << above, above, run);
     return hipGetLastError();
 }
 
@@ -391,19 +394,22 @@ __global__ __launch_bounds__(kPlanThreads) void plan_mask_kernel(const double* _
                                                                  const double* __restrict__ pyr_b, int64_t bdim,
                                                                  int lv, double tau, uint64_t* __restrict__ masks,
                                                                  int32_t* __restrict__ counts,
-                                                                 int32_t* __restrict__ block_sums) {
+                                                                 int32_t* __restrict__ block_sums,
+                                                                 const int32_t* run) {
+    if (closed(run)) return;
     plan_mask_block<MASKS, SKIPPED>(pyr_a, pyr_b, bdim, lv, tau, masks, counts, block_sums, blockIdx.x, blockIdx.y);
 }
 
 hipError_t launch_plan_mask(const double* pyr_a, const double* pyr_b, int64_t bdim, int lv, double tau, bool skipped,
-                            uint64_t* masks, int32_t* counts, int32_t* block_sums, hipStream_t s) {
+                            uint64_t* masks, int32_t* counts, int32_t* block_sums, hipStream_t s,
+                            const int32_t* run) {
     dim3 grid{unsigned((bdim + 63) / 64), unsigned(bdim), 1u};
     if (skipped)
         plan_mask_kernel<true, true><<<grid, kPlanThreads, 0, s>>>(pyr_a, pyr_b, bdim, lv, tau, masks, counts,
-                                                                   block_sums);
+                                                                   block_sums, run);
     else
         plan_mask_kernel<true, false><<<grid, kPlanThreads, 0, s>>>(pyr_a, pyr_b, bdim, lv, tau, masks, counts,
-                                                                    block_sums);
+                                                                    block_sums, run);
     return hipGetLastError();
 }
 
@@ -411,7 +417,7 @@ hipError_t launch_plan_count(const double* pyr_a, const double* pyr_b, int64_t b
                              int32_t* block_sums, hipStream_t s) {
     dim3 grid{unsigned((bdim + 63) / 64), unsigned(bdim), 1u};
     plan_mask_kernel<false, false><<<grid, kPlanThreads, 0, s>>>(pyr_a, pyr_b, bdim, lv, tau, nullptr, nullptr,
-                                                                 block_sums);
+                                                                 block_sums, nullptr);
     return hipGetLastError();
 }
 
@@ -455,13 +461,14 @@ __device__ __forceinline__ void plan_scan_block(const int32_t* __restrict__ bloc
 __global__ __launch_bounds__(kScanThreads) void plan_scan_kernel(const int32_t* __restrict__ block_sums,
                                                                  int64_t nb, int32_t* block_offsets,
                                                                  int32_t* offsets, int64_t nt,
-                                                                 int64_t* __restrict__ pairs) {
+                                                                 int64_t* __restrict__ pairs, const int32_t* run) {
+    if (closed(run)) return;
     plan_scan_block(block_sums, nb, block_offsets, offsets, nt, pairs);
 }
 
 hipError_t launch_plan_scan(const int32_t* block_sums, int64_t nblocks, int32_t* block_offsets, int32_t* offsets,
-                            int64_t ntiles, int64_t* pairs, hipStream_t s) {
-    plan_scan_kernel<<<1, kScanThreads, 0, s>>>(block_sums, nblocks, block_offsets, offsets, ntiles, pairs);
+                            int64_t ntiles, int64_t* pairs, hipStream_t s, const int32_t* run) {
+    plan_scan_kernel<<<1, kScanThreads, 0, s>>>(block_sums, nblocks, block_offsets, offsets, ntiles, pairs, run);
     return hipGetLastError();
 }
 
@@ -493,16 +500,18 @@ __device__ __forceinline__ void plan_fill_wave(const uint64_t* __restrict__ mask
 __global__ __launch_bounds__(256) void plan_fill_kernel(const uint64_t* __restrict__ masks,
                                                         const int32_t* __restrict__ counts,
                                                         const int32_t* __restrict__ block_offsets, int64_t bdim,
-                                                        int32_t* __restrict__ offsets, int32_t* __restrict__ klist) {
+                                                        int32_t* __restrict__ offsets, int32_t* __restrict__ klist,
+                                                        const int32_t* run) {
+    if (closed(run)) return;
     const int64_t t = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (t >= bdim * bdim) return;
     plan_fill_wave(masks, counts, block_offsets, bdim, offsets, klist, t);
 }
 
 hipError_t launch_plan_fill(const uint64_t* masks, const int32_t* counts, const int32_t* block_offsets,
-                            int64_t bdim, int32_t* offsets, int32_t* klist, hipStream_t s) {
+                            int64_t bdim, int32_t* offsets, int32_t* klist, hipStream_t s, const int32_t* run) {
     const int64_t nt = bdim * bdim;
-    plan_fill_kernel<<<unsigned((nt + 3) / 4), 256, 0, s>>>(masks, counts, block_offsets, bdim, offsets, klist);
+    plan_fill_kernel<<<unsigned((nt + 3) / 4), 256, 0, s>>>(masks, counts, block_offsets, bdim, offsets, klist, run);
     return hipGetLastError();
 }
 

@@ -86,7 +86,9 @@ template <int MODE, int T, int FROM>
 __global__ __launch_bounds__(kConvertThreads, 3) void multiply_convert_kernel(
     const float* __restrict__ A, const float* __restrict__ B, const int32_t* __restrict__ exps, float* __restrict__ C,
     int64_t n, int bdim, int nb, const double* __restrict__ na, const double* __restrict__ nbm, int64_t ld, double tau,
-    unsigned long long* __restrict__ pairs, const uint32_t* __restrict__ items, const int32_t* __restrict__ uprefix, BlockOrder order) {
+    unsigned long long* __restrict__ pairs, const uint32_t* __restrict__ items, const int32_t* __restrict__ uprefix,
+    BlockOrder order, const int32_t* planes) {
+    if (planes != nullptr && *planes != 0) return;
     using G = ConvertGeom<MODE, T>;
     constexpr bool F16 = G::F16;
     constexpr int KC = G::KC, R = G::R, PLANE = G::PLANE;
@@ -281,6 +283,31 @@ __global__ __launch_bounds__(kConvertThreads, 3) void multiply_convert_kernel(
             for (int r = 0; r < 16; ++r) __builtin_nontemporal_store(acc[u][v][r] * inv, &dst[(8 * (r >> 2) + (r & 3)) * n]);
         }
 }
+}  // namespace
+
+// BF16 with room for planes.  From the FP32 inputs every workgroup loads four bytes
+// an element; once the planes are there, two, for a pass over A and B (700 us at N =
+// 16384) and a plan.  Blocks of wide bands, at different k, share their panels least.
+// One call, planes against FP32 inputs, by kept pairs per output tile: N = 6912 37
+// pairs 702 and 677 us, 54 843 and 961; 8192 33 904 and 875, 49 1,117 and 1,254, 121
+// 2,298 and 3,044; 11008 26 1,359 and 1,434, 142 4,564 and 7,994; 16384 19 2,551 and
+// 2,186, 30 3,166 and 3,454, 137 10,036 and 17,052.  With every pair kept all blocks
+// start at k = 0 and share: where the strips of block_at come out even, N = 8192 2,270
+// and 1,874, 12288 7,258 and 6,647, but 11008 5,264 and 6,435, 20480 31,917 and 43,729.
+// The choice costs a product that stays with its FP32 inputs 9 us, three launches
+// that end at once: decay 0.05, N = 7040 126 -> 136, 16384 568 -> 577.  Below N = 6400
+// that is 10 % of a narrow band's call, and planes gain a wide one 7 at most (6016, 56
+// pairs: 681 and 732).
+constexpr int64_t kChoiceMinN = 6400, kFullFp32MaxN = 16384;
+bool bf16_choice(int64_t n, int64_t bdim, FormChoice* choice) {
+    if (n < kChoiceMinN) return false;
+    const int side = int(bdim / 2);
+    choice->pairs = n < 8192 ? 45 : 24;
+    choice->full_fp32 = n <= kFullFp32MaxN && dealt_rows(side, convert_order<kPrecBf16>(side).H) >= side;
+    return true;
+}
+
+namespace {
 
 // One leaf tile per workgroup up to this N, 2x2 above: four times the blocks
 // against half the loads and LDS reads per product (decay 0.0126 and 0.1, one leaf
@@ -293,7 +320,7 @@ constexpr int64_t kConvertSmallN = MODE == kPrecF16x3 ? 2048 : 1536;
 template <int MODE, int FROM>
 hipError_t launch(const float* a, const float* b, const int32_t* exps, float* c, int64_t n, int64_t bdim,
                   const double* na, const double* nb, int64_t ld, double tau, int64_t* pairs, const uint32_t* items,
-                  const int32_t* uprefix, hipStream_t s) {
+                  const int32_t* uprefix, const int32_t* planes, hipStream_t s) {
     if (n % 128 || n < 128 || bdim * 64 != n || bdim > kConvertEntries) return hipErrorInvalidValue;
     static int scratch_state[2] = {0, 0};
     const bool small = n <= kConvertSmallN<MODE>;
@@ -305,27 +332,29 @@ hipError_t launch(const float* a, const float* b, const int32_t* exps, float* c,
     const BlockOrder order = convert_order<MODE>(side);
     if (small)
         multiply_convert_kernel<MODE, 1, FROM><<<block_grid(side, order), kConvertThreads, 0, s>>>(
-            a, b, exps, c, n, int(bdim), side, na, nb, ld, tau, count, items, uprefix, order);
+            a, b, exps, c, n, int(bdim), side, na, nb, ld, tau, count, items, uprefix, order, planes);
     else
         multiply_convert_kernel<MODE, 2, FROM><<<block_grid(side, order), kConvertThreads, 0, s>>>(
-            a, b, exps, c, n, int(bdim), side, na, nb, ld, tau, count, items, uprefix, order);
+            a, b, exps, c, n, int(bdim), side, na, nb, ld, tau, count, items, uprefix, order, planes);
     return hipGetLastError();
 }
 }  // namespace
 
 hipError_t launch_convert_test(const float* a, const float* b, int precision, const int32_t* exps, float* c, int64_t n,
                                int64_t bdim, const double* na, const double* nb, int64_t ld, double tau,
-                               int64_t* pairs, hipStream_t s) {
+                               int64_t* pairs, const int32_t* planes, hipStream_t s) {
     return precision == kPrecBf16
-               ? launch<kPrecBf16, kKept>(a, b, exps, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, s)
-               : launch<kPrecF16x3, kKept>(a, b, exps, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, s);
+               ? launch<kPrecBf16, kKept>(a, b, exps, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, planes, s)
+               : launch<kPrecF16x3, kKept>(a, b, exps, c, n, bdim, na, nb, ld, tau, pairs, nullptr, nullptr, planes, s);
 }
 
 hipError_t launch_convert_plan(const float* a, const float* b, int precision, const int32_t* exps, float* c, int64_t n,
                                int64_t bdim, const uint32_t* items, const int32_t* uprefix, hipStream_t s) {
     return precision == kPrecBf16
-               ? launch<kPrecBf16, kPlanned>(a, b, exps, c, n, bdim, nullptr, nullptr, 0, 0.0, nullptr, items, uprefix, s)
-               : launch<kPrecF16x3, kPlanned>(a, b, exps, c, n, bdim, nullptr, nullptr, 0, 0.0, nullptr, items, uprefix, s);
+               ? launch<kPrecBf16, kPlanned>(a, b, exps, c, n, bdim, nullptr, nullptr, 0, 0.0, nullptr, items, uprefix,
+                                             nullptr, s)
+               : launch<kPrecF16x3, kPlanned>(a, b, exps, c, n, bdim, nullptr, nullptr, 0, 0.0, nullptr, items, uprefix,
+                                              nullptr, s);
 }
 
 }  // namespace spamm

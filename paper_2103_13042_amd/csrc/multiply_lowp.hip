@@ -226,7 +226,9 @@ template <int MODE>
 __global__ __launch_bounds__(kDmaThreads, 1) void multiply_lowp_kernel(
     const uint16_t* __restrict__ Ah, const uint16_t* __restrict__ Al, const uint16_t* __restrict__ Bh,
     const uint16_t* __restrict__ Bl, const int32_t* __restrict__ exps, float* __restrict__ C, int64_t n,
-    int64_t bdim, int64_t mb, const uint32_t* __restrict__ items, const int32_t* __restrict__ uprefix) {
+    int64_t bdim, int64_t mb, const uint32_t* __restrict__ items, const int32_t* __restrict__ uprefix,
+    const int32_t* run) {
+    if (closed(run)) return;
     using G = LowpGeom<MODE>;
     constexpr int LEAF = 64, S = G::S;
     static_assert(S * G::STAGE + kDealBytes <= 160 * 1024, "LDS budget");
@@ -330,7 +332,8 @@ __global__ __launch_bounds__(kDmaThreads, 1) void multiply_lowp_kernel(
 }
 
 hipError_t launch_lowp_multiply(const SplitLayout& L, float* c, int64_t n, int64_t bdim, int precision,
-                                const uint32_t* items, const int32_t* uprefix, int num_cus, hipStream_t s) {
+                                const uint32_t* items, const int32_t* uprefix, int num_cus, hipStream_t s,
+                                const int32_t* run) {
     const int64_t mb = (bdim + 1) / 2, nm = mb * mb;
     const int64_t cap = ((nm + 7) / 8) * 8;
     int64_t groups = int64_t(num_cus);
@@ -341,12 +344,12 @@ hipError_t launch_lowp_multiply(const SplitLayout& L, float* c, int64_t n, int64
         const hipError_t ce = check_no_scratch(multiply_lowp_kernel<kPrecBf16>, &scratch_bf16);
         if (ce != hipSuccess) return ce;
         multiply_lowp_kernel<kPrecBf16><<<unsigned(groups), kDmaThreads, 0, s>>>(
-            L.a_hi, L.a_lo, L.bt_hi, L.bt_lo, L.exps, c, n, bdim, mb, items, uprefix);
+            L.a_hi, L.a_lo, L.bt_hi, L.bt_lo, L.exps, c, n, bdim, mb, items, uprefix, run);
     } else {
         const hipError_t ce = check_no_scratch(multiply_lowp_kernel<kPrecF16x3>, &scratch_f16);
         if (ce != hipSuccess) return ce;
         multiply_lowp_kernel<kPrecF16x3><<<unsigned(groups), kDmaThreads, 0, s>>>(
-            L.a_hi, L.a_lo, L.bt_hi, L.bt_lo, L.exps, c, n, bdim, mb, items, uprefix);
+            L.a_hi, L.a_lo, L.bt_hi, L.bt_lo, L.exps, c, n, bdim, mb, items, uprefix, run);
     }
     return hipGetLastError();
 }

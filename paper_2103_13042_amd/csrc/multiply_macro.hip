@@ -27,20 +27,20 @@ namespace spamm {
 __global__ __launch_bounds__(256) void macro_words_kernel(const int32_t* __restrict__ off,
                                                           const int32_t* __restrict__ klist, int64_t bdim, int64_t mb,
                                                           int nw, uint64_t* __restrict__ words,
-                                                          int32_t* __restrict__ ucount) {
+                                                          int32_t* __restrict__ ucount, const int32_t* run) {
     __shared__ unsigned long long sw[4][4][16];  // [wave][tile][word]
     const int wave = threadIdx.x >> 6;
     const int64_t m = int64_t(blockIdx.x) * 4 + wave;
-    if (m >= mb * mb) return;
+    if (closed(run) || m >= mb * mb) return;
     macro_words_wave(off, klist, bdim, mb, nw, words, ucount, m, sw[wave]);
 }
 
 // One wave per macro tile: its packed items (macro_items_wave).
 __global__ __launch_bounds__(256) void macro_items_kernel(const uint64_t* __restrict__ words,
                                                           const int32_t* __restrict__ uprefix, int64_t mb, int nw,
-                                                          uint32_t* __restrict__ items) {
+                                                          uint32_t* __restrict__ items, const int32_t* run) {
     const int64_t m = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    if (m >= mb * mb) return;
+    if (closed(run) || m >= mb * mb) return;
     macro_items_wave(words, uprefix, mb, nw, items, m);
 }
 
@@ -568,15 +568,15 @@ hipError_t launch_leaf128_multiply(const float* a, const float* b, float* c, int
 }
 
 hipError_t launch_macro_schedule(const int32_t* offsets, const int32_t* klist, int64_t bdim, const MacroSchedule& ms,
-                                 hipStream_t s) {
+                                 hipStream_t s, const int32_t* run) {
     const int64_t mb = (bdim + 1) / 2, nm = mb * mb;
     const int nw = int((bdim + 63) / 64);
-    macro_words_kernel<<<unsigned((nm + 3) / 4), 256, 0, s>>>(offsets, klist, bdim, mb, nw, ms.words, ms.ucount);
+    macro_words_kernel<<<unsigned((nm + 3) / 4), 256, 0, s>>>(offsets, klist, bdim, mb, nw, ms.words, ms.ucount, run);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = launch_plan_scan(ms.ucount, nm, ms.uprefix, ms.uprefix, nm, nullptr, s);
+    e = launch_plan_scan(ms.ucount, nm, ms.uprefix, ms.uprefix, nm, nullptr, s, run);
     if (e != hipSuccess) return e;
-    macro_items_kernel<<<unsigned((nm + 3) / 4), 256, 0, s>>>(ms.words, ms.uprefix, mb, nw, ms.items);
+    macro_items_kernel<<<unsigned((nm + 3) / 4), 256, 0, s>>>(ms.words, ms.uprefix, mb, nw, ms.items, run);
     return hipGetLastError();
 }
 

@@ -82,6 +82,7 @@ __global__ __launch_bounds__(kPmThreads) void plan_macro_kernel(const double* __
     __shared__ int64_t s_row;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (closed(o.run)) return;
     if (tid == 0) s_row = atomicAdd(o.ticket, 1u);
     const int64_t mb = (bdim + 1) / 2, nm = mb * mb;
     const int nw = int((bdim + 63) / 64);

@@ -84,38 +84,28 @@ struct Conv<kPrecF16x3> {
     }
 };
 
-// A: row-major, 4 elements per thread per step (n % 4 == 0)
+// four elements of a row-major plane
 template <int MODE>
-__global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict__ x, int64_t count,
-                                                         const int32_t* __restrict__ exps, uint16_t* __restrict__ hi,
-                                                         uint16_t* __restrict__ lo) {
-    const float s = MODE == kPrecF16x3 ? ldexpf(1.0f, exps[0]) : 1.0f;
-    const int64_t n4 = count / 4;
-    const f4* x4 = reinterpret_cast<const f4*>(x);
-    for (int64_t q = int64_t(blockIdx.x) * 256 + threadIdx.x; q < n4; q += int64_t(gridDim.x) * 256) {
-        const f4 v = x4[q];
-        uint16_t h[4], l[4] = {0, 0, 0, 0};
+__device__ __forceinline__ void split_row4(const f4* __restrict__ x4, int64_t q, float s, uint16_t* __restrict__ hi,
+                                           uint16_t* __restrict__ lo) {
+    const f4 v = x4[q];
+    uint16_t h[4], l[4] = {0, 0, 0, 0};
 #pragma unroll
-        for (int i = 0; i < 4; ++i) Conv<MODE>::run(v[i], s, &h[i], &l[i]);
-        const uint64_t hp = uint64_t(h[0]) | uint64_t(h[1]) << 16 | uint64_t(h[2]) << 32 | uint64_t(h[3]) << 48;
-        reinterpret_cast<uint64_t*>(hi)[q] = hp;
-        if (MODE == kPrecF16x3) {
-            const uint64_t lp = uint64_t(l[0]) | uint64_t(l[1]) << 16 | uint64_t(l[2]) << 32 | uint64_t(l[3]) << 48;
-            reinterpret_cast<uint64_t*>(lo)[q] = lp;
-        }
+    for (int i = 0; i < 4; ++i) Conv<MODE>::run(v[i], s, &h[i], &l[i]);
+    const uint64_t hp = uint64_t(h[0]) | uint64_t(h[1]) << 16 | uint64_t(h[2]) << 32 | uint64_t(h[3]) << 48;
+    reinterpret_cast<uint64_t*>(hi)[q] = hp;
+    if (MODE == kPrecF16x3) {
+        const uint64_t lp = uint64_t(l[0]) | uint64_t(l[1]) << 16 | uint64_t(l[2]) << 32 | uint64_t(l[3]) << 48;
+        reinterpret_cast<uint64_t*>(lo)[q] = lp;
     }
 }
 
-// B transposed, one 64 x 64 tile per block through LDS (n % 64 == 0):
-// read rows of B coalesced, write rows of Bt (= columns of B) coalesced.
+// The 64 x 64 tile at (r0, c0) of B transposed, by 256 threads (tid) through LDS (n %
+// 64 == 0): read rows of B coalesced, write rows of Bt (= columns of B) coalesced.
 template <int MODE>
-__global__ __launch_bounds__(256) void split_transpose_kernel(const float* __restrict__ x, int64_t n,
-                                                              const int32_t* __restrict__ exps,
-                                                              uint16_t* __restrict__ hi, uint16_t* __restrict__ lo) {
-    __shared__ float t[64][65];
-    const float s = MODE == kPrecF16x3 ? ldexpf(1.0f, exps[1]) : 1.0f;
-    const int64_t r0 = int64_t(blockIdx.y) * 64, c0 = int64_t(blockIdx.x) * 64;
-    const int tid = threadIdx.x;
+__device__ __forceinline__ void split_tile(const float* __restrict__ x, int64_t n, int64_t r0, int64_t c0, float s,
+                                           uint16_t* __restrict__ hi, uint16_t* __restrict__ lo, float (*t)[65],
+                                           int tid) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {  // 64 rows x 16 float4
         const int e = tid + 256 * u, r = e >> 4, c4 = e & 15;
@@ -149,6 +139,84 @@ __global__ __launch_bounds__(256) void split_transpose_kernel(const float* __res
             *reinterpret_cast<uint4*>(lo + off) = lp;
         }
     }
+}
+
+// A: row-major, 4 elements per thread per step (n % 4 == 0)
+template <int MODE>
+__global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict__ x, int64_t count,
+                                                         const int32_t* __restrict__ exps, uint16_t* __restrict__ hi,
+                                                         uint16_t* __restrict__ lo) {
+    const float s = MODE == kPrecF16x3 ? ldexpf(1.0f, exps[0]) : 1.0f;
+    const f4* x4 = reinterpret_cast<const f4*>(x);
+    for (int64_t q = int64_t(blockIdx.x) * 256 + threadIdx.x; q < count / 4; q += int64_t(gridDim.x) * 256)
+        split_row4<MODE>(x4, q, s, hi, lo);
+}
+
+// B transposed, one tile per block
+template <int MODE>
+__global__ __launch_bounds__(256) void split_transpose_kernel(const float* __restrict__ x, int64_t n,
+                                                              const int32_t* __restrict__ exps,
+                                                              uint16_t* __restrict__ hi, uint16_t* __restrict__ lo) {
+    __shared__ float t[64][65];
+    const float s = MODE == kPrecF16x3 ? ldexpf(1.0f, exps[1]) : 1.0f;
+    split_tile<MODE>(x, n, int64_t(blockIdx.y) * 64, int64_t(blockIdx.x) * 64, s, hi, lo, t, threadIdx.x);
+}
+
+// The choice of launch_split_choice, then both BF16 planes if they are taken:
+// blockIdx.y = 0 the rows of A, 1 the tiles of B.  Every block works the choice
+// out by itself from the same products, one per thread (i, k and j spread evenly
+// by multiples of the powers of a constant); block 0 writes it down.  A product
+// that does not take the planes pays for this, so the grid is one round of large
+// blocks, each with few reads (2048 blocks of 256 threads took 18 us to end).
+constexpr int kChoiceThreads = 1024;  // and products looked at
+constexpr int kChoiceBlocks = 256;
+
+__global__ __launch_bounds__(kChoiceThreads) void split_choice_kernel(const float* __restrict__ a,
+                                                                      const float* __restrict__ b, int64_t n,
+                                                                      int64_t bdim, FormChoice ch, SplitLayout L) {
+    constexpr int kTiles = kChoiceThreads / 256;  // of B at a time
+    __shared__ float t[kTiles][64][65];
+    __shared__ int kept[kChoiceThreads / 64];
+    const int tid = threadIdx.x;
+    // multiples of 2^32 / 1.2207440846, its square and its cube
+    auto at = [&](uint32_t step) {
+        return int64_t((uint64_t(uint32_t(tid) * step + (step >> 1)) * uint64_t(bdim)) >> 32);
+    };
+    const int64_t i = at(3518319155u), k = at(2882110345u), j = at(2360945575u);
+    const uint64_t hit = __ballot(ch.na[i * ch.ld + k] * ch.nb[k * ch.ld + j] >= ch.tau);
+    if ((tid & 63) == 0) kept[tid >> 6] = __popcll(hit);
+    __syncthreads();
+    int total = 0;
+#pragma unroll
+    for (int w = 0; w < kChoiceThreads / 64; ++w) total += kept[w];
+    const bool planes =
+        total * bdim >= int64_t(ch.pairs) * kChoiceThreads && !(ch.full_fp32 && total == kChoiceThreads);
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+        if (tid == 0) *ch.form = planes ? 1 : 0;
+        for (int64_t w = tid; w < ch.clear_count; w += kChoiceThreads) ch.clear[w] = 0;
+    }
+    if (!planes) return;
+    if (blockIdx.y == 0) {
+        const f4* x4 = reinterpret_cast<const f4*>(a);
+        const int64_t step = int64_t(gridDim.x) * kChoiceThreads, count = n * n / 4;
+#pragma unroll 4
+        for (int64_t q = int64_t(blockIdx.x) * kChoiceThreads + tid; q < count; q += step)
+            split_row4<kPrecBf16>(x4, q, 1.0f, L.a_hi, nullptr);
+        return;
+    }
+    const int64_t side = n / 64, sub = tid >> 8;  // side is even: four tiles at a time come out even
+    for (int64_t e = int64_t(blockIdx.x) * kTiles; e < side * side; e += int64_t(gridDim.x) * kTiles) {
+        split_tile<kPrecBf16>(b, n, (e + sub) / side * 64, (e + sub) % side * 64, 1.0f, L.bt_hi, nullptr, t[sub],
+                              tid & 255);
+        __syncthreads();  // t is used again
+    }
+}
+
+hipError_t launch_split_choice(const float* a, const float* b, int64_t n, int64_t bdim, const FormChoice& choice,
+                               const SplitLayout& L, hipStream_t s) {
+    if (n % 128 != 0 || bdim * 64 != n || !choice.form) return hipErrorInvalidValue;
+    split_choice_kernel<<<dim3{unsigned(kChoiceBlocks), 2u, 1u}, kChoiceThreads, 0, s>>>(a, b, n, bdim, choice, L);
+    return hipGetLastError();
 }
 
 hipError_t launch_split_scales(int64_t bdim, int lv, const double* pyr_a, const double* pyr_b, int32_t* header,
