@@ -161,27 +161,29 @@ __global__ __launch_bounds__(kTileThreads, 4) void multiply_tile_kernel(
     }
 }
 
+template <int LEAF>
+hipError_t launch_tile(const float* a, const float* b, float* c, int64_t n, const double* na, const double* nb,
+                       int64_t ld, double tau, int64_t* pairs, hipStream_t s) {
+    static int scratch_state = 0;
+    const hipError_t ce = check_no_scratch(multiply_tile_kernel<LEAF>, &scratch_state);
+    if (ce != hipSuccess) return ce;
+    const int tiles = int((n + 31) / 32);
+    multiply_tile_kernel<LEAF><<<unsigned((tiles + 7) / 8 * tiles * 8), kTileThreads, 0, s>>>(
+        a, b, c, int(n), tiles, na, nb, int(ld), tau, reinterpret_cast<unsigned long long*>(pairs));
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_tile_multiply(const float* a, const float* b, float* c, int64_t n, int32_t leaf, const double* na,
                                 const double* nb, int64_t ld, double tau, int64_t* pairs, hipStream_t s) {
     if (n < 1 || n > kTileMaxN || ld > 2048) return hipErrorInvalidValue;
-    const int tiles = int((n + 31) / 32);
-    const unsigned grid = unsigned((tiles + 7) / 8 * tiles * 8);
-    auto* count = reinterpret_cast<unsigned long long*>(pairs);
     switch (leaf) {
-        case 32:
-            multiply_tile_kernel<32><<<grid, kTileThreads, 0, s>>>(a, b, c, int(n), tiles, na, nb, int(ld), tau, count);
-            break;
-        case 64:
-            multiply_tile_kernel<64><<<grid, kTileThreads, 0, s>>>(a, b, c, int(n), tiles, na, nb, int(ld), tau, count);
-            break;
-        case 128:
-            multiply_tile_kernel<128><<<grid, kTileThreads, 0, s>>>(a, b, c, int(n), tiles, na, nb, int(ld), tau, count);
-            break;
+        case 32: return launch_tile<32>(a, b, c, n, na, nb, ld, tau, pairs, s);
+        case 64: return launch_tile<64>(a, b, c, n, na, nb, ld, tau, pairs, s);
+        case 128: return launch_tile<128>(a, b, c, n, na, nb, ld, tau, pairs, s);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 }  // namespace spamm
