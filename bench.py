@@ -104,10 +104,10 @@ def parse_args():
                     help="leaf-product precision (the mask is always the FP32 inputs')")
     ap.add_argument("--form", choices=["auto", "planes", "registers"], default="auto",
                     help="reduced precision: split planes, or conversion of the FP32 inputs in the multiply (auto, "
-                         "registers: the latter, as spamm_multiply_precision)")
+                         "registers: the latter; spamm_multiply_precision picks the planes for wide bands in bf16)")
     ap.add_argument("--one-call", action="store_true",
-                    help="time spamm_multiply as one call (fp32; leaf 16 and 32, and leaf 64 and 128 up to N = 5120, "
-                         "take two launches)")
+                    help="time spamm_multiply as one call (fp32; leaf 16 and 32, and leaf 64 and 128 up to N = 5120 but "
+                         "for multiples of 128 in 2176 .. 3968, take two launches)")
     ap.add_argument("--sweep", default="1e-8,1e-4", help="other tau values timed briefly (empty: none)")
     ap.add_argument("--no-dense", action="store_true", help="skip the dense FP32 GEMM comparison")
     ap.add_argument("--no-cpu-baseline", action="store_true", help="skip timing the CPU oracle")
@@ -268,7 +268,7 @@ def main() -> int:
     # library launches on (torch's current stream, passed by the binding)
     # bracket the multiply kernel alone.
     # Reduced-precision products: the multiply converts the FP32 tiles as it
-    # loads them, as in spamm_multiply_precision (BF16: spamm_prepare_schedule,
+    # loads them (BF16: spamm_prepare_schedule,
     # spamm_execute_bf16_scheduled; FP16 hi+lo: the first stage adds the scale
     # exponents, spamm_prepare_schedule_scales, then
     # spamm_execute_f16x3_scheduled); with --form planes the first stage also
@@ -276,7 +276,6 @@ def main() -> int:
     # them.
     staged = False
     if prec != "fp32":
-        sp.prepare(a, b, tau, leaf, bufs=bufs, ws=ws)
         staged = args.form == "planes"
         if staged:
             split_buf = sp.split_buffer(n, prec, dev)

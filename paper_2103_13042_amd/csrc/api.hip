@@ -267,14 +267,14 @@ spamm_status enqueue_pyramids(const Geom& g, const float* const* x, int nmat, do
     return hip_check(spamm::launch_pyramid(pj, nmat, g.bdim, g.lv, s), "pyramid kernel");
 }
 
-spamm_status enqueue_plan(const Geom& g, const double* pa, const double* pb, double tau, bool skipped,
-                          int32_t* offsets, int32_t* klist, int64_t* pairs, void* ws, hipStream_t s) {
+spamm_status enqueue_plan(const Geom& g, const double* pa, const double* pb, double tau, int32_t* offsets,
+                          int32_t* klist, int64_t* pairs, void* ws, hipStream_t s) {
     const Layout L = make_layout(g);
     uint64_t* masks = at<uint64_t>(ws, L.masks);
     int32_t* counts = at<int32_t>(ws, L.counts);
     int32_t* bsums = at<int32_t>(ws, L.bsums);
     int32_t* boffs = at<int32_t>(ws, L.boffs);
-    spamm_status st = hip_check(spamm::launch_plan_mask(pa, pb, g.bdim, g.lv, tau, skipped, masks, counts, bsums, s),
+    spamm_status st = hip_check(spamm::launch_plan_mask(pa, pb, g.bdim, g.lv, tau, masks, counts, bsums, s),
                                 "plan mask kernel");
     if (st != SPAMM_OK) return st;
     st = hip_check(spamm::launch_plan_scan(bsums, g.bdim * g.nwords, boffs, offsets, g.ntiles, pairs, s),
@@ -297,7 +297,7 @@ spamm_status enqueue_prepare(const Geom& g, const float* a, const float* b, doub
                                        fused ? spamm::plan_macro_clear_words(g.bdim) : 0, !fused);
     if (st != SPAMM_OK) return st;
     if (!fused) {
-        if ((st = enqueue_plan(g, pa, pb, tau, false, offsets, klist, pairs, ws, s)) != SPAMM_OK) return st;
+        if ((st = enqueue_plan(g, pa, pb, tau, offsets, klist, pairs, ws, s)) != SPAMM_OK) return st;
         return schedule ? enqueue_schedule(g, offsets, klist, ws, s) : SPAMM_OK;
     }
     const spamm::MacroSchedule ms = macro_schedule(L, ws);
@@ -491,7 +491,7 @@ spamm_status spamm_plan(const double* pyr_a, const double* pyr_b, int64_t n, int
     if (klist_capacity < g.ntiles * g.bdim)
         return fail(SPAMM_ENOSPACE, "klist capacity %lld < bdim^3 = %lld", (long long)klist_capacity,
                     (long long)(g.ntiles * g.bdim));
-    return enqueue_plan(g, pyr_a, pyr_b, tau, false, offsets, klist, pairs, workspace, static_cast<hipStream_t>(stream));
+    return enqueue_plan(g, pyr_a, pyr_b, tau, offsets, klist, pairs, workspace, static_cast<hipStream_t>(stream));
 }
 
 spamm_status spamm_execute(const float* a, const float* b, int64_t n, int32_t leaf, const int32_t* offsets,
@@ -572,11 +572,10 @@ spamm_status spamm_prepare_schedule(const float* a, const float* b, int64_t n, d
 }
 
 namespace {
-// The leaf norm pass (which also clears the pair counter), then the threshold
-// test and the multiply in one launch.
-// The leaf norms of a and b into the workspace pyramids (norms[2]), *pairs = 0.
-spamm_status enqueue_leaf_norms(const Geom& g, const float* a, const float* b, int64_t* pairs, double** norms,
-                                void* ws, hipStream_t s) {
+// The leaf norms of a and b into the workspace pyramids (norms[2]), with `sums`
+// also their squares, which a pyramid is built from; *pairs = 0.
+spamm_status enqueue_leaf_norms(const Geom& g, const float* a, const float* b, int64_t* pairs, bool sums,
+                                double** norms, void* ws, hipStream_t s) {
     const Layout L = make_layout(g);
     const int64_t leaf_level = spamm::level_offset(g.lv);
     spamm::NormJob nj{};
@@ -585,17 +584,19 @@ spamm_status enqueue_leaf_norms(const Geom& g, const float* a, const float* b, i
     const float* xs[2] = {a, b};
     for (int m = 0; m < 2; ++m) {
         nj.x[m] = xs[m];
-        nj.sumsq[m] = at<double>(ws, L.spyr[m]) + leaf_level;
+        nj.sumsq[m] = sums ? at<double>(ws, L.spyr[m]) + leaf_level : nullptr;
         nj.norms[m] = norms[m] = at<double>(ws, L.pyr[m]) + leaf_level;
     }
     const bool vec = (g.n % 4) == 0 && aligned16(a) && aligned16(b);
     return hip_check(spamm::launch_leaf_norms(nj, 2, g.n, g.leaf, vec, s), "leaf norm kernel");
 }
 
+// The leaf norm pass (which also clears the pair counter), then the threshold
+// test and the multiply in one launch.
 spamm_status enqueue_direct(const Geom& g, const float* a, const float* b, double tau, float* c, int64_t* pairs,
                            void* ws, hipStream_t s) {
     double* norms[2];
-    const spamm_status st = enqueue_leaf_norms(g, a, b, pairs, norms, ws, s);
+    const spamm_status st = enqueue_leaf_norms(g, a, b, pairs, false, norms, ws, s);
     if (st != SPAMM_OK) return st;
     if (g.leaf >= 32 && g.n <= spamm::kTileMaxN)
         return hip_check(spamm::launch_tile_multiply(a, b, c, g.n, g.leaf, norms[0], norms[1], g.side, tau, pairs, s),
@@ -639,8 +640,7 @@ spamm_status enqueue_planes(const Geom& g, const float* a, const float* b, spamm
                                    {at<double>(ws, L.pyr[0]), at<double>(ws, L.pyr[1])}};
         hipError_t e = spamm::launch_pyramid(pj, 2, g.bdim, g.lv, s, run);
         if (e == hipSuccess)
-            e = spamm::launch_plan_mask(pj.pyr[0], pj.pyr[1], g.bdim, g.lv, choice.tau, false, masks, counts, bsums, s,
-                                        run);
+            e = spamm::launch_plan_mask(pj.pyr[0], pj.pyr[1], g.bdim, g.lv, choice.tau, masks, counts, bsums, s, run);
         if (e == hipSuccess)
             e = spamm::launch_plan_scan(bsums, g.bdim * g.nwords, boffs, offsets, g.ntiles, pairs, s, run);
         if (e == hipSuccess) e = spamm::launch_plan_fill(masks, counts, boffs, g.bdim, offsets, klist, s, run);
@@ -883,13 +883,17 @@ spamm_status spamm_multiply_precision(const float* a, const float* b, int64_t n,
             overlaps(split, kSplitHeaderBytes, c, mbytes))
             return fail(SPAMM_EINVAL, "header overlaps a, b or c");
     }
-    double* norms[2];
-    if ((st = enqueue_leaf_norms(g, a, b, np, norms, workspace, s)) != SPAMM_OK) return st;
     // BF16 with room for the planes (at the alignment that spamm_split asks for):
     // the device picks between them and the FP32 inputs; both give the same C
     const int32_t* form = nullptr;
     spamm::FormChoice choice{};
-    if (!f16 && planes && (reinterpret_cast<uintptr_t>(split) & 255u) == 0 && spamm::bf16_choice(n, g.bdim, &choice)) {
+    const bool choose = !f16 && planes && (reinterpret_cast<uintptr_t>(split) & 255u) == 0 &&
+                        spamm::bf16_choice(n, g.bdim, &choice);
+    double* norms[2];
+    if ((st = enqueue_leaf_norms(g, a, b, np, choose && g.bdim > spamm::kPlanMacroMaxBdim, norms, workspace, s)) !=
+        SPAMM_OK)
+        return st;
+    if (choose) {
         choice.na = norms[0];
         choice.nb = norms[1];
         choice.ld = g.side;

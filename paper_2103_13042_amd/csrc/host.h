@@ -76,10 +76,9 @@ spamm_status enqueue_pyramids(const Geom& g, const float* const* x, int nmat, do
 // multiply schedule, the plan and schedule then coming from one launch.
 spamm_status enqueue_prepare(const Geom& g, const float* a, const float* b, double tau, int32_t* offsets,
                              int32_t* klist, int64_t* pairs, void* ws, hipStream_t s, bool schedule);
-// Plan of the kept triples (norm product >= tau), or with `skipped` of the
-// triples SpAMM drops (norm product < tau).
-spamm_status enqueue_plan(const Geom& g, const double* pa, const double* pb, double tau, bool skipped,
-                          int32_t* offsets, int32_t* klist, int64_t* pairs, void* ws, hipStream_t s);
+// Plan of the kept triples (norm product >= tau).
+spamm_status enqueue_plan(const Geom& g, const double* pa, const double* pb, double tau, int32_t* offsets,
+                          int32_t* klist, int64_t* pairs, void* ws, hipStream_t s);
 // Multiply of the pairs of a plan into c (every tile of c is written): the
 // schedule the multiply kernel streams (workspace), then the multiply kernel.
 // The macro-tile schedule arrays of the workspace at ws.

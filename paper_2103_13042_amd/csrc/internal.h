@@ -41,8 +41,7 @@ hipError_t launch_pyramid(const PyramidJob& job, int nmat, int64_t bdim, int lv,
 
 // Plan: per output tile, the ballot bitmap of kept k (words of 64) and its
 // count V; per block of 64 tiles (i, 64*jb ..) the sum of V (block b = i*nw + jb).
-// With `skipped` the bitmaps select the dropped triples instead.
-hipError_t launch_plan_mask(const double* pyr_a, const double* pyr_b, int64_t bdim, int lv, double tau, bool skipped,
+hipError_t launch_plan_mask(const double* pyr_a, const double* pyr_b, int64_t bdim, int lv, double tau,
                             uint64_t* masks, int32_t* counts, int32_t* block_sums, hipStream_t s,
                             const int32_t* run = nullptr);
 // Plan counts only (no bitmaps): per block of 64 tiles the number of kept triples.
@@ -205,18 +204,16 @@ struct MlpLayout {
     int64_t w3 = b2 + kMlpHid;
     int64_t b3 = w3 + kMlpHid;
     int64_t count = b3 + 1;
-    // activations: Z1 H1 Z2 H2 D1 D2 [B][128] each, then y, dy [B]
-    int64_t z1 = 0, h1 = 0, z2 = 0, h2 = 0, d1 = 0, d2 = 0, y = 0, dy = 0, acts_total = 0;
+    // activations: H1 H2 D1 D2 [B][128] each, then y, dy [B]
+    int64_t h1 = 0, h2 = 0, d1 = 0, d2 = 0, y = 0, dy = 0, acts_total = 0;
     static MlpLayout acts(int batch) {
         MlpLayout L{};
         const int64_t bh = int64_t(batch) * kMlpHid;
-        L.z1 = 0;
-        L.h1 = bh;
-        L.z2 = 2 * bh;
-        L.h2 = 3 * bh;
-        L.d1 = 4 * bh;
-        L.d2 = 5 * bh;
-        L.y = 6 * bh;
+        L.h1 = 0;
+        L.h2 = bh;
+        L.d1 = 2 * bh;
+        L.d2 = 3 * bh;
+        L.y = 4 * bh;
         L.dy = L.y + batch;
         L.acts_total = L.dy + batch;
         return L;

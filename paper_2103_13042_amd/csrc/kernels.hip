@@ -302,13 +302,10 @@ hipError_t launch_pyramid(const PyramidJob& job, int nmat, int64_t bdim, int lv,
 // chunk is settled for all 64 tiles at once (uniform branch).  Otherwise the
 // chunk's 64 x 64 block of B leaf norms is staged in LDS, each lane takes one
 // k, and one ballot per tile gives the 64-bit bitmap of selected k.
-//
-// SKIPPED selects the complement: the triples whose product is below tau, the
-// pairs SpAMM drops (their product sum is the error matrix AB - SpAMM).
 
 constexpr int kPlanThreads = 256;
 
-template <bool MASKS, bool SKIPPED>
+template <bool MASKS>
 __device__ __forceinline__ void plan_mask_block(const double* __restrict__ pyr_a, const double* __restrict__ pyr_b,
                                                 int64_t bdim, int lv, double tau, uint64_t* __restrict__ masks,
                                                 int32_t* __restrict__ counts, int32_t* __restrict__ block_sums,
@@ -335,15 +332,12 @@ __device__ __forceinline__ void plan_mask_block(const double* __restrict__ pyr_a
             below = !(pyr_a[0] * pyr_b[0] >= tau);
         }
         if (below) {
-            // every real triple of the chunk is dropped: none selected, or all
-            // of them in the complement
-            const int64_t k = int64_t(c) * 64 + lane;
+            if (MASKS && lane == 0) {
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int64_t j = j0 + wave + 4 * u;
-                const uint64_t mk = SKIPPED ? __ballot(k < bdim && j < bdim) : 0ull;
-                if (MASKS && lane == 0 && j < bdim) masks[(i * bdim + j) * nw + c] = mk;
-                cnt[u] += __popcll(mk);
+                for (int u = 0; u < 16; ++u) {
+                    const int64_t j = j0 + wave + 4 * u;
+                    if (j < bdim) masks[(i * bdim + j) * nw + c] = 0;
+                }
             }
             continue;
         }
@@ -369,7 +363,7 @@ __device__ __forceinline__ void plan_mask_block(const double* __restrict__ pyr_a
             const int jj = wave + 4 * u;
             const int64_t j = j0 + jj;
             const double p = a * sb[lane][jj];
-            const bool bit = (SKIPPED ? !(p >= tau) : (p >= tau)) && (k < bdim) && (j < bdim);
+            const bool bit = p >= tau && k < bdim && j < bdim;
             const uint64_t mk = __ballot(bit);
             if (MASKS && lane == 0 && j < bdim) masks[(i * bdim + j) * nw + c] = mk;
             cnt[u] += __popcll(mk);
@@ -389,7 +383,7 @@ __device__ __forceinline__ void plan_mask_block(const double* __restrict__ pyr_a
     if (threadIdx.x == 0) block_sums[i * nw + jb] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
 }
 
-template <bool MASKS, bool SKIPPED>
+template <bool MASKS>
 __global__ __launch_bounds__(kPlanThreads) void plan_mask_kernel(const double* __restrict__ pyr_a,
                                                                  const double* __restrict__ pyr_b, int64_t bdim,
                                                                  int lv, double tau, uint64_t* __restrict__ masks,
@@ -397,27 +391,22 @@ __global__ __launch_bounds__(kPlanThreads) void plan_mask_kernel(const double* _
                                                                  int32_t* __restrict__ block_sums,
                                                                  const int32_t* run) {
     if (closed(run)) return;
-    plan_mask_block<MASKS, SKIPPED>(pyr_a, pyr_b, bdim, lv, tau, masks, counts, block_sums, blockIdx.x, blockIdx.y);
+    plan_mask_block<MASKS>(pyr_a, pyr_b, bdim, lv, tau, masks, counts, block_sums, blockIdx.x, blockIdx.y);
 }
 
-hipError_t launch_plan_mask(const double* pyr_a, const double* pyr_b, int64_t bdim, int lv, double tau, bool skipped,
+hipError_t launch_plan_mask(const double* pyr_a, const double* pyr_b, int64_t bdim, int lv, double tau,
                             uint64_t* masks, int32_t* counts, int32_t* block_sums, hipStream_t s,
                             const int32_t* run) {
     dim3 grid{unsigned((bdim + 63) / 64), unsigned(bdim), 1u};
-    if (skipped)
-        plan_mask_kernel<true, true><<<grid, kPlanThreads, 0, s>>>(pyr_a, pyr_b, bdim, lv, tau, masks, counts,
-                                                                   block_sums, run);
-    else
-        plan_mask_kernel<true, false><<<grid, kPlanThreads, 0, s>>>(pyr_a, pyr_b, bdim, lv, tau, masks, counts,
-                                                                    block_sums, run);
+    plan_mask_kernel<true><<<grid, kPlanThreads, 0, s>>>(pyr_a, pyr_b, bdim, lv, tau, masks, counts, block_sums, run);
     return hipGetLastError();
 }
 
 hipError_t launch_plan_count(const double* pyr_a, const double* pyr_b, int64_t bdim, int lv, double tau,
                              int32_t* block_sums, hipStream_t s) {
     dim3 grid{unsigned((bdim + 63) / 64), unsigned(bdim), 1u};
-    plan_mask_kernel<false, false><<<grid, kPlanThreads, 0, s>>>(pyr_a, pyr_b, bdim, lv, tau, nullptr, nullptr,
-                                                                 block_sums, nullptr);
+    plan_mask_kernel<false><<<grid, kPlanThreads, 0, s>>>(pyr_a, pyr_b, bdim, lv, tau, nullptr, nullptr, block_sums,
+                                                          nullptr);
     return hipGetLastError();
 }
 
