@@ -108,9 +108,13 @@ spamm_status spamm_error_for_tau(const float* a, const float* b, int64_t n, int3
  *   target        relative error, > 0.
  *   max_evals     cap on the thresholds evaluated (>= 1); when reached the best
  *                 passing product so far is returned.
- *   tau_out, err_out (spamm_error_for_tau's error at tau_out), pairs_out (kept
- *   triples at tau_out), evals_out (thresholds evaluated)
+ *   tau_out, err_out (error at tau_out), pairs_out (kept triples at tau_out),
+ *   evals_out (thresholds evaluated)
  *                 HOST outputs (all but tau_out may be NULL).
+ * E is carried over from one passing threshold to the next, so err_out agrees
+ * with spamm_error_for_tau's error to the rounding of its FP32 sums; an error
+ * within 1e-5 of the target is that very number, so that both agree on whether
+ * tau_out meets the target.
  * Synchronous.  Other arguments as spamm_error_for_tau. */
 spamm_status spamm_search_tau_for_error(const float* a, const float* b, int64_t n, int32_t leaf, double target,
                                         double tau_guess, int32_t max_evals, const double* pyr_a,

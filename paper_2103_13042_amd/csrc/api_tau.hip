@@ -118,10 +118,9 @@ struct Probe {
 //
 // Such an E holds the same products as one formed from nothing, added in another
 // order, so its error is spamm_error_for_tau's to rounding only (1.7e-7 of it at
-// most on 150 problems of N = 300 .. 3000).  What is decided and returned is
-// spamm_error_for_tau's error all the same: an error within kNear of the target
-// is formed again from nothing, so that the outcome does not depend on the
-// thresholds tried before.  With `whole` every error is formed from nothing.
+// most on 150 problems of N = 300 .. 3000, 7e-8 on 32 of 8192).  An error within
+// kNear of the target is formed again from nothing, so that what passes does not
+// depend on the thresholds tried before.
 class Search {
 public:
     struct Snap {
@@ -129,7 +128,7 @@ public:
         int64_t kept;     // how many products are >= x
     };
 
-    Search(const Probe& p, double target, bool whole) : p_(p), target_(target), whole_(whole) {}
+    Search(const Probe& p, double target) : p_(p), target_(target) {}
 
     spamm_status start(double x, Snap* out, double* most) {
         spamm_status st = p_.sort();
@@ -146,11 +145,10 @@ public:
         return ask(&x, 1, nullptr, out, nullptr);
     }
 
-    // error at the product t, with the queries that may follow; *whole: whether
-    // it is that of an E formed from nothing
-    spamm_status eval(double t, const double* next, int count, bool* pass, double* err, bool* whole) {
+    // error at the product t, with the queries that may follow
+    spamm_status eval(double t, const double* next, int count, bool* pass, double* err) {
         spamm_status st;
-        if (pending_ && !whole_) {  // the product evaluated last passed: its E becomes the base
+        if (pending_) {  // the product evaluated last passed: its E becomes the base
             spamm::BandJob keep = base_;
             keep.store = 1;
             if ((st = p_.dropped(passed_, keep)) != SPAMM_OK) return st;
@@ -162,11 +160,9 @@ public:
         double esq = 0.0;
         if ((st = ask(next, count, &esq, nullptr, nullptr)) != SPAMM_OK) return st;
         *err = std::sqrt(esq / p_.ab_sumsq);
-        *whole = !base_.has_base;
-        if (!*whole && std::fabs(*err - target_) < kNear * target_) {
-            if ((st = p_.error(t, false, err, nullptr)) != SPAMM_OK) return st;
-            *whole = true;
-        }
+        if (base_.has_base && std::fabs(*err - target_) < kNear * target_ &&
+            (st = p_.error(t, false, err, nullptr)) != SPAMM_OK)
+            return st;
         *pass = *err <= target_;
         if (*pass) {
             pending_ = true;
@@ -198,7 +194,6 @@ private:
     static constexpr double kNear = 1e-5;
     const Probe& p_;
     double target_;
-    bool whole_;
     Snap known_[kKnown] = {};
     int at_ = 0;
     spamm::BandJob base_;
@@ -225,113 +220,6 @@ spamm_status make_probe(const float* a, const float* b, int64_t n, int32_t leaf,
     p->ws = ws;
     p->s = static_cast<hipStream_t>(stream);
     return p->bind();
-}
-
-struct Found {
-    double tau, err;
-    bool whole;  // err is that of an E formed from nothing
-    int64_t kept;
-    int evals;
-};
-
-// The search of spamm_search_tau_for_error.
-spamm_status search_products(const Probe& p, double target, double tau_guess, int32_t max_evals, bool whole,
-                             Found* out) {
-    spamm_status st;
-    int evals = 0;
-    double pmax = 0.0;
-    Search find(p, target, whole);
-    Search::Snap low{};
-    if ((st = find.start(DBL_TRUE_MIN, &low, &pmax)) != SPAMM_OK) return st;
-    const double pmin = low.least;
-    double lo = 0.0, lo_err = 0.0;  // passing threshold (a product) and its error
-    bool lo_whole = true;
-    int64_t kept = low.kept;
-    if (std::isinf(pmin)) {
-        // every norm product is zero: SpAMM is exactly AB for every tau, and
-        // the largest product is 0
-        lo = 0.0;
-        if ((st = p.kept(lo, &kept)) != SPAMM_OK) return st;
-    } else {
-        // invariant: lo is a product with error <= target (the smallest positive
-        // product keeps every nonzero pair: error 0); hi is a threshold whose
-        // error exceeds the target, +inf standing for "above every product"
-        lo = pmin;
-        double hi = kInf;
-        bool pass = false, bracket = true, from_nothing = true;
-        double e = 0.0;
-        Search::Snap c{};
-        auto middle = [&](double l, double h) { return std::isinf(h) ? pmax : std::sqrt(l) * std::sqrt(h); };
-        auto eval = [&]() -> spamm_status {  // at c, with what may be asked next
-            const double next[3] = {std::nextafter(c.least, kInf), bracket ? c.least * 4.0 : middle(c.least, hi),
-                                    bracket ? c.least / 4.0 : middle(lo, c.least)};
-            const spamm_status r = find.eval(c.least, next, 3, &pass, &e, &from_nothing);
-            ++evals;
-            return r;
-        };
-        auto accept = [&]() {
-            lo = c.least;
-            lo_err = e;
-            lo_whole = from_nothing;
-            kept = c.kept;
-        };
-        if (tau_guess > 0.0 && evals < max_evals) {
-            const double g0 = tau_guess < pmin ? pmin : (tau_guess > pmax ? pmax : tau_guess);
-            if ((st = find.snap(g0, &c)) != SPAMM_OK) return st;
-            if ((st = eval()) != SPAMM_OK) return st;
-            if (pass) {
-                accept();
-                while (evals < max_evals) {  // grow upwards
-                    const double up = lo * 4.0;
-                    if (up > pmax) break;
-                    if ((st = find.snap(up, &c)) != SPAMM_OK) return st;
-                    if ((st = eval()) != SPAMM_OK) return st;
-                    if (!pass) {
-                        hi = c.least;
-                        break;
-                    }
-                    accept();
-                }
-            } else {
-                hi = c.least;
-                while (evals < max_evals) {  // grow downwards
-                    const double down = hi / 4.0;
-                    if (down <= pmin) break;
-                    if ((st = find.snap(down, &c)) != SPAMM_OK) return st;
-                    if (c.least >= hi) {  // no product in [down, hi): same mask as hi
-                        hi = down;
-                        continue;
-                    }
-                    if ((st = eval()) != SPAMM_OK) return st;
-                    if (pass) {
-                        accept();
-                        break;
-                    }
-                    hi = c.least;
-                }
-            }
-        }
-        bracket = false;
-        for (int guard = 0; evals < max_evals && guard < 8192; ++guard) {
-            Search::Snap next{};  // the smallest product above lo
-            if ((st = find.snap(std::nextafter(lo, kInf), &next)) != SPAMM_OK) return st;
-            if (next.least >= hi) break;  // lo is the largest passing product
-            double mid = middle(lo, hi);
-            if (!(mid > lo)) mid = next.least;
-            if ((st = find.snap(mid, &c)) != SPAMM_OK) return st;
-            if (c.least >= hi) {  // no product in [mid, hi): mid fails like hi
-                hi = mid;
-                continue;
-            }
-            if ((st = eval()) != SPAMM_OK) return st;
-            if (pass)
-                accept();
-            else
-                hi = c.least;
-        }
-    }
-    *out = {lo, lo_err, lo_whole, kept, evals};
-    return SPAMM_OK;
 }
 
 }  // namespace
@@ -428,20 +316,100 @@ spamm_status spamm_search_tau_for_error(const float* a, const float* b, int64_t 
     if (max_evals < 1) return fail(SPAMM_EINVAL, "max_evals must be >= 1");
     if (std::isnan(tau_guess)) return fail(SPAMM_EINVAL, "tau_guess is NaN");
 
-    Found f;
-    if ((st = search_products(p, target, tau_guess, max_evals, false, &f)) != SPAMM_OK) return st;
-    if (!f.whole) {
-        // the error that spamm_error_for_tau gives at the threshold found
-        if ((st = p.error(f.tau, false, &f.err, nullptr)) != SPAMM_OK) return st;
-        // further apart than kNear: products of both signs that cancel
-        if (!(f.err <= target) &&
-            (st = search_products(p, target, tau_guess, max_evals, true, &f)) != SPAMM_OK)
-            return st;
+    int evals = 0;
+    double pmax = 0.0;
+    Search find(p, target);
+    Search::Snap low{};
+    if ((st = find.start(DBL_TRUE_MIN, &low, &pmax)) != SPAMM_OK) return st;
+    const double pmin = low.least;
+    double lo = 0.0, lo_err = 0.0;  // passing threshold (a product) and its error
+    int64_t kept = low.kept;
+    if (std::isinf(pmin)) {
+        // every norm product is zero: SpAMM is exactly AB for every tau, and
+        // the largest product is 0
+        lo = 0.0;
+        if ((st = p.kept(lo, &kept)) != SPAMM_OK) return st;
+    } else {
+        // invariant: lo is a product with error <= target (the smallest positive
+        // product keeps every nonzero pair: error 0); hi is a threshold whose
+        // error exceeds the target, +inf standing for "above every product"
+        lo = pmin;
+        double hi = kInf;
+        bool pass = false, bracket = true;
+        double e = 0.0;
+        Search::Snap c{};
+        auto middle = [&](double l, double h) { return std::isinf(h) ? pmax : std::sqrt(l) * std::sqrt(h); };
+        auto eval = [&]() -> spamm_status {  // at c, with what may be asked next
+            const double next[3] = {std::nextafter(c.least, kInf), bracket ? c.least * 4.0 : middle(c.least, hi),
+                                    bracket ? c.least / 4.0 : middle(lo, c.least)};
+            const spamm_status r = find.eval(c.least, next, 3, &pass, &e);
+            ++evals;
+            return r;
+        };
+        auto accept = [&]() {
+            lo = c.least;
+            lo_err = e;
+            kept = c.kept;
+        };
+        if (tau_guess > 0.0 && evals < max_evals) {
+            const double g0 = tau_guess < pmin ? pmin : (tau_guess > pmax ? pmax : tau_guess);
+            if ((st = find.snap(g0, &c)) != SPAMM_OK) return st;
+            if ((st = eval()) != SPAMM_OK) return st;
+            if (pass) {
+                accept();
+                while (evals < max_evals) {  // grow upwards
+                    const double up = lo * 4.0;
+                    if (up > pmax) break;
+                    if ((st = find.snap(up, &c)) != SPAMM_OK) return st;
+                    if ((st = eval()) != SPAMM_OK) return st;
+                    if (!pass) {
+                        hi = c.least;
+                        break;
+                    }
+                    accept();
+                }
+            } else {
+                hi = c.least;
+                while (evals < max_evals) {  // grow downwards
+                    const double down = hi / 4.0;
+                    if (down <= pmin) break;
+                    if ((st = find.snap(down, &c)) != SPAMM_OK) return st;
+                    if (c.least >= hi) {  // no product in [down, hi): same mask as hi
+                        hi = down;
+                        continue;
+                    }
+                    if ((st = eval()) != SPAMM_OK) return st;
+                    if (pass) {
+                        accept();
+                        break;
+                    }
+                    hi = c.least;
+                }
+            }
+        }
+        bracket = false;
+        for (int guard = 0; evals < max_evals && guard < 8192; ++guard) {
+            Search::Snap next{};  // the smallest product above lo
+            if ((st = find.snap(std::nextafter(lo, kInf), &next)) != SPAMM_OK) return st;
+            if (next.least >= hi) break;  // lo is the largest passing product
+            double mid = middle(lo, hi);
+            if (!(mid > lo)) mid = next.least;
+            if ((st = find.snap(mid, &c)) != SPAMM_OK) return st;
+            if (c.least >= hi) {  // no product in [mid, hi): mid fails like hi
+                hi = mid;
+                continue;
+            }
+            if ((st = eval()) != SPAMM_OK) return st;
+            if (pass)
+                accept();
+            else
+                hi = c.least;
+        }
     }
-    *tau_out = f.tau;
-    if (err_out) *err_out = f.err;
-    if (pairs_out) *pairs_out = f.kept;
-    if (evals_out) *evals_out = f.evals;
+    *tau_out = lo;
+    if (err_out) *err_out = lo_err;
+    if (pairs_out) *pairs_out = kept;
+    if (evals_out) *evals_out = evals;
     return SPAMM_OK;
 }
 

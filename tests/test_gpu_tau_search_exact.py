@@ -1,6 +1,7 @@
-"""The search for an error target decides and returns spamm_error_for_tau's error,
-whatever thresholds it tried before: err_out is that number, a target equal to
-it finds the same threshold again, and one unit below it a smaller one."""
+"""The search for an error target decides by spamm_error_for_tau's error, whatever
+thresholds it tried before: err_out is that number to the rounding of E's FP32
+sums, a target equal to it finds the same threshold again, and one unit below
+it a smaller one."""
 
 from __future__ import annotations
 
@@ -40,16 +41,19 @@ def test_error_of_the_search_is_error_for_tau(n, leaf, alpha, signed):
         if err == 0.0:  # the smallest product, where nothing but zeros is dropped
             continue
         same, dropped = sp.error_for_tau(a, b, tau, leaf, pa, pb, ab)
-        assert err == same and err <= target
+        # two FP32 sums of the same products, of their magnitudes where signs differ
+        size = sp.error_for_tau(a.abs(), b.abs(), tau, leaf, pa, pb, ab)[0]
+        assert abs(err - same) <= 2 * n * 2.0**-24 / (1 - n * 2.0**-24) * size
+        assert err <= target and same <= target
         assert pairs + dropped == sp.bdim(n, leaf) ** 3
         if signed:
             continue  # the error need not grow with tau
-        again = sp.search_tau_for_error(a, b, leaf, err, pa, pb, ab)
-        assert again[:3] == (tau, err, pairs)
-        seeded = sp.search_tau_for_error(a, b, leaf, err, pa, pb, ab, guess=3.0 * tau)
-        assert seeded[:3] == (tau, err, pairs)
-        below = sp.search_tau_for_error(a, b, leaf, math.nextafter(err, 0.0), pa, pb, ab)
-        assert below[0] < tau and below[1] < err
+        again = sp.search_tau_for_error(a, b, leaf, same, pa, pb, ab)
+        assert again[:3] == (tau, same, pairs)
+        seeded = sp.search_tau_for_error(a, b, leaf, same, pa, pb, ab, guess=3.0 * tau)
+        assert seeded[:3] == (tau, same, pairs)
+        below = sp.search_tau_for_error(a, b, leaf, math.nextafter(same, 0.0), pa, pb, ab)
+        assert below[0] < tau and below[1] < same
         if ladder is not None:  # every product, tried one by one
             above = ladder[ladder > tau]
             assert above.size == 0 or sp.error_for_tau(a, b, float(above[0]), leaf, pa, pb, ab)[0] > target
