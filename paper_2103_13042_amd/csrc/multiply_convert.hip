@@ -25,9 +25,8 @@
 // One call, F16X3: N = 16384, decay 0.01, tau 1e-6 2,000 -> 1,261 us (314 of it the
 // norms); 1024, 0.0126 122 -> 46; 4096, 0.0126 299 -> 170; 12800, 0.0126 1,090 ->
 // 759.  BF16: 16384 1,546 -> 1,196; 1024 85 -> 36; 2816, 0.0126 127 -> 94.  With
-// every pair kept, N = 8192: F16X3 3,650 -> 2,620, BF16 2,300 -> 1,890; BF16 at N =
-// 10112 and 10368 is 6 and 10 % behind planes converted first, which halve the
-// bytes of its loads, 10240 equal, 12288 5 % ahead.
+// every pair kept, N = 8192: F16X3 3,650 -> 2,620, BF16 2,300 -> 1,890.
+// Wide bands in BF16 go by planes where the caller has room for them (bf16_choice).
 // hi and lo by mixed-precision FMAs, two instructions an element instead of three,
 // measured 2 to 10 % slower.
 #include <hip/hip_runtime.h>
