@@ -107,7 +107,7 @@ def parse_args():
                          "registers: the latter; spamm_multiply_precision picks the planes for wide bands in bf16)")
     ap.add_argument("--one-call", action="store_true",
                     help="time spamm_multiply as one call (fp32; leaf 16 and 32, and leaf 64 and 128 up to N = 5120 but "
-                         "for multiples of 128 in 2176 .. 3968, take two launches)")
+                         "for multiples of 128 from 2176 on (leaf 64: to 3968), take two launches)")
     ap.add_argument("--sweep", default="1e-8,1e-4", help="other tau values timed briefly (empty: none)")
     ap.add_argument("--no-dense", action="store_true", help="skip the dense FP32 GEMM comparison")
     ap.add_argument("--no-cpu-baseline", action="store_true", help="skip timing the CPU oracle")

@@ -114,14 +114,17 @@ hipError_t launch_small_multiply16(const float* a, const float* b, float* c, int
 //    3584: 69, 354, 647 against 65, 380, 718): the blocks gain on narrow bands, but
 //    lose up to a third on wide ones (2688, decay 0.0065: 301 against 397);
 //  to 5120: blocks (4096: 62, 467, 943 against 78, 428, 890; 5120: 96, 616, 1547
-//    against 119, 584, 1448), and below 4096 at ragged n, where macro tiles at the
-//    edge cost more (2500: 43, 237, 321 against 57, 226, 294; 3001: 46, 325, 471 against
-//    66, 296, 449).
+//    against 119, 584, 1448), but at leaf 128, whose macro tiles have no idle quarter,
+//    they stay at multiples of 128 (4096: 94, 487, 920 against 81, 533, 1002, a tenth of the
+//    tiles at random 173 against 200);
+//  to 5120, ragged n: blocks, macro tiles at the edge cost more (2500: 43, 237, 321
+//    against 57, 226, 294; 3001: 46, 325, 471 against 66, 296, 449).
 constexpr int64_t kBlockCoarseFullN = 2048, kBlockCoarseRoundsN = 4096, kBlockCoarseMaxN = 5120;
 inline bool block_product(int64_t n, int32_t leaf) {
     if (leaf == 16 || leaf == 32) return true;
     if (leaf != 64 && leaf != 128) return false;
-    return n <= kBlockCoarseFullN || (n <= kBlockCoarseMaxN && (n >= kBlockCoarseRoundsN || n % 128 != 0));
+    return n <= kBlockCoarseFullN ||
+           (n <= kBlockCoarseMaxN && (n % 128 != 0 || (leaf == 64 && n >= kBlockCoarseRoundsN)));
 }
 hipError_t launch_block_test(const float* a, const float* b, float* c, int64_t n, int32_t leaf, int64_t bdim,
                              const double* na, const double* nb, int64_t ld, double tau, int64_t* pairs,

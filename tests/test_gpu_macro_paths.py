@@ -55,11 +55,11 @@ def staged(a, b, tau, leaf, *, scheduled, c=None):
     return run(a, b, leaf, offsets, klist, c=c), int(pairs.item())
 
 
-@pytest.mark.parametrize("leaf", [64, 128])
-@pytest.mark.parametrize("n", [2176, 2688, 3968])
+@pytest.mark.parametrize("n,leaf", [(2176, 64), (2688, 64), (3968, 64), (2176, 128), (3968, 128), (4096, 128),
+                                    (5120, 128)])
 def test_one_call_between_the_block_ranges_runs_on_macro_tiles(n, leaf):
-    """Multiples of 128 between 2048 and 4096: one call is the staged calls, sum
-    for sum, at a narrow band and with every pair kept."""
+    """Multiples of 128 above 2048 (leaf 64: to 3968): one call is the staged calls,
+    sum for sum, at a narrow band and with every pair kept."""
     for alpha, tau in ((0.05, 1e-6), (0.01, 0.0)):
         a, b = (inputs.exp_decay_torch(n, alpha, s, DEV) for s in (21, 22))
         c, pairs = sp.multiply(a, b, tau, leaf)
