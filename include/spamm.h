@@ -285,7 +285,7 @@ spamm_status spamm_prepare_split(const float* a, const float* b, int64_t n, doub
  * exponents into the first 256 bytes of `split` (spamm_split_scales), and one
  * multiply launch that tests the products on the norms and converts A and B as
  * it loads them; no plan is formed and the planes of `split` are not written.
- * BF16 from n = 6400 with a 256-byte aligned split of at least
+ * BF16 from n = 4352 with a 256-byte aligned split of at least
  * spamm_split_bytes: the device picks, from an estimate of the kept share,
  * between that and the planes (as spamm_split writes them) with a plan and
  * their multiply.  Either way C is bitwise the C of spamm_prepare + spamm_split +

@@ -268,9 +268,10 @@ hipError_t launch_lowp_multiply(const SplitLayout& L, float* c, int64_t n, int64
                                 const int32_t* run = nullptr);
 
 // BF16, one call, a caller with room for planes: which form multiplies is picked
-// on the device from the leaf norms na, nb (row stride ld).  The planes are
-// taken from `pairs` kept pairs per output tile on average (an estimate from 1024
-// products), unless every one is kept and full_fp32 is set.  launch_split_choice
+// on the device from the leaf norms na, nb (row stride ld).  With V the kept pairs
+// per output tile and U the k that any of a 2x2 block of tiles keeps, both
+// estimated from 1024 such blocks and k, the planes are taken if 4 U - 3 V >=
+// weight, unless every pair is kept and full_fp32 is set.  launch_split_choice
 // writes *form (1: planes, 0: FP32 inputs), the planes if they are taken, and
 // zeros to clear_count words at clear.  bf16_choice: whether there is a choice
 // at this size, and its constants (multiply_convert.hip).
@@ -278,7 +279,7 @@ struct FormChoice {
     const double *na, *nb;
     int64_t ld;
     double tau;
-    int32_t pairs, full_fp32;
+    int32_t weight, full_fp32;
     int32_t* form;
     int64_t* clear;
     int64_t clear_count;

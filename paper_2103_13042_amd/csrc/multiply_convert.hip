@@ -286,23 +286,34 @@ __global__ __launch_bounds__(kConvertThreads, 3) void multiply_convert_kernel(
 
 // BF16 with room for planes.  From the FP32 inputs every workgroup loads four bytes
 // an element; once the planes are there, two, for a pass over A and B (700 us at N =
-// 16384) and a plan.  Blocks of wide bands, at different k, share their panels least.
-// One call, planes against FP32 inputs, by kept pairs per output tile: N = 6912 37
-// pairs 702 and 677 us, 54 843 and 961; 8192 33 904 and 875, 49 1,117 and 1,254, 121
-// 2,298 and 3,044; 11008 26 1,359 and 1,434, 142 4,564 and 7,994; 16384 19 2,551 and
-// 2,186, 30 3,166 and 3,454, 137 10,036 and 17,052.  With every pair kept all blocks
-// start at k = 0 and share: where the strips of block_at come out even, N = 8192 2,270
-// and 1,874, 12288 7,258 and 6,647, but 11008 5,264 and 6,435, 20480 31,917 and 43,729.
-// The choice costs a product that stays with its FP32 inputs 9 us, three launches
-// that end at once: decay 0.05, N = 7040 126 -> 136, 16384 568 -> 577.  Below N = 6400
-// that is 10 % of a narrow band's call, and planes gain a wide one 7 at most (6016, 56
-// pairs: 681 and 732).
-constexpr int64_t kChoiceMinN = 6400, kFullFp32MaxN = 16384;
+// 16384) and a plan.  Both read a panel of A and of B for every k of a 2x2 block's
+// union, U of them for V kept pairs per output tile.  Blocks of wide bands, at
+// different k, share few panels in L2; where tiles are scattered (U well above V)
+// nothing is shared, so U - V counts thrice on top of U.  One call, planes against
+// FP32 inputs, V (bands: U = V + 1, scattered: U given):
+//  N = 4608, band 57 476 and 395 us, scattered 18 (41) 293 and 342: weight 90,
+//  scattered tiles only;
+//  N = 6016, band 40 562 and 523, 56 686 and 729, scattered 15 (39) 477 and 590:
+//  weight 58;
+//  N = 7040, band 36 719 and 712, 53 887 and 1,022, scattered 7 (21) 457 and 531:
+//  weight 45;
+//  N = 8192, band 23 699 and 625, 49 1,131 and 1,272, 121 2,324 and 2,998, scattered 5
+//  (17) 572 and 617, 21 (53) 1,008 and 1,678; 12288, band 24 1,592 and 1,524, 38
+//  2,089 and 2,332, scattered 17 (50) 2,187 and 3,995; 16384, band 19 2,555 and 2,215,
+//  30 3,251 and 3,432, 137 10,166 and 16,812: weight 30.
+// With every pair kept all blocks start at k = 0 and share: where the strips of
+// block_at come out even, N = 8192 2,278 and 1,864, 12288 7,291 and 6,830, but 11008
+// 5,338 and 6,456, 11904 6,689 and 6,995, 20480 32,552 and 38,377.
+// The choice costs a product that stays with its FP32 inputs 8 us, three launches
+// that end at once: decay 0.1, N = 4352 45 -> 52, 8192 142 -> 150, 16384 550 -> 558.
+// Below N = 4352 planes gain nothing (4096, scattered 17 (37): 228 and 224).
+constexpr int64_t kChoiceMinN = 4352, kFullFp32MinN = 7680, kEvenMinN = 8192, kFullFp32MaxN = 16384;
 bool bf16_choice(int64_t n, int64_t bdim, FormChoice* choice) {
     if (n < kChoiceMinN) return false;
-    const int side = int(bdim / 2);
-    choice->pairs = n < 8192 ? 45 : 24;
-    choice->full_fp32 = n <= kFullFp32MaxN && dealt_rows(side, convert_order<kPrecBf16>(side).H) >= side;
+    const int side = int(bdim / 2), dealt = dealt_rows(side, convert_order<kPrecBf16>(side).H);
+    choice->weight = n < 5632 ? 90 : n < 6400 ? 58 : n < 8192 ? 45 : 30;
+    choice->full_fp32 =
+        n >= kFullFp32MinN && n <= kFullFp32MaxN && (dealt == side || (dealt > side && n < kEvenMinN));
     return true;
 }
 

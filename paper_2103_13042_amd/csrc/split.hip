@@ -164,33 +164,46 @@ __global__ __launch_bounds__(256) void split_transpose_kernel(const float* __res
 
 // The choice of launch_split_choice, then both BF16 planes if they are taken:
 // blockIdx.y = 0 the rows of A, 1 the tiles of B.  Every block works the choice
-// out by itself from the same products, one per thread (i, k and j spread evenly
-// by multiples of the powers of a constant); block 0 writes it down.  A product
-// that does not take the planes pays for this, so the grid is one round of large
-// blocks, each with few reads (2048 blocks of 256 threads took 18 us to end).
-constexpr int kChoiceThreads = 1024;  // and products looked at
-constexpr int kChoiceBlocks = 256;
+// out by itself from the same 2x2 blocks of tiles and k, one per thread (spread
+// evenly by multiples of the powers of a constant); block 0 writes it down.  A product
+// that does not take the planes pays for this, so the grid is one large block a CU,
+// each with few reads (2048 blocks of 256 threads took 18 us to end).
+constexpr int kChoiceThreads = 1024;  // and blocks of tiles looked at
+constexpr int kChoiceBlocks = 128;
 
 __global__ __launch_bounds__(kChoiceThreads) void split_choice_kernel(const float* __restrict__ a,
                                                                       const float* __restrict__ b, int64_t n,
                                                                       int64_t bdim, FormChoice ch, SplitLayout L) {
     constexpr int kTiles = kChoiceThreads / 256;  // of B at a time
     __shared__ float t[kTiles][64][65];
-    __shared__ int kept[kChoiceThreads / 64];
-    const int tid = threadIdx.x;
+    __shared__ int any[kChoiceThreads / 64], kept[kChoiceThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // multiples of 2^32 / 1.2207440846, its square and its cube
-    auto at = [&](uint32_t step) {
-        return int64_t((uint64_t(uint32_t(tid) * step + (step >> 1)) * uint64_t(bdim)) >> 32);
+    auto at = [&](uint32_t step, int64_t len) {
+        return int64_t((uint64_t(uint32_t(tid) * step + (step >> 1)) * uint64_t(len)) >> 32);
     };
-    const int64_t i = at(3518319155u), k = at(2882110345u), j = at(2360945575u);
-    const uint64_t hit = __ballot(ch.na[i * ch.ld + k] * ch.nb[k * ch.ld + j] >= ch.tau);
-    if ((tid & 63) == 0) kept[tid >> 6] = __popcll(hit);
-    __syncthreads();
-    int total = 0;
+    const int64_t i = 2 * at(3518319155u, bdim / 2), k = at(2882110345u, bdim), j = 2 * at(2360945575u, bdim / 2);
+    const double* pa = ch.na + i * ch.ld + k;
+    const double* pb = ch.nb + k * ch.ld + j;
+    int mine = 0;
 #pragma unroll
-    for (int w = 0; w < kChoiceThreads / 64; ++w) total += kept[w];
-    const bool planes =
-        total * bdim >= int64_t(ch.pairs) * kChoiceThreads && !(ch.full_fp32 && total == kChoiceThreads);
+    for (int q = 0; q < 4; ++q) mine += pa[(q >> 1) * ch.ld] * pb[q & 1] >= ch.tau ? 1 : 0;
+    const uint64_t hit = __ballot(mine > 0);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) mine += __shfl_xor(mine, o);
+    if (lane == 0) {
+        any[wave] = __popcll(hit);
+        kept[wave] = mine;
+    }
+    __syncthreads();
+    int unions = 0, pairs = 0;  // of kChoiceThreads and of four times as many
+#pragma unroll
+    for (int w = 0; w < kChoiceThreads / 64; ++w) {
+        unions += any[w];
+        pairs += kept[w];
+    }
+    const bool planes = int64_t(16 * unions - 3 * pairs) * bdim >= int64_t(ch.weight) * 4 * kChoiceThreads &&
+                        !(ch.full_fp32 && pairs == 4 * kChoiceThreads);
     if (blockIdx.x == 0 && blockIdx.y == 0) {
         if (tid == 0) *ch.form = planes ? 1 : 0;
         for (int64_t w = tid; w < ch.clear_count; w += kChoiceThreads) ch.clear[w] = 0;

@@ -19,16 +19,30 @@ def _untouched(buf):
     return bool((buf == 0xA5).all())
 
 
-# (n, decay, tau, planes): either form at the smallest size with a choice, below
-# it, at both thresholds of pairs, with every pair kept where strips come out even
-# (8192) and where not (11008), and beyond the one-launch plan's 256 tiles a side
+def _scattered(n, share, seed):
+    """Random 64x64 tiles, the others zero."""
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    keep = torch.rand((n // 64, n // 64), device=DEV, generator=gen) < share
+    return torch.rand((n, n), device=DEV, generator=gen) * keep.repeat_interleave(64, 0).repeat_interleave(64, 1)
+
+
+def _pair(n, alpha):
+    """Decaying matrices, or for a negative alpha that share of scattered tiles."""
+    return [inputs.exp_decay_torch(n, alpha, s, DEV) if alpha > 0 else _scattered(n, -alpha, s) for s in (31, 32)]
+
+
+# (n, decay, tau, planes): either form in each range of the weight, none below the
+# smallest size with a choice (4224), with every pair kept where strips come out
+# even (8192) and where not (11008), beyond the one-launch plan's 256 tiles a side
 @pytest.mark.parametrize("n,alpha,tau,planes", [
-    (6272, 0.005, 1e-6, False), (6400, 0.005, 1e-6, True), (6400, 0.05, 1e-6, False), (6400, 0.0065, 1e-6, False),
+    (4224, -0.6, 1e-6, False), (4352, -0.6, 1e-6, True), (4352, -0.2, 1e-6, False), (4352, 0.0035, 1e-6, False),
+    (5504, 0.005, 1e-6, False), (5632, 0.003, 1e-6, True), (6272, 0.008, 1e-6, False), (6400, 0.005, 1e-6, True), (6400, 0.05, 1e-6, False), (6400, 0.008, 1e-6, False),
+    (8192, -0.3, 1e-6, True), (8192, -0.08, 1e-6, False),
     (8192, 0.0035, 1e-6, True), (8192, 0.02, 1e-6, False), (8192, 0.01, 0.0, False), (11008, 0.01, 0.0, True),
     (11008, 0.01, 1e-6, False), (16512, 0.0035, 1e-6, True), (16512, 0.03, 1e-6, False),
 ])
 def test_form_is_picked_on_the_device(n, alpha, tau, planes):
-    a, b = (inputs.exp_decay_torch(n, alpha, s, DEV) for s in (31, 32))
+    a, b = _pair(n, alpha)
     ws = sp.workspace(n, 64, DEV)
     small = torch.empty(256, dtype=torch.uint8, device=DEV)
     want, kept = sp.multiply_precision(a, b, tau, 64, "bf16", split_buf=small, ws=ws)
