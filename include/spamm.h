@@ -174,9 +174,9 @@ spamm_status spamm_prepare_schedule(const float* a, const float* b, int64_t n, d
  *   pairs  one int64 in device memory (may be NULL): number of multiplied
  *          leaf-tile pairs, i.e. the valid ratio of section 3.5.2 times bdim^3.
  * Leaf 16 and 32, and leaf 64 and 128 up to n = 5120 but for multiples of 128
- * from 2176 on (leaf 64: to 3968), take two launches instead: the leaf norm pass, then one kernel that applies the
- * threshold test of Algorithm 1 to the leaf norms and multiplies the kept
- * pairs.  The pairs are those of the plan; C differs from spamm_prepare +
+ * from 2176 on (leaf 64: to 3968), take two launches instead: the leaf norm
+ * pass, then one kernel that applies the threshold test of Algorithm 1 to the
+ * leaf norms and multiplies the kept pairs.  The pairs are those of the plan; C differs from spamm_prepare +
  * spamm_execute at most in the order of the FP32 additions (up to n = 1920 the
  * k-range of an output tile is split four ways above leaf 16 and the parts are
  * added in a fixed order; repeated calls agree bitwise); the workspace then
